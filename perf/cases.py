@@ -131,27 +131,40 @@ def _lists(g, case, W, b, C):
     return off, member.nonzero()[:, 1].to(torch.int32).cpu().numpy()
 
 
-def prepare(case, seed):
+def _training(case, seed):
     g = torch.Generator("cuda")
     g.manual_seed(seed)
-    kind, d = case["kind"], case["d"]
-    if kind == "kmeans":
-        n, K = case["n"], case["K"]
-        X = _rows(g, torch.randn((K, d), generator=g, device="cuda").half(), n)
-        start = X[torch.randperm(n, generator=g, device="cuda")[:K]].clone()
-        ws = torch.empty(P.vp.vp_kmeans_workspace_bytes(n, d, K), dtype=torch.uint8, device="cuda")
-        return dict(kind=kind, X=X, start=start, iters=case["iters"], ws=ws)
-    V, N, k = case["V"], case["N"], case["k"]
-    W, b = _model(g, d, V)
+    n, d, K = case["n"], case["d"], case["K"]
+    X = _rows(g, torch.randn((K, d), generator=g, device="cuda").half(), n)
+    return X, X[torch.randperm(n, generator=g, device="cuda")[:K]].clone()
+
+
+def _inputs(case, seed):
+    """Weights, bias, centroids, active sets, hidden rows and (beam search) scores of the hypotheses."""
+    g = torch.Generator("cuda")
+    g.manual_seed(seed)
+    kind, d, N = case["kind"], case["d"], case["N"]
+    W, b = _model(g, d, case["V"])
     C = torch.randn((case.get("K", 1), d), generator=g, device="cuda").half()
     if kind == "full":       # an index for the plain projection alone: one cluster with one token
         off, ids = np.array([0, 1], np.int64), np.array([0], np.int32)
     else:
         off, ids = _lists(g, case, W, b, C)
+    centers = torch.randn((1000, d), generator=g, device="cuda").half() if kind == "full" else C
+    hidden = _rows(g, centers, N, _zipf(C.shape[0]) if case.get("rows") == "zipf" else None)
+    scores = torch.randn((N,), generator=g, device="cuda") - 20.0 if kind == "beam" else None
+    return W, b, C, off, ids, hidden, scores
+
+
+def prepare(case, seed):
+    kind, d = case["kind"], case["d"]
+    if kind == "kmeans":
+        X, start = _training(case, seed)
+        ws = torch.empty(P.vp.vp_kmeans_workspace_bytes(case["n"], d, case["K"]), dtype=torch.uint8, device="cuda")
+        return dict(kind=kind, X=X, start=start, iters=case["iters"], ws=ws)
+    N, k = case["N"], case["k"]
+    W, b, C, off, ids, hidden, scores = _inputs(case, seed)
     index = P.vp_build(W, b, C, off, ids, k_max=max(8, k))
-    if kind == "full":
-        C = torch.randn((1000, d), generator=g, device="cuda").half()
-    hidden = _rows(g, C, N, _zipf(C.shape[0]) if case.get("rows") == "zipf" else None)
     st = dict(kind=kind, index=index, hidden=hidden, k=k)
     # what a decode loop keeps from step to step: its outputs and its workspace
     st["ids"] = torch.empty((N, k), dtype=torch.int32, device="cuda")
@@ -163,8 +176,8 @@ def prepare(case, seed):
         st["size"] = torch.zeros((1,), dtype=torch.int32, device="cuda")
     if kind == "beam":
         st["B"] = case["B"]
-        st["scores"] = torch.randn((N,), generator=g, device="cuda") - 20.0
-        st["out"] = (torch.empty_like(st["scores"]), torch.empty((N,), dtype=torch.int32, device="cuda"),
+        st["scores"] = scores
+        st["out"] = (torch.empty_like(scores), torch.empty((N,), dtype=torch.int32, device="cuda"),
                      torch.empty((N,), dtype=torch.int32, device="cuda"))
     return st
 
@@ -220,3 +233,39 @@ def tolerance(case):
         return dict(rel=1e-3, max=0.1, differ=1e-3)
     # log-probs against fp64 logits: up to 1.9e-7 (norm) and 6.3e-7 (largest); ids and clusters equal but for ties in fp32
     return dict(rel=2e-6, max=4e-6, differ=1e-3)
+
+
+# ---------------------------------------------------------------- the same in 64 bits
+def exact(case, seed):
+    """The log-probabilities (and a beam step's scores) in 64 bits.  Whole numbers have no rounding; the training has
+    no value of its own to compare with, since a vector halfway between two centroids goes to either."""
+    if case["kind"] == "kmeans":
+        return None
+    W, b, C, off, ids, hidden, scores = _inputs(case, seed)
+    kind, V, k = case["kind"], case["V"], case["k"]
+    W, b, h = W.double(), b.double(), hidden.double()
+    member = None
+    if kind != "full":
+        C = C.double()
+        cluster = (C.square().sum(1) - 2.0 * (h @ C.T)).argmin(1)
+        counts = torch.from_numpy(np.diff(off)).cuda()
+        owner = torch.repeat_interleave(torch.arange(len(off) - 1, device="cuda"), counts)
+        member = torch.zeros((len(off) - 1, V), dtype=torch.bool, device="cuda")
+        member[owner, torch.from_numpy(ids).cuda().long()] = True
+        if kind == "union":
+            member[:] = member[cluster.unique()].any(0)
+    logp = []
+    for r in range(0, h.shape[0], 512):
+        z = h[r:r + 512] @ W + b
+        if member is not None:
+            z.masked_fill_(~member[cluster[r:r + 512]], -math.inf)
+        logp.append(z.topk(k, 1).values - z.logsumexp(1, keepdim=True))
+    logp = torch.cat(logp)
+    if kind == "full":
+        return None, logp
+    if kind == "union":
+        return None, logp, None, None
+    if kind == "beam":
+        sums = (scores.double()[:, None] + logp).reshape(-1, case["B"] * k)
+        return None, logp, None, sums.topk(case["B"], 1).values.reshape(-1), None, None
+    return None, logp, None
