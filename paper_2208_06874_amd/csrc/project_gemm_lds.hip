@@ -427,7 +427,8 @@ __global__ __launch_bounds__(L_NW * 64) void project_gemm_lds_kernel(
 {
     if (MASKED ? hdr->mode != 1 : hdr->mode != 0) return;   // the planner chose the other form
     const int total_items = hdr->total_items;
-    const int it = item_of_workgroup(hdr);
+    // (hdr->swz_rgs > 1: several row groups and enough candidate ranges for the 8 XCDs)
+    const int it = hdr->swz_rgs > 1 ? vp_item_of_workgroup_even(blockIdx.x, total_items) : (int)blockIdx.x;
     if (it < 0 || it >= total_items) return;
     const VpItem item = items[it];
     if (item.shared || GATHER)

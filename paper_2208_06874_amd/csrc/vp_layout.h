@@ -180,6 +180,21 @@ static inline __host__ __device__ int vp_item_of_workgroup(int wg, int total_ite
     return wg;
 }
 
+// The same for the kernel that runs one workgroup per compute unit (rows in LDS), where a plan fills
+// whole rounds of the chip: every XCD takes an eighth of the item list, one item more or less.
+// Dealing whole candidate ranges instead leaves XCDs with more items than compute units whenever the
+// ranges do not divide by eight - 6 row groups x 42 ranges are 252 items for 256 compute units, but 36 for
+// two of the XCDs and their 32 compute units, a second round for four workgroups (333 rows of
+// d = 1000, V = 150,001: 227 us in the kernel, 149 us with this map).  The row groups of
+// a range still follow each other on one XCD, but for the ranges at the seven seams.
+static inline __host__ __device__ int vp_item_of_workgroup_even(int wg, int total_items)
+{
+    const int per = (total_items + 7) / 8;
+    const int l = wg >> 3;
+    const int it = (wg & 7) * per + l;
+    return l < per && it < total_items ? it : -1;
+}
+
 // What the masked full projection needs besides the slab set: each row's cluster
 // and the per-cluster membership bit lists over the vocabulary.
 struct VpMaskInfo {

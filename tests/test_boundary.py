@@ -298,6 +298,18 @@ def test_workgroup_to_item_maps_take_every_item_once(layout):
     assert [layout.shim_item_of_workgroup(wg, 10, 0, 0) for wg in range(10)] == list(range(10))
 
 
+def test_even_workgroup_map_takes_every_item_once_and_balances_the_xcds(layout):
+    """The map of the one-workgroup-per-compute-unit kernel: over the smallest grid the host launches (the items
+    rounded up to eight, or more) every item is taken once, and no XCD gets more than its eighth."""
+    r = np.random.default_rng(12)
+    for total in [1, 7, 8, 9, 240, 252, 255, 256, 257, 1978, 2048] + [int(x) for x in r.integers(1, 20000, 40)]:
+        for grid in (-(-total // 8) * 8, total + 8, -(-total // 8) * 8 + 40):
+            got = [layout.shim_item_of_workgroup_even(wg, total) for wg in range(grid)]
+            assert sorted(x for x in got if x >= 0) == list(range(total)), (total, grid)
+            per_xcd = [sum(1 for wg in range(x, grid, 8) if got[wg] >= 0) for x in range(8)]
+            assert max(per_xcd) <= -(-total // 8)
+
+
 def _fake_index(d=64, k_max=4):
     """An Index object without a library handle: the binding's own checks run before any C call."""
     import torch
