@@ -44,6 +44,12 @@ def test_beam_step_matches_the_oracle(oracle, S, B, k):
         assert np.array_equal(g, w), name
 
 
+@pytest.mark.parametrize("S,B,k", [(4, 16, 4), (3, 13, 5), (2, 32, 8), (1, 257, 1), (2, 16, 32)])
+def test_beam_step_around_the_one_wavefront_sizes(oracle, S, B, k):
+    """B * k at 64, 65, 256, 257 and 512: the edges of the forms with one wavefront per sentence."""
+    test_beam_step_matches_the_oracle(oracle, S, B, k)
+
+
 def test_beam_step_edge_cases(oracle):
     # first step of a search (one live hypothesis), nothing alive at all, fewer continuations than B
     ids = np.array([[1, 2], [3, 4], [5, 6]], np.int32)
