@@ -10,6 +10,7 @@
 // double precision, to binary16 (nearest, ties to even).  A cluster without members keeps its
 // centroid.
 #include <hip/hip_runtime.h>
+#include <algorithm>
 #include "vp_kernels.h"
 #include "project_common.h"
 
@@ -145,6 +146,239 @@ __global__ __launch_bounds__(256, (KW <= 8 ? 2 : 1)) void kmeans_assign_gemm_ker
         assign[row] = best_j;
         atomicAdd(&counts[best_j], 1);
     }
+}
+
+// rows-in-LDS membership kernel: wavefronts per workgroup, centroid groups per step, row tiles per item
+constexpr int KL_NW = 8;
+constexpr int KL_G = 2;
+constexpr int km_lds_row_tiles(int kt) { return kt == 48 ? 3 : 4; }
+
+// The same membership pass with the vectors held in LDS (d_pad = 512, 1024 and 1536): the split-k kernel above
+// meets in LDS behind a barrier for every 16 centroids, which leaves the matrix cores idle most of the time.
+// An item is 64 vectors (48 at d_pad = 1536, where 64 do not fit) against all centroids; eight wavefronts walk
+// steps of two groups of 16 centroids on their own (w, w + 8, ...), the centroid tiles streaming
+// from the L2 through a ring of four k-tiles that runs across steps and items, the vectors' operands
+// from LDS; no barrier but the two of an item.  A workgroup owns its compute unit and walks
+// items, and during an item's last step it touches the next item's vectors, so that staging them finds them in
+// the L2.  Every sum is formed as the split-k kernel forms it - four quarters of the k-extent, each a chain of its own
+// from zero, added as (s0 + s1) + (s2 + s3) - so the memberships are the same to the bit; two groups, not
+// four, because three sets of accumulators must fit the registers.
+// Ten iterations of vp_kmeans with it, us per iteration, split-k kernel -> this one: 131,072 vectors x 1,000 clusters
+// d = 1024: 417 -> 405, d = 512: 312 -> 274, d = 1536: 892 -> 746; 6,000 x 1,000, d = 1024: 108 -> 77;
+// 4,099 x 1,000, d = 512: 84 -> 52.  (Steps of three groups spill: 526 at the first.)
+template <int KT>
+__global__ __launch_bounds__(KL_NW * 64) void kmeans_assign_lds_kernel(
+    const uint4 *__restrict__ X, long n, int d, const uint4 *__restrict__ cp, const float *__restrict__ cnorm, int K,
+    int ctiles, int nitems, int32_t *__restrict__ assign, int32_t *__restrict__ counts)
+{
+    constexpr int RT = km_lds_row_tiles(KT);
+    constexpr int ROWS = 16 * RT;
+    constexpr int G = KL_G;
+    constexpr int PF = 4;                 // k-tiles in flight
+    constexpr int KW = KT / 4;            // k-tiles per quarter
+    constexpr int XP = KT * 4;            // 16-byte pieces per padded vector
+    constexpr int THREADS = KL_NW * 64;
+    constexpr int PER = ROWS * XP / THREADS;
+    constexpr int TOUCH = (ROWS * XP / 8 + THREADS - 1) / THREADS;   // 128-byte lines per thread
+    static_assert(PER * THREADS == ROWS * XP && KW % PF == 0, "whole pieces and passes");
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63;
+    const int nn = lane & 15;
+    const int q = lane >> 4;
+    extern __shared__ uint4 lds[];        // [RT][KT][64]: the vectors in MFMA operand order
+    float *red_s = reinterpret_cast<float *>(lds + RT * KT * 64);   // [KL_NW][ROWS]
+    int *red_j = reinterpret_cast<int *>(red_s + KL_NW * ROWS);      // [KL_NW][ROWS]
+
+    const int nsteps = (ctiles + G - 1) / G;   // >= KL_NW: every wavefront has a step
+    const int pieces_per_row = d >> 3;
+    const uint4 *tiles = cp + lane;
+    // groups past the last one repeat it (their centroid numbers are >= K: never looked at)
+    auto group_off = [&](int step, unsigned int (&off)[G]) {
+#pragma unroll
+        for (int j = 0; j < G; ++j) off[j] = (unsigned int)min(step * G + j, ctiles - 1) * (KT * 64);
+    };
+    unsigned int cur[G], nxt[G];
+    uint4 ring[PF][G];
+    group_off(wave, cur);
+#pragma unroll
+    for (int p = 0; p < PF; ++p)
+#pragma unroll
+        for (int j = 0; j < G; ++j) ring[p][j] = tiles[cur[j] + p * 64];
+
+    for (int item = blockIdx.x; item < nitems; item += gridDim.x) {
+        const long r0 = (long)item * ROWS;
+        {
+            int t = tid;
+            asm volatile("" : "+v"(t));   // the pieces' addresses are formed here, not kept in registers across the items
+            uint4 piece[PER];
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                const int e = t + i * THREADS;
+                const int r = e / XP;
+                const int x = e - r * XP;
+                // (without branches; vectors past the last repeat it and are never looked at)
+                const uint4 v = X[(size_t)min(r0 + r, n - 1) * pieces_per_row + min(x, pieces_per_row - 1)];
+                piece[i] = x < pieces_per_row ? v : make_uint4(0, 0, 0, 0);
+            }
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                const int e = t + i * THREADS;
+                const int r = e / XP;
+                const int x = e - r * XP;
+                lds[((r >> 4) * KT + (x >> 2)) * 64 + (x & 3) * 16 + (r & 15)] = piece[i];
+            }
+        }
+        __syncthreads();   // the vectors are staged; red_* of the item before has been read
+
+        float best_s[RT];
+        int best_j[RT];
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+            best_s[rt] = __builtin_inff();
+            best_j[rt] = VP_IDX_NONE;
+        }
+        uint32_t touched[TOUCH];
+#pragma unroll
+        for (int i = 0; i < TOUCH; ++i) touched[i] = 0;
+        uint4 bnext[RT];
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) bnext[rt] = lds[(rt * KT) * 64 + lane];
+
+#pragma unroll 1
+        for (int step = wave; step < nsteps; step += KL_NW) {
+            const bool last_step = step + KL_NW >= nsteps;
+            group_off(last_step ? wave : step + KL_NW, nxt);
+            if (last_step && item + (int)gridDim.x < nitems) {
+                const long r1 = r0 + (long)gridDim.x * ROWS;
+                const long lines = min((long)ROWS, n - r1) * pieces_per_row;   // in pieces; the vectors are contiguous
+                const uint32_t *nx = reinterpret_cast<const uint32_t *>(X + (size_t)r1 * pieces_per_row);
+#pragma unroll
+                for (int i = 0; i < TOUCH; ++i) {
+                    const int e = (tid + i * THREADS) * 8;
+                    if (e < lines) touched[i] = __hip_atomic_load(nx + (size_t)e * 4, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
+            }
+            auto quarter = [&](floatx4 (&acc)[RT][G], int sl) {
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                    for (int j = 0; j < G; ++j) acc[rt][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+                for (int b = 0; b < KW / PF; ++b) {
+                    const int kt0 = sl * KW + b * PF;
+                    const bool last = kt0 + PF == KT;
+                    unsigned int src[G];
+#pragma unroll
+                    for (int j = 0; j < G; ++j) src[j] = last ? nxt[j] : cur[j] + (kt0 + PF) * 64;
+#pragma unroll
+                    for (int u = 0; u < PF; ++u) {
+                        // the operands of the next k-tile are read in front of this k-tile's MFMAs and the ring
+                        // slot is refilled behind them; the scheduling barriers keep both where they are
+                        Frag bf[RT];
+                        const int kt_next = kt0 + u + 1 == KT ? 0 : kt0 + u + 1;
+#pragma unroll
+                        for (int rt = 0; rt < RT; ++rt) {
+                            bf[rt].u = bnext[rt];
+                            bnext[rt] = lds[(rt * KT + kt_next) * 64 + lane];
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                            for (int j = 0; j < G; ++j) {
+                                Frag a;
+                                a.u = ring[u][j];
+                                acc[rt][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a.h, bf[rt].h, acc[rt][j], 0, 0, 0);
+                            }
+#pragma unroll
+                        for (int j = 0; j < G; ++j) ring[u][j] = tiles[src[j] + u * 64];
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+            };
+            floatx4 dot[RT][G], s1[RT][G], s2[RT][G];
+            quarter(dot, 0);
+            quarter(s1, 1);
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int j = 0; j < G; ++j) dot[rt][j] = dot[rt][j] + s1[rt][j];
+            quarter(s1, 2);
+            quarter(s2, 3);
+#pragma unroll
+            for (int j = 0; j < G; ++j) {
+                const int g = step * G + j;
+                const float4 cn = *reinterpret_cast<const float4 *>(cnorm + min(g, ctiles - 1) * 16 + q * 4);
+                const float cnv[4] = {cn.x, cn.y, cn.z, cn.w};
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) {
+                    const floatx4 t = dot[rt][j] + (s1[rt][j] + s2[rt][j]);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int c = g * 16 + q * 4 + i;
+                        const float s = cnv[i] - 2.0f * t[i];
+                        const bool take = (c < K) & (s < best_s[rt]);   // c ascends within a lane: strict < keeps the lowest
+                        best_s[rt] = take ? s : best_s[rt];
+                        best_j[rt] = take ? c : best_j[rt];
+                    }
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < G; ++j) cur[j] = nxt[j];
+        }
+#pragma unroll
+        for (int i = 0; i < TOUCH; ++i) asm volatile("" ::"v"(touched[i]));   // (the touching loads have a use)
+
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+#pragma unroll
+            for (int off = 16; off <= 32; off <<= 1) {
+                const float s2 = __shfl_xor(best_s[rt], off);
+                const int j2 = __shfl_xor(best_j[rt], off);
+                const bool take = part_less(s2, j2, best_s[rt], best_j[rt]);
+                best_s[rt] = take ? s2 : best_s[rt];
+                best_j[rt] = take ? j2 : best_j[rt];
+            }
+            if (q == 0) {
+                red_s[wave * ROWS + rt * 16 + nn] = best_s[rt];
+                red_j[wave * ROWS + rt * 16 + nn] = best_j[rt];
+            }
+        }
+        __syncthreads();   // nobody reads the vectors any more; red_* is complete
+        if (tid < ROWS && r0 + tid < n) {
+            float bs = red_s[tid];
+            int bj = red_j[tid];
+#pragma unroll
+            for (int w = 1; w < KL_NW; ++w) {
+                const float s2 = red_s[w * ROWS + tid];
+                const int j2 = red_j[w * ROWS + tid];
+                if (part_less(s2, j2, bs, bj)) {
+                    bs = s2;
+                    bj = j2;
+                }
+            }
+            if ((unsigned)bj >= (unsigned)K) bj = 0;   // only when every score is NaN
+            assign[r0 + tid] = bj;
+            atomicAdd(&counts[bj], 1);
+        }
+    }
+}
+
+template <int KT>
+bool launch_assign_lds(const void *X, long n, int d, const void *cp, const float *cnorm, int K, int ctiles,
+                       int32_t *assign, int32_t *counts, hipStream_t st)
+{
+    constexpr int rows = 16 * km_lds_row_tiles(KT);
+    constexpr size_t bytes = (size_t)rows * KT * 64 + (size_t)KL_NW * rows * 8;
+    static_assert(bytes <= 160 * 1024, "vectors and reduction fit the LDS");
+    if (hipFuncSetAttribute(reinterpret_cast<const void *>(kmeans_assign_lds_kernel<KT>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess)
+        return false;
+    const int nitems = (int)((n + rows - 1) / rows);
+    hipLaunchKernelGGL((kmeans_assign_lds_kernel<KT>), dim3(std::min(nitems, 256)), dim3(KL_NW * 64), bytes, st,
+                       (const uint4 *)X, n, d, (const uint4 *)cp, cnorm, K, ctiles, nitems, assign, counts);
+    return true;
 }
 
 // start[j] = number of members of clusters below j; cursor[j] = start[j].  One workgroup.
@@ -575,6 +809,13 @@ void vpk_kmeans_assign(const void *cpart, int parts, int rows, int K, int32_t *a
 bool vpk_kmeans_assign_gemm(const void *X, long n, int d, const void *cp, const float *cnorm, int K, int kt, int ctiles,
                             int32_t *assign, int32_t *counts, hipStream_t st)
 {
+    // Enough centroids to give each of the eight wavefronts of the rows-in-LDS kernel a step of its own: with fewer, some
+    // would idle (and the ring in front of the first step would start past the last group).
+    if (ctiles >= KL_NW * KL_G) {
+        if (kt == 16) return launch_assign_lds<16>(X, n, d, cp, cnorm, K, ctiles, assign, counts, st);
+        if (kt == 32) return launch_assign_lds<32>(X, n, d, cp, cnorm, K, ctiles, assign, counts, st);
+        if (kt == 48) return launch_assign_lds<48>(X, n, d, cp, cnorm, K, ctiles, assign, counts, st);
+    }
     const dim3 grid((unsigned)((n + 63) / 64)), block(256);
 #define VP_KM_CASE(KW)                                                                                                \
     case KW * 4:                                                                                                      \

@@ -73,6 +73,19 @@ def test_lloyd_steps_match_the_oracle(oracle, name, n, scale):
     print("lloyd steps", name, n, scale, "excused memberships", excused)
 
 
+# the rows-in-LDS membership kernel (d_pad 512, 1024, 1536 and at least 16 groups of 16 centroids): the first K it takes and
+# the last it leaves, a last step of one group, a last item of few vectors, more items than compute units
+@pytest.mark.parametrize("n,d,K", [(4096, 1024, 240), (4099, 1000, 241), (16390, 504, 257), (4097, 1536, 273),
+                                   (12353, 1288, 256)])
+def test_membership_with_the_vectors_in_lds(oracle, n, d, K):
+    rs = np.random.default_rng(n + d)
+    X = (rs.standard_normal((K, d))[rs.integers(0, K, n)] + 0.3 * rs.standard_normal((n, d))).astype(np.float16)
+    C0 = X[np.sort(rs.choice(n, K, replace=False))].copy()
+    _same, assign, counts = _gpu_kmeans(X, C0, 0)
+    _check_membership(oracle, X, C0.view(np.uint16), assign)
+    assert np.array_equal(counts, np.bincount(assign, minlength=K))
+
+
 def test_twenty_iterations_and_determinism(oracle):
     cfg, X, q, C0 = _mixture("tiny", 8192)
     Cb, assign, counts = _gpu_kmeans(X, C0, 20)
