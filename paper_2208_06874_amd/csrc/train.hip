@@ -21,7 +21,7 @@ __device__ inline bool part_less(float s, int j, float s2, int j2) { return s < 
 // Finishes Eq. 2 for a chunk of rows (minimum over the centroid ranges) and counts the members.
 __global__ __launch_bounds__(256) void kmeans_assign_kernel(const int2 *__restrict__ cpart, int parts, int rows,
                                                             int K, int32_t *__restrict__ assign,
-                                                            int32_t *__restrict__ counts)
+                                                            int32_t *__restrict__ counts, int32_t *__restrict__ rank)
 {
     const int r = blockIdx.x * 256 + threadIdx.x;
     if (r >= rows) return;
@@ -37,7 +37,8 @@ __global__ __launch_bounds__(256) void kmeans_assign_kernel(const int2 *__restri
     }
     if ((unsigned)bj >= (unsigned)K) bj = 0;   // only when every score is NaN: keep the index in range
     assign[r] = bj;
-    atomicAdd(&counts[bj], 1);
+    const int before = atomicAdd(&counts[bj], 1);
+    if (rank) rank[r] = before;
 }
 
 // Membership of many vectors at once: Eq. 2 as a GEMM.  One workgroup takes 64 vectors and
@@ -49,7 +50,7 @@ __global__ __launch_bounds__(256) void kmeans_assign_kernel(const int2 *__restri
 template <int KW>
 __global__ __launch_bounds__(256, (KW <= 8 ? 2 : 1)) void kmeans_assign_gemm_kernel(
     const uint4 *__restrict__ X, long n, int d, const uint4 *__restrict__ cp, const float *__restrict__ cnorm, int K,
-    int ctiles, int32_t *__restrict__ assign, int32_t *__restrict__ counts)
+    int ctiles, int32_t *__restrict__ assign, int32_t *__restrict__ counts, int32_t *__restrict__ rank)
 {
     constexpr int KT = KW * 4;
     constexpr int RT = 4;
@@ -144,7 +145,8 @@ __global__ __launch_bounds__(256, (KW <= 8 ? 2 : 1)) void kmeans_assign_gemm_ker
     if (q == 0 && row < n) {
         if ((unsigned)best_j >= (unsigned)K) best_j = 0;   // only when every score is NaN
         assign[row] = best_j;
-        atomicAdd(&counts[best_j], 1);
+        const int before = atomicAdd(&counts[best_j], 1);
+        if (rank) rank[row] = before;
     }
 }
 
@@ -169,7 +171,7 @@ constexpr int km_lds_row_tiles(int kt) { return kt == 48 ? 3 : 4; }
 template <int KT>
 __global__ __launch_bounds__(KL_NW * 64) void kmeans_assign_lds_kernel(
     const uint4 *__restrict__ X, long n, int d, const uint4 *__restrict__ cp, const float *__restrict__ cnorm, int K,
-    int ctiles, int nitems, int32_t *__restrict__ assign, int32_t *__restrict__ counts)
+    int ctiles, int nitems, int32_t *__restrict__ assign, int32_t *__restrict__ counts, int32_t *__restrict__ rank)
 {
     constexpr int RT = km_lds_row_tiles(KT);
     constexpr int ROWS = 16 * RT;
@@ -206,6 +208,8 @@ __global__ __launch_bounds__(KL_NW * 64) void kmeans_assign_lds_kernel(
 #pragma unroll
         for (int j = 0; j < G; ++j) ring[p][j] = tiles[cur[j] + p * 64];
 
+    int before = 0;          // this thread's vector of the item before: members its cluster had before it
+    long before_row = -1;
     for (int item = blockIdx.x; item < nitems; item += gridDim.x) {
         const long r0 = (long)item * ROWS;
         {
@@ -229,6 +233,9 @@ __global__ __launch_bounds__(KL_NW * 64) void kmeans_assign_lds_kernel(
                 lds[((r >> 4) * KT + (x >> 2)) * 64 + (x & 3) * 16 + (r & 15)] = piece[i];
             }
         }
+        // (the item before: its atomics have come back with the vectors)
+        if (rank && before_row >= 0) rank[before_row] = before;
+        before_row = -1;
         __syncthreads();   // the vectors are staged; red_* of the item before has been read
 
         float best_s[RT];
@@ -360,14 +367,16 @@ __global__ __launch_bounds__(KL_NW * 64) void kmeans_assign_lds_kernel(
             }
             if ((unsigned)bj >= (unsigned)K) bj = 0;   // only when every score is NaN
             assign[r0 + tid] = bj;
-            atomicAdd(&counts[bj], 1);
+            before = atomicAdd(&counts[bj], 1);
+            before_row = r0 + tid;
         }
     }
+    if (rank && before_row >= 0) rank[before_row] = before;
 }
 
 template <int KT>
 bool launch_assign_lds(const void *X, long n, int d, const void *cp, const float *cnorm, int K, int ctiles,
-                       int32_t *assign, int32_t *counts, hipStream_t st)
+                       int32_t *assign, int32_t *counts, int32_t *rank, hipStream_t st)
 {
     constexpr int rows = 16 * km_lds_row_tiles(KT);
     constexpr size_t bytes = (size_t)rows * KT * 64 + (size_t)KL_NW * rows * 8;
@@ -377,7 +386,8 @@ bool launch_assign_lds(const void *X, long n, int d, const void *cp, const float
         return false;
     const int nitems = (int)((n + rows - 1) / rows);
     hipLaunchKernelGGL((kmeans_assign_lds_kernel<KT>), dim3(std::min(nitems, 256)), dim3(KL_NW * 64), bytes, st,
-                       (const uint4 *)X, n, d, (const uint4 *)cp, cnorm, K, ctiles, nitems, assign, counts);
+                       (const uint4 *)X, n, d, (const uint4 *)cp, cnorm, K, ctiles, nitems, assign, counts,
+                       rank);
     return true;
 }
 
@@ -431,6 +441,18 @@ __global__ __launch_bounds__(256) void kmeans_scatter_kernel(const int32_t *__re
     if (r >= n) return;
     const int pos = atomicAdd(&cursor[assign[r]], 1);
     perm[pos] = (int32_t)r;
+}
+
+// The same where the membership pass kept what its counting atomics returned, each vector's number among
+// its cluster's members: no second round of a hundred atomics on every counter, one behind the other
+// (131,072 vectors, 1,000 clusters: 35 us with the atomics, 5 us with the numbers).
+__global__ __launch_bounds__(256) void kmeans_place_kernel(const int32_t *__restrict__ assign,
+                                                           const int32_t *__restrict__ rank, long n,
+                                                           const int32_t *__restrict__ start, int32_t *__restrict__ perm)
+{
+    const long r = (long)blockIdx.x * 256 + threadIdx.x;
+    if (r >= n) return;
+    perm[start[assign[r]] + rank[r]] = (int32_t)r;
 }
 
 // Running sums of 8 coordinates.  They are kept in double precision: every binary16 value is
@@ -800,27 +822,27 @@ void vpk_fill_u32(void *p, size_t n, uint32_t v, hipStream_t st)
 }
 
 void vpk_kmeans_assign(const void *cpart, int parts, int rows, int K, int32_t *assign, int32_t *counts,
-                       hipStream_t st)
+                       int32_t *rank, hipStream_t st)
 {
     hipLaunchKernelGGL(kmeans_assign_kernel, dim3((rows + 255) / 256), dim3(256), 0, st, (const int2 *)cpart, parts,
-                       rows, K, assign, counts);
+                       rows, K, assign, counts, rank);
 }
 
 bool vpk_kmeans_assign_gemm(const void *X, long n, int d, const void *cp, const float *cnorm, int K, int kt, int ctiles,
-                            int32_t *assign, int32_t *counts, hipStream_t st)
+                            int32_t *assign, int32_t *counts, int32_t *rank, hipStream_t st)
 {
     // Enough centroids to give each of the eight wavefronts of the rows-in-LDS kernel a step of its own: with fewer, some
     // would idle (and the ring in front of the first step would start past the last group).
     if (ctiles >= KL_NW * KL_G) {
-        if (kt == 16) return launch_assign_lds<16>(X, n, d, cp, cnorm, K, ctiles, assign, counts, st);
-        if (kt == 32) return launch_assign_lds<32>(X, n, d, cp, cnorm, K, ctiles, assign, counts, st);
-        if (kt == 48) return launch_assign_lds<48>(X, n, d, cp, cnorm, K, ctiles, assign, counts, st);
+        if (kt == 16) return launch_assign_lds<16>(X, n, d, cp, cnorm, K, ctiles, assign, counts, rank, st);
+        if (kt == 32) return launch_assign_lds<32>(X, n, d, cp, cnorm, K, ctiles, assign, counts, rank, st);
+        if (kt == 48) return launch_assign_lds<48>(X, n, d, cp, cnorm, K, ctiles, assign, counts, rank, st);
     }
     const dim3 grid((unsigned)((n + 63) / 64)), block(256);
 #define VP_KM_CASE(KW)                                                                                                \
     case KW * 4:                                                                                                      \
         hipLaunchKernelGGL((kmeans_assign_gemm_kernel<KW>), grid, block, 0, st, (const uint4 *)X, n, d,               \
-                           (const uint4 *)cp, cnorm, K, ctiles, assign, counts);                                      \
+                           (const uint4 *)cp, cnorm, K, ctiles, assign, counts, rank);                                \
         return true;
     switch (kt) {
         VP_KM_CASE(2)
@@ -832,18 +854,25 @@ bool vpk_kmeans_assign_gemm(const void *X, long n, int d, const void *cp, const 
 #undef VP_KM_CASE
 }
 
-void vpk_kmeans_bucket(const int32_t *assign, long n, const int32_t *counts, int K, int32_t *start, int32_t *cursor,
-                       int32_t *perm, hipStream_t st)
+void vpk_kmeans_bucket(const int32_t *assign, const int32_t *rank, long n, const int32_t *counts, int K, int32_t *start,
+                       int32_t *cursor, int32_t *perm, hipStream_t st)
 {
     hipLaunchKernelGGL(kmeans_scan_kernel, dim3(1), dim3(1024), 0, st, counts, K, start, cursor);
+    if (rank) {
+        hipLaunchKernelGGL(kmeans_place_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, assign, rank, n, start,
+                           perm);
+        return;
+    }
     hipLaunchKernelGGL(kmeans_scatter_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, assign, n, cursor,
                        perm);
 }
 
+bool vpk_kmeans_mean_form(int K) { return K >= 256; }
+
 void vpk_kmeans_update(const void *X, int d, const int32_t *perm, const int32_t *start, const int32_t *counts, int K,
                        int splits, void *acc, void *C, hipStream_t st)
 {
-    if (K >= 256) {
+    if (vpk_kmeans_mean_form(K)) {
         // enough clusters to fill the chip with one workgroup each: no sums in memory at all
         hipLaunchKernelGGL(kmeans_mean_kernel, dim3(K), dim3(1024), 0, st, (const uint4 *)X, d / 8, perm, start,
                            (uint4 *)C);

@@ -84,7 +84,11 @@ vp_status vp_kmeans(const void *x, int64_t n, int32_t d, int32_t K, int32_t iter
     // clusters x splits workgroups of the summing kernel: a few thousand
     const int splits = std::max(1, std::min(64, 2048 / K));
 
-    vpk_fill_u32(acc, (size_t)K * d * 2, 0u, st);
+    // The sums in memory are needed for few clusters only; with many, their place holds each vector's number
+    // among its cluster's members, if it is large enough (at most 2 * d vectors per cluster on average).
+    const bool mean_form = vpk_kmeans_mean_form(K);
+    int32_t *const rank_buf = mean_form && (size_t)n * 4 <= (size_t)K * d * 8 ? (int32_t *)acc : nullptr;
+    if (!mean_form) vpk_fill_u32(acc, (size_t)K * d * 2, 0u, st);
     for (int it = 0; it <= iters; ++it) {
         // Eq. 2 operands of the current centroids
         vpk_pack_rows(centroids, K, d, L.kt, cp, st);
@@ -92,15 +96,16 @@ vp_status vp_kmeans(const void *x, int64_t n, int32_t d, int32_t K, int32_t iter
         vpk_fill_u32(counts, (size_t)K, 0u, st);
         // memberships: the GEMM-shaped kernel when there are enough vectors to fill the chip with
         // 64-vector workgroups, else (or for k-extents it is not built for) the decode-time kernel
-        const bool gemm = n >= 4096 && vpk_kmeans_assign_gemm(x, (long)n, d, cp, cnorm, K, L.kt, L.ctiles, assign, counts, st);
+        int32_t *const rank = it < iters ? rank_buf : nullptr;   // (the last pass only assigns)
+        const bool gemm = n >= 4096 && vpk_kmeans_assign_gemm(x, (long)n, d, cp, cnorm, K, L.kt, L.ctiles, assign, counts, rank, st);
         for (int64_t r0 = 0; !gemm && r0 < n; r0 += CHUNK_ROWS) {
             const int rows = (int)std::min<int64_t>(CHUNK_ROWS, n - r0);
             vpk_centroid((const char *)x + (size_t)r0 * d * 2, rows, d, cp, cnorm, K, L.kt, L.ctiles, L.tpw, L.parts,
                          cpart, st);
-            vpk_kmeans_assign(cpart, L.parts, rows, K, assign + r0, counts, st);
+            vpk_kmeans_assign(cpart, L.parts, rows, K, assign + r0, counts, rank ? rank + r0 : nullptr, st);
         }
         if (it == iters) break;   // the last pass only assigns
-        vpk_kmeans_bucket(assign, (long)n, counts, K, start, cursor, perm, st);
+        vpk_kmeans_bucket(assign, rank, (long)n, counts, K, start, cursor, perm, st);
         vpk_kmeans_update(x, d, perm, start, counts, K, splits, acc, centroids, st);
         if (flags & VP_KMEANS_SPLIT_EMPTY) vpk_kmeans_split(counts, K, d, centroids, st);
     }

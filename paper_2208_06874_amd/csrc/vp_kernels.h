@@ -90,12 +90,14 @@ void vpk_union_gather(const void *wt, int kt, const int32_t *uids, const VpUnion
 
 // offline training of the clusters (section 2.2)
 void vpk_fill_u32(void *p, size_t n, uint32_t v, hipStream_t st);
+// (rank: nullptr, or each vector's number among its cluster's members, for vpk_kmeans_bucket)
 void vpk_kmeans_assign(const void *cpart, int parts, int rows, int K, int32_t *assign, int32_t *counts,
-                       hipStream_t st);
+                       int32_t *rank, hipStream_t st);
 bool vpk_kmeans_assign_gemm(const void *X, long n, int d, const void *cp, const float *cnorm, int K, int kt, int ctiles,
-                            int32_t *assign, int32_t *counts, hipStream_t st);
-void vpk_kmeans_bucket(const int32_t *assign, long n, const int32_t *counts, int K, int32_t *start, int32_t *cursor,
-                       int32_t *perm, hipStream_t st);
+                            int32_t *assign, int32_t *counts, int32_t *rank, hipStream_t st);
+void vpk_kmeans_bucket(const int32_t *assign, const int32_t *rank, long n, const int32_t *counts, int K, int32_t *start,
+                       int32_t *cursor, int32_t *perm, hipStream_t st);
+bool vpk_kmeans_mean_form(int K);   // vpk_kmeans_update needs no sums in memory (acc)
 void vpk_kmeans_update(const void *X, int d, const int32_t *perm, const int32_t *start, const int32_t *counts, int K,
                        int splits, void *acc, void *C, hipStream_t st);
 void vpk_kmeans_split(const int32_t *counts, int K, int d, void *C, hipStream_t st);
