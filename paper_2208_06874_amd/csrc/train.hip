@@ -375,20 +375,29 @@ __global__ __launch_bounds__(KL_NW * 64) void kmeans_assign_lds_kernel(
 }
 
 template <int KT>
-bool launch_assign_lds(const void *X, long n, int d, const void *cp, const float *cnorm, int K, int ctiles,
-                       int32_t *assign, int32_t *counts, int32_t *rank, hipStream_t st)
+constexpr size_t km_lds_bytes()
 {
     constexpr int rows = 16 * km_lds_row_tiles(KT);
     constexpr size_t bytes = (size_t)rows * KT * 64 + (size_t)KL_NW * rows * 8;
     static_assert(bytes <= 160 * 1024, "vectors and reduction fit the LDS");
-    if (hipFuncSetAttribute(reinterpret_cast<const void *>(kmeans_assign_lds_kernel<KT>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess)
-        return false;
+    return bytes;
+}
+
+template <int KT>
+hipError_t prepare_assign_lds()
+{
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(kmeans_assign_lds_kernel<KT>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)km_lds_bytes<KT>());
+}
+
+template <int KT>
+void launch_assign_lds(const void *X, long n, int d, const void *cp, const float *cnorm, int K, int ctiles,
+                       int32_t *assign, int32_t *counts, int32_t *rank, hipStream_t st)
+{
+    constexpr int rows = 16 * km_lds_row_tiles(KT);
     const int nitems = (int)((n + rows - 1) / rows);
-    hipLaunchKernelGGL((kmeans_assign_lds_kernel<KT>), dim3(std::min(nitems, 256)), dim3(KL_NW * 64), bytes, st,
-                       (const uint4 *)X, n, d, (const uint4 *)cp, cnorm, K, ctiles, nitems, assign, counts,
-                       rank);
-    return true;
+    hipLaunchKernelGGL((kmeans_assign_lds_kernel<KT>), dim3(std::min(nitems, 256)), dim3(KL_NW * 64), km_lds_bytes<KT>(),
+                       st, (const uint4 *)X, n, d, (const uint4 *)cp, cnorm, K, ctiles, nitems, assign, counts, rank);
 }
 
 // start[j] = number of members of clusters below j; cursor[j] = start[j].  One workgroup.
@@ -828,15 +837,29 @@ void vpk_kmeans_assign(const void *cpart, int parts, int rows, int K, int32_t *a
                        rows, K, assign, counts, rank);
 }
 
-bool vpk_kmeans_assign_gemm(const void *X, long n, int d, const void *cp, const float *cnorm, int K, int kt, int ctiles,
-                            int32_t *assign, int32_t *counts, int32_t *rank, hipStream_t st)
+bool vpk_kmeans_rows_in_lds(int kt, int ctiles)
 {
     // Enough centroids to give each of the eight wavefronts of the rows-in-LDS kernel a step of its own: with fewer, some
     // would idle (and the ring in front of the first step would start past the last group).
-    if (ctiles >= KL_NW * KL_G) {
-        if (kt == 16) return launch_assign_lds<16>(X, n, d, cp, cnorm, K, ctiles, assign, counts, rank, st);
-        if (kt == 32) return launch_assign_lds<32>(X, n, d, cp, cnorm, K, ctiles, assign, counts, rank, st);
-        if (kt == 48) return launch_assign_lds<48>(X, n, d, cp, cnorm, K, ctiles, assign, counts, rank, st);
+    if (ctiles < KL_NW * KL_G) return false;
+    hipError_t e;
+    if (kt == 16) e = prepare_assign_lds<16>();
+    else if (kt == 32) e = prepare_assign_lds<32>();
+    else if (kt == 48) e = prepare_assign_lds<48>();
+    else return false;
+    if (e == hipSuccess) return true;
+    (void)hipGetLastError();   // the split-k kernel serves the call: no error of its
+    return false;
+}
+
+bool vpk_kmeans_assign_gemm(const void *X, long n, int d, const void *cp, const float *cnorm, int K, int kt, int ctiles,
+                            bool rows_in_lds, int32_t *assign, int32_t *counts, int32_t *rank, hipStream_t st)
+{
+    if (rows_in_lds) {
+        if (kt == 16) launch_assign_lds<16>(X, n, d, cp, cnorm, K, ctiles, assign, counts, rank, st);
+        else if (kt == 32) launch_assign_lds<32>(X, n, d, cp, cnorm, K, ctiles, assign, counts, rank, st);
+        else launch_assign_lds<48>(X, n, d, cp, cnorm, K, ctiles, assign, counts, rank, st);
+        return true;
     }
     const dim3 grid((unsigned)((n + 63) / 64)), block(256);
 #define VP_KM_CASE(KW)                                                                                                \

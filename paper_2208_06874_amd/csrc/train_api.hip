@@ -89,6 +89,7 @@ vp_status vp_kmeans(const void *x, int64_t n, int32_t d, int32_t K, int32_t iter
     const bool mean_form = vpk_kmeans_mean_form(K);
     int32_t *const rank_buf = mean_form && (size_t)n * 4 <= (size_t)K * d * 8 ? (int32_t *)acc : nullptr;
     if (!mean_form) vpk_fill_u32(acc, (size_t)K * d * 2, 0u, st);
+    const bool rows_in_lds = n >= 4096 && vpk_kmeans_rows_in_lds(L.kt, L.ctiles);
     for (int it = 0; it <= iters; ++it) {
         // Eq. 2 operands of the current centroids
         vpk_pack_rows(centroids, K, d, L.kt, cp, st);
@@ -97,7 +98,7 @@ vp_status vp_kmeans(const void *x, int64_t n, int32_t d, int32_t K, int32_t iter
         // memberships: the GEMM-shaped kernel when there are enough vectors to fill the chip with
         // 64-vector workgroups, else (or for k-extents it is not built for) the decode-time kernel
         int32_t *const rank = it < iters ? rank_buf : nullptr;   // (the last pass only assigns)
-        const bool gemm = n >= 4096 && vpk_kmeans_assign_gemm(x, (long)n, d, cp, cnorm, K, L.kt, L.ctiles, assign, counts, rank, st);
+        const bool gemm = n >= 4096 && vpk_kmeans_assign_gemm(x, (long)n, d, cp, cnorm, K, L.kt, L.ctiles, rows_in_lds, assign, counts, rank, st);
         for (int64_t r0 = 0; !gemm && r0 < n; r0 += CHUNK_ROWS) {
             const int rows = (int)std::min<int64_t>(CHUNK_ROWS, n - r0);
             vpk_centroid((const char *)x + (size_t)r0 * d * 2, rows, d, cp, cnorm, K, L.kt, L.ctiles, L.tpw, L.parts,

@@ -1,0 +1,43 @@
+"""Which membership kernel vp_kmeans takes, read from the launches it makes (no GPU: the program of
+kmeans_launch_main.cpp stands in front of the HIP runtime)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+MEMBERSHIP = ("kmeans_assign_lds_kernel", "kmeans_assign_gemm_kernel", "centroid_small_kernel", "centroid_kernel")
+
+
+@pytest.fixture(scope="module")
+def launches(tmp_path_factory):
+    from paper_2208_06874_amd import vp
+    if shutil.which("g++") is None:
+        pytest.skip("needs g++")
+    if not os.path.exists(vp.LIB_PATH):
+        pytest.skip("libvp.so is not built")
+    exe = tmp_path_factory.mktemp("kmeans") / "kmeans_launch"
+    libdir = os.path.dirname(vp.LIB_PATH)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-rdynamic", "-I", os.path.join(ROOT, "include"),
+                    os.path.join(ROOT, "tests", "kmeans_launch_main.cpp"), "-L", libdir, "-lvp", "-Wl,-rpath," + libdir,
+                    "-Wl,--allow-shlib-undefined", "-o", str(exe)], check=True, capture_output=True)
+
+    def run(n, d, K, iters=0, fail_attribute=False):
+        """(status, attribute calls, error left behind, the membership kernel of every pass)"""
+        r = subprocess.run([str(exe), str(int(fail_attribute)), str(n), str(d), str(K), str(iters)], capture_output=True,
+                           text=True, timeout=60)
+        assert r.returncode == 0, r.stdout + r.stderr
+        lines = r.stdout.split("\n")
+        passes = [m for name in lines[3:] for m in MEMBERSHIP if m in name]
+        return int(lines[0]), int(lines[1]), int(lines[2]), passes
+
+    return run
+
+
+@pytest.mark.parametrize("d", [512, 1024, 1536])
+def test_lds_size_is_asked_for_once_and_may_be_refused(launches, d):
+    """The rows-in-LDS kernel needs its LDS size set.  That is done once a call; if it is refused, the split-k
+    kernel serves every pass and the call succeeds with no error left behind."""
+    assert launches(8192, d, 1000, iters=3, fail_attribute=True) == (0, 1, 0, ["kmeans_assign_gemm_kernel"] * 4)
+    assert launches(8192, d, 1000, iters=3) == (0, 1, 0, ["kmeans_assign_lds_kernel"] * 4)
