@@ -18,7 +18,13 @@ namespace {
 
 __device__ inline bool part_less(float s, int j, float s2, int j2) { return s < s2 || (s == s2 && j < j2); }
 
+// The membership kernels below count the members.  With RANK they keep what the counting atomics return, each vector's
+// number among its cluster's members (kmeans_place_kernel); without it they do not ask, because a wavefront waits for
+// what it asks for: the split-k kernel at 49,200 vectors, 240 clusters, d = 1024: 87 us per call without, 96 with it;
+// 16,400 vectors, 150 clusters, d = 1536: 59 and 64.
+
 // Finishes Eq. 2 for a chunk of rows (minimum over the centroid ranges) and counts the members.
+template <bool RANK>
 __global__ __launch_bounds__(256) void kmeans_assign_kernel(const int2 *__restrict__ cpart, int parts, int rows,
                                                             int K, int32_t *__restrict__ assign,
                                                             int32_t *__restrict__ counts, int32_t *__restrict__ rank)
@@ -37,8 +43,10 @@ __global__ __launch_bounds__(256) void kmeans_assign_kernel(const int2 *__restri
     }
     if ((unsigned)bj >= (unsigned)K) bj = 0;   // only when every score is NaN: keep the index in range
     assign[r] = bj;
-    const int before = atomicAdd(&counts[bj], 1);
-    if (rank) rank[r] = before;
+    if (RANK)
+        rank[r] = atomicAdd(&counts[bj], 1);
+    else
+        atomicAdd(&counts[bj], 1);
 }
 
 // Membership of many vectors at once: Eq. 2 as a GEMM.  One workgroup takes 64 vectors and
@@ -47,7 +55,7 @@ __global__ __launch_bounds__(256) void kmeans_assign_kernel(const int2 *__restri
 // streaming its slice of every packed centroid tile (the centroids stay in the caches), so
 // each 1 KiB load feeds four MFMAs; the partial inner products of a group of 16 centroids meet
 // in LDS and wavefront w keeps the running (min, argmin) of vector tile w.
-template <int KW>
+template <int KW, bool RANK>
 __global__ __launch_bounds__(256, (KW <= 8 ? 2 : 1)) void kmeans_assign_gemm_kernel(
     const uint4 *__restrict__ X, long n, int d, const uint4 *__restrict__ cp, const float *__restrict__ cnorm, int K,
     int ctiles, int32_t *__restrict__ assign, int32_t *__restrict__ counts, int32_t *__restrict__ rank)
@@ -145,8 +153,10 @@ __global__ __launch_bounds__(256, (KW <= 8 ? 2 : 1)) void kmeans_assign_gemm_ker
     if (q == 0 && row < n) {
         if ((unsigned)best_j >= (unsigned)K) best_j = 0;   // only when every score is NaN
         assign[row] = best_j;
-        const int before = atomicAdd(&counts[best_j], 1);
-        if (rank) rank[row] = before;
+        if (RANK)
+            rank[row] = atomicAdd(&counts[best_j], 1);
+        else
+            atomicAdd(&counts[best_j], 1);
     }
 }
 
@@ -168,7 +178,7 @@ constexpr int km_lds_row_tiles(int kt) { return kt == 48 ? 3 : 4; }
 // Ten iterations of vp_kmeans with it, us per iteration, split-k kernel -> this one: 131,072 vectors x 1,000 clusters
 // d = 1024: 417 -> 405, d = 512: 312 -> 274, d = 1536: 892 -> 746; 6,000 x 1,000, d = 1024: 108 -> 77;
 // 4,099 x 1,000, d = 512: 84 -> 52.  (Steps of three groups spill: 526 at the first.)
-template <int KT>
+template <int KT, bool RANK>
 __global__ __launch_bounds__(KL_NW * 64) void kmeans_assign_lds_kernel(
     const uint4 *__restrict__ X, long n, int d, const uint4 *__restrict__ cp, const float *__restrict__ cnorm, int K,
     int ctiles, int nitems, int32_t *__restrict__ assign, int32_t *__restrict__ counts, int32_t *__restrict__ rank)
@@ -234,7 +244,7 @@ __global__ __launch_bounds__(KL_NW * 64) void kmeans_assign_lds_kernel(
             }
         }
         // (the item before: its atomics have come back with the vectors)
-        if (rank && before_row >= 0) rank[before_row] = before;
+        if (RANK && before_row >= 0) rank[before_row] = before;
         before_row = -1;
         __syncthreads();   // the vectors are staged; red_* of the item before has been read
 
@@ -367,11 +377,15 @@ __global__ __launch_bounds__(KL_NW * 64) void kmeans_assign_lds_kernel(
             }
             if ((unsigned)bj >= (unsigned)K) bj = 0;   // only when every score is NaN
             assign[r0 + tid] = bj;
-            before = atomicAdd(&counts[bj], 1);
-            before_row = r0 + tid;
+            if (RANK) {
+                before = atomicAdd(&counts[bj], 1);
+                before_row = r0 + tid;
+            } else {
+                atomicAdd(&counts[bj], 1);
+            }
         }
     }
-    if (rank && before_row >= 0) rank[before_row] = before;
+    if (RANK && before_row >= 0) rank[before_row] = before;
 }
 
 template <int KT>
@@ -386,8 +400,12 @@ constexpr size_t km_lds_bytes()
 template <int KT>
 hipError_t prepare_assign_lds()
 {
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(kmeans_assign_lds_kernel<KT>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)km_lds_bytes<KT>());
+    const int bytes = (int)km_lds_bytes<KT>();
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kmeans_assign_lds_kernel<KT, false>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e != hipSuccess) return e;
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(kmeans_assign_lds_kernel<KT, true>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 
 template <int KT>
@@ -396,8 +414,9 @@ void launch_assign_lds(const void *X, long n, int d, const void *cp, const float
 {
     constexpr int rows = 16 * km_lds_row_tiles(KT);
     const int nitems = (int)((n + rows - 1) / rows);
-    hipLaunchKernelGGL((kmeans_assign_lds_kernel<KT>), dim3(std::min(nitems, 256)), dim3(KL_NW * 64), km_lds_bytes<KT>(),
-                       st, (const uint4 *)X, n, d, (const uint4 *)cp, cnorm, K, ctiles, nitems, assign, counts, rank);
+    const auto kernel = rank ? kmeans_assign_lds_kernel<KT, true> : kmeans_assign_lds_kernel<KT, false>;
+    hipLaunchKernelGGL(kernel, dim3(std::min(nitems, 256)), dim3(KL_NW * 64), km_lds_bytes<KT>(), st, (const uint4 *)X, n,
+                       d, (const uint4 *)cp, cnorm, K, ctiles, nitems, assign, counts, rank);
 }
 
 // start[j] = number of members of clusters below j; cursor[j] = start[j].  One workgroup.
@@ -833,8 +852,9 @@ void vpk_fill_u32(void *p, size_t n, uint32_t v, hipStream_t st)
 void vpk_kmeans_assign(const void *cpart, int parts, int rows, int K, int32_t *assign, int32_t *counts,
                        int32_t *rank, hipStream_t st)
 {
-    hipLaunchKernelGGL(kmeans_assign_kernel, dim3((rows + 255) / 256), dim3(256), 0, st, (const int2 *)cpart, parts,
-                       rows, K, assign, counts, rank);
+    const auto kernel = rank ? kmeans_assign_kernel<true> : kmeans_assign_kernel<false>;
+    hipLaunchKernelGGL(kernel, dim3((rows + 255) / 256), dim3(256), 0, st, (const int2 *)cpart, parts, rows, K, assign,
+                       counts, rank);
 }
 
 bool vpk_kmeans_rows_in_lds(int kt, int ctiles)
@@ -864,8 +884,9 @@ bool vpk_kmeans_assign_gemm(const void *X, long n, int d, const void *cp, const 
     const dim3 grid((unsigned)((n + 63) / 64)), block(256);
 #define VP_KM_CASE(KW)                                                                                                \
     case KW * 4:                                                                                                      \
-        hipLaunchKernelGGL((kmeans_assign_gemm_kernel<KW>), grid, block, 0, st, (const uint4 *)X, n, d,               \
-                           (const uint4 *)cp, cnorm, K, ctiles, assign, counts, rank);                                \
+        hipLaunchKernelGGL((rank ? kmeans_assign_gemm_kernel<KW, true> : kmeans_assign_gemm_kernel<KW, false>), grid, \
+                           block, 0, st, (const uint4 *)X, n, d, (const uint4 *)cp, cnorm, K, ctiles, assign, counts, \
+                           rank);                                                                                     \
         return true;
     switch (kt) {
         VP_KM_CASE(2)

@@ -1,6 +1,7 @@
 """Which membership kernel vp_kmeans takes, read from the launches it makes (no GPU: the program of
 kmeans_launch_main.cpp stands in front of the HIP runtime)."""
 import os
+import re
 import shutil
 import subprocess
 
@@ -24,20 +25,33 @@ def launches(tmp_path_factory):
                     "-Wl,--allow-shlib-undefined", "-o", str(exe)], check=True, capture_output=True)
 
     def run(n, d, K, iters=0, fail_attribute=False):
-        """(status, attribute calls, error left behind, the membership kernel of every pass)"""
+        """(status, attribute calls, error left behind, the membership kernel of every pass, which passes keep numbers)"""
         r = subprocess.run([str(exe), str(int(fail_attribute)), str(n), str(d), str(K), str(iters)], capture_output=True,
                            text=True, timeout=60)
         assert r.returncode == 0, r.stdout + r.stderr
         lines = r.stdout.split("\n")
         passes = [m for name in lines[3:] for m in MEMBERSHIP if m in name]
-        return int(lines[0]), int(lines[1]), int(lines[2]), passes
+        # the counting kernels' RANK argument, as it stands in the mangled names
+        kept = [bool(int(b)) for name in lines[3:] for b in re.findall(r"kmeans_assign\w*_kernelI(?:Li\d+E)?Lb([01])E", name)]
+        return int(lines[0]), int(lines[1]), int(lines[2]), passes, kept
 
     return run
 
 
 @pytest.mark.parametrize("d", [512, 1024, 1536])
 def test_lds_size_is_asked_for_once_and_may_be_refused(launches, d):
-    """The rows-in-LDS kernel needs its LDS size set.  That is done once a call; if it is refused, the split-k
-    kernel serves every pass and the call succeeds with no error left behind."""
-    assert launches(8192, d, 1000, iters=3, fail_attribute=True) == (0, 1, 0, ["kmeans_assign_gemm_kernel"] * 4)
-    assert launches(8192, d, 1000, iters=3) == (0, 1, 0, ["kmeans_assign_lds_kernel"] * 4)
+    """The rows-in-LDS kernel needs its LDS size set.  That is done once a call (for its two forms); if it is refused,
+    the split-k kernel serves every pass and the call succeeds with no error left behind."""
+    assert launches(8192, d, 1000, iters=3, fail_attribute=True)[:4] == (0, 1, 0, ["kmeans_assign_gemm_kernel"] * 4)
+    assert launches(8192, d, 1000, iters=3)[:4] == (0, 2, 0, ["kmeans_assign_lds_kernel"] * 4)
+
+
+@pytest.mark.parametrize("n,d,K,numbers", [(8192, 1024, 1000, True), (8192, 1024, 200, False), (8192, 256, 256, True),
+                                           (8192, 256, 255, False), (3000, 1024, 1000, True), (3000, 1024, 100, False),
+                                           (8192, 768, 300, True), (8192, 768, 100, False),
+                                           (2 * 256 * 128, 128, 256, True), (2 * 256 * 128 + 1, 128, 256, False)])
+def test_members_are_numbered_only_where_the_numbers_are_used(launches, n, d, K, numbers):
+    """Passes in front of the means number the members of many clusters, where there is room for the numbers; the last
+    pass, and every pass over few clusters, only counts them."""
+    assert launches(n, d, K, iters=2)[4] == [numbers, numbers, False]
+    assert launches(n, d, K, iters=0)[4] == [False]
