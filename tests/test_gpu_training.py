@@ -86,6 +86,25 @@ def test_membership_with_the_vectors_in_lds(oracle, n, d, K):
     assert np.array_equal(counts, np.bincount(assign, minlength=K))
 
 
+# The means need the members of every cluster in one place: a vector goes where the counting atomics' numbers put it.
+# Rows-in-LDS kernel with workgroups that carry the numbers from one item to the next (more than 256 items at d_pad 512, 1024
+# and 1536); the split-k kernel; two chunks of 65,536 vectors of the decode-time kernel (d_pad 768); and the scatter that
+# stays where the numbers have no room (256 clusters or more and n > 2 * K * d).
+@pytest.mark.parametrize("n,d,K", [(16390, 504, 257), (16390, 1000, 256), (15400, 1288, 256), (16390, 1024, 257),
+                                   (65800, 520, 256), (4200, 8, 256)])
+def test_members_are_placed_by_their_numbers(oracle, n, d, K):
+    rs = np.random.default_rng(n + d + K)
+    X = (rs.standard_normal((K, d))[rs.integers(0, K, n)] + 0.3 * rs.standard_normal((n, d))).astype(np.float16)
+    C0 = X[np.sort(rs.choice(n, K, replace=False))].copy()
+    print("members", n, d, K, flush=True)
+    _same, assign, counts = _gpu_kmeans(X, C0, 0)
+    assert np.array_equal(counts, np.bincount(assign, minlength=K))
+    new, _a, _c = _gpu_kmeans(X, C0, 1)
+    st = oracle.kmeans_step(X, C0.astype(np.float64), forced=assign)
+    want = st["C"].astype(np.float16).view(np.uint16)
+    assert np.array_equal(new, want), "%d centroid coordinates differ" % (new != want).sum()
+
+
 def test_twenty_iterations_and_determinism(oracle):
     cfg, X, q, C0 = _mixture("tiny", 8192)
     Cb, assign, counts = _gpu_kmeans(X, C0, 20)
