@@ -419,6 +419,34 @@ void launch_assign_lds(const void *X, long n, int d, const void *cp, const float
                        d, (const uint4 *)cp, cnorm, K, ctiles, nitems, assign, counts, rank);
 }
 
+// Whether the rows-in-LDS kernel is the faster one for the membership of n vectors.  From 16 groups of centroids on each
+// of its eight wavefronts has a step of two groups.  With a few groups more some wavefronts take a second step and the
+// others wait, and just past whole rounds of 256 items most of the chip waits; the split-k kernel has no steps to hand
+// out, and its workgroups come 512 (d_pad 1536: 256) at a time.  The kernel stays ahead of either loss but not of both.  The lines are
+// where the two cross on 1,500 sizes of 241 to 1,300 clusters and 4,096 to 131,072 vectors; us per call without
+// iterations, split-k kernel -> this one:
+//   d_pad 1024, 288 clusters: 16,384 vectors 45 -> 39, 16,400 47 -> 50, 26,000 55 -> 53, 49,200 85 -> 94, 82,000 120 -> 135;
+//     384 clusters: 49 -> 42, 49 -> 49, 59 -> 53, 94 -> 88, 136 -> 136; 1,000 clusters: 16,400 82 -> 77, 131,072 321 -> 303
+//   d_pad 1536 (48 vectors an item here, 64 there), 288 clusters: 12,288 vectors 49 -> 42, 12,290 47 -> 55, 16,500 72 -> 57,
+//     25,000 80 -> 83, 131,072 293 -> 280; 480 clusters: 61 -> 47, 59 -> 63, 97 -> 64, 102 -> 90, 394 -> 315
+//   d_pad 512: faster everywhere (288 clusters: 16,400 36 -> 31, 131,072 140 -> 116)
+bool rows_in_lds_faster(int kt, int ctiles, long n)
+{
+    if (ctiles < KL_NW * KL_G || (kt != 16 && kt != 32 && kt != 48)) return false;
+    const long rows = 16 * km_lds_row_tiles(kt);
+    const long items = (n + rows - 1) / rows;
+    if (kt == 16 || items <= 256) return true;
+    if (kt == 32) {
+        // a last round of 256 that is up to half full, where the other kernel's last round of 512 is as well
+        const long last = items % 512;
+        const bool uneven = ctiles > 16 && ctiles <= (items <= 512 ? 27 : 19);
+        return !(uneven && last > 256 && last <= (items <= 512 ? 320 : 384));
+    }
+    // two rounds here and one there; three rounds and hardly two
+    if (n <= 64 * 256) return ctiles > 30;
+    return !(ctiles > 16 && ctiles <= 19 && items > 512 && n <= 64 * 440);
+}
+
 // start[j] = number of members of clusters below j; cursor[j] = start[j].  One workgroup.
 __global__ __launch_bounds__(1024) void kmeans_scan_kernel(const int32_t *__restrict__ counts, int K,
                                                            int32_t *__restrict__ start, int32_t *__restrict__ cursor)
@@ -857,11 +885,9 @@ void vpk_kmeans_assign(const void *cpart, int parts, int rows, int K, int32_t *a
                        counts, rank);
 }
 
-bool vpk_kmeans_rows_in_lds(int kt, int ctiles)
+bool vpk_kmeans_rows_in_lds(int kt, int ctiles, long n)
 {
-    // Enough centroids to give each of the eight wavefronts of the rows-in-LDS kernel a step of its own: with fewer, some
-    // would idle (and the ring in front of the first step would start past the last group).
-    if (ctiles < KL_NW * KL_G) return false;
+    if (!rows_in_lds_faster(kt, ctiles, n)) return false;
     hipError_t e;
     if (kt == 16) e = prepare_assign_lds<16>();
     else if (kt == 32) e = prepare_assign_lds<32>();

@@ -89,7 +89,7 @@ vp_status vp_kmeans(const void *x, int64_t n, int32_t d, int32_t K, int32_t iter
     const bool mean_form = vpk_kmeans_mean_form(K);
     int32_t *const rank_buf = mean_form && (size_t)n * 4 <= (size_t)K * d * 8 ? (int32_t *)acc : nullptr;
     if (!mean_form) vpk_fill_u32(acc, (size_t)K * d * 2, 0u, st);
-    const bool rows_in_lds = n >= 4096 && vpk_kmeans_rows_in_lds(L.kt, L.ctiles);
+    const bool rows_in_lds = n >= 4096 && vpk_kmeans_rows_in_lds(L.kt, L.ctiles, (long)n);
     for (int it = 0; it <= iters; ++it) {
         // Eq. 2 operands of the current centroids
         vpk_pack_rows(centroids, K, d, L.kt, cp, st);

@@ -94,7 +94,7 @@ void vpk_fill_u32(void *p, size_t n, uint32_t v, hipStream_t st);
 void vpk_kmeans_assign(const void *cpart, int parts, int rows, int K, int32_t *assign, int32_t *counts,
                        int32_t *rank, hipStream_t st);
 // (true: the rows-in-LDS kernel takes the passes of this call, and its LDS size is set)
-bool vpk_kmeans_rows_in_lds(int kt, int ctiles);
+bool vpk_kmeans_rows_in_lds(int kt, int ctiles, long n);
 bool vpk_kmeans_assign_gemm(const void *X, long n, int d, const void *cp, const float *cnorm, int K, int kt, int ctiles,
                             bool rows_in_lds, int32_t *assign, int32_t *counts, int32_t *rank, hipStream_t st);
 void vpk_kmeans_bucket(const int32_t *assign, const int32_t *rank, long n, const int32_t *counts, int K, int32_t *start,

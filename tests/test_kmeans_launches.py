@@ -55,3 +55,21 @@ def test_members_are_numbered_only_where_the_numbers_are_used(launches, n, d, K,
     pass, and every pass over few clusters, only counts them."""
     assert launches(n, d, K, iters=2)[4] == [numbers, numbers, False]
     assert launches(n, d, K, iters=0)[4] == [False]
+
+
+@pytest.mark.parametrize("d,n,K,lds", [
+    (1024, 4096, 240, False), (1024, 4096, 241, True),                                    # a step for every wavefront
+    (1024, 16384, 257, True), (1024, 16385, 257, False), (1024, 16385, 256, True),        # a nearly empty second round
+    (1024, 20480, 432, False), (1024, 20481, 432, True), (1000, 16385, 433, True),
+    (1024, 49152, 257, True), (1024, 49153, 257, False), (1024, 49153, 304, False), (1024, 49153, 305, True),
+    (1024, 57344, 272, False), (1024, 57345, 272, True), (1000, 82000, 272, False), (1024, 98304, 272, True),
+    (1536, 12288, 257, True), (1536, 12289, 241, False), (1440, 16384, 480, False),       # one round of the split-k kernel
+    (1536, 16384, 481, True), (1536, 16385, 257, True), (1536, 24576, 257, True),
+    (1536, 24577, 304, False), (1536, 28160, 272, False), (1536, 28161, 272, True), (1536, 24577, 305, True),
+    (1536, 24577, 256, True), (1536, 131072, 272, True),
+    (512, 16385, 257, True), (512, 131072, 257, True), (512, 131072, 240, False),
+])
+def test_membership_kernel_by_size(launches, d, n, K, lds):
+    """Both sides of every line of the rule: where the rows-in-LDS kernel measured slower, the other one runs."""
+    want = "kmeans_assign_lds_kernel" if lds else "kmeans_assign_gemm_kernel"
+    assert launches(n, d, K)[:4] == (0, 2 * int(lds), 0, [want])
