@@ -132,7 +132,8 @@ __device__ inline uint4 load_piece(const uint4 *p)
     return *p;
 }
 
-// Which item a workgroup takes.  Workgroups are handed to the 8 XCDs in turn; for a
+// Which item a workgroup takes (in the rows-in-LDS kernel vp_item_of_workgroup_even says so
+// instead).  Workgroups are handed to the 8 XCDs in turn; for a
 // single bucket whose row groups share tiles (the full projection) each XCD gets its
 // own candidate ranges and all row groups of a range follow each other on that XCD,
 // so the range is fetched from HBM once and then served by that XCD's L2.  In a clustered

@@ -501,8 +501,9 @@ vp_status run_full(const char *fn, const vp_index *I, const void *hidden, int N,
     const int max_items = max_items_full(I, N);
     vpk_plan_full(N, I->V, I->L.vtiles, rpi, sb_target(I, N, row_tiles, k), sb_min(I, N, row_tiles, k), max_items, perm, rowplan,
                   floors, items, hdr, dbg_row_off, st);
-    // the same split the planning kernel makes; with several row groups the projection kernel
-    // deals candidate ranges to the XCDs, which needs the grid padded to 8 ranges at a time
+    // the same split the planning kernel makes; with several row groups the kernels that deal whole
+    // candidate ranges to the XCDs need the grid padded to 8 ranges at a time (the rows-in-LDS kernel,
+    // which splits the items evenly, would do with the items rounded up to 8)
     const int rgs = ceil_div(N, rpi);
     const int tpw = sb_tiles_per_wave(I, N, rgs, row_tiles, k);
     const int chunks = ceil_div(I->L.vtiles, (long)tpw * VP_WG_WAVES);

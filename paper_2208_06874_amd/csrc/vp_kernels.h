@@ -59,7 +59,7 @@ void vpk_project_gemm(const VpSlabSet &set, const void *hidden, int d, const int
                       const VpPlanHeader *hdr, int grid_items, int k, float *partials, unsigned int *bounds,
                       const VpMaskInfo *mask, hipStream_t st);
 
-// the same with the 64 rows of an item held in LDS (d_pad <= 1024, k <= 8); floors: [N] per-row bounds
+// the same with the 64 rows of an item (48 at d_pad 1536) held in LDS; floors: [N] per-row bounds
 size_t vpk_project_rows_lds_bytes(int k, int kt);
 bool vpk_project_rows_lds_supported(int kt, int k);
 int vpk_project_rows_lds_row_tiles(int kt);

@@ -59,7 +59,9 @@ struct VpPlanHeader {
     int32_t overflow;        // set if the item list did not fit (never expected)
     int32_t total_tiles;
     // Workgroup -> item swizzle.  > 1: a single bucket whose row groups share tiles (the
-    // full-vocabulary projection): the number of row groups, with swz_chunks candidate ranges.
+    // full-vocabulary projection, masked or not): the number of row groups, with swz_chunks candidate
+    // ranges.  The kernels of 16 and 32 rows and the split-k one deal whole ranges to the XCDs; the
+    // rows-in-LDS kernel takes it as a mere sign and splits the item list evenly.
     // < 0: a clustered plan with buckets of many row groups: -(items per block), blocks of
     // consecutive items are dealt to the 8 XCDs in turn and every XCD starts at another place
     // of the list (see item_of_workgroup).  0: none.
@@ -185,8 +187,8 @@ static inline __host__ __device__ int vp_item_of_workgroup(int wg, int total_ite
 // Dealing whole candidate ranges instead leaves XCDs with more items than compute units whenever the
 // ranges do not divide by eight - 6 row groups x 42 ranges are 252 items for 256 compute units, but 36 for
 // two of the XCDs and their 32 compute units, a second round for four workgroups (333 rows of
-// d = 1000, V = 150,001: 227 us in the kernel, 149 us with this map).  The row groups of
-// a range still follow each other on one XCD, but for the ranges at the seven seams.
+// d = 1000, V = 150,001: 208 us in the kernel, 129 us with this map).  The row groups of
+// a range still follow each other on one XCD, but for the ranges at the seven seams, which two XCDs read.
 static inline __host__ __device__ int vp_item_of_workgroup_even(int wg, int total_items)
 {
     const int per = (total_items + 7) / 8;
