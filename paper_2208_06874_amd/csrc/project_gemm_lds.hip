@@ -3,7 +3,7 @@
 // masked full projection, the batch-union form) of more than 16 rows and k-extents up to
 // d_pad = 1536.
 //
-// An item is 64 rows (48 at d_pad = 1536, where 64 do not fit) x a range of candidate groups, one
+// An item is 64 rows (48 at d_pad = 1280 and 1536, where 64 do not fit) x a range of candidate groups, one
 // workgroup of eight wavefronts.  The rows are staged once in LDS in MFMA operand order (4 or 3
 // row tiles x KT KiB) and never move again.  The range is cut into steps of four candidate groups (64 candidates); wavefront w
 // takes steps w, w + 8, ...  A step streams the four groups' tiles straight into registers
@@ -39,8 +39,9 @@ namespace {
 
 constexpr int L_NW = 8;        // wavefronts per workgroup
 constexpr int L_G = 4;         // candidate groups per step
-// row tiles per item: four (64 rows), or three where four do not fit the LDS (d_pad = 1536: 48 rows, 144 KiB)
-constexpr int lds_row_tiles(int kt) { return kt == 48 ? 3 : 4; }
+// row tiles per item: four (64 rows), or three where four do not fit the LDS (48 rows: 120 KiB at d_pad = 1280,
+// 144 KiB at 1536)
+constexpr int lds_row_tiles(int kt) { return kt > 32 ? 3 : 4; }
 constexpr int L_PF = 4;        // k-tiles of the four groups kept in flight
 constexpr int VP_MAX_TOPK_LANES = 32;   // the epilogue writes a row's list with one lane per entry
 
@@ -476,10 +477,13 @@ size_t vpk_project_rows_lds_bytes(int k, int kt)
     return (size_t)rows * kt * (VP_TILE_BYTES / 16) + (size_t)k * rows * 8 + rows * 4;
 }
 
-// built for d_pad = 256, 512, 1024 and 1536 (the rows of an item must fit the LDS beside its lists)
+// Built for d_pad = 256 to 1536 (beyond, the rows of an item do not fit the LDS beside its lists).  The alternative at 768
+// and 1280, items of 16 rows, reads W once per 16 rows through the L2; full projection, V = 150,000, top-3, us per call,
+// those -> this kernel: d = 768, N = 17: 102 -> 50, 64: 119 -> 55, 256: 216 -> 82, 1,024: 660 -> 227, 8,192: 6,290 -> 1,667;
+// d = 1280: 142 -> 73, 195 -> 90, 431 -> 161, 1,356 -> 502, 10,036 -> 3,596.
 bool vpk_project_rows_lds_supported(int kt, int k)
 {
-    return (kt == 8 || kt == 16 || kt == 32 || kt == 48) && k >= 1 && k <= VP_MAX_TOPK_LANES;
+    return kt % 8 == 0 && kt >= 8 && kt <= 48 && k >= 1 && k <= VP_MAX_TOPK_LANES;
 }
 // row tiles of an item of that kernel
 int vpk_project_rows_lds_row_tiles(int kt) { return lds_row_tiles(kt); }
@@ -488,7 +492,9 @@ hipError_t vpk_project_rows_lds_prepare()
 {
     hipError_t e = allow_lds_bytes<8>();
     if (e == hipSuccess) e = allow_lds_bytes<16>();
+    if (e == hipSuccess) e = allow_lds_bytes<24>();
     if (e == hipSuccess) e = allow_lds_bytes<32>();
+    if (e == hipSuccess) e = allow_lds_bytes<40>();
     if (e == hipSuccess) e = allow_lds_bytes<48>();
     return e;
 }
@@ -511,7 +517,9 @@ void vpk_project_rows_lds(const VpSlabSet &set, const void *hidden, int d, const
     switch (set.kt) {
         VP_LDS_CASE(8)
         VP_LDS_CASE(16)
+        VP_LDS_CASE(24)
         VP_LDS_CASE(32)
+        VP_LDS_CASE(40)
         VP_LDS_CASE(48)
         default: break;   // callers check vpk_project_rows_lds_supported
     }

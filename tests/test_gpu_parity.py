@@ -699,6 +699,31 @@ def test_many_row_kernels_beyond_d_1024(oracle, d, gemm_lds):
         pu.check_projection(oracle, W, b, C, off, ids, H, k, m_ids, m_logp, m_g)
 
 
+@pytest.mark.parametrize("d", [760, 768, 1032, 1280])
+def test_many_row_kernel_at_d_pad_768_and_1280(oracle, d):
+    """The rows-in-LDS kernel at d_pad 768 (64 rows per item) and 1280 (48): row counts around its items, a width
+    that fills the last k-tiles with zeros, top-1 (kept in registers) to top-32, plain, union and masked."""
+    r, W, b, C = _small_model(30 + d, d, 1200, 4)
+    off, ids = _random_lists(r, 4, 1200, 100, 500)
+    B = Built(W, b, C, off, ids, k_max=32)
+    per = 64 if d <= 768 else 48
+    for N, k in ((17, 1), (per, 8), (per + 1, 32), (2 * per + 1, 2)):
+        H = _rows(r, C, N)
+        f_ids, f_logp = B.project_full(H, k)
+        pu.check_full(oracle, W, b, H, k, f_ids, f_logp)
+        u_ids, u_logp, u_g, u_n = B.project_union(H, k)
+        pu.check_union(oracle, W, b, C, off, ids, H, k, u_ids, u_logp, u_g, u_n)
+        B.index.set_option("dispatch", 1)
+        B.index.set_option("cost_bw_slab_gbs", 1)      # force the masked projection
+        try:
+            m_ids, m_logp, m_g = B.project(H, k)
+            assert _planner_mode(B.index, N) == 1
+        finally:
+            B.index.set_option("cost_bw_slab_gbs", 6800)
+            B.index.set_option("dispatch", 0)
+        pu.check_projection(oracle, W, b, C, off, ids, H, k, m_ids, m_logp, m_g)
+
+
 def test_empty_active_sets(oracle):
     """A cluster whose active set is empty (a cluster that lost its members in training): rows that fall into
     it get ids -1 and log-probs -inf in every form of the projection; the other rows are untouched."""
