@@ -210,7 +210,8 @@ int max_items_clustered(const vp_index *I, int N)
 // (the grid of the full projection is padded to 8 candidate ranges at a time, one per XCD)
 int max_items_full(const vp_index *I, int N)
 {
-    // (the kernel with the rows in LDS takes up to eight rounds of its one item per compute unit)
+    // (the kernel with the rows in LDS takes up to eight rounds of its one item per compute unit, and with many row
+    // groups at least eight ranges of each)
     return std::max(I->full_target_items, std::max(I->gemm_target_items, 8 * I->gemm_lds_items)) +
            8 * ceil_div(N, VP_ROWS_PER_ITEM) + 2;
 }
@@ -305,10 +306,11 @@ inline bool use_gemm_lds(const vp_index *I, int row_tiles, int k)
            row_tiles == vpk_project_rows_lds_row_tiles(I->L.kt);
 }
 // Item count of the kernel that keeps an item's rows in LDS: whole rounds of its one workgroup per
-// compute unit (vp_rounds_item_count).
+// compute unit (vp_swept_item_count).
 inline int gemm_lds_item_count(const vp_index *I, int N, int row_tiles)
 {
-    return vp_rounds_item_count(ceil_div(N, VP_ROWS_PER_ITEM * row_tiles), I->gemm_lds_items, I->L.vtiles);
+    return vp_swept_item_count(ceil_div(N, VP_ROWS_PER_ITEM * row_tiles), I->gemm_lds_items, I->L.vtiles, I->L.kt,
+                               max_items_full(I, N));
 }
 inline int sb_target(const vp_index *I, int N, int row_tiles, int k)
 {

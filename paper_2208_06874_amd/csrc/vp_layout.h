@@ -133,6 +133,39 @@ static inline __host__ __device__ int vp_rounds_item_count(int rgs, int slots, i
     return best;
 }
 
+// The same with 16 row groups and more, where it matters which items run side by side.  An XCD walks its eighth of the
+// item list (vp_item_of_workgroup_even), the row groups of a range one behind the other, and its workgroups read the range
+// from one L2 only while they stay within a few steps of each other.  They do where every XCD has ranges of its own
+// (their number a multiple of eight); ranges that straddle XCDs cost about 6 %, and over long ranges that several XCDs
+// share the workgroups drift apart until most of them read W through the memory side.  Full projection, top-4, V = 250,000,
+// us with the rule above -> with eight ranges or a multiple: d = 1024, N = 4,096: 2,849 -> 1,764, 8,192: 4,986 -> 3,494,
+// 12,000: 7,131 -> 5,143, 16,384: 7,571 -> 6,946; d = 1536, N = 3,000: 4,398 -> 2,252, 6,000: 8,115 -> 4,438; d = 512,
+// 4,096: 1,220 -> 984.  Which multiple follows from how full it leaves an XCD's last round (N = 4,096, d = 1536, 86 row
+// groups: 8, 16 and 24 ranges fill 0.90 of their rounds, 3,400 to 3,547 us, 32 fill 0.98, 3,098 us) and from the 40
+// candidate groups or so that another round of shorter items costs (18 row groups, d = 1024: 14 ranges, one round, 535 us,
+// 56 ranges 571).  Ranges of up to 64 MB are short enough to be shared (8,192 rows, V = 60,000: two 882 us, eight 924).
+static inline __host__ __device__ int vp_swept_item_count(int rgs, int slots, int vtiles, int kt, int max_items)
+{
+    const int whole = vp_rounds_item_count(rgs, slots, vtiles);
+    if (rgs < 16) return whole;
+    const int per_xcd = slots / 8 > 0 ? slots / 8 : 1;
+    int best = whole;
+    float best_cost = 0.f;
+    for (int m = 0; m <= 8; ++m) {
+        const int ranges = m == 0 ? whole / rgs : 8 * m;
+        if (m > 0 && (ranges > vtiles || (long long)rgs * ranges > max_items)) break;
+        const int len = (vtiles + ranges - 1) / ranges;
+        const int rounds = ((rgs * ranges + 7) / 8 + per_xcd - 1) / per_xcd;
+        float cost = (float)rounds * (float)(len + 40);
+        if (ranges % 8 != 0) cost *= rgs > per_xcd && ranges < 8 && (long long)len * kt > 64 * 1024 ? 1.5f : 1.06f;
+        if (m == 0 || cost < best_cost) {
+            best_cost = cost;
+            best = rgs * ranges;
+        }
+    }
+    return best;
+}
+
 // The same for the clustered plan, which also knows its number of (bucket, row group) units:
 // every unit ends with a partly filled item, so the plan has at most total / (4 tpw) + units
 // items.  When that lies between one and two times the resident workgroup slots (min_items),

@@ -24,3 +24,7 @@ extern "C" int shim_item_of_workgroup(int wg, int total_items, int swz_rgs, int 
 extern "C" int shim_xcd_block_items(void) { return VP_XCD_BLOCK_ITEMS; }
 extern "C" int shim_rounds_item_count(int rgs, int slots, int vtiles) { return vp_rounds_item_count(rgs, slots, vtiles); }
 extern "C" int shim_item_of_workgroup_even(int wg, int total_items) { return vp_item_of_workgroup_even(wg, total_items); }
+extern "C" int shim_swept_item_count(int rgs, int slots, int vtiles, int kt, int max_items)
+{
+    return vp_swept_item_count(rgs, slots, vtiles, kt, max_items);
+}

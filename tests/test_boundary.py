@@ -252,6 +252,25 @@ def test_round_filling_item_count_of_the_many_row_kernel(layout):
                 break
 
 
+def test_item_count_of_many_row_groups(layout):
+    """vp_swept_item_count: whole row groups, never more items than the list holds, ranges that every XCD has for itself
+    where several XCDs' worth of row groups meet a long vocabulary, and fewer than 16 row groups as ever."""
+    r = np.random.default_rng(8)
+    for _ in range(400):
+        rgs = int(r.integers(1, 1400))
+        slots = int(r.choice([1, 7, 64, 104, 256, 304]))
+        vtiles = int(np.exp(r.uniform(0, np.log(40000))))
+        kt = int(r.choice([8, 16, 24, 32, 40, 48]))
+        most = 8 * slots + 8 * rgs * 3
+        items = layout.shim_swept_item_count(rgs, slots, vtiles, kt, most)
+        rounds = layout.shim_rounds_item_count(rgs, slots, vtiles)
+        assert items % rgs == 0 and 1 <= items // rgs <= max(1, vtiles) and items <= max(most, rounds)
+        if rgs < 16:
+            assert items == rounds
+        if slots == 256 and rgs >= 48 and vtiles >= 12000 and kt >= 40:
+            assert items // rgs % 8 == 0, (rgs, vtiles, kt, items)
+
+
 def test_short_items_bound_of_the_raw_logit_form(layout):
     """The host considers raw logits only for calls of at most 8,192 candidate tiles.  With the default
     sizing (8,192 items asked for, 1,024 workgroup slots) such a plan has at most VP_RAW_TILES tiles per
