@@ -37,6 +37,10 @@ MEASURED_TRAFFIC_BYTES = {
 }
 
 
+# the planner's decision (mode word of the plan header)
+FORMS = {0: "per-cluster slabs", 1: "masked full projection", 2: "some clusters masked, the others on their slabs"}
+
+
 def cluster_sweep(args, dev):
     """Synthetic analogue of the hyper-parameter study of section 3.5: number of centroids x recorded likely
     tokens per training vector -> size of the active sets, how often the full projection's best token lies in
@@ -259,7 +263,7 @@ def measure(wk, N, k, steps, warmup, nb=16, want_full=True, oracle_rows=4, singl
         return max(nbytes / HBM_PEAK_BYTES, flops / MFMA_PEAK_FLOPS) * 1e3
 
     res = {"workload": cfg.name, "N": N, "k": k, "rows_per_s": N / (ms_step * 1e-3), "ms_per_step": ms_step,
-           "planner_chose": "masked full projection" if mode == 1 else "per-cluster slabs",
+           "planner_chose": FORMS[mode],
            "plan_overflow": overflow, "occupied_clusters_per_step": occupied}
     if mode == 1:
         b_ms = bound_ms(alg_full + side, flops_full + 2.0 * N * cfg.K * d)
@@ -270,6 +274,13 @@ def measure(wk, N, k, steps, warmup, nb=16, want_full=True, oracle_rows=4, singl
                          "mfma_tflops": flops_full / (ms_kernel * 1e-3) / 1e12,
                          "mfma_frac": flops_full / (ms_kernel * 1e-3) / MFMA_PEAK_FLOPS,
                          "bound": "hbm" if alg_full / HBM_PEAK_BYTES >= flops_full / MFMA_PEAK_FLOPS else "mfma"}
+    elif mode == 2:
+        # both kernels, one after the other; what either form needs at least is the smaller of the two byte counts
+        least = min(alg_slab, alg_full)
+        b_ms = bound_ms(least + side, flops_slab)
+        res["kernel"] = {"name": slab_kernel_name(wk.info, k, N, True) + " + project_gemm_lds_kernel (masked clusters)",
+                         "kernel_ms": ms_kernel, "algorithmic_bytes": least, "hbm_gbs": least / (ms_kernel * 1e-3) / 1e9,
+                         "hbm_frac": least / (ms_kernel * 1e-3) / HBM_PEAK_BYTES, "bound": "hbm"}
     else:
         b_ms = bound_ms(alg_slab + side, flops_slab)
         res["kernel"] = {"name": slab_kernel_name(wk.info, k, N, True), "kernel_ms": ms_kernel,
@@ -278,7 +289,7 @@ def measure(wk, N, k, steps, warmup, nb=16, want_full=True, oracle_rows=4, singl
     res["whole_call"] = {"bound_ms": b_ms, "frac_of_bound": b_ms / ms_step}
 
     # the same call confined to the per-cluster slabs (the form the method's byte count belongs to)
-    if mode == 1:
+    if mode != 0:
         index.set_option("dispatch", 0)
         ms_s, ms_sk, _ = timed(index, step, max(2, warmup // 2), max(5, steps // 2), warm_ms=warm_ms)
         index.set_option("dispatch", 1)
@@ -743,7 +754,7 @@ def decode_loop(P, wl, index, cfg, C, dev):
     index.set_option("dispatch", 1)
     return {"sentences": S_d, "beam": B_d, "topk": k_d, "steps": T_d, "ms_per_step": ms_dec,
             "rows_per_s": n_d / (ms_dec * 1e-3),
-            "planner_chose_last_step": "masked full projection" if mode == 1 else "per-cluster slabs",
+            "planner_chose_last_step": FORMS[mode],
             "slabs_only_ms_per_step": ms_dec_s, "slabs_only_rows_per_s": n_d / (ms_dec_s * 1e-3),
             "finished_hypotheses": int(torch.isfinite(final).sum().item()),
             "note": "vp_project + vp_beam_step + a gather of the next rows per step"}

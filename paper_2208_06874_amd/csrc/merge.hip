@@ -28,7 +28,6 @@ __global__ __launch_bounds__(MERGE_THREADS) void merge_kernel(
     int32_t *__restrict__ out_ids, float *__restrict__ out_logp)
 {
     const VpRowPlan rp = rowplan[blockIdx.x];
-    const int rpi = hdr->rows_per_item;
     const int tid = threadIdx.x;
     if (hdr->overflow) {
         // The plan did not fit its item list (a bound of the host side is wrong): rows would silently
@@ -43,8 +42,8 @@ __global__ __launch_bounds__(MERGE_THREADS) void merge_kernel(
     const int wave = tid >> 6;
     const int nit = rp.nit;
     const int PFL = vp_partial_floats(k);
-    const float *base = partials + ((size_t)rp.item0 * rpi + rp.local) * PFL;
-    const size_t part_stride = (size_t)rp.stride * rpi * PFL;
+    const float *base = partials + (size_t)rp.slot0 * PFL;
+    const size_t part_stride = (size_t)rp.slot_stride * PFL;
 
     extern __shared__ float staged[];            // [2k][256]: entries of each thread's first part
     __shared__ float red_v[MERGE_THREADS / 64];
@@ -84,7 +83,7 @@ __global__ __launch_bounds__(MERGE_THREADS) void merge_kernel(
     const float lse = M + __builtin_amdgcn_logf(S) * LN2;   // (red_v / red_s are not written again)
 
     // (in the masked full projection candidate positions are token ids already)
-    const int32_t *ids = (set.ids && hdr->mode == 0) ? set.ids + rp.ids_off : nullptr;
+    const int32_t *ids = (set.ids && rp.ids_off >= 0) ? set.ids + rp.ids_off : nullptr;
 
     int pos = 0;                                  // entries of the first part already taken
     float cv = -__builtin_inff();

@@ -3,7 +3,8 @@
 // The paper unions the active sets of a batch (section 2.3); here each row is
 // instead projected against its own cluster's slab, so rows are first grouped
 // by cluster: histogram of the cluster ids -> exclusive prefix scan -> scatter
-// of the row numbers into bucket order.  The same kernel finishes Eq. 2 (it
+// of the row numbers into bucket order (or all or some of the clusters are left to the
+// masked full projection, where that is cheaper).  The same kernel finishes Eq. 2 (it
 // reduces the per-part minima of the centroid kernel) and cuts the projection
 // work into items of equal slab bytes: (bucket, group of up to 16 rows, range
 // of candidate tiles).  The number of tiles per item adapts to the total work
@@ -90,28 +91,57 @@ __device__ inline void block_sum3(int a, int b, int c, int *ta, int *tb, int *tc
     *tc = __builtin_amdgcn_readlane(wave_inclusive_sum(lane < nw ? wsum3[32 + lane] : 0), nw - 1);
 }
 
+// The form is chosen per cluster where the matrix cores, not one pass over W, set the time of the masked
+// projection: there every row costs it the same, so a cluster is masked when its slab takes longer than that for its
+// rows (few rows, long list) and keeps its slab otherwise.  Which price per row is the best one depends on how much of
+// the pass over W the masked rows fill; four prices are tried, MIX_PRICES halvings of the full one, and the cheapest total wins
+// if it is 5 % cheaper than either form for the whole batch (both projection kernels then have work, in one plan).
+// 4,096 Zipf(1.1) rows on 500 clusters of 2,000 to 40,000 tokens, d = 1536, top-8: slabs 2,830 us, masked 3,360, both
+// 2,100; 1,024 rows on lists of up to 30,000, d = 1024, top-4: 823, 521, 365; 400 rows of that: 267 masked, 256.
+constexpr int MIX_PRICES = 4;
+static_assert(MIX_PRICES * PLAN_THREADS / 64 == 64, "one lane per price and wavefront");
+// the matrix cores' rate over many row groups against the rate of the few that the choice between the two whole forms turns
+// on (N = 512 -> 4,096 masked rows: 14.1 -> 17.5 TB/s of W at d = 1024, 10 -> 15 at d = 512, 16.8 -> 18.9 at d = 1536)
+constexpr float MIX_GEMM = 1.3f;
+constexpr float MIX_TIME = 40e-6f;   // a second kernel's start and end, and buckets of many rows in a slab kernel with little to do
+
+// candidate tiles of a cluster; those of a masked cluster are stored complemented
+__device__ inline int plan_tiles(int t) { return t < 0 ? ~t : t; }
+
+// one cluster's slab with its share of the rows' time
+__device__ inline float slab_time(int rows, int tiles, float t_row, const VpCostModel &cost)
+{
+    return tiles / cost.bw_slab + (ceil_div(rows, VP_ROWS_PER_ITEM) - 1) * tiles / cost.bw_l2 + rows * t_row;
+}
+
 __global__ __launch_bounds__(PLAN_THREADS) void plan_kernel(
     const int2 *__restrict__ cpart, int parts, int N, int K, const int32_t *__restrict__ n_cand,
     const int32_t *__restrict__ tile_off, int target_items, int min_items, int max_items, int32_t *__restrict__ g,
     int32_t *__restrict__ out_cluster, int32_t *__restrict__ perm, VpRowPlan *__restrict__ rowplan,
     unsigned int *__restrict__ floors, VpItem *__restrict__ items, VpPlanHeader *__restrict__ hdr,
     int64_t *__restrict__ dbg_row_off, int dispatch, VpCostModel cost, int k, int V, int vtiles,
-    int full_target_items, int full_min_items, int max_items_full)
+    int full_target_items, int full_min_items, int max_items_full, VpMixLimits mix)
 {
     extern __shared__ int lds[];
-    int *cnt = lds;             // [K]   rows per cluster, later the scatter cursor
-    int *off = cnt + K;         // [K+1] first perm position of each bucket
-    int *ioff = off + K + 1;    // [K+1] first item of each bucket
-    int *tl = ioff + K + 1;     // [K]   candidate tiles of each cluster
+    int *cnt = lds;             // [K]   rows per cluster
+    int *off = cnt + K;         // [K]   first perm position of each bucket
+    int *ioff = off + K;        // [K+1] first item of each bucket
+    int *tl = ioff + K + 1;     // [K]   candidate tiles of each cluster (plan_tiles)
+    int *cur = tl + K;          // [K]   scatter cursor
     __shared__ int wsum[PLAN_THREADS / 64 + 1];
     __shared__ long long wsum64[PLAN_THREADS / 64 + 1];
     __shared__ int wsum3[48];
+    __shared__ float mix_t[MIX_PRICES][PLAN_THREADS / 64];
+    __shared__ int mix_n[MIX_PRICES][PLAN_THREADS / 64];
     __shared__ int max_rgs;     // most row groups any bucket has
     const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
     if (tid == 0) max_rgs = 0;
     for (int j = tid; j < K; j += PLAN_THREADS) {
         cnt[j] = 0;
+        cur[j] = 0;
         tl[j] = tile_off[j + 1] - tile_off[j];
     }
     __syncthreads();
@@ -125,75 +155,172 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_kernel(
     __threadfence_block();   // the scatter below reads g[] written by other threads of this workgroup
     __syncthreads();
 
-    // exclusive scan of the histogram -> bucket offsets; total candidate tiles of all row groups
-    int carry = 0;
+    // total candidate tiles of all row groups
     int my_tiles = 0, my_occ_tiles = 0, my_units = 0;
-    for (int base = 0; base < K; base += PLAN_THREADS) {
-        const int j = base + tid;
-        const int c = j < K ? cnt[j] : 0;
-        int tot;
-        const int ex = block_exscan_int(c, &tot, wsum);
-        if (j < K) {
-            off[j] = carry + ex;
-            my_tiles += ceil_div(c, VP_ROWS_PER_ITEM) * tl[j];
-            my_units += ceil_div(c, VP_ROWS_PER_ITEM);
-            if (c > 4 * VP_ROWS_PER_ITEM) atomicMax(&max_rgs, ceil_div(c, VP_ROWS_PER_ITEM));
-            if (c > 0) my_occ_tiles += tl[j];
-        }
-        carry += tot;
+    for (int j = tid; j < K; j += PLAN_THREADS) {
+        const int c = cnt[j];
+        my_tiles += ceil_div(c, VP_ROWS_PER_ITEM) * tl[j];
+        my_units += ceil_div(c, VP_ROWS_PER_ITEM);
+        if (c > 0) my_occ_tiles += tl[j];
     }
-    if (tid == 0) off[K] = carry;
     int total_tiles, units, occ_tiles;
     block_sum3(my_tiles, my_units, my_occ_tiles, &total_tiles, &units, &occ_tiles, wsum3);
 
-    // both forms give the same results, so the cheaper one is taken (cost model in plan_common.h)
+    // all forms give the same results, so the cheapest one is taken (cost model in plan_common.h)
+    int masked_rows = 0;
+    int m_rgs = 0, m_chunks = 0, m_tpi = 0;   // the masked projection's items, where some clusters are masked
     if (dispatch) {
-        const int rpi_full = dispatch;   // rows per item of the masked projection (16 or 64)
-        if (vp_full_is_cheaper(occ_tiles, total_tiles, N, rpi_full, vtiles, k, cost)) {
+        const int rpi = dispatch;   // rows per item of the masked projection (16, 48 or 64)
+        const float t_slab = vp_time_slabs(occ_tiles, total_tiles, N, cost);
+        const float t_full = vp_time_masked(N, rpi, vtiles, k, cost);
+        const float pass = vtiles / (cost.bw_gemm * MIX_GEMM);   // of one row group
+        const float one_pass = vtiles / cost.bw_full;
+        const float k_factor = 1.f + k * 0.0125f;
+        const float best = 0.95f * fminf(t_slab, ceil_div(N, rpi) * pass * k_factor);
+        // (whatever is masked, W is streamed once)
+        if (mix.slots > 0 && best > MIX_TIME + one_pass * k_factor) {
+            const float t_row = vp_rows_time(N, cost.t_row_slab) / N;
+            const float price = pass / rpi * k_factor;
+            float t[MIX_PRICES];
+            int n[MIX_PRICES];
+#pragma unroll
+            for (int i = 0; i < MIX_PRICES; ++i) {
+                t[i] = 0.f;
+                n[i] = 0;
+            }
+            for (int j = tid; j < K; j += PLAN_THREADS) {
+                const int c = cnt[j];
+                if (c == 0) continue;
+                const float tj = slab_time(c, tl[j], t_row, cost);
+#pragma unroll
+                for (int i = 0; i < MIX_PRICES; ++i) {
+                    const bool masked = tj > c * price * (1.f / (1 << i));
+                    t[i] += masked ? 0.f : tj;
+                    n[i] += masked ? c : 0;
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < MIX_PRICES; ++i) {
+                const float ts = wave_sum_float(t[i]);
+                const int ns = wave_sum(n[i]);
+                if (lane == 0) {
+                    mix_t[i][wave] = ts;
+                    mix_n[i][wave] = ns;
+                }
+            }
             __syncthreads();
-            vp_plan_single_bucket(N, V, vtiles, rpi_full, full_target_items, full_min_items, max_items_full, perm,
-                                  rowplan, floors, items, hdr, nullptr, tid, PLAN_THREADS);
-            if (tid == 0) hdr->mode = 1;
+            // lane l adds up wavefront l % 16's share at price l / 16
+            const float ts = row_sum_float(mix_t[lane >> 4][lane & 15]);
+            const int ns = row_sum(mix_n[lane >> 4][lane & 15]);
+            float both = ts + MIX_TIME + fmaxf(one_pass, ceil_div(ns, rpi) * pass) * k_factor;
+            if (ns == 0 || ns == N) both = __builtin_inff();
+            float chosen = -1.f, least = best;
+#pragma unroll
+            for (int i = 0; i < MIX_PRICES; ++i) {
+                const float t_i = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(both), 16 * i + 15));
+                if (t_i < least) {
+                    least = t_i;
+                    chosen = price * (1.f / (1 << i));
+                }
+            }
+            if (chosen >= 0.f) {
+                int s_tiles, s_units, my_rows = 0;
+                my_tiles = my_units = 0;
+                for (int j = tid; j < K; j += PLAN_THREADS) {
+                    const int c = cnt[j];
+                    if (c == 0) continue;
+                    if (slab_time(c, tl[j], t_row, cost) > c * chosen) {
+                        tl[j] = ~tl[j];
+                        my_rows += c;
+                    } else {
+                        my_tiles += ceil_div(c, VP_ROWS_PER_ITEM) * tl[j];
+                        my_units += ceil_div(c, VP_ROWS_PER_ITEM);
+                    }
+                }
+                block_sum3(my_tiles, my_units, my_rows, &s_tiles, &s_units, &masked_rows, wsum3);
+                // whole rounds of the compute units for the masked items, as in a plan of its own, and no
+                // more of them than workgroups
+                m_rgs = ceil_div(masked_rows, rpi);
+                int target = vp_swept_item_count(max(m_rgs, 1), mix.slots, vtiles, mix.kt, mix.grid);
+                if (target > mix.grid) target = mix.grid / m_rgs * m_rgs;
+                const int m_tpw = vp_tiles_per_wave((long long)m_rgs * vtiles, max(target, 1), max(target, 1));
+                m_tpi = m_tpw * VP_WG_WAVES;
+                m_chunks = ceil_div(vtiles, m_tpi);
+                // both item lists and their partial results have to fit the workspace, which is laid out for one
+                // form at a time: the slabs get fewer, longer items if need be
+                const int m_items = m_rgs * m_chunks;
+                const long long room = min((long long)mix.list - m_items,
+                                           (mix.row_slots - (long long)m_items * rpi) / VP_ROWS_PER_ITEM) - s_units;
+                if (masked_rows > 0 && m_items <= mix.grid && room >= min_items) {
+                    target_items = (int)min((long long)target_items, room);
+                    total_tiles = s_tiles;
+                    units = s_units;
+                } else {
+                    masked_rows = 0;
+                    for (int j = tid; j < K; j += PLAN_THREADS) tl[j] = plan_tiles(tl[j]);
+                }
+            }
+        }
+        if (masked_rows == 0 && t_full < t_slab) {
+            __syncthreads();
+            vp_plan_single_bucket(N, V, vtiles, rpi, full_target_items, full_min_items, max_items_full, perm,
+                                  rowplan, floors, items, hdr, nullptr, tid, PLAN_THREADS, true);
             return;
         }
     }
     const int tpw = vp_tiles_per_wave_units(total_tiles, units, target_items, min_items);
     const int tpi = tpw * VP_WG_WAVES;
+    const int slab_rows = N - masked_rows;
 
-    // items per bucket -> item offsets
-    carry = 0;
+    // exclusive scans: rows -> bucket offsets (the masked clusters' rows behind all others), items -> item offsets
+    int carry = 0, icarry = 0, mcarry = slab_rows;
     for (int base = 0; base < K; base += PLAN_THREADS) {
         const int j = base + tid;
-        int c = 0;
-        if (j < K) c = ceil_div(cnt[j], VP_ROWS_PER_ITEM) * ceil_div(tl[j], tpi);
+        const int c = j < K ? cnt[j] : 0;
+        const int t = j < K ? tl[j] : 0;
+        const int rgs = ceil_div(c, VP_ROWS_PER_ITEM);
         int tot;
-        const int ex = block_exscan_int(c, &tot, wsum);
-        if (j < K) ioff[j] = carry + ex;
+        const int ex = block_exscan_int(t < 0 ? 0 : c, &tot, wsum);
+        if (j < K && t >= 0) off[j] = carry + ex;
         carry += tot;
+        const int iex = block_exscan_int(t < 0 ? 0 : rgs * ceil_div(t, tpi), &tot, wsum);
+        if (j < K) ioff[j] = icarry + iex;
+        icarry += tot;
+        if (masked_rows > 0) {
+            const int mex = block_exscan_int(t < 0 ? c : 0, &tot, wsum);
+            if (j < K && t < 0) off[j] = mcarry + mex;
+            mcarry += tot;
+        }
+        if (t >= 0 && rgs > 4) atomicMax(&max_rgs, rgs);
     }
-    if (tid == 0) ioff[K] = carry;
+    if (tid == 0) ioff[K] = icarry;
     __syncthreads();
-    const int total_items = min(ioff[K], max_items);
+    const int total_items = min(icarry, max_items);
+    const int m_slot0 = total_items * VP_ROWS_PER_ITEM;
 
-    // scatter rows into bucket order (cnt becomes the per-bucket cursor) and tell the
-    // merge kernel where the partial results of each row will be
-    for (int j = tid; j < K; j += PLAN_THREADS) cnt[j] = 0;
-    __syncthreads();
+    // scatter rows into bucket order and tell the merge kernel where the partial results of each row will be
     for (int r = tid; r < N; r += PLAN_THREADS) {
         const int j = g[r];
-        const int local = atomicAdd(&cnt[j], 1);
+        const int local = atomicAdd(&cur[j], 1);
         const int p = off[j] + local;
         perm[p] = r;
         floors[r] = VP_FLOOR_NONE;   // no lower bound of the row's k-th best logit known yet
         VpRowPlan rp;
         rp.row = r;
         rp.cluster = j;
-        rp.item0 = ioff[j] + local / VP_ROWS_PER_ITEM;
-        rp.stride = ceil_div(off[j + 1] - off[j], VP_ROWS_PER_ITEM);
-        rp.nit = ceil_div(tl[j], tpi);
-        rp.local = local % VP_ROWS_PER_ITEM;
-        rp.ids_off = tile_off[j] * VP_TILE_ITEMS;
-        rp.pad = 0;
+        if (tl[j] >= 0) {
+            const int rgs = ceil_div(cnt[j], VP_ROWS_PER_ITEM);
+            rp.slot0 = (ioff[j] + local / VP_ROWS_PER_ITEM) * VP_ROWS_PER_ITEM + local % VP_ROWS_PER_ITEM;
+            rp.slot_stride = rgs * VP_ROWS_PER_ITEM;
+            rp.nit = ceil_div(tl[j], tpi);
+            rp.ids_off = tile_off[j] * VP_TILE_ITEMS;
+        } else {
+            rp.slot0 = m_slot0 + p - slab_rows;   // (row group, slot of it) of the first candidate range
+            rp.slot_stride = m_rgs * dispatch;
+            rp.nit = m_chunks;
+            rp.ids_off = -1;
+        }
+        rp.pad[0] = rp.pad[1] = 0;
         rowplan[p] = rp;
     }
 
@@ -206,7 +333,7 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_kernel(
             if (ioff[mid] <= it) lo = mid; else hi = mid;
         }
         const int j = lo;
-        const int rows = off[j + 1] - off[j];
+        const int rows = cnt[j];
         const int rgs = ceil_div(rows, VP_ROWS_PER_ITEM);
         const int local = it - ioff[j];
         const int ch = local / rgs;
@@ -222,16 +349,35 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_kernel(
         v.ncand = n_cand[j];
         items[it] = v;
     }
+    // and those of the masked clusters, as a single-bucket plan has them
+    for (int it = tid; it < m_rgs * m_chunks && masked_rows > 0; it += PLAN_THREADS) {
+        const int ch = it / m_rgs;
+        const int rg = it - ch * m_rgs;
+        VpItem v;
+        v.cluster = 0;
+        v.perm_start = slab_rows + rg * dispatch;
+        v.nrows = min(dispatch, masked_rows - rg * dispatch);
+        v.tile0 = ch * m_tpi;
+        v.ntiles = min(m_tpi, vtiles - ch * m_tpi);
+        v.shared = m_rgs > 1;
+        v.tile_off = 0;
+        v.ncand = V;
+        items[total_items + it] = v;
+    }
     if (tid == 0) {
         hdr->total_items = total_items;
         hdr->tiles_per_wave = tpw;
-        hdr->overflow = ioff[K] > max_items;
+        hdr->overflow = icarry > max_items;
         hdr->total_tiles = total_tiles;
         // buckets of five row groups and more: keep the row groups of a candidate range on one XCD
         hdr->swz_rgs = max_rgs > 4 ? -VP_XCD_BLOCK_ITEMS : 0;
         hdr->swz_chunks = 0;
         hdr->rows_per_item = VP_ROWS_PER_ITEM;
-        hdr->mode = 0;
+        hdr->mode = masked_rows > 0 ? 2 : 0;
+        hdr->masked_items = masked_rows > 0 ? m_rgs * m_chunks : 0;
+        hdr->masked_item0 = total_items;
+        hdr->masked_slot0 = m_slot0;
+        hdr->masked_swz = m_rgs > 1 && m_chunks >= 8 ? m_rgs : 0;
     }
 
     // debug entry only: where each row's candidate logits start
@@ -263,24 +409,25 @@ __global__ __launch_bounds__(256) void plan_full_kernel(
 
 }  // namespace
 
-size_t vpk_plan_lds_bytes(int K) { return (size_t)(4 * K + 2) * sizeof(int); }
+size_t vpk_plan_lds_bytes(int K) { return (size_t)(5 * K + 1) * sizeof(int); }
 
 hipError_t vpk_plan_prepare()
 {
-    // clusters up to VP_MAX_CLUSTERS need a little over 64 KiB of dynamic LDS; allow it explicitly
+    // clusters up to VP_MAX_CLUSTERS need a little over 80 KiB of dynamic LDS; allow it explicitly
     return hipFuncSetAttribute(reinterpret_cast<const void *>(plan_kernel),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, 72 * 1024);
+                               hipFuncAttributeMaxDynamicSharedMemorySize, 88 * 1024);
 }
 
 void vpk_plan(const void *cpart, int parts, int N, int K, const int32_t *n_cand, const int32_t *tile_off,
               int target_items, int min_items, int max_items, int32_t *g, int32_t *out_cluster, int32_t *perm,
               VpRowPlan *rowplan, unsigned int *floors, VpItem *items, VpPlanHeader *hdr, int64_t *dbg_row_off,
               int dispatch, const VpCostModel &cost, int k, int V, int vtiles, int full_target_items,
-              int full_min_items, int max_items_full, hipStream_t st)
+              int full_min_items, int max_items_full, const VpMixLimits &mix, hipStream_t st)
 {
     hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(PLAN_THREADS), vpk_plan_lds_bytes(K), st, (const int2 *)cpart,
                        parts, N, K, n_cand, tile_off, target_items, min_items, max_items, g, out_cluster, perm, rowplan, floors,
-                       items, hdr, dbg_row_off, dispatch, cost, k, V, vtiles, full_target_items, full_min_items, max_items_full);
+                       items, hdr, dbg_row_off, dispatch, cost, k, V, vtiles, full_target_items, full_min_items, max_items_full,
+                       mix);
 }
 
 void vpk_plan_full(int N, int V, int vtiles, int rpi, int target_items, int min_items, int max_items, int32_t *perm,

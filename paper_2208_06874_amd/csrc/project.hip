@@ -425,7 +425,7 @@ __global__ __launch_bounds__(VP_WG_THREADS) void project_kernel(
     const VpItem probe = items[blockIdx.x];
     const int total_items = hdr->total_items;
     const int tpw = hdr->tiles_per_wave;
-    if (hdr->mode != 0) return;   // the planner chose the masked full projection for this batch
+    if (hdr->mode == 1) return;   // the planner chose the masked full projection for the whole batch
     const int it = item_of_workgroup(hdr);
     if (it < 0 || it >= total_items) return;
     const VpItem item = it == (int)blockIdx.x ? probe : items[it];
@@ -527,7 +527,7 @@ __device__ inline void project_small(const VpSlabSet &set, const uint4 *__restri
             a.g[r] = j;
             if (a.out_cluster) a.out_cluster[r] = j;
             if (tl == 0) {   // a cluster without candidates has no items: its rows' records come from here
-                VpRowPlan rp = {r, j, 0, 1, 0, 0, to * VP_TILE_ITEMS, 0};
+                VpRowPlan rp = {r, j, 0, VP_ROWS_PER_ITEM, 0, to * VP_TILE_ITEMS, {0, 0}};
                 a.rowplan[r] = rp;
             }
         }
@@ -559,7 +559,7 @@ __device__ inline void project_small(const VpSlabSet &set, const uint4 *__restri
     item.tile_off = __builtin_amdgcn_readlane(to, src);
     item.ncand = __builtin_amdgcn_readlane(nc, src);
     if (it == ioff_b && tid < 64 && sub == 0 && j == jb) {
-        VpRowPlan rp = {r, j, ioff_b, 1, nit, same_before, to * VP_TILE_ITEMS, 0};
+        VpRowPlan rp = {r, j, ioff_b * VP_ROWS_PER_ITEM + same_before, VP_ROWS_PER_ITEM, nit, to * VP_TILE_ITEMS, {0, 0}};
         a.rowplan[r] = rp;
     }
     // row slot s of the item holds the bucket's s-th row
@@ -598,7 +598,7 @@ __global__ __launch_bounds__(VP_WG_THREADS) void project_pf16_kernel(
     const VpItem probe = items[blockIdx.x];
     const int total_items = hdr->total_items;
     const int tpw = hdr->tiles_per_wave;
-    if (hdr->mode != 0) return;
+    if (hdr->mode == 1) return;
     const int it = item_of_workgroup(hdr);
     if (it < 0 || it >= total_items) return;
     const VpItem item = it == (int)blockIdx.x ? probe : items[it];

@@ -52,7 +52,7 @@ template <int KT, bool MASKED, bool NT, bool TOP1, bool GATHER>
 __device__ inline void gemm_lds_item(const VpSlabSet &set, const uint4 *__restrict__ hidden, int d,
                                      const VpItem &item, int it, int k,
                                      float *__restrict__ partials, unsigned int *__restrict__ floors,
-                                     const VpMaskInfo &mask)
+                                     const VpMaskInfo &mask, const int32_t *__restrict__ perm)
 {
     constexpr int L_RT = lds_row_tiles(KT);
     constexpr int L_ROWS = 16 * L_RT;
@@ -100,14 +100,15 @@ __device__ inline void gemm_lds_item(const VpSlabSet &set, const uint4 *__restri
     };
 
     // The rows of this item -> LDS, MFMA operand order (row slots beyond nrows: zeros).  A
-    // single-bucket plan keeps the rows in their own order: slot r of the item is row perm_start + r.
+    // single-bucket plan keeps the rows in their own order: slot r of the item is row perm_start + r; where only
+    // some clusters are masked (perm given), it is the row at that position of the bucket order.
     // All of a thread's pieces are fetched in one batch, in front of the first slab loads (loads
     // return in order: behind them, the rows would wait for bytes from HBM they do not depend on).
     constexpr int X = KT * 4;   // 16-byte pieces per padded row
     constexpr int PER = L_ROWS * X / (L_NW * 64);   // pieces per thread
     static_assert(PER * L_NW * 64 == L_ROWS * X, "the rows' pieces divide evenly over the threads");
     uint4 piece[PER];
-    {
+    auto fetch = [&](auto row_of) {
         const int pieces_per_row = d >> 3;
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
@@ -115,8 +116,16 @@ __device__ inline void gemm_lds_item(const VpSlabSet &set, const uint4 *__restri
             const int r = e / X;
             const int x = e - r * X;
             piece[i] = make_uint4(0, 0, 0, 0);
-            if (r < item.nrows && x < pieces_per_row) piece[i] = hidden[(size_t)(item.perm_start + r) * pieces_per_row + x];
+            if (r < item.nrows && x < pieces_per_row) piece[i] = hidden[(size_t)row_of(i, r) * pieces_per_row + x];
         }
+    };
+    if (MASKED && perm) {
+        int row[PER];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) row[i] = perm[item.perm_start + min((tid + i * (L_NW * 64)) / X, item.nrows - 1)];
+        fetch([&](int i, int) { return row[i]; });
+    } else {
+        fetch([&](int, int r) { return item.perm_start + r; });
     }
 
     uint4 ring[L_PF][L_G];
@@ -146,9 +155,12 @@ __device__ inline void gemm_lds_item(const VpSlabSet &set, const uint4 *__restri
     for (int rt = 0; rt < L_RT; ++rt) {
         const int slot = rt * 16 + n;
         row_valid[rt] = slot < item.nrows;
-        myrow[rt] = row_valid[rt] ? item.perm_start + slot : -1;
+        myrow[rt] = row_valid[rt] ? (MASKED && perm ? perm[item.perm_start + slot] : item.perm_start + slot) : -1;
     }
-    if (tid < L_ROWS) wg_floor[tid] = (!TOP1 && tid < item.nrows) ? floors[item.perm_start + tid] : VP_FLOOR_NONE;
+    // (the bounds are kept by row number, whichever form a row's cluster takes)
+    if (tid < L_ROWS)
+        wg_floor[tid] = !TOP1 && tid < item.nrows ? floors[MASKED && perm ? perm[item.perm_start + tid] : item.perm_start + tid]
+                                                  : VP_FLOOR_NONE;
     __syncthreads();
 
     // per row tile: running maximum, sum of exponentials, k-th best of this wavefront's list
@@ -393,7 +405,7 @@ __device__ inline void gemm_lds_item(const VpSlabSet &set, const uint4 *__restri
     }
     if (!top1 && tid < item.nrows) {
         const unsigned int kth = (unsigned int)(lkey[(k - 1) * L_ROWS + tid] >> 32);
-        atomicMax(floors + item.perm_start + tid, max(max(kth, wg_floor[tid]), (unsigned int)VP_FLOOR_NONE));
+        atomicMax(floors + (MASKED && perm ? perm[item.perm_start + tid] : item.perm_start + tid), max(max(kth, wg_floor[tid]), (unsigned int)VP_FLOOR_NONE));
     }
     __syncthreads();
 
@@ -424,33 +436,38 @@ template <int KT, bool MASKED, bool TOP1, bool GATHER>
 __global__ __launch_bounds__(L_NW * 64) void project_gemm_lds_kernel(
     VpSlabSet set, const uint4 *__restrict__ hidden, int d,
     const VpItem *__restrict__ items, const VpPlanHeader *__restrict__ hdr, int k,
-    float *__restrict__ partials, unsigned int *__restrict__ floors, VpMaskInfo mask)
+    float *__restrict__ partials, unsigned int *__restrict__ floors, VpMaskInfo mask, const int32_t *__restrict__ perm)
 {
-    if (MASKED ? hdr->mode != 1 : hdr->mode != 0) return;   // the planner chose the other form
-    const int total_items = hdr->total_items;
-    // (hdr->swz_rgs > 1: several row groups and enough candidate ranges for the 8 XCDs)
-    const int it = hdr->swz_rgs > 1 ? vp_item_of_workgroup_even(blockIdx.x, total_items) : (int)blockIdx.x;
+    if (MASKED ? hdr->mode == 0 : hdr->mode != 0) return;   // the planner chose the other form
+    const int total_items = MASKED ? hdr->masked_items : hdr->total_items;
+    // (> 1: several row groups and enough candidate ranges for the 8 XCDs)
+    const int swz = MASKED ? hdr->masked_swz : hdr->swz_rgs;
+    const int it = swz > 1 ? vp_item_of_workgroup_even(blockIdx.x, total_items) : (int)blockIdx.x;
     if (it < 0 || it >= total_items) return;
-    const VpItem item = items[it];
+    const VpItem item = items[MASKED ? hdr->masked_item0 + it : it];
+    if (MASKED) {
+        partials += (size_t)hdr->masked_slot0 * vp_partial_floats(k);
+        if (hdr->mode == 1) perm = nullptr;   // the whole batch, in its own order
+    }
     if (item.shared || GATHER)
-        gemm_lds_item<KT, MASKED, false, TOP1, GATHER>(set, hidden, d, item, it, TOP1 ? 1 : k, partials, floors, mask);
+        gemm_lds_item<KT, MASKED, false, TOP1, GATHER>(set, hidden, d, item, it, TOP1 ? 1 : k, partials, floors, mask, perm);
     else
-        gemm_lds_item<KT, MASKED, true, TOP1, false>(set, hidden, d, item, it, TOP1 ? 1 : k, partials, floors, mask);
+        gemm_lds_item<KT, MASKED, true, TOP1, false>(set, hidden, d, item, it, TOP1 ? 1 : k, partials, floors, mask, perm);
 }
 
 template <int KT, bool MASKED, bool GATHER>
 void launch_lds(const VpSlabSet &set, const void *hidden, int d, const VpItem *items,
                 const VpPlanHeader *hdr, int grid_items, int k, float *partials, unsigned int *floors,
-                const VpMaskInfo &mask, hipStream_t st)
+                const VpMaskInfo &mask, const int32_t *perm, hipStream_t st)
 {
     if (k == 1)
         hipLaunchKernelGGL((project_gemm_lds_kernel<KT, MASKED, true, GATHER>), dim3(grid_items), dim3(L_NW * 64),
                            vpk_project_rows_lds_bytes(k, KT), st, set, (const uint4 *)hidden, d, items, hdr, k,
-                           partials, floors, mask);
+                           partials, floors, mask, perm);
     else
         hipLaunchKernelGGL((project_gemm_lds_kernel<KT, MASKED, false, GATHER>), dim3(grid_items), dim3(L_NW * 64),
                            vpk_project_rows_lds_bytes(k, KT), st, set, (const uint4 *)hidden, d, items, hdr, k,
-                           partials, floors, mask);
+                           partials, floors, mask, perm);
 }
 
 template <int KT>
@@ -501,8 +518,8 @@ hipError_t vpk_project_rows_lds_prepare()
 
 // mask: nullptr, or the membership lists of the masked full projection.  gather: the set's tiles
 // are the token-major copy of W and its ids the batch's union U (no mask then); the slab operands
-// are read through U instead of from a packed copy.  (perm is not read: a single-bucket plan keeps
-// the rows in their own order.)
+// are read through U instead of from a packed copy.  perm is read only where the planner masks some of
+// the clusters: a single-bucket plan keeps the rows in their own order.
 void vpk_project_rows_lds(const VpSlabSet &set, const void *hidden, int d, const int32_t *perm, const VpItem *items,
                           const VpPlanHeader *hdr, int grid_items, int k, float *partials, unsigned int *floors,
                           const VpMaskInfo *mask, bool gather, hipStream_t st)
@@ -510,9 +527,9 @@ void vpk_project_rows_lds(const VpSlabSet &set, const void *hidden, int d, const
     const VpMaskInfo none = {nullptr, nullptr, 0};
 #define VP_LDS_CASE(KT)                                                                                                   \
     case KT:                                                                                                              \
-        if (mask) launch_lds<KT, true, false>(set, hidden, d, items, hdr, grid_items, k, partials, floors, *mask, st); \
-        else if (gather) launch_lds<KT, false, true>(set, hidden, d, items, hdr, grid_items, k, partials, floors, none, st); \
-        else launch_lds<KT, false, false>(set, hidden, d, items, hdr, grid_items, k, partials, floors, none, st);     \
+        if (mask) launch_lds<KT, true, false>(set, hidden, d, items, hdr, grid_items, k, partials, floors, *mask, perm, st); \
+        else if (gather) launch_lds<KT, false, true>(set, hidden, d, items, hdr, grid_items, k, partials, floors, none, nullptr, st); \
+        else launch_lds<KT, false, false>(set, hidden, d, items, hdr, grid_items, k, partials, floors, none, nullptr, st); \
         break;
     switch (set.kt) {
         VP_LDS_CASE(8)

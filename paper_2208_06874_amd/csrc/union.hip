@@ -137,9 +137,7 @@ __global__ __launch_bounds__(UNION_THREADS) void union_emit_kernel(
                 uh->tiles = 0;   // nothing to gather
             }
             vp_plan_single_bucket(N, V, vtiles, rpi, target_items, min_items, max_items_full, perm, rowplan, floors,
-                                  items, hdr, nullptr, tid, UNION_THREADS);
-            __syncthreads();   // the header's mode after the planner's own write of it
-            if (tid == 0) hdr->mode = 1;
+                                  items, hdr, nullptr, tid, UNION_THREADS, true);
             return;
         }
     }

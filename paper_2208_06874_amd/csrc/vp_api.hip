@@ -200,6 +200,7 @@ vp_status plan_arena(const vp_build_desc *D, bool check_ids, ArenaLayout *L)
 // Byte offsets of the per-call scratch inside the workspace.
 struct WsLayout {
     int max_items;
+    size_t row_slots;   // of the partial results
     size_t hdr, cpart, g, perm, rowplan, floors, items, partials, total;
 };
 
@@ -232,7 +233,7 @@ WsLayout plan_workspace(const vp_index *I, int N)
     // (workgroups read the record at their own index before they know the item count)
     W.items = take((size_t)(W.max_items + 8 * VP_XCD_BLOCK_ITEMS) * sizeof(VpItem));
     // one partial result per (item, row slot): 16 slots in the clustered plan, up to 64 in single-bucket plans
-    const size_t slots = std::max((size_t)max_items_clustered(I, N) * VP_ROWS_PER_ITEM,
+    const size_t slots = W.row_slots = std::max((size_t)max_items_clustered(I, N) * VP_ROWS_PER_ITEM,
                                   (size_t)max_items_full(I, N) * VP_MAX_ROWS_PER_ITEM);
     W.partials = take(slots * vp_partial_floats(I->k_max) * sizeof(float));
     W.total = o;
@@ -402,16 +403,24 @@ vp_status run_clustered(const char *fn, const vp_index *I, const void *hidden, i
     // are the clusters with the longest lists (the planner's cost model on that worst case), the planner has nothing to
     // decide and the masked full projection is not launched at all (learned active sets of a
     // fraction of a percent of V: the common case).
+    VpMixLimits mix = {};
     if (dispatch) {
         const int buckets = std::min(N, I->K);
         const float occ = (float)I->longest_tiles[buckets];
         const float total = occ + (float)row_tiles * I->L.max_tiles;
-        const float t_slab = occ / cost.bw_slab + (total - occ) / cost.bw_l2 + N * cost.t_row_slab;
+        const float t_slab = occ / cost.bw_slab + (total - occ) / cost.bw_l2 + vp_rows_time(N, cost.t_row_slab);
         const int rgs_full = ceil_div(N, dispatch);
         const float t_full = dispatch >= 48
             ? std::max(I->L.vtiles / cost.bw_full, rgs_full * (I->L.vtiles / cost.bw_gemm)) * (1.f + k * 0.0125f)
             : std::max(I->L.vtiles / cost.bw_full, (float)rgs_full * I->L.vtiles / cost.bw_l2) * (1.f + k * 0.125f);
-        if (t_slab <= t_full) dispatch = 0;
+        // Where the matrix cores set the masked projection's time, twice what a pass over W takes at least, the
+        // planner may also mask some clusters only (unless even the longest list is cheaper as a slab of one row).
+        // Below that nothing is saved: 300 rows, d = 1024: 215 us masked, 254 us with the crowded clusters on slabs.
+        const bool may_mix = dispatch >= 48 && use_gemm_lds(I, rt_masked, k) &&
+                             rgs_full * (I->L.vtiles / cost.bw_gemm) > 2 * (I->L.vtiles / cost.bw_full) &&
+                             I->L.max_tiles / cost.bw_slab > I->L.vtiles / cost.bw_gemm / dispatch;
+        if (t_slab <= t_full && !may_mix) dispatch = 0;
+        mix.slots = dispatch && may_mix ? I->gemm_lds_items : 0;
     }
     // Batches of a few rows: no planning kernel; the projection workgroups find their own work
     // (project_small_kernel) - unless the planner has a choice to make.
@@ -451,10 +460,27 @@ vp_status run_clustered(const char *fn, const vp_index *I, const void *hidden, i
         vpk_merge(I->clusters, rowplan, hdr, partials, k, N, out_ids, out_logp, st);
         return launch_status(fn);
     }
+    // the masked projection's grid: what the whole batch would take, a round of the compute units at least where
+    // the planner may mask some clusters only (workgroups beyond that have to be handed out to leave at once:
+    // 5 us for 2,048 of them)
+    int grid_full = 0;
+    if (dispatch) {
+        const int rgs = ceil_div(N, dispatch);
+        const int tpw = sb_tiles_per_wave(I, N, rgs, rt_masked, k);
+        const int chunks = ceil_div(I->L.vtiles, (long)tpw * VP_WG_WAVES);
+        grid_full = (rgs > 1 && chunks >= 8) ? ceil_div(chunks, 8) * 8 * rgs : chunks * rgs;
+        if (mix.slots) {
+            grid_full = ceil_div(std::max(grid_full, I->gemm_lds_items), 8) * 8;
+            mix.kt = I->L.kt;
+            mix.grid = grid_full;
+            mix.list = W.max_items;
+            mix.row_slots = (int64_t)W.row_slots;
+        }
+    }
     const int parts = launch_eq2(I, hidden, N, cpart, st);
     vpk_plan(cpart, parts, N, I->K, I->clusters.n_cand, I->clusters.tile_off, I->target_items, I->min_items, max_items, g,
              out_cluster, perm, rowplan, floors, items, hdr, dbg_row_off, dispatch, cost, k, I->V, I->L.vtiles,
-             sb_target(I, N, rt_masked, k), sb_min(I, N, rt_masked, k), max_full, st);
+             sb_target(I, N, rt_masked, k), sb_min(I, N, rt_masked, k), max_full, mix, st);
 
     auto *ev = profile_slot(I);
     if (ev) (void)hipEventRecord(ev->first, st);
@@ -467,11 +493,7 @@ vp_status run_clustered(const char *fn, const vp_index *I, const void *hidden, i
     vpk_project(I->clusters, hidden, I->d, perm, items, hdr, grid_items, 1, k, I->rstar, partials, floors, dbg_logits,
                 dbg_row_off, raw_ok, st);
     if (dispatch) {
-        // launched as well; exactly one of the two does the work, as the planner decided
-        const int rgs = ceil_div(N, dispatch);
-        const int tpw = sb_tiles_per_wave(I, N, rgs, rt_masked, k);
-        const int chunks = ceil_div(I->L.vtiles, (long)tpw * VP_WG_WAVES);
-        const int grid_full = (rgs > 1 && chunks >= 8) ? ceil_div(chunks, 8) * 8 * rgs : chunks * rgs;
+        // launched as well; one of the two does the work, or each its clusters' share, as the planner decided
         const VpMaskInfo mask = {g, I->bitmaps, I->L.bm_words};
         if (use_gemm_lds(I, rt_masked, k))
             vpk_project_rows_lds(I->full, hidden, I->d, perm, items, hdr, grid_full, k, partials, floors, &mask, false, st);

@@ -31,7 +31,7 @@ void vpk_plan(const void *cpart, int parts, int N, int K, const int32_t *n_cand,
               int target_items, int min_items, int max_items, int32_t *g, int32_t *out_cluster, int32_t *perm,
               VpRowPlan *rowplan, unsigned int *floors, VpItem *items, VpPlanHeader *hdr, int64_t *dbg_row_off,
               int dispatch, const VpCostModel &cost, int k, int V, int vtiles, int full_target_items,
-              int full_min_items, int max_items_full, hipStream_t st);
+              int full_min_items, int max_items_full, const VpMixLimits &mix, hipStream_t st);
 void vpk_plan_full(int N, int V, int vtiles, int rpi, int target_items, int min_items, int max_items, int32_t *perm,
                    VpRowPlan *rowplan, unsigned int *floors, VpItem *items, VpPlanHeader *hdr,
                    int64_t *dbg_row_off, hipStream_t st);

@@ -39,17 +39,16 @@ struct VpItem {
 };
 
 // Where the merge kernel finds everything about the row at one position of
-// the bucket order: partial results sit at items item0, item0 + stride, ...
-// (nit of them), in row slot `local` of each.
+// the bucket order: its partial results sit in row slots slot0, slot0 + slot_stride, ...
+// (nit of them) of the call's partial results.
 struct VpRowPlan {
     int32_t row;        // row number in the caller's batch
     int32_t cluster;
-    int32_t item0;
-    int32_t stride;
+    int32_t slot0;
+    int32_t slot_stride;
     int32_t nit;
-    int32_t local;
-    int32_t ids_off;    // first entry of the cluster's token-id list
-    int32_t pad;
+    int32_t ids_off;    // first entry of the cluster's token-id list; < 0: candidate positions are token ids
+    int32_t pad[2];
 };
 
 // Header the planning kernel leaves for the projection and merge kernels.
@@ -68,8 +67,14 @@ struct VpPlanHeader {
     int32_t swz_rgs;
     int32_t swz_chunks;
     int32_t rows_per_item;   // row slots per item in the partial results (16, or 32 with two row tiles)
-    int32_t mode;            // 0: per-cluster slabs; 1: masked full projection chosen by the planner
-    int32_t pad[56];
+    int32_t mode;            // 0: per-cluster slabs; 1: masked full projection; 2: some clusters by the one, the others by the other
+    // modes 1 and 2: the masked projection's items (from masked_item0 in the item list) and the first
+    // row slot of its partial results; mode 1 repeats the counts above
+    int32_t masked_items;
+    int32_t masked_item0;
+    int32_t masked_slot0;
+    int32_t masked_swz;
+    int32_t pad[52];
 };
 
 // State of one batch-union projection (see union.hip).
@@ -118,15 +123,15 @@ static inline __host__ __device__ int vp_rounds_item_count(int rgs, int slots, i
     int best = rgs;
     double best_fill = 0.0;
     for (int rounds = 1; rounds <= 8; ++rounds) {
-        long long ranges = (long long)rounds * slots / rgs;
+        int ranges = rounds * slots / rgs;   // (slots are at most 2^20)
         if (ranges > vtiles) ranges = vtiles;
         if (ranges < 1) continue;
-        const long long items = (long long)rgs * ranges;
-        const long long full = (items + slots - 1) / slots * slots;
+        const int items = rgs * ranges;
+        const int full = (items + slots - 1) / slots * slots;
         const double fill = (double)items / (double)full;
         if (fill > best_fill + 1e-9) {
             best_fill = fill;
-            best = (int)items;
+            best = items;
         }
         if (fill > 0.97) break;
     }
@@ -248,6 +253,23 @@ struct VpCostModel {
     float bw_gather; // batch-union form: columns of U gathered from the packed W into the union slab
     float t_gather;  // ... and the fixed time of the kernels only that gather needs (seconds)
     float t_row_slab;  // per-cluster slabs: time per row beyond the bytes (staging, lists, partial results; seconds)
+};
+
+// What N rows add to the time of the slabs beyond the bytes.  Up to 512 rows the workgroups wait for their rows and
+// lists (72 us for 10 us of bytes: 512 rows against 32 short lists); more rows mostly find others' bytes to wait for
+// (4,096 rows, 300 clusters of 1,000 to 12,000 tokens, d = 512: 265 us in the kernel for 242 us of bytes).
+static inline __host__ __device__ float vp_rows_time(int N, float t_row)
+{
+    return N <= 512 ? N * t_row : (512 + (N - 512) / 8) * t_row;
+}
+
+// What a plan that masks some of the clusters and keeps the slabs of the others has to fit.
+struct VpMixLimits {
+    int32_t kt;           // k-tiles of a candidate group
+    int32_t slots;        // workgroups of the masked projection that run at a time (0: no such plan)
+    int32_t grid;         // its workgroups (a multiple of 8)
+    int32_t list;         // records of the item list
+    int64_t row_slots;    // row slots of the partial results
 };
 
 #define VP_SMALL_ROWS 16   // batches up to this size are planned by the projection workgroups themselves

@@ -58,8 +58,36 @@ __device__ inline int wave_inclusive_sum(int v)
     return v;
 }
 
+// Sums over rows of 16 lanes (the last lane of a row ends with its total).
+__device__ inline int row_sum(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);   // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);   // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);   // row_shr:8
+    return v;
+}
+#define VP_DPP_ADD(ctrl, rows) v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, rows, 0xf, false));
+__device__ inline float row_sum_float(float v)   // (the order of the additions is fixed)
+{
+    VP_DPP_ADD(0x111, 0xf)
+    VP_DPP_ADD(0x112, 0xf)
+    VP_DPP_ADD(0x114, 0xf)
+    VP_DPP_ADD(0x118, 0xf)
+    return v;
+}
+
 // Sum over the wavefront, to every lane.
 __device__ inline int wave_sum(int v) { return __builtin_amdgcn_readlane(wave_inclusive_sum(v), 63); }
+
+__device__ inline float wave_sum_float(float v)
+{
+    v = row_sum_float(v);
+    VP_DPP_ADD(0x142, 0xa)
+    VP_DPP_ADD(0x143, 0xc)
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+#undef VP_DPP_ADD
 
 // Running maximum m and sum of exp(x - m) over the wavefront's (m, s) pairs, to every lane.
 __device__ inline void wave_log_sum_exp(float &m, float &s)

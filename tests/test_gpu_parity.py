@@ -724,6 +724,46 @@ def test_many_row_kernel_at_d_pad_768_and_1280(oracle, d):
         pu.check_projection(oracle, W, b, C, off, ids, H, k, m_ids, m_logp, m_g)
 
 
+@pytest.mark.parametrize("d,k,N", [(256, 8, 700), (512, 1, 1009), (1000, 8, 640), (1280, 32, 701), (1536, 2, 661)])
+def test_some_clusters_masked_and_some_on_slabs(oracle, d, k, N):
+    """Crowded and nearly empty clusters in one batch: the planner masks the full projection for the rows of some clusters
+    and keeps the slabs of the others (plan mode 2).  Same results as the slabs alone and as the oracle, run twice to
+    the bit, with an empty active set among the clusters, top-1 to top-32, 64 and 48 rows per masked item."""
+    V, K = 3000, 40
+    r, W, b, C = _small_model(60 + d + k, d, V, K)
+    lists = [np.sort(r.choice(V, size=n, replace=False)) for n in np.r_[0, r.integers(1, 20, 3), r.integers(200, 1500, K - 4)]]
+    off = np.zeros(K + 1, np.int64)
+    np.cumsum([len(x) for x in lists], out=off[1:])
+    ids = np.concatenate(lists).astype(np.int32)
+    B = Built(W, b, C, off, ids, k_max=32)
+    p = np.arange(1, K + 1) ** -1.3
+    q = r.choice(r.permutation(K), size=N, p=p / p.sum())
+    q[:K] = np.arange(K)
+    H = _rows(r, C, N, clusters=q)
+    base = B.project(H, k)
+    B.index.set_option("dispatch", 1)
+    # rates that make a slab's price its bytes alone, however many rows share it, and the times long beside the
+    # planner's fixed ones
+    rates = {"cost_row_slab_ns": (0, 60), "cost_bw_l2_gbs": (1000000, 17000), "cost_bw_full_gbs": (1000000, 5100),
+             "cost_bw_slab_gbs": (7, 6800), "cost_bw_gemm_gbs": (14, 14000)}
+    try:
+        for name, (v, _) in rates.items():
+            B.index.set_option(name, v)
+        got = B.project(H, k)
+        assert _planner_mode(B.index, N) == 2
+        assert _overflow(B.index, N) == 0
+        again = B.project(H, k)
+    finally:
+        for name, (_, v) in rates.items():
+            B.index.set_option(name, v)
+        B.index.set_option("dispatch", 0)
+    for x, y in zip(got, again):
+        assert np.array_equal(x, y)
+    assert np.array_equal(got[0], base[0]) and np.array_equal(got[2], base[2])
+    assert np.allclose(got[1], base[1], rtol=0, atol=1e-4)
+    pu.check_projection(oracle, W, b, C, off, ids, H, k, got[0], got[1], got[2])
+
+
 def test_empty_active_sets(oracle):
     """A cluster whose active set is empty (a cluster that lost its members in training): rows that fall into
     it get ids -1 and log-probs -inf in every form of the projection; the other rows are untouched."""
