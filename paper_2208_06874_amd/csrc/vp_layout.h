@@ -141,7 +141,7 @@ static inline __host__ __device__ int vp_rounds_item_count(int rgs, int slots, i
 // The same with 16 row groups and more, where it matters which items run side by side.  An XCD walks its eighth of the
 // item list (vp_item_of_workgroup_even), the row groups of a range one behind the other, and its workgroups read the range
 // from one L2 only while they stay within a few steps of each other.  They do where every XCD has ranges of its own
-// (their number a multiple of eight); ranges that straddle XCDs cost about 6 %, and over long ranges that several XCDs
+// (their number a multiple of eight); ranges that straddle XCDs cost 3 to 6 %, and over long ranges that several XCDs
 // share the workgroups drift apart until most of them read W through the memory side.  Full projection, top-4, V = 250,000,
 // us with the rule above -> with eight ranges or a multiple: d = 1024, N = 4,096: 2,849 -> 1,764, 8,192: 4,986 -> 3,494,
 // 12,000: 7,131 -> 5,143, 16,384: 7,571 -> 6,946; d = 1536, N = 3,000: 4,398 -> 2,252, 6,000: 8,115 -> 4,438; d = 512,
@@ -162,7 +162,7 @@ static inline __host__ __device__ int vp_swept_item_count(int rgs, int slots, in
         const int len = (vtiles + ranges - 1) / ranges;
         const int rounds = ((rgs * ranges + 7) / 8 + per_xcd - 1) / per_xcd;
         float cost = (float)rounds * (float)(len + 40);
-        if (ranges % 8 != 0) cost *= rgs > per_xcd && ranges < 8 && (long long)len * kt > 64 * 1024 ? 1.5f : 1.06f;
+        if (ranges % 8 != 0) cost *= rgs > per_xcd && ranges < 8 && (long long)len * kt > 64 * 1024 ? 1.5f : 1.03f;
         if (m == 0 || cost < best_cost) {
             best_cost = cost;
             best = rgs * ranges;
