@@ -456,7 +456,7 @@ def main():
     rows_per_s = N / (ms_step * 1e-3)
 
     kern = head["kernel"]
-    form = "masked" if head["planner_chose"].startswith("masked") else "slabs"
+    form = {FORMS[0]: "slabs", FORMS[1]: "masked"}.get(head["planner_chose"], "mixed")
     traffic, traffic_source = MEASURED_TRAFFIC_BYTES.get((args.workload, N, form), (None, "none"))
     result = {
         "metric": "projected rows/sec fp16 at V=250K,d=1024; speedup vs full-vocab projection",
