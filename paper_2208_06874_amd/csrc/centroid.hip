@@ -31,8 +31,9 @@ __device__ inline bool score_less(float s, int j, float s2, int j2)
 __global__ __launch_bounds__(256) void centroid_kernel(
     const uint4 *__restrict__ hidden, int N, int d, const uint4 *__restrict__ cp,
     const float *__restrict__ cnorm, int K, int kt_count, int ctiles, int tiles_per_wave, int parts,
-    int2 *__restrict__ cpart)
+    int2 *__restrict__ cpart, const int32_t *__restrict__ go)
 {
+    if (go && *go == 0) return;   // (training: no centroid is another one than in the pass before)
     const int wave = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63;
     const int n = lane & 15;
@@ -180,9 +181,9 @@ void vpk_centroid_small(const void *hidden, int N, int d, const void *cp, const 
 
 // parts: workgroups along the centroid axis; each of their 4 wavefronts takes tiles_per_wave tiles.
 void vpk_centroid(const void *hidden, int N, int d, const void *cp, const float *cnorm, int K, int kt,
-                  int ctiles, int tiles_per_wave, int parts, void *cpart, hipStream_t st)
+                  int ctiles, int tiles_per_wave, int parts, void *cpart, const int32_t *go, hipStream_t st)
 {
     dim3 grid((N + 15) / 16, parts);
     hipLaunchKernelGGL(centroid_kernel, grid, dim3(256), 0, st, (const uint4 *)hidden, N, d, (const uint4 *)cp,
-                       cnorm, K, kt, ctiles, tiles_per_wave, parts, (int2 *)cpart);
+                       cnorm, K, kt, ctiles, tiles_per_wave, parts, (int2 *)cpart, go);
 }

@@ -9,26 +9,62 @@
 // order of the additions (and of the atomics), and the mean sum / count is rounded once, in
 // double precision, to binary16 (nearest, ties to even).  A cluster without members keeps its
 // centroid.
+//
+// An iteration redoes only what the last one changed, with the same results to the bit.  The sums are
+// exact, so they are carried from iteration to iteration: a vector that changes its cluster is taken
+// from one sum and added to the other.  A centroid that came out as it was has the same scores as
+// before, so a vector whose own centroid is one of those stays with it unless a changed centroid now
+// beats it; and where no centroid changed nothing can, and the remaining kernels leave at once.
+// 131,072 vectors, 1,000 clusters, d = 1024, 20 iterations of the benchmark's mixture (1,000, 567, 68, 2 and
+// 0 centroids change): 7,770 -> 1,470 us; 108,433 vectors, 481 clusters, d = 768, 16 iterations: 860 us; 60,000 vectors, 64
+// clusters, d = 512, where it takes 17 iterations to come to rest: 890 us.
 #include <hip/hip_runtime.h>
 #include <algorithm>
 #include "vp_kernels.h"
 #include "project_common.h"
+#include "wave_ops.h"
 
 namespace {
 
 __device__ inline bool part_less(float s, int j, float s2, int j2) { return s < s2 || (s == s2 && j < j2); }
 
-// The membership kernels below count the members.  With RANK they keep what the counting atomics return, each vector's
-// number among its cluster's members (kmeans_place_kernel); without it they do not ask, because a wavefront waits for
-// what it asks for: the split-k kernel at 49,200 vectors, 240 clusters, d = 1024: 87 us per call without, 96 with it;
-// 16,400 vectors, 150 clusters, d = 1536: 59 and 64.
-
-// Finishes Eq. 2 for a chunk of rows (minimum over the centroid ranges) and counts the members.
+// What the membership kernels leave behind.  The first pass counts the members; later passes compare with the pass
+// before, count the events of every cluster (a member that came or went) and keep the counts up to date.  With RANK
+// they keep what the counting atomics return, each vector's number among its cluster's members or events
+// (kmeans_place_kernel); without it they do not ask, because a wavefront waits for what it asks for: the split-k kernel at
+// 49,200 vectors, 240 clusters, d = 1024: 87 us per call without, 96 with it; 16,400 vectors, 150 clusters, d = 1536: 59
+// and 64.
 template <bool RANK>
-__global__ __launch_bounds__(256) void kmeans_assign_kernel(const int2 *__restrict__ cpart, int parts, int rows,
-                                                            int K, int32_t *__restrict__ assign,
-                                                            int32_t *__restrict__ counts, int32_t *__restrict__ rank)
+__device__ __forceinline__ void record_member(VpKmPass p, long row, int j)
 {
+    int *const assign = p.assign;
+    if (p.first) {
+        assign[row] = j;
+        if (RANK) p.rank[row] = atomicAdd(&p.counts[j], 1);
+        else atomicAdd(&p.counts[j], 1);
+        return;
+    }
+    const int old = assign[row];
+    p.prev[row] = old;
+    if (j == old) return;
+    assign[row] = j;
+    atomicAdd(&p.counts[j], 1);
+    atomicSub(&p.counts[old], 1);
+    if (RANK) {
+        p.rank[row] = atomicAdd(&p.events[j], 1);
+        p.rank_old[row] = atomicAdd(&p.events[old], 1);
+    } else {
+        atomicAdd(&p.events[j], 1);
+        atomicAdd(&p.events[old], 1);
+    }
+}
+
+// Finishes Eq. 2 for a chunk of rows (minimum over the centroid ranges).
+template <bool RANK>
+__global__ __launch_bounds__(256) void kmeans_assign_kernel(const int2 *__restrict__ cpart, int parts, long row0, int rows,
+                                                            int K, VpKmPass pass)
+{
+    if (!pass.first && pass.state->changed == 0) return;
     const int r = blockIdx.x * 256 + threadIdx.x;
     if (r >= rows) return;
     float bs = __builtin_inff();
@@ -42,12 +78,78 @@ __global__ __launch_bounds__(256) void kmeans_assign_kernel(const int2 *__restri
         }
     }
     if ((unsigned)bj >= (unsigned)K) bj = 0;   // only when every score is NaN: keep the index in range
-    assign[r] = bj;
-    if (RANK)
-        rank[r] = atomicAdd(&counts[bj], 1);
-    else
-        atomicAdd(&counts[bj], 1);
+    record_member<RANK>(pass, row0 + r, bj);
 }
+
+// The operands of Eq. 2 for a pass: 16 centroids a workgroup, one a wavefront, into the packed tiles, their squared
+// norms, and from the second pass on which of them are others than in the pass before.  Changed centroids are also packed
+// side by side (in no particular order; their numbers beside them), where a pass can meet them without the others.  The
+// norm is summed as cnorm_kernel sums it.  `always`: centroids may change without events (VP_KMEANS_SPLIT_EMPTY).
+__global__ __launch_bounds__(1024) void kmeans_prepare_kernel(const uint16_t *__restrict__ C, int K, int d, int kt_count,
+                                                              int always, VpKmPass pass)
+{
+    if (!pass.first && !always && pass.state->total_events == 0) return;   // (changed is 0 already)
+    __shared__ int is_changed[16];
+    __shared__ int slot0;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    const int j = blockIdx.x * 16 + wave;
+    const int pieces = d >> 3, X = kt_count * 4;
+    uint4 *const cp = reinterpret_cast<uint4 *>(pass.cp);
+    auto place = [&](int slot, int x) { return ((size_t)(slot >> 4) * kt_count + (x >> 2)) * 64 + (x & 3) * 16 + (slot & 15); };
+    const uint4 *row = reinterpret_cast<const uint4 *>(C + (size_t)min(j, K - 1) * d);
+    bool differs = pass.first != 0;
+    float acc = 0.f;
+    if (j < K) {
+        for (int x = lane; x < X; x += 64) {
+            const uint4 v = x < pieces ? row[x] : make_uint4(0, 0, 0, 0);
+            if (!pass.first) {
+                const uint4 was = cp[place(j, x)];
+                differs |= (v.x != was.x) | (v.y != was.y) | (v.z != was.z) | (v.w != was.w);
+            }
+            if (differs) cp[place(j, x)] = v;
+        }
+        for (int i = lane; i < d; i += 64) {
+            const float c = (float)__builtin_bit_cast(_Float16, C[(size_t)j * d + i]);
+            acc += c * c;
+        }
+        for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+    } else if (pass.first) {   // the last group's padding
+        for (int x = lane; x < X; x += 64) cp[place(j, x)] = make_uint4(0, 0, 0, 0);
+        if (lane == 0) pass.cnorm[j] = __builtin_inff();
+    }
+    const bool changed = j < K && __ballot(differs) != 0;
+    if (lane == 0 && j < K) {
+        if (pass.first) pass.counts[j] = 0;
+        pass.events[j] = 0;
+        pass.cursor[j] = 0;
+        pass.flag[j] = changed;
+        if (changed) pass.cnorm[j] = acc;
+    }
+    if (pass.first) return;
+    if (blockIdx.x == 0 && threadIdx.x == 0) pass.state->unsettled = pass.state->settled = 0;
+    if (lane == 0) is_changed[wave] = changed;
+    __syncthreads();
+    int before = 0, total = 0;
+    for (int w = 0; w < 16; ++w) {
+        if (w < wave) before += is_changed[w];
+        total += is_changed[w];
+    }
+    if (threadIdx.x == 0 && total > 0) slot0 = atomicAdd(&pass.state->changed, total);
+    __syncthreads();
+    if (!changed) return;
+    const int slot = __builtin_amdgcn_readfirstlane(slot0 + before);
+    if (lane == 0) {
+        pass.cnorm_changed[slot] = acc;
+        pass.which_changed[slot] = j;
+    }
+    uint4 *const cc = reinterpret_cast<uint4 *>(pass.cp_changed);
+    for (int x = lane; x < X; x += 64) cc[place(slot, x)] = x < pieces ? row[x] : make_uint4(0, 0, 0, 0);
+}
+
+// Whether a later pass is worth taking apart (below): with more centroids changed, nearly every vector meets
+// nearly all of them again.
+__device__ inline bool few_changed(int changed, int K) { return 5 * changed <= 2 * K; }
 
 // Membership of many vectors at once: Eq. 2 as a GEMM.  One workgroup takes 64 vectors and
 // all centroids.  As in the GEMM-shaped projection kernel the k-extent is split over the four
@@ -55,48 +157,76 @@ __global__ __launch_bounds__(256) void kmeans_assign_kernel(const int2 *__restri
 // streaming its slice of every packed centroid tile (the centroids stay in the caches), so
 // each 1 KiB load feeds four MFMAs; the partial inner products of a group of 16 centroids meet
 // in LDS and wavefront w keeps the running (min, argmin) of vector tile w.
-template <int KW, bool RANK>
-__global__ __launch_bounds__(256, (KW <= 8 ? 2 : 1)) void kmeans_assign_gemm_kernel(
-    const uint4 *__restrict__ X, long n, int d, const uint4 *__restrict__ cp, const float *__restrict__ cnorm, int K,
-    int ctiles, int32_t *__restrict__ assign, int32_t *__restrict__ counts, int32_t *__restrict__ rank)
+// A pass in which few centroids changed takes the vectors in another order: those whose own centroids changed in front
+// (PARTED: kmeans_assign_lds_kernel has parted them), or else as the first pass placed them, members of a cluster
+// side by side.  64 vectors none of whose own centroids changed meet the changed centroids only, and
+// each keeps its cluster where its old score is not beaten (ties to the lowest number, as everywhere); it is then
+// the vectors' bytes that take the time.  131,072 vectors, 1,000 clusters, d = 1024, us per pass: all centroids 310 (rows-in-LDS kernel),
+// 68 changed ones 130, two 99.
+template <int KW, bool RANK, bool PARTED>
+__device__ __forceinline__ void assign_split_k(const uint4 *__restrict__ X, long n, int d, int K, int ctiles, const VpKmPass &pass)
 {
     constexpr int KT = KW * 4;
     constexpr int RT = 4;
-    const int wave = threadIdx.x >> 6;
+    const bool first = pass.first != 0;
+    const int changed = first ? K : pass.state->changed;
+    const bool few = !first && few_changed(changed, K);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     const int nn = lane & 15;
     const int q = lane >> 4;
     __shared__ floatx4 xbuf[2 * RT * 4 * 64];
 
-    const uint4 *tiles = cp + (size_t)wave * KW * 64 + lane;
+    const long r0 = (long)blockIdx.x * (16 * RT);
+    const int pieces_per_row = d >> 3;
+    bool all = true;
+    const uint4 *tiles = reinterpret_cast<const uint4 *>(pass.cp) + (size_t)wave * KW * 64 + lane;
+    const float *cnorm = pass.cnorm;
+    int nc = K, groups = ctiles;
     Frag Xb[KW], Yb[KW];
     auto issue = [&](Frag(&buf)[KW], int g) {
         const uint4 *p = tiles + (size_t)g * KT * 64;
 #pragma unroll
         for (int i = 0; i < KW; ++i) buf[i].u = p[i * 64];
     };
-    issue(Xb, 0);
-    if (1 < ctiles) issue(Yb, 1);
-
-    const long r0 = (long)blockIdx.x * (16 * RT);
-    const int pieces_per_row = d >> 3;
     Frag B[RT][KW];
+    auto fetch_vectors = [&](auto vector_of) {
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-        const long row = r0 + rt * 16 + nn;
+        for (int rt = 0; rt < RT; ++rt) {
+            const long row = vector_of(rt * 16 + nn);
 #pragma unroll
-        for (int i = 0; i < KW; ++i) {
-            const int piece = (wave * KW + i) * 4 + q;
-            B[rt][i].u = make_uint4(0, 0, 0, 0);
-            if (row < n && piece < pieces_per_row) B[rt][i].u = X[(size_t)row * pieces_per_row + piece];
+            for (int i = 0; i < KW; ++i) {
+                const int piece = (wave * KW + i) * 4 + q;
+                B[rt][i].u = make_uint4(0, 0, 0, 0);
+                if (row >= 0 && piece < pieces_per_row) B[rt][i].u = X[(size_t)row * pieces_per_row + piece];
+            }
         }
+    };
+    int vec = -1;   // lane l's vector of the 64, in a pass that is taken apart
+    if (!few) {
+        issue(Xb, 0);
+        if (1 < groups) issue(Yb, 1);
+        fetch_vectors([&](int slot) { return r0 + slot < n ? r0 + slot : -1l; });
+    } else {
+        if (r0 + lane < n) vec = (PARTED ? pass.parted : pass.order)[r0 + lane];
+        fetch_vectors([&](int slot) { return (long)__shfl(vec, slot); });
+        if (PARTED) all = r0 < pass.state->unsettled;
+        else all = __ballot(vec >= 0 && pass.flag[pass.assign[max(vec, 0)]] != 0) != 0;   // (the same in every wavefront)
+        if (!all) {
+            tiles = reinterpret_cast<const uint4 *>(pass.cp_changed) + (size_t)wave * KW * 64 + lane;
+            cnorm = pass.cnorm_changed;
+            nc = changed;
+            groups = (changed + 15) >> 4;
+        }
+        issue(Xb, 0);
+        if (1 < groups) issue(Yb, 1);
     }
 
     float best_s = __builtin_inff();
-    int best_j = VP_IDX_NONE;
+    int best_j = -1;               // (a score of +infinity is never taken)
     floatx4 acc[RT];
     auto compute = [&](Frag(&buf)[KW], int gnext) {
-        const bool more = gnext < ctiles;
+        const bool more = gnext < groups;
         const uint4 *p = tiles + (size_t)gnext * KT * 64;
 #pragma unroll
         for (int i = 0; i < KW; ++i) {
@@ -114,32 +244,46 @@ __global__ __launch_bounds__(256, (KW <= 8 ? 2 : 1)) void kmeans_assign_gemm_ker
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) xw[(rt * 4 + wave) * 64 + lane] = acc[rt];
         const float4 cn = *reinterpret_cast<const float4 *>(cnorm + g * 16 + q * 4);
+        int4 which = make_int4(0, 0, 0, 0);
+        if (!all) which = *reinterpret_cast<const int4 *>(pass.which_changed + g * 16 + q * 4);
         __syncthreads();
         const floatx4 dot = (xw[(wave * 4 + 0) * 64 + lane] + xw[(wave * 4 + 1) * 64 + lane]) +
                             (xw[(wave * 4 + 2) * 64 + lane] + xw[(wave * 4 + 3) * 64 + lane]);
         const float cnv[4] = {cn.x, cn.y, cn.z, cn.w};
+        if (all) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int j = g * 16 + q * 4 + i;
-            const float s = cnv[i] - 2.0f * dot[i];
-            if (j < K && s < best_s) {   // j ascends within a lane: strict < keeps the lowest
-                best_s = s;
-                best_j = j;
+            for (int i = 0; i < 4; ++i) {
+                const int j = g * 16 + q * 4 + i;
+                const float s = cnv[i] - 2.0f * dot[i];
+                if (j < K && s < best_s) {   // j ascends within a lane: strict < keeps the lowest
+                    best_s = s;
+                    best_j = j;
+                }
+            }
+        } else {
+            const int num[4] = {which.x, which.y, which.z, which.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {   // (in any order)
+                const float s = cnv[i] - 2.0f * dot[i];
+                const bool take = (g * 16 + q * 4 + i < nc) & ((s < best_s) | ((s == best_s) & (num[i] < best_j)));
+                best_s = take ? s : best_s;
+                best_j = take ? num[i] : best_j;
             }
         }
     };
     int g = 0, par = 0;
-    while (g < ctiles) {
+    while (g < groups) {
         compute(Xb, g + 2);
         finish(g, par);
         par ^= 1;
         ++g;
-        if (g >= ctiles) break;
+        if (g >= groups) break;
         compute(Yb, g + 2);
         finish(g, par);
         par ^= 1;
         ++g;
     }
+    if (best_j < 0) best_j = VP_IDX_NONE;
 #pragma unroll
     for (int off = 16; off <= 32; off <<= 1) {
         const float s2 = __shfl_xor(best_s, off);
@@ -149,45 +293,110 @@ __global__ __launch_bounds__(256, (KW <= 8 ? 2 : 1)) void kmeans_assign_gemm_ker
             best_j = j2;
         }
     }
-    const long row = r0 + wave * 16 + nn;
-    if (q == 0 && row < n) {
+    long row = r0 + wave * 16 + nn;
+    if (few) row = __shfl(vec, wave * 16 + nn);
+    if (q == 0 && row >= 0 && row < n) {
+        if (!all) {
+            const float old_s = pass.best[row];
+            const int old_j = pass.assign[row];
+            if (!part_less(best_s, best_j, old_s, old_j)) {
+                best_s = old_s;
+                best_j = old_j;
+            }
+        }
         if ((unsigned)best_j >= (unsigned)K) best_j = 0;   // only when every score is NaN
-        assign[row] = best_j;
-        if (RANK)
-            rank[row] = atomicAdd(&counts[best_j], 1);
-        else
-            atomicAdd(&counts[best_j], 1);
+        pass.best[row] = best_s;
+        record_member<RANK>(pass, row, best_j);
     }
+}
+
+template <int KW, bool RANK>
+__global__ __launch_bounds__(256, (KW <= 8 ? 2 : 1)) void kmeans_assign_gemm_kernel(const uint4 *__restrict__ X, long n, int d,
+                                                                                    int K, int ctiles, VpKmPass pass)
+{
+    if (!pass.first && pass.state->changed == 0) return;   // nobody moves
+    assign_split_k<KW, RANK, false>(X, n, d, K, ctiles, pass);
+}
+
+// The later passes of a call whose passes over everything run on the rows-in-LDS kernel: those in which few centroids changed.
+template <int KW, bool RANK>
+__global__ __launch_bounds__(256, (KW <= 8 ? 2 : 1)) void kmeans_reassign_kernel(const uint4 *__restrict__ X, long n, int d,
+                                                                                 int K, int ctiles, VpKmPass pass)
+{
+    const int changed = pass.state->changed;
+    if (changed == 0 || !few_changed(changed, K)) return;
+    assign_split_k<KW, RANK, true>(X, n, d, K, ctiles, pass);
 }
 
 // rows-in-LDS membership kernel: wavefronts per workgroup, centroid groups per step, row tiles per item
 constexpr int KL_NW = 8;
 constexpr int KL_G = 2;
-constexpr int km_lds_row_tiles(int kt) { return kt == 48 ? 3 : 4; }
+constexpr int km_lds_row_tiles(int kt) { return kt > 32 ? 3 : 4; }
 
-// The same membership pass with the vectors held in LDS (d_pad = 512, 1024 and 1536): the split-k kernel above
+// Parts the vectors for the kernel above: those whose own centroids changed from the front of the list, the others from
+// its end (in no particular order).  Called by all workgroups of a grid of `threads` threads each; one pair of
+// atomics per workgroup and chunk.
+__device__ inline void part_vectors(long n, const VpKmPass &pass, int *lds, int threads)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, waves = threads >> 6;
+    for (long c0 = (long)blockIdx.x * threads; c0 < n; c0 += (long)gridDim.x * threads) {
+        const long r = c0 + tid;
+        const bool is = r < n;
+        const bool unsettled = is && pass.flag[pass.assign[is ? r : 0]] != 0;
+        const unsigned long long u = __ballot(unsettled), v = __ballot(is && !unsettled);
+        if (lane == 0) {
+            lds[wave] = __popcll(u);
+            lds[waves + wave] = __popcll(v);
+        }
+        __syncthreads();
+        if (tid < 2) {
+            int sum = 0;
+            for (int w = 0; w < waves; ++w) {   // counts -> where each wavefront's vectors start in the workgroup's share
+                const int c = lds[tid * waves + w];
+                lds[tid * waves + w] = sum;
+                sum += c;
+            }
+            lds[2 * waves + tid] = sum ? atomicAdd(tid == 0 ? &pass.state->unsettled : &pass.state->settled, sum) : 0;
+        }
+        __syncthreads();
+        const unsigned long long below = (1ull << lane) - 1;
+        if (unsettled) pass.parted[lds[2 * waves] + lds[wave] + __popcll(u & below)] = (int32_t)r;
+        else if (is) pass.parted[n - 1 - (lds[2 * waves + 1] + lds[waves + wave] + __popcll(v & below))] = (int32_t)r;
+        __syncthreads();   // lds is written again
+    }
+}
+
+// A membership pass over all vectors and centroids with the vectors held in LDS (d_pad = 512 to 1536): the split-k kernel above
 // meets in LDS behind a barrier for every 16 centroids, which leaves the matrix cores idle most of the time.
-// An item is 64 vectors (48 at d_pad = 1536, where 64 do not fit) against all centroids; eight wavefronts walk
+// An item is 64 vectors (48 at d_pad = 1280 and 1536, where 64 do not fit) against all centroids; eight wavefronts walk
 // steps of two groups of 16 centroids on their own (w, w + 8, ...), the centroid tiles streaming
-// from the L2 through a ring of four k-tiles that runs across steps and items, the vectors' operands
+// from the L2 through a ring of k-tiles that runs across steps and items, the vectors' operands
 // from LDS; no barrier but the two of an item.  A workgroup owns its compute unit and walks
 // items, and during an item's last step it touches the next item's vectors, so that staging them finds them in
 // the L2.  Every sum is formed as the split-k kernel forms it - four quarters of the k-extent, each a chain of its own
 // from zero, added as (s0 + s1) + (s2 + s3) - so the memberships are the same to the bit; two groups, not
 // four, because three sets of accumulators must fit the registers.
-// Ten iterations of vp_kmeans with it, us per iteration, split-k kernel -> this one: 131,072 vectors x 1,000 clusters
+// Ten iterations of vp_kmeans with it in every pass, us per iteration, split-k kernel -> this one: 131,072 vectors x 1,000 clusters
 // d = 1024: 417 -> 405, d = 512: 312 -> 274, d = 1536: 892 -> 746; 6,000 x 1,000, d = 1024: 108 -> 77;
 // 4,099 x 1,000, d = 512: 84 -> 52.  (Steps of three groups spill: 526 at the first.)
 template <int KT, bool RANK>
-__global__ __launch_bounds__(KL_NW * 64) void kmeans_assign_lds_kernel(
-    const uint4 *__restrict__ X, long n, int d, const uint4 *__restrict__ cp, const float *__restrict__ cnorm, int K,
-    int ctiles, int nitems, int32_t *__restrict__ assign, int32_t *__restrict__ counts, int32_t *__restrict__ rank)
+__global__ __launch_bounds__(KL_NW * 64) void kmeans_assign_lds_kernel(const uint4 *__restrict__ X, long n, int d, int K,
+                                                                       int ctiles, int nitems, VpKmPass pass)
 {
+    const bool first = pass.first != 0;
+    extern __shared__ uint4 lds[];        // [RT][KT][64]: the vectors in MFMA operand order
+    if (!first && few_changed(pass.state->changed, K)) {
+        // kmeans_reassign_kernel takes the pass
+        if (pass.state->changed > 0) part_vectors(n, pass, reinterpret_cast<int *>(lds), KL_NW * 64);
+        return;
+    }
+    const uint4 *const cp = reinterpret_cast<const uint4 *>(pass.cp);
+    const float *const cnorm = pass.cnorm;
     constexpr int RT = km_lds_row_tiles(KT);
     constexpr int ROWS = 16 * RT;
     constexpr int G = KL_G;
-    constexpr int PF = 4;                 // k-tiles in flight
     constexpr int KW = KT / 4;            // k-tiles per quarter
+    constexpr int PF = KW % 4 == 0 ? 4 : KW / 2;   // k-tiles in flight
     constexpr int XP = KT * 4;            // 16-byte pieces per padded vector
     constexpr int THREADS = KL_NW * 64;
     constexpr int PER = ROWS * XP / THREADS;
@@ -198,7 +407,6 @@ __global__ __launch_bounds__(KL_NW * 64) void kmeans_assign_lds_kernel(
     const int lane = tid & 63;
     const int nn = lane & 15;
     const int q = lane >> 4;
-    extern __shared__ uint4 lds[];        // [RT][KT][64]: the vectors in MFMA operand order
     float *red_s = reinterpret_cast<float *>(lds + RT * KT * 64);   // [KL_NW][ROWS]
     int *red_j = reinterpret_cast<int *>(red_s + KL_NW * ROWS);      // [KL_NW][ROWS]
 
@@ -218,7 +426,7 @@ __global__ __launch_bounds__(KL_NW * 64) void kmeans_assign_lds_kernel(
 #pragma unroll
         for (int j = 0; j < G; ++j) ring[p][j] = tiles[cur[j] + p * 64];
 
-    int before = 0;          // this thread's vector of the item before: members its cluster had before it
+    int before = 0, before_old = 0;   // this thread's vector of the item before: the numbers its atomics returned
     long before_row = -1;
     for (int item = blockIdx.x; item < nitems; item += gridDim.x) {
         const long r0 = (long)item * ROWS;
@@ -244,8 +452,13 @@ __global__ __launch_bounds__(KL_NW * 64) void kmeans_assign_lds_kernel(
             }
         }
         // (the item before: its atomics have come back with the vectors)
-        if (RANK && before_row >= 0) rank[before_row] = before;
+        if (RANK && before_row >= 0) {
+            pass.rank[before_row] = before;
+            if (!first) pass.rank_old[before_row] = before_old;
+        }
         before_row = -1;
+        int old = 0;
+        if (!first && tid < ROWS && r0 + tid < n) old = pass.assign[r0 + tid];   // (fetched well before it is compared)
         __syncthreads();   // the vectors are staged; red_* of the item before has been read
 
         float best_s[RT];
@@ -376,16 +589,38 @@ __global__ __launch_bounds__(KL_NW * 64) void kmeans_assign_lds_kernel(
                 }
             }
             if ((unsigned)bj >= (unsigned)K) bj = 0;   // only when every score is NaN
-            assign[r0 + tid] = bj;
-            if (RANK) {
-                before = atomicAdd(&counts[bj], 1);
-                before_row = r0 + tid;
+            const long row = r0 + tid;
+            pass.best[row] = bs;
+            if (first) {
+                pass.assign[row] = bj;
+                if (RANK) {
+                    before = atomicAdd(&pass.counts[bj], 1);
+                    before_row = row;
+                } else {
+                    atomicAdd(&pass.counts[bj], 1);
+                }
             } else {
-                atomicAdd(&counts[bj], 1);
+                pass.prev[row] = old;
+                if (bj != old) {
+                    pass.assign[row] = bj;
+                    atomicAdd(&pass.counts[bj], 1);
+                    atomicSub(&pass.counts[old], 1);
+                    if (RANK) {
+                        before = atomicAdd(&pass.events[bj], 1);
+                        before_old = atomicAdd(&pass.events[old], 1);
+                        before_row = row;
+                    } else {
+                        atomicAdd(&pass.events[bj], 1);
+                        atomicAdd(&pass.events[old], 1);
+                    }
+                }
             }
         }
     }
-    if (RANK && before_row >= 0) rank[before_row] = before;
+    if (RANK && before_row >= 0) {
+        pass.rank[before_row] = before;
+        if (!first) pass.rank_old[before_row] = before_old;
+    }
 }
 
 template <int KT>
@@ -409,14 +644,13 @@ hipError_t prepare_assign_lds()
 }
 
 template <int KT>
-void launch_assign_lds(const void *X, long n, int d, const void *cp, const float *cnorm, int K, int ctiles,
-                       int32_t *assign, int32_t *counts, int32_t *rank, hipStream_t st)
+void launch_assign_lds(const void *X, long n, int d, int K, int ctiles, const VpKmPass &pass, hipStream_t st)
 {
     constexpr int rows = 16 * km_lds_row_tiles(KT);
     const int nitems = (int)((n + rows - 1) / rows);
-    const auto kernel = rank ? kmeans_assign_lds_kernel<KT, true> : kmeans_assign_lds_kernel<KT, false>;
+    const auto kernel = pass.rank ? kmeans_assign_lds_kernel<KT, true> : kmeans_assign_lds_kernel<KT, false>;
     hipLaunchKernelGGL(kernel, dim3(std::min(nitems, 256)), dim3(KL_NW * 64), km_lds_bytes<KT>(), st, (const uint4 *)X, n,
-                       d, (const uint4 *)cp, cnorm, K, ctiles, nitems, assign, counts, rank);
+                       d, K, ctiles, nitems, pass);
 }
 
 // Whether the rows-in-LDS kernel is the faster one for the membership of n vectors.  From 16 groups of centroids on each
@@ -432,11 +666,11 @@ void launch_assign_lds(const void *X, long n, int d, const void *cp, const float
 //   d_pad 512: faster everywhere (288 clusters: 16,400 36 -> 31, 131,072 140 -> 116)
 bool rows_in_lds_faster(int kt, int ctiles, long n)
 {
-    if (ctiles < KL_NW * KL_G || (kt != 16 && kt != 32 && kt != 48)) return false;
+    if (ctiles < KL_NW * KL_G || (kt != 16 && kt != 24 && kt != 32 && kt != 40 && kt != 48)) return false;
     const long rows = 16 * km_lds_row_tiles(kt);
     const long items = (n + rows - 1) / rows;
     if (kt == 16 || items <= 256) return true;
-    if (kt == 32) {
+    if (kt == 24 || kt == 32) {
         // a last round of 256 that is up to half full, where the other kernel's last round of 512 is as well
         const long last = items % 512;
         const bool uneven = ctiles > 16 && ctiles <= (items <= 512 ? 27 : 19);
@@ -447,68 +681,78 @@ bool rows_in_lds_faster(int kt, int ctiles, long n)
     return !(ctiles > 16 && ctiles <= 19 && items > 512 && n <= 64 * 440);
 }
 
-// start[j] = number of members of clusters below j; cursor[j] = start[j].  One workgroup.
-__global__ __launch_bounds__(1024) void kmeans_scan_kernel(const int32_t *__restrict__ counts, int K,
-                                                           int32_t *__restrict__ start, int32_t *__restrict__ cursor)
+// Where the members (first pass) or the events of the clusters go: every workgroup adds the counts up for itself (they
+// are a few kilobytes; a kernel of its own for that costs 4 us a pass), then writes its vectors' entries into cluster order
+// (the order inside a cluster is arbitrary: the sums are exact).  An entry is a vector's number, its highest bit set where
+// the vector left the cluster.  With the numbers of the counting atomics an entry's place is known; without, a workgroup
+// counts its own vectors in LDS and takes a run of places from every cluster's cursor (131,072 vectors, first pass: 1,000
+// clusters 5 us with the numbers; 200 clusters 6.5 us with the runs, 115 with an atomic for every vector).
+// Where more than half of the vectors moved, the sums are begun anew from all members.
+constexpr int PLACE_THREADS = 1024;
+__global__ __launch_bounds__(PLACE_THREADS) void kmeans_place_kernel(long n, int K, VpKmPass pass, int32_t *__restrict__ start,
+                                                                     int32_t *__restrict__ list,
+                                                                     unsigned long long *__restrict__ acc, size_t acc_n)
 {
-    __shared__ int wsum[17];
-    __shared__ int carry;
-    if (threadIdx.x == 0) carry = 0;
-    __syncthreads();
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int base = 0; base < K; base += 1024) {
-        const int j = base + threadIdx.x;
-        const int v = j < K ? counts[j] : 0;
-        int inc = v;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int up = __shfl_up(inc, off);
-            if (lane >= off) inc += up;
+    extern __shared__ int base[];   // [K + 1]
+    int *const mine = base + K + 1; // [K] this workgroup's members, then the first place of their run
+    __shared__ int wsum[PLACE_THREADS / 64];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool first = pass.first != 0;
+    auto scan = [&](const int32_t *v) {
+        int carry = 0;
+        for (int j0 = 0; j0 < K; j0 += PLACE_THREADS) {
+            const int j = j0 + tid;
+            const int c = j < K ? v[j] : 0;
+            const int inc = wave_inclusive_sum(c);
+            __syncthreads();   // wsum has been read
+            if (lane == 63) wsum[wave] = inc;
+            __syncthreads();
+            const int w = wave_inclusive_sum(lane < PLACE_THREADS / 64 ? wsum[lane] : 0);
+            const int below = wave ? __builtin_amdgcn_readlane(w, wave - 1) : 0;
+            if (j < K) base[j] = carry + below + inc - c;
+            carry += __builtin_amdgcn_readlane(w, PLACE_THREADS / 64 - 1);
         }
-        if (lane == 63) wsum[wave] = inc;
+        if (tid == 0) base[K] = carry;
         __syncthreads();
-        if (threadIdx.x == 0) {
-            int run = carry;
-            for (int w = 0; w < 16; ++w) {
-                const int t = wsum[w];
-                wsum[w] = run;
-                run += t;
-            }
-            wsum[16] = run;
-        }
-        __syncthreads();
-        if (j < K) {
-            const int ex = wsum[wave] + inc - v;
-            start[j] = ex;
-            cursor[j] = ex;
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) carry = wsum[16];
-        __syncthreads();
+        return carry;
+    };
+    const int total = scan(first ? pass.counts : pass.events);
+    const bool anew = first || total > n;
+    if (blockIdx.x == 0 && tid == 0) {
+        pass.state->total_events = total;
+        pass.state->anew = anew;
+        pass.state->changed = 0;   // (read by the membership pass before, counted again by the next one's preparation)
     }
-    if (threadIdx.x == 0) start[K] = carry;
-}
-
-// Row numbers in cluster order (the order inside a cluster is arbitrary: the sums are exact).
-__global__ __launch_bounds__(256) void kmeans_scatter_kernel(const int32_t *__restrict__ assign, long n,
-                                                             int32_t *__restrict__ cursor, int32_t *__restrict__ perm)
-{
-    const long r = (long)blockIdx.x * 256 + threadIdx.x;
-    if (r >= n) return;
-    const int pos = atomicAdd(&cursor[assign[r]], 1);
-    perm[pos] = (int32_t)r;
-}
-
-// The same where the membership pass kept what its counting atomics returned, each vector's number among
-// its cluster's members: no second round of a hundred atomics on every counter, one behind the other
-// (131,072 vectors, 1,000 clusters: 35 us with the atomics, 5 us with the numbers).
-__global__ __launch_bounds__(256) void kmeans_place_kernel(const int32_t *__restrict__ assign,
-                                                           const int32_t *__restrict__ rank, long n,
-                                                           const int32_t *__restrict__ start, int32_t *__restrict__ perm)
-{
-    const long r = (long)blockIdx.x * 256 + threadIdx.x;
-    if (r >= n) return;
-    perm[start[assign[r]] + rank[r]] = (int32_t)r;
+    if (total == 0) return;
+    if (anew && !first) scan(pass.counts);
+    if (blockIdx.x == 0)
+        for (int j = tid; j <= K; j += PLACE_THREADS) start[j] = base[j];
+    if (anew && !first)
+        for (size_t e = (size_t)blockIdx.x * PLACE_THREADS + tid; e < acc_n; e += (size_t)gridDim.x * PLACE_THREADS) acc[e] = 0ull;
+    const long r = (long)blockIdx.x * PLACE_THREADS + tid;
+    const bool is = r < n;
+    const int j = is ? pass.assign[r] : 0;
+    if (anew && first && pass.rank) {
+        if (is) list[base[j] + pass.rank[r]] = (int32_t)r;
+        return;
+    }
+    if (anew) {
+        for (int c = tid; c < K; c += PLACE_THREADS) mine[c] = 0;
+        __syncthreads();
+        const int local = is ? atomicAdd(&mine[j], 1) : 0;
+        __syncthreads();
+        for (int c = tid; c < K; c += PLACE_THREADS)
+            if (mine[c]) mine[c] = atomicAdd(&pass.cursor[c], mine[c]);
+        __syncthreads();
+        if (is) list[base[j] + mine[j] + local] = (int32_t)r;
+        return;
+    }
+    if (!is) return;
+    const int old = pass.prev[r];
+    if (j == old) return;
+    list[base[j] + (pass.rank ? pass.rank[r] : atomicAdd(&pass.cursor[j], 1))] = (int32_t)r;
+    list[base[old] + (pass.rank ? pass.rank_old[r] : atomicAdd(&pass.cursor[old], 1))] = (int32_t)((uint32_t)r | 0x80000000u);
 }
 
 // Running sums of 8 coordinates.  They are kept in double precision: every binary16 value is
@@ -518,9 +762,12 @@ __global__ __launch_bounds__(256) void kmeans_place_kernel(const int32_t *__rest
 // atomics.
 typedef _Float16 half2t __attribute__((ext_vector_type(2)));
 
-__device__ inline void add_units(double (&s)[8], const uint4 v)
+// entry: a vector's number; where they are EVENTS its highest bit takes the vector away (its signs are turned)
+template <bool EVENTS>
+__device__ inline void add_units(double (&s)[8], const uint4 v, uint32_t entry)
 {
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    const uint32_t turn = EVENTS ? (entry >> 31) * 0x80008000u : 0u;
+    const uint32_t w[4] = {v.x ^ turn, v.y ^ turn, v.z ^ turn, v.w ^ turn};
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const half2t h = __builtin_bit_cast(half2t, w[e]);
@@ -531,19 +778,45 @@ __device__ inline void add_units(double (&s)[8], const uint4 v)
 
 __device__ inline unsigned long long to_units(double sum) { return (unsigned long long)(long long)(sum * 0x1p24); }
 
-// Sum of the members of cluster blockIdx.x that fall to this workgroup (every `splits`-th one
-// starting at blockIdx.y).  A thread owns one 16-byte piece (8 coordinates) of the vectors; when
-// a vector has fewer than 256 pieces the workgroup's threads form several member lanes that take
-// the workgroup's members in turn.  Eight rows are in flight per thread.
-__global__ __launch_bounds__(256) void kmeans_sum_kernel(const uint4 *__restrict__ X, int pieces,
-                                                         const int32_t *__restrict__ perm,
-                                                         const int32_t *__restrict__ start, int splits,
-                                                         unsigned long long *__restrict__ acc)
+// Sum of the entries [first, last) taken every `step`-th, coordinates 8 * piece and following.
+template <bool EVENTS>
+__device__ inline void sum_entries(double (&s)[8], const uint4 *__restrict__ X, int pieces, int piece,
+                                   const int32_t *__restrict__ list, int first, int last, int step)
 {
+    int m = first;
+    for (; m + 7 * step < last; m += 8 * step) {
+        // entries first, then all eight rows: written as one expression the loads of an entry and of its row
+        // alternate and every one waits for the one before
+        uint32_t r[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) r[u] = (uint32_t)list[m + u * step];
+        uint4 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = X[(size_t)(r[u] & 0x7fffffffu) * pieces + piece];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) add_units<EVENTS>(s, v[u], r[u]);
+    }
+    for (; m < last; m += step) {
+        const uint32_t r = (uint32_t)list[m];
+        add_units<EVENTS>(s, X[(size_t)(r & 0x7fffffffu) * pieces + piece], r);
+    }
+}
+
+// Sum of the entries of cluster blockIdx.x that fall to this workgroup (every `splits`-th one
+// starting at blockIdx.y), added to the sums in memory.  A thread owns one 16-byte piece (8 coordinates) of the vectors;
+// when a vector has fewer than 256 pieces the workgroup's threads form several member lanes that take
+// the workgroup's entries in turn.  Eight rows are in flight per thread.
+__global__ __launch_bounds__(256) void kmeans_sum_kernel(const uint4 *__restrict__ X, int pieces,
+                                                         const int32_t *__restrict__ list,
+                                                         const int32_t *__restrict__ start, int splits,
+                                                         unsigned long long *__restrict__ acc, const VpKmState *__restrict__ state)
+{
+    if (state->total_events == 0) return;
     const int j = blockIdx.x;
     const int m0 = start[j], m1 = start[j + 1];
     const int lanes = pieces <= 128 ? 256 / pieces : 1;       // member lanes per workgroup
     const int ml = lanes > 1 ? threadIdx.x / pieces : 0;       // this thread's member lane
+    if (m0 + (int)blockIdx.y * lanes >= m1) return;            // nothing falls to this workgroup
     __shared__ unsigned long long lsum[128 * 8];
     if (lanes > 1) {
         for (int e = threadIdx.x; e < pieces * 8; e += 256) lsum[e] = 0ull;
@@ -553,34 +826,21 @@ __global__ __launch_bounds__(256) void kmeans_sum_kernel(const uint4 *__restrict
     const int first = m0 + blockIdx.y * lanes + ml;
     for (int piece = lanes > 1 ? threadIdx.x - ml * pieces : threadIdx.x; piece < pieces && ml < lanes; piece += 256) {
         double s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        int m = first;
-        for (; m + 7 * step < m1; m += 8 * step) {
-            int r[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) r[u] = perm[m + u * step];
-            uint4 v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = X[(size_t)r[u] * pieces + piece];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) add_units(s, v[u]);
-        }
-        for (; m < m1; m += step) add_units(s, X[(size_t)perm[m] * pieces + piece]);
+        if (state->anew) sum_entries<false>(s, X, pieces, piece, list, first, m1, step);
+        else sum_entries<true>(s, X, pieces, piece, list, first, m1, step);
         if (lanes > 1) {
             // the member lanes meet in LDS; one global addition per coordinate and workgroup
             unsigned long long *slot = lsum + (size_t)piece * 8;
 #pragma unroll
             for (int e = 0; e < 8; ++e) atomicAdd(slot + e, to_units(s[e]));
-        } else if (first < m1) {
+        } else {
 #pragma unroll
             for (int e = 0; e < 8; ++e) atomicAdd(&acc[((size_t)j * pieces + piece) * 8 + e], to_units(s[e]));
         }
     }
     if (lanes > 1) {
         __syncthreads();
-        if (m0 + (int)blockIdx.y * lanes < m1) {
-            for (int e = threadIdx.x; e < pieces * 8; e += 256)
-                atomicAdd(&acc[(size_t)j * pieces * 8 + e], lsum[e]);
-        }
+        for (int e = threadIdx.x; e < pieces * 8; e += 256) atomicAdd(&acc[(size_t)j * pieces * 8 + e], lsum[e]);
     }
 }
 
@@ -618,80 +878,74 @@ __host__ __device__ inline uint16_t double_to_half_bits(double v)
     return (uint16_t)(sign | h);
 }
 
-// One workgroup per cluster: sums all its members and writes the new centroid at once (no
-// sums in memory, no atomics between workgroups).  Used when there are enough clusters to fill
-// the chip this way; the member lanes of the workgroup meet in LDS.
-__global__ __launch_bounds__(1024) void kmeans_mean_kernel(const uint4 *__restrict__ X, int pieces,
-                                                          const int32_t *__restrict__ perm,
-                                                          const int32_t *__restrict__ start, uint4 *__restrict__ C)
+// One workgroup per cluster: brings the cluster's sum up to date with its entries and writes the new centroid at once
+// (no atomics between workgroups).  Used when there are enough clusters to fill
+// the chip this way; the member lanes of the workgroup (two at least) meet in LDS.
+constexpr int MEAN_THREADS = 1024;
+static_assert(VP_KM_MAX_PIECES <= MEAN_THREADS / 2, "two member lanes at the largest width");
+__global__ __launch_bounds__(MEAN_THREADS) void kmeans_mean_kernel(const uint4 *__restrict__ X, int pieces,
+                                                          const int32_t *__restrict__ list,
+                                                          const int32_t *__restrict__ start,
+                                                          const int32_t *__restrict__ counts,
+                                                          unsigned long long *__restrict__ acc,
+                                                          const VpKmState *__restrict__ state, uint4 *__restrict__ C)
 {
+    if (state->total_events == 0) return;
     const int j = blockIdx.x;
     const int m0 = start[j], m1 = start[j + 1];
-    if (m0 == m1) return;                                      // no members: the centroid stays
-    constexpr int T = 1024;                                   // threads per workgroup
-    const int lanes = pieces <= T / 2 ? T / pieces : 1;       // member lanes
-    const int ml = lanes > 1 ? threadIdx.x / pieces : 0;
-    __shared__ unsigned long long lsum[(T / 2) * 8];
-    if (lanes > 1) {
-        for (int e = threadIdx.x; e < pieces * 8; e += T) lsum[e] = 0ull;
-        __syncthreads();
+    const bool anew = state->anew != 0;
+    unsigned long long *const sum = acc + (size_t)j * pieces * 8;
+    if (m0 == m1) {                                            // nobody came or went: the centroid stays
+        if (anew)
+            for (int e = threadIdx.x; e < pieces * 8; e += MEAN_THREADS) sum[e] = 0ull;
+        return;
     }
-    const double inv_units = 0x1p-24;
-    const double count = (double)(m1 - m0);
-    for (int piece = lanes > 1 ? threadIdx.x - ml * pieces : threadIdx.x; piece < pieces && ml < lanes; piece += T) {
+    const int lanes = MEAN_THREADS / pieces;                   // member lanes
+    const int ml = threadIdx.x / pieces;
+    __shared__ unsigned long long lsum[(MEAN_THREADS / 2) * 8];
+    for (int e = threadIdx.x; e < pieces * 8; e += MEAN_THREADS) lsum[e] = anew ? 0ull : sum[e];
+    __syncthreads();
+    const int piece = threadIdx.x - ml * pieces;
+    if (ml < lanes && m0 + ml < m1) {
         double s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        int m = m0 + ml;
-        for (; m + 7 * lanes < m1; m += 8 * lanes) {
-            // row numbers first, then all eight rows: written as one expression the loads of a row
-            // number and of its row alternate and every one waits for the one before
-            int r[8];
+        if (anew) sum_entries<false>(s, X, pieces, piece, list, m0 + ml, m1, lanes);
+        else sum_entries<true>(s, X, pieces, piece, list, m0 + ml, m1, lanes);
 #pragma unroll
-            for (int u = 0; u < 8; ++u) r[u] = perm[m + u * lanes];
-            uint4 v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = X[(size_t)r[u] * pieces + piece];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) add_units(s, v[u]);
-        }
-        for (; m < m1; m += lanes) add_units(s, X[(size_t)perm[m] * pieces + piece]);
-        if (lanes > 1) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) atomicAdd(lsum + (size_t)piece * 8 + e, to_units(s[e]));
-        } else {
-            uint32_t h[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) h[e] = double_to_half_bits(s[e] / count);
-            C[(size_t)j * pieces + piece] = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16),
-                                                       h[6] | (h[7] << 16));
-        }
+        for (int e = 0; e < 8; ++e) atomicAdd(lsum + (size_t)piece * 8 + e, to_units(s[e]));
     }
-    if (lanes > 1) {
-        __syncthreads();
-        for (int piece = threadIdx.x; piece < pieces; piece += T) {
-            uint32_t h[8];
+    __syncthreads();
+    const int c = counts[j];
+    for (int p = threadIdx.x; p < pieces; p += MEAN_THREADS) {
+        uint32_t h[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
-                h[e] = double_to_half_bits((double)(long long)lsum[piece * 8 + e] * inv_units / count);
-            C[(size_t)j * pieces + piece] = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16),
-                                                       h[6] | (h[7] << 16));
+        for (int e = 0; e < 8; ++e) {
+            const unsigned long long v = lsum[p * 8 + e];
+            sum[p * 8 + e] = v;
+            h[e] = double_to_half_bits((double)(long long)v * 0x1p-24 / (double)c);
         }
+        // (a cluster that lost its last member keeps its centroid)
+        if (c > 0)
+            C[(size_t)j * pieces + p] = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16),
+                                                   h[6] | (h[7] << 16));
     }
 }
 
-// New centroids from the sums; the sums are cleared for the next iteration.
-__global__ __launch_bounds__(256) void kmeans_update_kernel(unsigned long long *__restrict__ acc,
-                                                            const int32_t *__restrict__ counts, int K, int d,
+// New centroids from the sums in memory, of the clusters with events.
+__global__ __launch_bounds__(256) void kmeans_update_kernel(const unsigned long long *__restrict__ acc,
+                                                            const int32_t *__restrict__ start,
+                                                            const int32_t *__restrict__ counts,
+                                                            const VpKmState *__restrict__ state, int K, int d,
                                                             uint16_t *__restrict__ C)
 {
+    if (state->total_events == 0) return;
     const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
     if (e >= (size_t)K * d) return;
     const int j = (int)(e / d);
     const int c = counts[j];
-    if (c > 0) {
+    if (c > 0 && start[j] != start[j + 1]) {
         const double sum = (double)(long long)acc[e];
         C[e] = double_to_half_bits(sum * 0x1p-24 / (double)c);
     }
-    acc[e] = 0ull;
 }
 
 // binary16 bits -> double, exactly
@@ -877,12 +1131,16 @@ void vpk_fill_u32(void *p, size_t n, uint32_t v, hipStream_t st)
     hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, (uint32_t *)p, n, v);
 }
 
-void vpk_kmeans_assign(const void *cpart, int parts, int rows, int K, int32_t *assign, int32_t *counts,
-                       int32_t *rank, hipStream_t st)
+void vpk_kmeans_prepare(const void *C, int K, int d, int kt, int K_pad, bool always, const VpKmPass &pass, hipStream_t st)
 {
-    const auto kernel = rank ? kmeans_assign_kernel<true> : kmeans_assign_kernel<false>;
-    hipLaunchKernelGGL(kernel, dim3((rows + 255) / 256), dim3(256), 0, st, (const int2 *)cpart, parts, rows, K, assign,
-                       counts, rank);
+    hipLaunchKernelGGL(kmeans_prepare_kernel, dim3(K_pad / 16), dim3(1024), 0, st, (const uint16_t *)C, K, d, kt, always ? 1 : 0,
+                       pass);
+}
+
+void vpk_kmeans_assign(const void *cpart, int parts, long row0, int rows, int K, const VpKmPass &pass, hipStream_t st)
+{
+    const auto kernel = pass.rank ? kmeans_assign_kernel<true> : kmeans_assign_kernel<false>;
+    hipLaunchKernelGGL(kernel, dim3((rows + 255) / 256), dim3(256), 0, st, (const int2 *)cpart, parts, row0, rows, K, pass);
 }
 
 bool vpk_kmeans_rows_in_lds(int kt, int ctiles, long n)
@@ -890,7 +1148,9 @@ bool vpk_kmeans_rows_in_lds(int kt, int ctiles, long n)
     if (!rows_in_lds_faster(kt, ctiles, n)) return false;
     hipError_t e;
     if (kt == 16) e = prepare_assign_lds<16>();
+    else if (kt == 24) e = prepare_assign_lds<24>();
     else if (kt == 32) e = prepare_assign_lds<32>();
+    else if (kt == 40) e = prepare_assign_lds<40>();
     else if (kt == 48) e = prepare_assign_lds<48>();
     else return false;
     if (e == hipSuccess) return true;
@@ -898,61 +1158,69 @@ bool vpk_kmeans_rows_in_lds(int kt, int ctiles, long n)
     return false;
 }
 
-bool vpk_kmeans_assign_gemm(const void *X, long n, int d, const void *cp, const float *cnorm, int K, int kt, int ctiles,
-                            bool rows_in_lds, int32_t *assign, int32_t *counts, int32_t *rank, hipStream_t st)
+bool vpk_kmeans_assign_gemm(const void *X, long n, int d, int K, int kt, int ctiles, bool rows_in_lds, const VpKmPass &pass,
+                            hipStream_t st)
 {
+    const dim3 grid((unsigned)((n + 63) / 64)), block(256);
+#define VP_KM_LAUNCH(kernel, KW)                                                                                     \
+    hipLaunchKernelGGL((pass.rank ? kernel<KW, true> : kernel<KW, false>), grid, block, 0, st, (const uint4 *)X, n, d, K, \
+                       ctiles, pass)
     if (rows_in_lds) {
-        if (kt == 16) launch_assign_lds<16>(X, n, d, cp, cnorm, K, ctiles, assign, counts, rank, st);
-        else if (kt == 32) launch_assign_lds<32>(X, n, d, cp, cnorm, K, ctiles, assign, counts, rank, st);
-        else launch_assign_lds<48>(X, n, d, cp, cnorm, K, ctiles, assign, counts, rank, st);
+#define VP_KM_CASE(KT)                                                            \
+    case KT:                                                                      \
+        launch_assign_lds<KT>(X, n, d, K, ctiles, pass, st);                      \
+        if (!pass.first) VP_KM_LAUNCH(kmeans_reassign_kernel, KT / 4);            \
+        break;
+        switch (kt) {
+            VP_KM_CASE(16)
+            VP_KM_CASE(24)
+            VP_KM_CASE(32)
+            VP_KM_CASE(40)
+            VP_KM_CASE(48)
+            default: break;   // callers ask vpk_kmeans_rows_in_lds
+        }
+#undef VP_KM_CASE
         return true;
     }
-    const dim3 grid((unsigned)((n + 63) / 64)), block(256);
-#define VP_KM_CASE(KW)                                                                                                \
-    case KW * 4:                                                                                                      \
-        hipLaunchKernelGGL((rank ? kmeans_assign_gemm_kernel<KW, true> : kmeans_assign_gemm_kernel<KW, false>), grid, \
-                           block, 0, st, (const uint4 *)X, n, d, (const uint4 *)cp, cnorm, K, ctiles, assign, counts, \
-                           rank);                                                                                     \
+#define VP_KM_CASE(KW)                                       \
+    case KW * 4:                                             \
+        VP_KM_LAUNCH(kmeans_assign_gemm_kernel, KW);         \
         return true;
     switch (kt) {
         VP_KM_CASE(2)
         VP_KM_CASE(4)
+        VP_KM_CASE(6)
         VP_KM_CASE(8)
+        VP_KM_CASE(10)
         VP_KM_CASE(12)
         default: return false;   // other k-extents: the caller falls back to the decode-time kernel
     }
 #undef VP_KM_CASE
+#undef VP_KM_LAUNCH
 }
 
-void vpk_kmeans_bucket(const int32_t *assign, const int32_t *rank, long n, const int32_t *counts, int K, int32_t *start,
-                       int32_t *cursor, int32_t *perm, hipStream_t st)
+void vpk_kmeans_place(long n, int K, int d, const VpKmPass &pass, int32_t *start, int32_t *list, void *acc, hipStream_t st)
 {
-    hipLaunchKernelGGL(kmeans_scan_kernel, dim3(1), dim3(1024), 0, st, counts, K, start, cursor);
-    if (rank) {
-        hipLaunchKernelGGL(kmeans_place_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, assign, rank, n, start,
-                           perm);
-        return;
-    }
-    hipLaunchKernelGGL(kmeans_scatter_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, assign, n, cursor,
-                       perm);
+    hipLaunchKernelGGL(kmeans_place_kernel, dim3((unsigned)((n + PLACE_THREADS - 1) / PLACE_THREADS)), dim3(PLACE_THREADS),
+                       (size_t)(2 * K + 1) * sizeof(int), st, n, K, pass, start, list, (unsigned long long *)acc, (size_t)K * d);
 }
 
 bool vpk_kmeans_mean_form(int K) { return K >= 256; }
 
-void vpk_kmeans_update(const void *X, int d, const int32_t *perm, const int32_t *start, const int32_t *counts, int K,
-                       int splits, void *acc, void *C, hipStream_t st)
+void vpk_kmeans_update(const void *X, int d, const int32_t *list, const int32_t *start, const int32_t *counts, int K,
+                       int splits, void *acc, const VpKmState *state, void *C, hipStream_t st)
 {
     if (vpk_kmeans_mean_form(K)) {
-        // enough clusters to fill the chip with one workgroup each: no sums in memory at all
-        hipLaunchKernelGGL(kmeans_mean_kernel, dim3(K), dim3(1024), 0, st, (const uint4 *)X, d / 8, perm, start,
-                           (uint4 *)C);
+        // enough clusters to fill the chip with one workgroup each
+        hipLaunchKernelGGL(kmeans_mean_kernel, dim3(K), dim3(MEAN_THREADS), 0, st, (const uint4 *)X, d / 8, list, start,
+                           counts, (unsigned long long *)acc, state, (uint4 *)C);
         return;
     }
-    hipLaunchKernelGGL(kmeans_sum_kernel, dim3(K, splits), dim3(256), 0, st, (const uint4 *)X, d / 8, perm, start,
-                       splits, (unsigned long long *)acc);
+    hipLaunchKernelGGL(kmeans_sum_kernel, dim3(K, splits), dim3(256), 0, st, (const uint4 *)X, d / 8, list, start,
+                       splits, (unsigned long long *)acc, state);
     const size_t e = (size_t)K * d;
     hipLaunchKernelGGL(kmeans_update_kernel, dim3((unsigned)((e + 255) / 256)), dim3(256), 0, st,
-                       (unsigned long long *)acc, counts, K, d, (uint16_t *)C);
+                       (const unsigned long long *)acc, start, counts, state, K, d, (uint16_t *)C);
 }
 
 void vpk_kmeans_split(const int32_t *counts, int K, int d, void *C, hipStream_t st)

@@ -19,7 +19,8 @@ constexpr int CHUNK_ROWS = 65536;   // vectors per launch of the Eq. 2 kernel
 
 struct KmeansLayout {
     int d_pad, kt, ctiles, K_pad, parts, tpw;
-    size_t cp, cnorm, cpart, start, cursor, perm, acc, total;
+    size_t cp, cnorm, cp_changed, cnorm_changed, which_changed, flag, cpart, start, cursor, events, order, list, prev, rank,
+        rank_old, parted, best, acc, state, total;
 };
 
 vp_status kmeans_layout(int64_t n, int d, int K, KmeansLayout *L)
@@ -37,13 +38,26 @@ vp_status kmeans_layout(int64_t n, int d, int K, KmeansLayout *L)
     L->tpw = ceil_div(L->ctiles, parts * 4);
     L->parts = ceil_div(L->ctiles, L->tpw * 4);
     size_t o = 0;
-    L->cp = o;      o += align_up((size_t)L->K_pad * L->d_pad * 2);
-    L->cnorm = o;   o += align_up((size_t)L->K_pad * 4);
-    L->cpart = o;   o += align_up((size_t)chunk * L->parts * 8);
-    L->start = o;   o += align_up((size_t)(K + 1) * 4);
-    L->cursor = o;  o += align_up((size_t)K * 4);
-    L->perm = o;    o += align_up((size_t)n * 4);
-    L->acc = o;     o += align_up((size_t)K * d * 8);
+    auto take = [&](size_t bytes) { size_t at = o; o += align_up(bytes); return at; };
+    L->cp = take((size_t)L->K_pad * L->d_pad * 2);
+    L->cnorm = take((size_t)L->K_pad * 4);
+    L->cp_changed = take((size_t)L->K_pad * L->d_pad * 2);
+    L->cnorm_changed = take((size_t)L->K_pad * 4);
+    L->which_changed = take((size_t)L->K_pad * 4);
+    L->flag = take((size_t)K * 4);
+    L->cpart = take((size_t)chunk * L->parts * 8);
+    L->start = take((size_t)(K + 1) * 4);
+    L->cursor = take((size_t)K * 4);
+    L->events = take((size_t)K * 4);
+    L->order = take((size_t)n * 4);
+    L->list = take((size_t)n * 4);
+    L->prev = take((size_t)n * 4);
+    L->rank = take((size_t)n * 4);
+    L->rank_old = take((size_t)n * 4);
+    L->parted = take((size_t)n * 4);
+    L->best = take((size_t)n * 4);
+    L->acc = take((size_t)K * d * 8);
+    L->state = take(sizeof(VpKmState));
     L->total = o;
     return VP_OK;
 }
@@ -76,39 +90,57 @@ vp_status vp_kmeans(const void *x, int64_t n, int32_t d, int32_t K, int32_t iter
     if (workspace_bytes < L.total) return (vp_status)vpi_fail(VP_ERR_WORKSPACE, "workspace of %zu bytes, %zu needed", workspace_bytes, L.total);
     hipStream_t st = (hipStream_t)hip_stream;
     char *ws = (char *)workspace;
-    void *cp = ws + L.cp;
-    float *cnorm = (float *)(ws + L.cnorm);
+    auto ints = [&](size_t at) { return (int32_t *)(ws + at); };
     void *cpart = ws + L.cpart;
-    int32_t *start = (int32_t *)(ws + L.start), *cursor = (int32_t *)(ws + L.cursor), *perm = (int32_t *)(ws + L.perm);
+    int32_t *start = ints(L.start), *order = ints(L.order), *list = ints(L.list);
     void *acc = ws + L.acc;
+    VpKmState *state = (VpKmState *)(ws + L.state);
+    VpKmPass pass = {};
+    pass.state = state;
+    pass.cp = ws + L.cp;
+    pass.cnorm = (float *)(ws + L.cnorm);
+    pass.cp_changed = ws + L.cp_changed;
+    pass.cnorm_changed = (float *)(ws + L.cnorm_changed);
+    pass.which_changed = ints(L.which_changed);
+    pass.flag = ints(L.flag);
+    pass.assign = assign;
+    pass.counts = counts;
+    pass.events = ints(L.events);
+    pass.cursor = ints(L.cursor);
+    pass.prev = ints(L.prev);
+    pass.best = (float *)(ws + L.best);
+    pass.order = order;
+    pass.parted = ints(L.parted);
     // clusters x splits workgroups of the summing kernel: a few thousand
     const int splits = std::max(1, std::min(64, 2048 / K));
 
-    // The sums in memory are needed for few clusters only; with many, their place holds each vector's number
-    // among its cluster's members, if it is large enough (at most 2 * d vectors per cluster on average).
+    // Numbers of the counting atomics: with many clusters of at most 2 * d vectors on average.  Few clusters have
+    // many members each, and what their counters return is long in coming (record_member).
     const bool mean_form = vpk_kmeans_mean_form(K);
-    int32_t *const rank_buf = mean_form && (size_t)n * 4 <= (size_t)K * d * 8 ? (int32_t *)acc : nullptr;
+    const bool numbers = mean_form && (size_t)n * 4 <= (size_t)K * d * 8;
     if (!mean_form) vpk_fill_u32(acc, (size_t)K * d * 2, 0u, st);
     const bool rows_in_lds = n >= 4096 && vpk_kmeans_rows_in_lds(L.kt, L.ctiles, (long)n);
+    const bool split = (flags & VP_KMEANS_SPLIT_EMPTY) != 0;
     for (int it = 0; it <= iters; ++it) {
+        pass.first = it == 0;
+        pass.rank = it < iters && numbers ? ints(L.rank) : nullptr;   // (the last pass only assigns)
+        pass.rank_old = ints(L.rank_old);
         // Eq. 2 operands of the current centroids
-        vpk_pack_rows(centroids, K, d, L.kt, cp, st);
-        vpk_cnorm(centroids, K, d, L.K_pad, cnorm, st);
-        vpk_fill_u32(counts, (size_t)K, 0u, st);
-        // memberships: the GEMM-shaped kernel when there are enough vectors to fill the chip with
-        // 64-vector workgroups, else (or for k-extents it is not built for) the decode-time kernel
-        int32_t *const rank = it < iters ? rank_buf : nullptr;   // (the last pass only assigns)
-        const bool gemm = n >= 4096 && vpk_kmeans_assign_gemm(x, (long)n, d, cp, cnorm, K, L.kt, L.ctiles, rows_in_lds, assign, counts, rank, st);
+        vpk_kmeans_prepare(centroids, K, d, L.kt, L.K_pad, split, pass, st);
+        // memberships: the GEMM-shaped kernels when there are enough vectors to fill the chip with
+        // 64-vector workgroups, else (or for k-extents they are not built for) the decode-time kernel
+        const bool gemm = n >= 4096 && vpk_kmeans_assign_gemm(x, (long)n, d, K, L.kt, L.ctiles, rows_in_lds, pass, st);
         for (int64_t r0 = 0; !gemm && r0 < n; r0 += CHUNK_ROWS) {
             const int rows = (int)std::min<int64_t>(CHUNK_ROWS, n - r0);
-            vpk_centroid((const char *)x + (size_t)r0 * d * 2, rows, d, cp, cnorm, K, L.kt, L.ctiles, L.tpw, L.parts,
-                         cpart, st);
-            vpk_kmeans_assign(cpart, L.parts, rows, K, assign + r0, counts, rank ? rank + r0 : nullptr, st);
+            vpk_centroid((const char *)x + (size_t)r0 * d * 2, rows, d, pass.cp, pass.cnorm, K, L.kt, L.ctiles, L.tpw, L.parts,
+                         cpart, pass.first ? nullptr : &state->changed, st);
+            vpk_kmeans_assign(cpart, L.parts, (long)r0, rows, K, pass, st);
         }
         if (it == iters) break;   // the last pass only assigns
-        vpk_kmeans_bucket(assign, rank, (long)n, counts, K, start, cursor, perm, st);
-        vpk_kmeans_update(x, d, perm, start, counts, K, splits, acc, centroids, st);
-        if (flags & VP_KMEANS_SPLIT_EMPTY) vpk_kmeans_split(counts, K, d, centroids, st);
+        int32_t *const entries = pass.first ? order : list;
+        vpk_kmeans_place((long)n, K, d, pass, start, entries, acc, st);
+        vpk_kmeans_update(x, d, entries, start, counts, K, splits, acc, state, centroids, st);
+        if (split) vpk_kmeans_split(counts, K, d, centroids, st);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return (vp_status)vpi_fail(VP_ERR_HIP, "vp_kmeans: %s", hipGetErrorString(e));

@@ -360,7 +360,7 @@ int launch_eq2(const vp_index *I, const void *hidden, int N, void *cpart, hipStr
     int parts = std::min(ceil_div(I->L.ctiles, 4), std::max(1, 2048 / (4 * row_tiles)));
     const int tpw_c = ceil_div(I->L.ctiles, parts * 4);
     parts = ceil_div(I->L.ctiles, tpw_c * 4);
-    vpk_centroid(hidden, N, I->d, I->cp, I->cnorm, I->K, I->L.kt, I->L.ctiles, tpw_c, parts, cpart, st);
+    vpk_centroid(hidden, N, I->d, I->cp, I->cnorm, I->K, I->L.kt, I->L.ctiles, tpw_c, parts, cpart, nullptr, st);
     return parts;
 }
 

@@ -19,7 +19,7 @@ void vpk_bitmaps(const int32_t *ids_pad, const int32_t *tile_off, int K, long to
 
 // centroid selection (Eq. 2)
 void vpk_centroid(const void *hidden, int N, int d, const void *cp, const float *cnorm, int K, int kt,
-                  int ctiles, int tiles_per_part, int parts, void *cpart, hipStream_t st);
+                  int ctiles, int tiles_per_part, int parts, void *cpart, const int32_t *go, hipStream_t st);
 
 void vpk_centroid_small(const void *hidden, int N, int d, const void *cp, const float *cnorm, int K, int kt,
                         int ctiles, void *cpart, hipStream_t st);
@@ -90,18 +90,16 @@ void vpk_union_gather(const void *wt, int kt, const int32_t *uids, const VpUnion
 
 // offline training of the clusters (section 2.2)
 void vpk_fill_u32(void *p, size_t n, uint32_t v, hipStream_t st);
-// (rank: nullptr, or each vector's number among its cluster's members, for vpk_kmeans_bucket)
-void vpk_kmeans_assign(const void *cpart, int parts, int rows, int K, int32_t *assign, int32_t *counts,
-                       int32_t *rank, hipStream_t st);
+void vpk_kmeans_prepare(const void *C, int K, int d, int kt, int K_pad, bool always, const VpKmPass &pass, hipStream_t st);
+void vpk_kmeans_assign(const void *cpart, int parts, long row0, int rows, int K, const VpKmPass &pass, hipStream_t st);
 // (true: the rows-in-LDS kernel takes the passes of this call, and its LDS size is set)
 bool vpk_kmeans_rows_in_lds(int kt, int ctiles, long n);
-bool vpk_kmeans_assign_gemm(const void *X, long n, int d, const void *cp, const float *cnorm, int K, int kt, int ctiles,
-                            bool rows_in_lds, int32_t *assign, int32_t *counts, int32_t *rank, hipStream_t st);
-void vpk_kmeans_bucket(const int32_t *assign, const int32_t *rank, long n, const int32_t *counts, int K, int32_t *start,
-                       int32_t *cursor, int32_t *perm, hipStream_t st);
-bool vpk_kmeans_mean_form(int K);   // vpk_kmeans_update needs no sums in memory (acc)
-void vpk_kmeans_update(const void *X, int d, const int32_t *perm, const int32_t *start, const int32_t *counts, int K,
-                       int splits, void *acc, void *C, hipStream_t st);
+bool vpk_kmeans_assign_gemm(const void *X, long n, int d, int K, int kt, int ctiles, bool rows_in_lds, const VpKmPass &pass,
+                            hipStream_t st);
+void vpk_kmeans_place(long n, int K, int d, const VpKmPass &pass, int32_t *start, int32_t *list, void *acc, hipStream_t st);
+bool vpk_kmeans_mean_form(int K);   // one workgroup per cluster
+void vpk_kmeans_update(const void *X, int d, const int32_t *list, const int32_t *start, const int32_t *counts, int K,
+                       int splits, void *acc, const VpKmState *state, void *C, hipStream_t st);
 void vpk_kmeans_split(const int32_t *counts, int K, int d, void *C, hipStream_t st);
 void vpk_aset_flags(const int32_t *top, const int32_t *assign, long n, int T, int K, int V, int words,
                     uint32_t *bitmaps, int32_t *sizes, int64_t *cand_off, hipStream_t st);

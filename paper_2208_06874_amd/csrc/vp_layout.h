@@ -287,6 +287,36 @@ struct VpSmallArgs {
     VpPlanHeader *hdr;          // (out)
 };
 
+// What one iteration of the training leaves for the next kernels.
+struct VpKmState {
+    int32_t changed;        // centroids that are other ones than in the pass before (later passes)
+    int32_t total_events;   // members that came or went, both counted (first pass: all vectors)
+    int32_t anew;           // the entries are all members, the sums begin at zero
+    int32_t unsettled, settled;   // vectors in VpKmPass.parted from its front and from its end
+    int32_t pad[3];
+};
+
+// The buffers of a membership pass.
+struct VpKmPass {
+    int32_t first;          // every vector against every centroid, nothing known before
+    int32_t pad;
+    VpKmState *state;
+    void *cp;               // packed centroids, padded to whole groups
+    float *cnorm;
+    void *cp_changed;       // the changed ones side by side, their norms and numbers
+    float *cnorm_changed;
+    int32_t *which_changed;
+    int32_t *flag;          // [K] centroid changed
+    int32_t *assign, *counts;
+    int32_t *events, *cursor;   // [K]
+    int32_t *prev;          // [n] the cluster in the pass before
+    int32_t *rank, *rank_old;   // [n] numbers of the counting atomics (null: not kept)
+    float *best;            // [n] score of the vector's cluster (rows-in-LDS kernel)
+    const int32_t *order;   // [n] vectors in the order of their first clusters
+    int32_t *parted;        // [n] those whose own centroids changed in front
+};
+#define VP_KM_MAX_PIECES 512   // 16-byte pieces of the widest vector
+
 // Size in floats of one partial result: running max, sum of exponentials, then
 // k logits and k candidate positions.
 static inline __host__ __device__ int vp_partial_floats(int k) { return 2 + 2 * k; }

@@ -105,6 +105,32 @@ def test_members_are_placed_by_their_numbers(oracle, n, d, K):
     assert np.array_equal(new, want), "%d centroid coordinates differ" % (new != want).sum()
 
 
+# What one call carries from iteration to iteration (sums, scores, which centroids changed) against calls of one iteration,
+# which know nothing before: rows-in-LDS kernel with its companion at d_pad 512 to 1536, split-k kernel, decode-time
+# kernel, few clusters (sums in memory), many vectors per cluster (no numbers), vectors in no clusters at all, most
+# of which move (the sums are begun anew), and centroids that are equal to the bit.
+@pytest.mark.parametrize("n,d,K,noise,split", [
+    (6000, 512, 300, 0.3, False), (5000, 760, 260, 0.3, False), (9000, 1024, 500, 0.3, True), (4500, 1280, 250, 0.3, False),
+    (5001, 1536, 256, 0.3, False), (20000, 256, 40, 0.3, False), (6000, 768, 100, 0.5, True), (4200, 8, 256, 0.3, False),
+    (3000, 264, 300, 0.3, False), (500, 64, 9, 1.0, False), (6000, 512, 300, None, False), (6000, 256, 30, None, True)])
+def test_many_iterations_equal_single_ones(n, d, K, noise, split):
+    rs = np.random.default_rng(n + d + K)
+    if noise is None:
+        X = rs.standard_normal((n, d)).astype(np.float16)
+    else:
+        X = (rs.standard_normal((K, d))[rs.integers(0, K, n)] + noise * rs.standard_normal((n, d))).astype(np.float16)
+    C0 = X[rs.choice(n, K, replace=False)].copy()
+    C0[1::7] = C0[0]                     # equal centroids: all but the first lose their members to it
+    C = C0.copy()
+    for it in range(8):
+        one, assign, counts = _gpu_kmeans(X, C, 1, split_empty=split)
+        C = one.view(np.float16)
+        many, assign_m, counts_m = _gpu_kmeans(X, C0, it + 1, split_empty=split)
+        assert np.array_equal(many, one), (it, int((many != one).sum()))
+        assert np.array_equal(assign_m, assign) and np.array_equal(counts_m, counts), it
+        assert np.array_equal(counts, np.bincount(assign, minlength=K))
+
+
 def test_twenty_iterations_and_determinism(oracle):
     cfg, X, q, C0 = _mixture("tiny", 8192)
     Cb, assign, counts = _gpu_kmeans(X, C0, 20)
