@@ -38,17 +38,22 @@
 namespace {
 
 constexpr int L_NW = 8;        // wavefronts per workgroup
-constexpr int L_G = 4;         // candidate groups per step
 // row tiles per item: four (64 rows), or three where four do not fit the LDS (48 rows: 120 KiB at d_pad = 1280,
 // 144 KiB at 1536)
 constexpr int lds_row_tiles(int kt) { return kt > 32 ? 3 : 4; }
-constexpr int L_PF = 4;        // k-tiles of the four groups kept in flight
+// Candidate groups per step: four (one 1 KiB read of the rows from LDS per four MFMAs), or one for items with less than
+// a step of four groups for every wavefront, which would leave wavefronts without work and the others
+// with a long chain of loads (full projection, V = 32,000, d = 1024, 64 rows, us: top-1 28.2 -> 26.4, top-4 37.1 -> 31.7,
+// top-8 47.8 -> 36.9; d = 1536, 48 rows, top-8: 45.3 -> 37.9, but 56.2 -> 57.2 with 16 groups an item, V = 60,000: the
+// line there).
+// About 16 KiB per wavefront are kept in flight either way.
+constexpr int lds_k_tiles_in_flight(int kt, int g) { return g == 4 ? 4 : kt % 16 == 0 ? 16 : 8; }
 constexpr int VP_MAX_TOPK_LANES = 32;   // the epilogue writes a row's list with one lane per entry
 
 // (logit descending, position ascending), without branches
 __device__ inline bool before_entry(float v, int i, float v2, int i2) { return (v > v2) | ((v == v2) & (i < i2)); }
 
-template <int KT, bool MASKED, bool NT, bool TOP1, bool GATHER>
+template <int KT, int L_G, bool MASKED, bool NT, bool TOP1, bool GATHER>
 __device__ inline void gemm_lds_item(const VpSlabSet &set, const uint4 *__restrict__ hidden, int d,
                                      const VpItem &item, int it, int k,
                                      float *__restrict__ partials, unsigned int *__restrict__ floors,
@@ -56,6 +61,8 @@ __device__ inline void gemm_lds_item(const VpSlabSet &set, const uint4 *__restri
 {
     constexpr int L_RT = lds_row_tiles(KT);
     constexpr int L_ROWS = 16 * L_RT;
+    constexpr int L_PF = lds_k_tiles_in_flight(KT, L_G);
+    static_assert(KT % L_PF == 0 && (L_G == 4 || L_G == 1), "whole passes; the mask's words");
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // (uniform: step numbers and tile offsets stay in scalar registers)
     const int lane = tid & 63;
@@ -198,8 +205,11 @@ __device__ inline void gemm_lds_item(const VpSlabSet &set, const uint4 *__restri
             // the step's 64 candidates start at a multiple of 64: one aligned pair of 32-bit words (the
             // lists are padded to an even number of words)
 #pragma unroll
-            for (int rt = 0; rt < L_RT; ++rt)
-                mw[rt] = *reinterpret_cast<const uint2 *>(mask.bitmaps + (moff[rt] + ((g0 * VP_TILE_ITEMS) >> 5)));
+            for (int rt = 0; rt < L_RT; ++rt) {
+                const uint32_t *words = mask.bitmaps + (moff[rt] + ((g0 * VP_TILE_ITEMS) >> 5));
+                if (L_G == 4) mw[rt] = *reinterpret_cast<const uint2 *>(words);
+                else mw[rt].x = words[0] >> ((g0 & 1) * VP_TILE_ITEMS);   // (one group: half a word)
+            }
         }
 
         floatx4 acc[L_RT][L_G];
@@ -449,10 +459,15 @@ __global__ __launch_bounds__(L_NW * 64) void project_gemm_lds_kernel(
         partials += (size_t)hdr->masked_slot0 * vp_partial_floats(k);
         if (hdr->mode == 1) perm = nullptr;   // the whole batch, in its own order
     }
-    if (item.shared || GATHER)
-        gemm_lds_item<KT, MASKED, false, TOP1, GATHER>(set, hidden, d, item, it, TOP1 ? 1 : k, partials, floors, mask, perm);
-    else
-        gemm_lds_item<KT, MASKED, true, TOP1, false>(set, hidden, d, item, it, TOP1 ? 1 : k, partials, floors, mask, perm);
+    const int kk = TOP1 ? 1 : k;
+    const bool brief = item.ntiles < (KT > 32 ? 2 : 4) * L_NW;   // (see lds_k_tiles_in_flight)
+    if (item.shared || GATHER) {
+        if (brief) gemm_lds_item<KT, 1, MASKED, false, TOP1, GATHER>(set, hidden, d, item, it, kk, partials, floors, mask, perm);
+        else gemm_lds_item<KT, 4, MASKED, false, TOP1, GATHER>(set, hidden, d, item, it, kk, partials, floors, mask, perm);
+    } else {
+        if (brief) gemm_lds_item<KT, 1, MASKED, true, TOP1, false>(set, hidden, d, item, it, kk, partials, floors, mask, perm);
+        else gemm_lds_item<KT, 4, MASKED, true, TOP1, false>(set, hidden, d, item, it, kk, partials, floors, mask, perm);
+    }
 }
 
 template <int KT, bool MASKED, bool GATHER>
