@@ -91,28 +91,42 @@ __device__ inline void block_sum3(int a, int b, int c, int *ta, int *tb, int *tc
     *tc = __builtin_amdgcn_readlane(wave_inclusive_sum(lane < nw ? wsum3[32 + lane] : 0), nw - 1);
 }
 
-// The form is chosen per cluster where the matrix cores, not one pass over W, set the time of the masked
-// projection: there every row costs it the same, so a cluster is masked when its slab takes longer than that for its
+// The form is chosen per cluster in large batches.  A crowded cluster's slab is read once per 16 rows by the slab kernel,
+// once per 48 or 64 by the many-row kernel, which takes it from about 33 rows on ("grouped").  And where the matrix
+// cores, not one pass over W, set the time of the masked projection, every row costs that the same, so a cluster is masked
+// when its slab takes longer than that for its
 // rows (few rows, long list) and keeps its slab otherwise.  Which price per row is the best one depends on how much of
-// the pass over W the masked rows fill; four prices are tried, MIX_PRICES halvings of the full one, and the cheapest total wins
-// if it is 5 % cheaper than either form for the whole batch (both projection kernels then have work, in one plan).
+// the pass over W the masked rows fill; the full one, its half and its quarter are tried, and masking nothing, and the cheapest
+// total wins if it is 5 % cheaper than either form for the whole batch (both projection kernels then have work, in one plan).
 // 4,096 Zipf(1.1) rows on 500 clusters of 2,000 to 40,000 tokens, d = 1536, top-8: slabs 2,830 us, masked 3,360, both
-// 2,100; 1,024 rows on lists of up to 30,000, d = 1024, top-4: 823, 521, 365; 400 rows of that: 267 masked, 256.
-constexpr int MIX_PRICES = 4;
-static_assert(MIX_PRICES * PLAN_THREADS / 64 == 64, "one lane per price and wavefront");
+// 2,100, crowded clusters grouped as well 1,500; 4,096 rows spread over 40 clusters of 8,000 to 16,000, d = 1024, top-6: 624
+// without groups, 322 with; 1,024 rows on lists of up to 30,000, d = 1024, top-4: 823, 521, 365;
+// 400 rows of that: 267 masked, 256.
+constexpr int MIX_CHOICES = 4;   // prices 1, 1/2, 1/4; nothing masked
+static_assert(MIX_CHOICES * PLAN_THREADS / 64 == 64, "one lane per choice and wavefront");
 // the matrix cores' rate over many row groups against the rate of the few that the choice between the two whole forms turns
 // on (N = 512 -> 4,096 masked rows: 14.1 -> 17.5 TB/s of W at d = 1024, 10 -> 15 at d = 512, 16.8 -> 18.9 at d = 1536)
 constexpr float MIX_GEMM = 1.3f;
-constexpr float MIX_TIME = 40e-6f;   // a second kernel's start and end, and buckets of many rows in a slab kernel with little to do
+constexpr float MIX_TIME = VP_MIX_TIME;
+constexpr int GROUP_TILES = 32;      // fewest candidate tiles of a grouped item
 
-// candidate tiles of a cluster; those of a masked cluster are stored complemented
-__device__ inline int plan_tiles(int t) { return t < 0 ? ~t : t; }
+enum { ON_SLAB = 0, GROUPED = 1, MASKED_OUT = 2 };   // a cluster's form
 
-// one cluster's slab with its share of the rows' time
-__device__ inline float slab_time(int rows, int tiles, float t_row, const VpCostModel &cost)
-{
-    return tiles / cost.bw_slab + (ceil_div(rows, VP_ROWS_PER_ITEM) - 1) * tiles / cost.bw_l2 + rows * t_row;
-}
+// one cluster on its slab, with its share of the rows' time, and grouped
+struct ClusterTimes {
+    float t_row, pass_rate, k_factor;
+    int rpi;
+    bool group;
+    __device__ float slab(int rows, int tiles, const VpCostModel &cost) const
+    {
+        return tiles / cost.bw_slab + (ceil_div(rows, VP_ROWS_PER_ITEM) - 1) * tiles / cost.bw_l2 + rows * t_row;
+    }
+    __device__ float grouped(int rows, int tiles, const VpCostModel &cost) const
+    {
+        // (the many-row kernel streams a little slower than the slab kernel: 5.1 against 6.8 TB/s on W)
+        return group ? fmaxf(1.33f * tiles / cost.bw_slab, ceil_div(rows, rpi) * tiles / pass_rate) * k_factor : __builtin_inff();
+    }
+};
 
 __global__ __launch_bounds__(PLAN_THREADS) void plan_kernel(
     const int2 *__restrict__ cpart, int parts, int N, int K, const int32_t *__restrict__ n_cand,
@@ -126,13 +140,15 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_kernel(
     int *cnt = lds;             // [K]   rows per cluster
     int *off = cnt + K;         // [K]   first perm position of each bucket
     int *ioff = off + K;        // [K+1] first item of each bucket
-    int *tl = ioff + K + 1;     // [K]   candidate tiles of each cluster (plan_tiles)
+    int *tl = ioff + K + 1;     // [K]   candidate tiles of each cluster
     int *cur = tl + K;          // [K]   scatter cursor
+    int *form = cur + K;        // [K]   ON_SLAB, GROUPED or MASKED_OUT
+    int *goff = form + K;       // [K+1] first grouped item of each bucket
     __shared__ int wsum[PLAN_THREADS / 64 + 1];
     __shared__ long long wsum64[PLAN_THREADS / 64 + 1];
     __shared__ int wsum3[48];
-    __shared__ float mix_t[MIX_PRICES][PLAN_THREADS / 64];
-    __shared__ int mix_n[MIX_PRICES][PLAN_THREADS / 64];
+    __shared__ float mix_t[MIX_CHOICES][PLAN_THREADS / 64];
+    __shared__ int mix_n[MIX_CHOICES][PLAN_THREADS / 64];
     __shared__ int max_rgs;     // most row groups any bucket has
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -142,6 +158,7 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_kernel(
     for (int j = tid; j < K; j += PLAN_THREADS) {
         cnt[j] = 0;
         cur[j] = 0;
+        form[j] = ON_SLAB;
         tl[j] = tile_off[j + 1] - tile_off[j];
     }
     __syncthreads();
@@ -167,8 +184,9 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_kernel(
     block_sum3(my_tiles, my_units, my_occ_tiles, &total_tiles, &units, &occ_tiles, wsum3);
 
     // all forms give the same results, so the cheapest one is taken (cost model in plan_common.h)
-    int masked_rows = 0;
+    int masked_rows = 0, grouped_rows = 0;
     int m_rgs = 0, m_chunks = 0, m_tpi = 0;   // the masked projection's items, where some clusters are masked
+    int g_tpi = 0;                            // candidate tiles of a grouped item
     if (dispatch) {
         const int rpi = dispatch;   // rows per item of the masked projection (16, 48 or 64)
         const float t_slab = vp_time_slabs(occ_tiles, total_tiles, N, cost);
@@ -178,29 +196,29 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_kernel(
         const float k_factor = 1.f + k * 0.0125f;
         const float best = 0.95f * fminf(t_slab, ceil_div(N, rpi) * pass * k_factor);
         // (whatever is masked, W is streamed once)
-        if (mix.slots > 0 && best > MIX_TIME + one_pass * k_factor) {
-            const float t_row = vp_rows_time(N, cost.t_row_slab) / N;
+        if (mix.slots > 0 && (mix.group || best > MIX_TIME + one_pass * k_factor)) {
+            const ClusterTimes time = {vp_rows_time(N, cost.t_row_slab) / N, cost.bw_gemm * MIX_GEMM, k_factor, rpi, mix.group != 0};
             const float price = pass / rpi * k_factor;
-            float t[MIX_PRICES];
-            int n[MIX_PRICES];
+            float t[MIX_CHOICES];
+            int n[MIX_CHOICES];
 #pragma unroll
-            for (int i = 0; i < MIX_PRICES; ++i) {
+            for (int i = 0; i < MIX_CHOICES; ++i) {
                 t[i] = 0.f;
                 n[i] = 0;
             }
             for (int j = tid; j < K; j += PLAN_THREADS) {
                 const int c = cnt[j];
                 if (c == 0) continue;
-                const float tj = slab_time(c, tl[j], t_row, cost);
+                const float tj = fminf(time.slab(c, tl[j], cost), time.grouped(c, tl[j], cost));
 #pragma unroll
-                for (int i = 0; i < MIX_PRICES; ++i) {
-                    const bool masked = tj > c * price * (1.f / (1 << i));
+                for (int i = 0; i < MIX_CHOICES; ++i) {
+                    const bool masked = i < MIX_CHOICES - 1 && mix.mask && tj > c * price * (1.f / (1 << i));
                     t[i] += masked ? 0.f : tj;
                     n[i] += masked ? c : 0;
                 }
             }
 #pragma unroll
-            for (int i = 0; i < MIX_PRICES; ++i) {
+            for (int i = 0; i < MIX_CHOICES; ++i) {
                 const float ts = wave_sum_float(t[i]);
                 const int ns = wave_sum(n[i]);
                 if (lane == 0) {
@@ -209,59 +227,73 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_kernel(
                 }
             }
             __syncthreads();
-            // lane l adds up wavefront l % 16's share at price l / 16
+            // lane l adds up wavefront l % 16's share under choice l / 16
             const float ts = row_sum_float(mix_t[lane >> 4][lane & 15]);
             const int ns = row_sum(mix_n[lane >> 4][lane & 15]);
-            float both = ts + MIX_TIME + fmaxf(one_pass, ceil_div(ns, rpi) * pass) * k_factor;
-            if (ns == 0 || ns == N) both = __builtin_inff();
-            float chosen = -1.f, least = best;
+            float both = ts + MIX_TIME + (ns > 0 ? fmaxf(one_pass, ceil_div(ns, rpi) * pass) * k_factor : 0.f);
+            if (ns == N) both = __builtin_inff();
+            float chosen = -1.f, least = best;   // (the price above which a cluster is masked)
 #pragma unroll
-            for (int i = 0; i < MIX_PRICES; ++i) {
+            for (int i = 0; i < MIX_CHOICES; ++i) {
                 const float t_i = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(both), 16 * i + 15));
                 if (t_i < least) {
                     least = t_i;
-                    chosen = price * (1.f / (1 << i));
+                    chosen = i < MIX_CHOICES - 1 && mix.mask ? price * (1.f / (1 << i)) : __builtin_inff();
                 }
             }
             if (chosen >= 0.f) {
-                int s_tiles, s_units, my_rows = 0;
+                int my_masked = 0, my_grouped = 0, my_gtiles = 0, my_gunits = 0;
                 my_tiles = my_units = 0;
                 for (int j = tid; j < K; j += PLAN_THREADS) {
                     const int c = cnt[j];
                     if (c == 0) continue;
-                    if (slab_time(c, tl[j], t_row, cost) > c * chosen) {
-                        tl[j] = ~tl[j];
-                        my_rows += c;
+                    const float ta = time.slab(c, tl[j], cost), tb = time.grouped(c, tl[j], cost);
+                    if (fminf(ta, tb) > c * chosen) {
+                        form[j] = MASKED_OUT;
+                        my_masked += c;
+                    } else if (tb < ta) {
+                        form[j] = GROUPED;
+                        my_grouped += c;
+                        my_gtiles += ceil_div(c, rpi) * tl[j];
+                        my_gunits += ceil_div(c, rpi);
                     } else {
                         my_tiles += ceil_div(c, VP_ROWS_PER_ITEM) * tl[j];
                         my_units += ceil_div(c, VP_ROWS_PER_ITEM);
                     }
                 }
-                block_sum3(my_tiles, my_units, my_rows, &s_tiles, &s_units, &masked_rows, wsum3);
+                int s_tiles, s_units, g_tiles, g_units;
+                block_sum3(my_tiles, my_units, my_masked, &s_tiles, &s_units, &masked_rows, wsum3);
+                block_sum3(my_gtiles, my_gunits, my_grouped, &g_tiles, &g_units, &grouped_rows, wsum3);
                 // whole rounds of the compute units for the masked items, as in a plan of its own, and no
                 // more of them than workgroups
-                m_rgs = ceil_div(masked_rows, rpi);
-                int target = vp_swept_item_count(max(m_rgs, 1), mix.slots, vtiles, mix.kt, mix.grid);
-                if (target > mix.grid) target = mix.grid / m_rgs * m_rgs;
-                const int m_tpw = vp_tiles_per_wave((long long)m_rgs * vtiles, max(target, 1), max(target, 1));
-                m_tpi = m_tpw * VP_WG_WAVES;
-                m_chunks = ceil_div(vtiles, m_tpi);
-                // both item lists and their partial results have to fit the workspace, which is laid out for one
+                int m_items = 0;
+                if (masked_rows > 0) {
+                    m_rgs = ceil_div(masked_rows, rpi);
+                    int target = vp_swept_item_count(m_rgs, mix.slots, vtiles, mix.kt, mix.grid);
+                    if (target > mix.grid) target = mix.grid / m_rgs * m_rgs;
+                    const int m_tpw = vp_tiles_per_wave((long long)m_rgs * vtiles, max(target, 1), max(target, 1));
+                    m_tpi = m_tpw * VP_WG_WAVES;
+                    m_chunks = ceil_div(vtiles, m_tpi);
+                    m_items = m_rgs * m_chunks;
+                }
+                g_tpi = max(GROUP_TILES, (ceil_div(g_tiles, VP_GROUP_ITEMS) + 3) & ~3);
+                const int g_items = grouped_rows > 0 ? ceil_div(g_tiles, g_tpi) + g_units : 0;   // (at most)
+                // all item lists and their partial results have to fit the workspace, which is laid out for one
                 // form at a time: the slabs get fewer, longer items if need be
-                const int m_items = m_rgs * m_chunks;
-                const long long room = min((long long)mix.list - m_items,
-                                           (mix.row_slots - (long long)m_items * rpi) / VP_ROWS_PER_ITEM) - s_units;
-                if (masked_rows > 0 && m_items <= mix.grid && room >= min_items) {
+                const int mg_items = m_items + g_items;
+                const long long room = min((long long)mix.list - mg_items,
+                                           (mix.row_slots - (long long)mg_items * rpi) / VP_ROWS_PER_ITEM) - s_units;
+                if (masked_rows + grouped_rows > 0 && ((m_items + 7) & ~7) + ((g_items + 7) & ~7) <= mix.grid && room >= min_items) {
                     target_items = (int)min((long long)target_items, room);
                     total_tiles = s_tiles;
                     units = s_units;
                 } else {
-                    masked_rows = 0;
-                    for (int j = tid; j < K; j += PLAN_THREADS) tl[j] = plan_tiles(tl[j]);
+                    masked_rows = grouped_rows = 0;
+                    for (int j = tid; j < K; j += PLAN_THREADS) form[j] = ON_SLAB;
                 }
             }
         }
-        if (masked_rows == 0 && t_full < t_slab) {
+        if (masked_rows + grouped_rows == 0 && t_full < t_slab) {
             __syncthreads();
             vp_plan_single_bucket(N, V, vtiles, rpi, full_target_items, full_min_items, max_items_full, perm,
                                   rowplan, floors, items, hdr, nullptr, tid, PLAN_THREADS, true);
@@ -270,33 +302,48 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_kernel(
     }
     const int tpw = vp_tiles_per_wave_units(total_tiles, units, target_items, min_items);
     const int tpi = tpw * VP_WG_WAVES;
-    const int slab_rows = N - masked_rows;
+    const int slab_rows = N - masked_rows - grouped_rows;
 
-    // exclusive scans: rows -> bucket offsets (the masked clusters' rows behind all others), items -> item offsets
-    int carry = 0, icarry = 0, mcarry = slab_rows;
+    // exclusive scans: rows -> bucket offsets (the grouped clusters' rows behind the others, the masked ones' last),
+    // items -> item offsets
+    int carry = 0, icarry = 0, gcarry = slab_rows, gicarry = 0, mcarry = slab_rows + grouped_rows;
     for (int base = 0; base < K; base += PLAN_THREADS) {
         const int j = base + tid;
         const int c = j < K ? cnt[j] : 0;
         const int t = j < K ? tl[j] : 0;
+        const int f = j < K ? form[j] : ON_SLAB;
         const int rgs = ceil_div(c, VP_ROWS_PER_ITEM);
         int tot;
-        const int ex = block_exscan_int(t < 0 ? 0 : c, &tot, wsum);
-        if (j < K && t >= 0) off[j] = carry + ex;
+        const int ex = block_exscan_int(f == ON_SLAB ? c : 0, &tot, wsum);
+        if (j < K && f == ON_SLAB) off[j] = carry + ex;
         carry += tot;
-        const int iex = block_exscan_int(t < 0 ? 0 : rgs * ceil_div(t, tpi), &tot, wsum);
+        const int iex = block_exscan_int(f == ON_SLAB ? rgs * ceil_div(t, tpi) : 0, &tot, wsum);
         if (j < K) ioff[j] = icarry + iex;
         icarry += tot;
+        if (grouped_rows > 0) {
+            const int gex = block_exscan_int(f == GROUPED ? c : 0, &tot, wsum);
+            if (j < K && f == GROUPED) off[j] = gcarry + gex;
+            gcarry += tot;
+            const int giex = block_exscan_int(f == GROUPED ? ceil_div(c, dispatch) * ceil_div(t, g_tpi) : 0, &tot, wsum);
+            if (j < K) goff[j] = gicarry + giex;
+            gicarry += tot;
+        }
         if (masked_rows > 0) {
-            const int mex = block_exscan_int(t < 0 ? c : 0, &tot, wsum);
-            if (j < K && t < 0) off[j] = mcarry + mex;
+            const int mex = block_exscan_int(f == MASKED_OUT ? c : 0, &tot, wsum);
+            if (j < K && f == MASKED_OUT) off[j] = mcarry + mex;
             mcarry += tot;
         }
-        if (t >= 0 && rgs > 4) atomicMax(&max_rgs, rgs);
+        if (f == ON_SLAB && rgs > 4) atomicMax(&max_rgs, rgs);
     }
-    if (tid == 0) ioff[K] = icarry;
+    if (tid == 0) {
+        ioff[K] = icarry;
+        goff[K] = gicarry;
+    }
     __syncthreads();
     const int total_items = min(icarry, max_items);
+    const int m_items = m_rgs * m_chunks * (masked_rows > 0);
     const int m_slot0 = total_items * VP_ROWS_PER_ITEM;
+    const int m_row0 = slab_rows + grouped_rows;
 
     // scatter rows into bucket order and tell the merge kernel where the partial results of each row will be
     for (int r = tid; r < N; r += PLAN_THREADS) {
@@ -308,14 +355,18 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_kernel(
         VpRowPlan rp;
         rp.row = r;
         rp.cluster = j;
-        if (tl[j] >= 0) {
+        rp.ids_off = tile_off[j] * VP_TILE_ITEMS;
+        if (form[j] == ON_SLAB) {
             const int rgs = ceil_div(cnt[j], VP_ROWS_PER_ITEM);
             rp.slot0 = (ioff[j] + local / VP_ROWS_PER_ITEM) * VP_ROWS_PER_ITEM + local % VP_ROWS_PER_ITEM;
             rp.slot_stride = rgs * VP_ROWS_PER_ITEM;
             rp.nit = ceil_div(tl[j], tpi);
-            rp.ids_off = tile_off[j] * VP_TILE_ITEMS;
+        } else if (form[j] == GROUPED) {
+            rp.slot0 = m_slot0 + (m_items + goff[j]) * dispatch + local;   // (row group, slot of it) of the first range
+            rp.slot_stride = ceil_div(cnt[j], dispatch) * dispatch;
+            rp.nit = ceil_div(tl[j], g_tpi);
         } else {
-            rp.slot0 = m_slot0 + p - slab_rows;   // (row group, slot of it) of the first candidate range
+            rp.slot0 = m_slot0 + p - m_row0;
             rp.slot_stride = m_rgs * dispatch;
             rp.nit = m_chunks;
             rp.ids_off = -1;
@@ -326,36 +377,39 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_kernel(
 
     // the items: for each bucket, candidate ranges outermost and row groups
     // innermost, so items that re-read the same tiles sit next to each other
-    for (int it = tid; it < total_items; it += PLAN_THREADS) {
-        int lo = 0, hi = K;   // largest j with ioff[j] <= it (empty buckets have empty ranges)
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (ioff[mid] <= it) lo = mid; else hi = mid;
+    auto bucket_items = [&](const int *first, int count, int rows_per_item, int tiles_per_item, VpItem *out) {
+        for (int it = tid; it < count; it += PLAN_THREADS) {
+            int lo = 0, hi = K;   // largest j with first[j] <= it (buckets without items have empty ranges)
+            while (hi - lo > 1) {
+                const int mid = (lo + hi) >> 1;
+                if (first[mid] <= it) lo = mid; else hi = mid;
+            }
+            const int j = lo;
+            const int rows = cnt[j];
+            const int rgs = ceil_div(rows, rows_per_item);
+            const int local = it - first[j];
+            const int ch = local / rgs;
+            const int rg = local - ch * rgs;
+            VpItem v;
+            v.cluster = j;
+            v.perm_start = off[j] + rg * rows_per_item;
+            v.nrows = min(rows_per_item, rows - rg * rows_per_item);
+            v.tile0 = ch * tiles_per_item;
+            v.ntiles = min(tiles_per_item, tl[j] - ch * tiles_per_item);
+            v.shared = rgs > 1;
+            v.tile_off = tile_off[j];
+            v.ncand = n_cand[j];
+            out[it] = v;
         }
-        const int j = lo;
-        const int rows = cnt[j];
-        const int rgs = ceil_div(rows, VP_ROWS_PER_ITEM);
-        const int local = it - ioff[j];
-        const int ch = local / rgs;
-        const int rg = local - ch * rgs;
-        VpItem v;
-        v.cluster = j;
-        v.perm_start = off[j] + rg * VP_ROWS_PER_ITEM;
-        v.nrows = min(VP_ROWS_PER_ITEM, rows - rg * VP_ROWS_PER_ITEM);
-        v.tile0 = ch * tpi;
-        v.ntiles = min(tpi, tl[j] - ch * tpi);
-        v.shared = rgs > 1;
-        v.tile_off = tile_off[j];
-        v.ncand = n_cand[j];
-        items[it] = v;
-    }
-    // and those of the masked clusters, as a single-bucket plan has them
-    for (int it = tid; it < m_rgs * m_chunks && masked_rows > 0; it += PLAN_THREADS) {
+    };
+    bucket_items(ioff, total_items, VP_ROWS_PER_ITEM, tpi, items);
+    // those of the masked clusters, as a single-bucket plan has them
+    for (int it = tid; it < m_items; it += PLAN_THREADS) {
         const int ch = it / m_rgs;
         const int rg = it - ch * m_rgs;
         VpItem v;
-        v.cluster = 0;
-        v.perm_start = slab_rows + rg * dispatch;
+        v.cluster = -1;
+        v.perm_start = m_row0 + rg * dispatch;
         v.nrows = min(dispatch, masked_rows - rg * dispatch);
         v.tile0 = ch * m_tpi;
         v.ntiles = min(m_tpi, vtiles - ch * m_tpi);
@@ -364,6 +418,7 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_kernel(
         v.ncand = V;
         items[total_items + it] = v;
     }
+    if (grouped_rows > 0) bucket_items(goff, gicarry, dispatch, g_tpi, items + total_items + m_items);
     if (tid == 0) {
         hdr->total_items = total_items;
         hdr->tiles_per_wave = tpw;
@@ -373,11 +428,12 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_kernel(
         hdr->swz_rgs = max_rgs > 4 ? -VP_XCD_BLOCK_ITEMS : 0;
         hdr->swz_chunks = 0;
         hdr->rows_per_item = VP_ROWS_PER_ITEM;
-        hdr->mode = masked_rows > 0 ? 2 : 0;
-        hdr->masked_items = masked_rows > 0 ? m_rgs * m_chunks : 0;
+        hdr->mode = masked_rows + grouped_rows > 0 ? 2 : 0;
+        hdr->masked_items = m_items;
         hdr->masked_item0 = total_items;
         hdr->masked_slot0 = m_slot0;
         hdr->masked_swz = m_rgs > 1 && m_chunks >= 8 ? m_rgs : 0;
+        hdr->grouped_items = grouped_rows > 0 ? gicarry : 0;
     }
 
     // debug entry only: where each row's candidate logits start
@@ -409,13 +465,13 @@ __global__ __launch_bounds__(256) void plan_full_kernel(
 
 }  // namespace
 
-size_t vpk_plan_lds_bytes(int K) { return (size_t)(5 * K + 1) * sizeof(int); }
+size_t vpk_plan_lds_bytes(int K) { return (size_t)(7 * K + 2) * sizeof(int); }
 
 hipError_t vpk_plan_prepare()
 {
-    // clusters up to VP_MAX_CLUSTERS need a little over 80 KiB of dynamic LDS; allow it explicitly
+    // clusters up to VP_MAX_CLUSTERS need a little over 112 KiB of dynamic LDS; allow it explicitly
     return hipFuncSetAttribute(reinterpret_cast<const void *>(plan_kernel),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, 88 * 1024);
+                               hipFuncAttributeMaxDynamicSharedMemorySize, 120 * 1024);
 }
 
 void vpk_plan(const void *cpart, int parts, int N, int K, const int32_t *n_cand, const int32_t *tile_off,

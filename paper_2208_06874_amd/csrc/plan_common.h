@@ -84,7 +84,7 @@ __device__ inline void vp_plan_single_bucket(int N, int ncand, int vtiles, int r
         const int ch = it / rgs;
         const int rg = it - ch * rgs;
         VpItem v;
-        v.cluster = 0;
+        v.cluster = masked ? -1 : 0;
         v.perm_start = rg * rpi;
         v.nrows = min(rpi, N - rg * rpi);
         v.tile0 = ch * tpi;
@@ -108,6 +108,7 @@ __device__ inline void vp_plan_single_bucket(int N, int ncand, int vtiles, int r
         hdr->masked_item0 = 0;
         hdr->masked_slot0 = 0;
         hdr->masked_swz = hdr->swz_rgs;
+        hdr->grouped_items = 0;
         if (dbg_row_off) dbg_row_off[N] = (int64_t)N * ncand;
     }
 }

@@ -78,6 +78,7 @@ __device__ inline void gemm_lds_item(const VpSlabSet &set, const uint4 *__restri
     float *hdr_s = hdr_m + L_NW * L_ROWS;
 
     const int ncand = item.ncand;
+    const bool masked = MASKED && item.cluster < 0;   // (else a crowded cluster's own slab, in the same launch)
     const int gb = item.tile0;
     const int ge = item.tile0 + item.ntiles;
     const int nsteps = (item.ntiles + L_G - 1) / L_G;
@@ -181,7 +182,7 @@ __device__ inline void gemm_lds_item(const VpSlabSet &set, const uint4 *__restri
         s_run[rt] = 0.f;
         b1v[rt] = -__builtin_inff();
         b1i[rt] = VP_IDX_NONE;
-        moff[rt] = MASKED ? (unsigned int)(row_valid[rt] ? mask.g[myrow[rt]] : 0) * (unsigned int)mask.words : 0u;
+        moff[rt] = masked ? (unsigned int)(row_valid[rt] ? mask.g[myrow[rt]] : 0) * (unsigned int)mask.words : 0u;
     }
     constexpr bool top1 = TOP1;   // k == 1: the best entry stays in registers, no list traffic in the loop
     unsigned int pending[L_RT];
@@ -201,7 +202,11 @@ __device__ inline void gemm_lds_item(const VpSlabSet &set, const uint4 *__restri
 #pragma unroll
         for (int j = 0; j < L_G; ++j) bz[j] = *reinterpret_cast<const float4 *>(bias + (size_t)min(g0 + j, ge - 1) * VP_TILE_ITEMS);
         uint2 mw[L_RT];
-        if (MASKED) {
+        if (MASKED && !masked) {
+#pragma unroll
+            for (int rt = 0; rt < L_RT; ++rt) mw[rt] = make_uint2(~0u, ~0u);
+        }
+        if (masked) {
             // the step's 64 candidates start at a multiple of 64: one aligned pair of 32-bit words (the
             // lists are padded to an even number of words)
 #pragma unroll
@@ -446,15 +451,28 @@ template <int KT, bool MASKED, bool TOP1, bool GATHER>
 __global__ __launch_bounds__(L_NW * 64) void project_gemm_lds_kernel(
     VpSlabSet set, const uint4 *__restrict__ hidden, int d,
     const VpItem *__restrict__ items, const VpPlanHeader *__restrict__ hdr, int k,
-    float *__restrict__ partials, unsigned int *__restrict__ floors, VpMaskInfo mask, const int32_t *__restrict__ perm)
+    float *__restrict__ partials, unsigned int *__restrict__ floors, VpMaskInfo mask, const int32_t *__restrict__ perm,
+    VpSlabSet slabs)
 {
     if (MASKED ? hdr->mode == 0 : hdr->mode != 0) return;   // the planner chose the other form
     const int total_items = MASKED ? hdr->masked_items : hdr->total_items;
     // (> 1: several row groups and enough candidate ranges for the 8 XCDs)
     const int swz = MASKED ? hdr->masked_swz : hdr->swz_rgs;
-    const int it = swz > 1 ? vp_item_of_workgroup_even(blockIdx.x, total_items) : (int)blockIdx.x;
-    if (it < 0 || it >= total_items) return;
+    int it = swz > 1 ? vp_item_of_workgroup_even(blockIdx.x, total_items) : (int)blockIdx.x;
+    const int behind = (int)blockIdx.x - ((total_items + 7) & ~7);
+    if (MASKED && behind >= 0) {
+        // items of crowded clusters, dealt to the XCDs by themselves (they are shorter than the masked ones)
+        it = vp_item_of_workgroup_even(behind, hdr->grouped_items);
+        if (it < 0) return;
+        it += total_items;
+    } else if (it < 0 || it >= total_items) {
+        return;
+    }
     const VpItem item = items[MASKED ? hdr->masked_item0 + it : it];
+    if (MASKED && item.cluster >= 0) {
+        set.tiles = slabs.tiles;
+        set.bias = slabs.bias;
+    }
     if (MASKED) {
         partials += (size_t)hdr->masked_slot0 * vp_partial_floats(k);
         if (hdr->mode == 1) perm = nullptr;   // the whole batch, in its own order
@@ -473,16 +491,16 @@ __global__ __launch_bounds__(L_NW * 64) void project_gemm_lds_kernel(
 template <int KT, bool MASKED, bool GATHER>
 void launch_lds(const VpSlabSet &set, const void *hidden, int d, const VpItem *items,
                 const VpPlanHeader *hdr, int grid_items, int k, float *partials, unsigned int *floors,
-                const VpMaskInfo &mask, const int32_t *perm, hipStream_t st)
+                const VpMaskInfo &mask, const int32_t *perm, const VpSlabSet &slabs, hipStream_t st)
 {
     if (k == 1)
         hipLaunchKernelGGL((project_gemm_lds_kernel<KT, MASKED, true, GATHER>), dim3(grid_items), dim3(L_NW * 64),
                            vpk_project_rows_lds_bytes(k, KT), st, set, (const uint4 *)hidden, d, items, hdr, k,
-                           partials, floors, mask, perm);
+                           partials, floors, mask, perm, slabs);
     else
         hipLaunchKernelGGL((project_gemm_lds_kernel<KT, MASKED, false, GATHER>), dim3(grid_items), dim3(L_NW * 64),
                            vpk_project_rows_lds_bytes(k, KT), st, set, (const uint4 *)hidden, d, items, hdr, k,
-                           partials, floors, mask, perm);
+                           partials, floors, mask, perm, slabs);
 }
 
 template <int KT>
@@ -533,18 +551,18 @@ hipError_t vpk_project_rows_lds_prepare()
 
 // mask: nullptr, or the membership lists of the masked full projection.  gather: the set's tiles
 // are the token-major copy of W and its ids the batch's union U (no mask then); the slab operands
-// are read through U instead of from a packed copy.  perm is read only where the planner masks some of
-// the clusters: a single-bucket plan keeps the rows in their own order.
+// are read through U instead of from a packed copy.  perm, and slabs, the clusters' own, are read only where the planner
+// chooses the form per cluster: a single-bucket plan keeps the rows in their own order.
 void vpk_project_rows_lds(const VpSlabSet &set, const void *hidden, int d, const int32_t *perm, const VpItem *items,
                           const VpPlanHeader *hdr, int grid_items, int k, float *partials, unsigned int *floors,
-                          const VpMaskInfo *mask, bool gather, hipStream_t st)
+                          const VpMaskInfo *mask, const VpSlabSet *slabs, bool gather, hipStream_t st)
 {
     const VpMaskInfo none = {nullptr, nullptr, 0};
 #define VP_LDS_CASE(KT)                                                                                                   \
     case KT:                                                                                                              \
-        if (mask) launch_lds<KT, true, false>(set, hidden, d, items, hdr, grid_items, k, partials, floors, *mask, perm, st); \
-        else if (gather) launch_lds<KT, false, true>(set, hidden, d, items, hdr, grid_items, k, partials, floors, none, nullptr, st); \
-        else launch_lds<KT, false, false>(set, hidden, d, items, hdr, grid_items, k, partials, floors, none, nullptr, st); \
+        if (mask) launch_lds<KT, true, false>(set, hidden, d, items, hdr, grid_items, k, partials, floors, *mask, perm, slabs ? *slabs : set, st); \
+        else if (gather) launch_lds<KT, false, true>(set, hidden, d, items, hdr, grid_items, k, partials, floors, none, nullptr, set, st); \
+        else launch_lds<KT, false, false>(set, hidden, d, items, hdr, grid_items, k, partials, floors, none, nullptr, set, st); \
         break;
     switch (set.kt) {
         VP_LDS_CASE(8)

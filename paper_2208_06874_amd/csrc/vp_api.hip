@@ -336,7 +336,7 @@ void launch_single_bucket(const VpSlabSet &set, const vp_index *I, const void *h
                           hipStream_t st)
 {
     if (use_gemm_lds(I, row_tiles, k))
-        vpk_project_rows_lds(set, hidden, I->d, perm, items, hdr, grid_items, k, partials, floors, nullptr, false, st);
+        vpk_project_rows_lds(set, hidden, I->d, perm, items, hdr, grid_items, k, partials, floors, nullptr, nullptr, false, st);
     else if (row_tiles == 4)
         vpk_project_gemm(set, hidden, I->d, perm, items, hdr, grid_items, k, partials, floors + N, nullptr, st);
     else
@@ -418,9 +418,15 @@ vp_status run_clustered(const char *fn, const vp_index *I, const void *hidden, i
         // Below that nothing is saved: 300 rows, d = 1024: 215 us masked, 254 us with the crowded clusters on slabs.
         const bool may_mix = dispatch >= 48 && use_gemm_lds(I, rt_masked, k) &&
                              rgs_full * (I->L.vtiles / cost.bw_gemm) > 2 * (I->L.vtiles / cost.bw_full) &&
-                             I->L.max_tiles / cost.bw_slab > I->L.vtiles / cost.bw_gemm / dispatch;
-        if (t_slab <= t_full && !may_mix) dispatch = 0;
-        mix.slots = dispatch && may_mix ? I->gemm_lds_items : 0;
+                             I->L.max_tiles / cost.bw_slab > I->L.vtiles / cost.bw_gemm / dispatch &&
+                             occ / cost.bw_slab > I->L.vtiles / cost.bw_full + VP_MIX_TIME;   // (all that masking could save)
+        // Crowded clusters: a batch of a thousand rows may well have some, a smaller one if there are few clusters.
+        // (They gain where the many-row kernel outruns the slabs' stream.)
+        const bool may_group = dispatch >= 48 && use_gemm_lds(I, rt_masked, k) && cost.bw_gemm > cost.bw_slab && (N >= 1024 || (N >= 64 && N >= 32 * I->K));
+        if (t_slab <= t_full && !may_mix && !may_group) dispatch = 0;
+        mix.mask = may_mix;
+        mix.group = may_group;
+        mix.slots = dispatch && (may_mix || may_group) ? I->gemm_lds_items : 0;
     }
     // Batches of a few rows: no planning kernel; the projection workgroups find their own work
     // (project_small_kernel) - unless the planner has a choice to make.
@@ -471,6 +477,8 @@ vp_status run_clustered(const char *fn, const vp_index *I, const void *hidden, i
         grid_full = (rgs > 1 && chunks >= 8) ? ceil_div(chunks, 8) * 8 * rgs : chunks * rgs;
         if (mix.slots) {
             grid_full = ceil_div(std::max(grid_full, I->gemm_lds_items), 8) * 8;
+            // (the grouped items aimed at, and a partly filled one per row group of a bucket of 33 rows and more)
+            if (mix.group) grid_full += VP_GROUP_ITEMS + ceil_div(ceil_div(N, 33) + ceil_div(N, dispatch), 8) * 8;
             mix.kt = I->L.kt;
             mix.grid = grid_full;
             mix.list = W.max_items;
@@ -496,7 +504,7 @@ vp_status run_clustered(const char *fn, const vp_index *I, const void *hidden, i
         // launched as well; one of the two does the work, or each its clusters' share, as the planner decided
         const VpMaskInfo mask = {g, I->bitmaps, I->L.bm_words};
         if (use_gemm_lds(I, rt_masked, k))
-            vpk_project_rows_lds(I->full, hidden, I->d, perm, items, hdr, grid_full, k, partials, floors, &mask, false, st);
+            vpk_project_rows_lds(I->full, hidden, I->d, perm, items, hdr, grid_full, k, partials, floors, &mask, &I->clusters, false, st);
         else if (rt_masked == 4)
             vpk_project_gemm(I->full, hidden, I->d, perm, items, hdr, grid_full, k, partials, floors + N, &mask, st);
         else
@@ -1020,7 +1028,7 @@ vp_status vp_project_union(const vp_index *I, const void *hidden, int32_t N, int
     const int grid_items = std::min(max_items, ceil_div(rgs * (long)ceil_div(I->L.vtiles, VP_WG_WAVES), 8) * 8 + 8 * rgs);
     if (fused_gather) {
         uset.tiles = I->arena + I->L.wt;
-        vpk_project_rows_lds(uset, hidden, I->d, perm, items, hdr, grid_items, k, partials, floors, nullptr, true, st);
+        vpk_project_rows_lds(uset, hidden, I->d, perm, items, hdr, grid_items, k, partials, floors, nullptr, nullptr, true, st);
     } else {
         vpk_union_gather(I->arena + I->L.wt, I->L.kt, uids, uh, I->L.vtiles, uslab, st);
         uset.tiles = uslab;
@@ -1034,7 +1042,7 @@ vp_status vp_project_union(const vp_index *I, const void *hidden, int32_t N, int
         const int grid_full = (rgs > 1 && chunks >= 8) ? ceil_div(chunks, 8) * 8 * rgs : chunks * rgs;
         const VpMaskInfo umask = {zero_g, mask, 0};   // every row reads list 0: the boolean list of the batch
         if (use_gemm_lds(I, row_tiles_u, k))
-            vpk_project_rows_lds(I->full, hidden, I->d, perm, items, hdr, grid_full, k, partials, floors, &umask, false, st);
+            vpk_project_rows_lds(I->full, hidden, I->d, perm, items, hdr, grid_full, k, partials, floors, &umask, nullptr, false, st);
         else if (row_tiles_u == 4)
             vpk_project_gemm(I->full, hidden, I->d, perm, items, hdr, grid_full, k, partials, floors + N, &umask, st);
         else

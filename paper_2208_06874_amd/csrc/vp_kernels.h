@@ -66,7 +66,7 @@ int vpk_project_rows_lds_row_tiles(int kt);
 hipError_t vpk_project_rows_lds_prepare();
 void vpk_project_rows_lds(const VpSlabSet &set, const void *hidden, int d, const int32_t *perm, const VpItem *items,
                           const VpPlanHeader *hdr, int grid_items, int k, float *partials, unsigned int *floors,
-                          const VpMaskInfo *mask, bool gather, hipStream_t st);
+                          const VpMaskInfo *mask, const VpSlabSet *slabs, bool gather, hipStream_t st);
 
 // per-row merge
 size_t vpk_merge_lds_bytes(int k);

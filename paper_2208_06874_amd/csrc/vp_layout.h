@@ -28,7 +28,7 @@
 // One unit of projection work: up to 16 rows of one bucket against a range of
 // candidate tiles of that bucket's slab.
 struct VpItem {
-    int32_t cluster;     // slab set entry (cluster id; 0 for the full-vocabulary set)
+    int32_t cluster;     // slab set entry (cluster id; 0 for the full-vocabulary set, -1 where it is masked)
     int32_t perm_start;  // first position in perm[] of this item's rows
     int32_t nrows;       // 1..16
     int32_t tile0;       // first candidate tile, counted within the entry's slab
@@ -68,13 +68,15 @@ struct VpPlanHeader {
     int32_t swz_chunks;
     int32_t rows_per_item;   // row slots per item in the partial results (16, or 32 with two row tiles)
     int32_t mode;            // 0: per-cluster slabs; 1: masked full projection; 2: some clusters by the one, the others by the other
-    // modes 1 and 2: the masked projection's items (from masked_item0 in the item list) and the first
-    // row slot of its partial results; mode 1 repeats the counts above
+    // modes 1 and 2: the many-row kernel's items (from masked_item0 in the item list: first those that mask the full
+    // projection, then those of crowded clusters' slabs) and the first row slot of their partial results;
+    // mode 1 repeats the counts above
     int32_t masked_items;
     int32_t masked_item0;
     int32_t masked_slot0;
     int32_t masked_swz;
-    int32_t pad[52];
+    int32_t grouped_items;
+    int32_t pad[51];
 };
 
 // State of one batch-union projection (see union.hip).
@@ -263,10 +265,14 @@ static inline __host__ __device__ float vp_rows_time(int N, float t_row)
     return N <= 512 ? N * t_row : (512 + (N - 512) / 8) * t_row;
 }
 
-// What a plan that masks some of the clusters and keeps the slabs of the others has to fit.
+#define VP_MIX_TIME 40e-6f   // a second kernel's start and end, and buckets of many rows in a slab kernel with little to do
+#define VP_GROUP_ITEMS 512   // grouped items of such a plan aimed at: two rounds of the compute units
+// What a plan that chooses the form per cluster may do and has to fit.
 struct VpMixLimits {
+    int32_t mask;         // some of the clusters may be masked
+    int32_t group;        // crowded clusters' slabs may go to the many-row kernel
     int32_t kt;           // k-tiles of a candidate group
-    int32_t slots;        // workgroups of the masked projection that run at a time (0: no such plan)
+    int32_t slots;        // workgroups of the many-row kernel that run at a time (0: no such plan)
     int32_t grid;         // its workgroups (a multiple of 8)
     int32_t list;         // records of the item list
     int64_t row_slots;    // row slots of the partial results

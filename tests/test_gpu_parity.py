@@ -764,6 +764,49 @@ def test_some_clusters_masked_and_some_on_slabs(oracle, d, k, N):
     pu.check_projection(oracle, W, b, C, off, ids, H, k, got[0], got[1], got[2])
 
 
+@pytest.mark.parametrize("d,k,N,K", [(256, 1, 200, 3), (512, 8, 1100, 40), (768, 4, 65, 2), (1000, 32, 640, 12),
+                                     (1280, 2, 1031, 60), (1536, 8, 500, 9)])
+def test_crowded_clusters_on_the_many_row_kernel(oracle, d, k, N, K):
+    """Clusters of 33 rows and more go to the many-row kernel with their own slabs, clusters of a few rows stay on the slab
+    kernel or are masked, in one plan.  Row counts off every multiple, short and empty lists, top-1 to top-32."""
+    V = 12000
+    r, W, b, C = _small_model(90 + d + k, d, V, K)
+    sizes = np.r_[r.integers(300, 2000, K - 1), 7 if K > 2 else 500]
+    if K > 5:
+        sizes[2] = 0
+    lists = [np.sort(r.choice(V, size=n, replace=False)) for n in sizes]
+    off = np.zeros(K + 1, np.int64)
+    np.cumsum([len(x) for x in lists], out=off[1:])
+    ids = np.concatenate(lists).astype(np.int32)
+    B = Built(W, b, C, off, ids, k_max=32)
+    p = np.arange(1, K + 1) ** -1.0
+    q = r.choice(r.permutation(K), size=N, p=p / p.sum())
+    q[:K] = np.arange(K)
+    H = _rows(r, C, N, clusters=q)
+    base = B.project(H, k)
+    B.index.set_option("dispatch", 1)
+    # the usual rates, all a thousandth: times that are long beside the planner's fixed ones
+    rates = {"cost_row_slab_ns": (0, 60), "cost_bw_slab_gbs": (7, 6800), "cost_bw_l2_gbs": (17, 17000),
+             "cost_bw_full_gbs": (5, 5100), "cost_bw_gemm_gbs": (14, 14000)}
+    try:
+        for name, (v, _) in rates.items():
+            B.index.set_option(name, v)
+        got = B.project(H, k)
+        assert _planner_mode(B.index, N) == 2 and _overflow(B.index, N) == 0
+        ws = B.index.workspace(N)
+        assert int(ws[:64].view(_torch().int32)[12].item()) > 0      # (items of crowded clusters)
+        again = B.project(H, k)
+    finally:
+        for name, (_, v) in rates.items():
+            B.index.set_option(name, v)
+        B.index.set_option("dispatch", 0)
+    for x, y in zip(got, again):
+        assert np.array_equal(x, y)
+    assert np.array_equal(got[0], base[0]) and np.array_equal(got[2], base[2])
+    assert np.allclose(got[1], base[1], rtol=0, atol=1e-4, equal_nan=True)
+    pu.check_projection(oracle, W, b, C, off, ids, H, k, got[0], got[1], got[2])
+
+
 def test_empty_active_sets(oracle):
     """A cluster whose active set is empty (a cluster that lost its members in training): rows that fall into
     it get ids -1 and log-probs -inf in every form of the projection; the other rows are untouched."""
