@@ -116,7 +116,9 @@ vp_status vp_get_info(const vp_index *idx, vp_index_info *info);
  *                   to its own cluster's active set instead of streaming the occupied
  *                   slabs, when the planner's cost model says that is cheaper (many
  *                   occupied clusters whose slabs outweigh one pass over W); same token ids,
- *                   log-probs equal up to the order of the fp32 sums.  0: always the slabs.
+ *                   log-probs equal up to the order of the fp32 sums.  In large batches the
+ *                   form is chosen per cluster, and clusters of many rows take the many-row
+ *                   kernel with their own slabs.  0: always the slab kernel.
  *   "cost_bw_slab_gbs", "cost_bw_full_gbs", "cost_bw_l2_gbs", "cost_bw_gemm_gbs",
  *   "cost_bw_gemm_split_gbs", "cost_bw_gather_gbs"   GB/s of the cost model
  *   "cost_row_slab_ns"   its time per row of the slab form beyond the bytes (default 60)
@@ -261,7 +263,9 @@ vp_status vp_measure_ceilings(const void *buf, size_t bytes, int32_t repeats, do
  * exact (every fp16 value is a multiple of 2^-24; see the bound on x below) and each
  * mean is rounded once to fp16 (nearest, ties to even), so equal inputs give
  * bit-identical centroids and, given the memberships, the centroids equal the
- * correctly rounded means.
+ * correctly rounded means.  An iteration redoes only what the last one changed (the
+ * results are those of iterations that redo everything, to the bit), so training that has
+ * come to rest costs little more.
  *   x          device, fp16 [n, d] row-major, 16-byte aligned, finite values;
  *              per cluster and coordinate the sum of |x| must stay below 2^29
  *   centroids  device, fp16 [K, d]: starting centroids in, trained centroids out
