@@ -723,11 +723,14 @@ __global__ __launch_bounds__(PLACE_THREADS) void kmeans_place_kernel(long n, int
         pass.state->total_events = total;
         pass.state->anew = anew;
         pass.state->changed = 0;   // (read by the membership pass before, counted again by the next one's preparation)
+        if (first) pass.state->split = 0;
     }
-    if (total == 0) return;
+    // (without events the means of split clusters are still to be written again)
+    if (total == 0 && !(pass.was_split && pass.state->split)) return;
     if (anew && !first) scan(pass.counts);
     if (blockIdx.x == 0)
         for (int j = tid; j <= K; j += PLACE_THREADS) start[j] = base[j];
+    if (total == 0) return;
     if (anew && !first)
         for (size_t e = (size_t)blockIdx.x * PLACE_THREADS + tid; e < acc_n; e += (size_t)gridDim.x * PLACE_THREADS) acc[e] = 0ull;
     const long r = (long)blockIdx.x * PLACE_THREADS + tid;
@@ -878,6 +881,13 @@ __host__ __device__ inline uint16_t double_to_half_bits(double v)
     return (uint16_t)(sign | h);
 }
 
+// Without events the centroids are the means already, but for those that a split moved (kmeans_split_kernel).
+// (was_split: null where empty clusters are left alone)
+__device__ inline bool nothing_to_update(const VpKmState *state, const int32_t *was_split)
+{
+    return state->total_events == 0 && !(was_split && state->split);
+}
+
 // One workgroup per cluster: brings the cluster's sum up to date with its entries and writes the new centroid at once
 // (no atomics between workgroups).  Used when there are enough clusters to fill
 // the chip this way; the member lanes of the workgroup (two at least) meet in LDS.
@@ -888,14 +898,15 @@ __global__ __launch_bounds__(MEAN_THREADS) void kmeans_mean_kernel(const uint4 *
                                                           const int32_t *__restrict__ start,
                                                           const int32_t *__restrict__ counts,
                                                           unsigned long long *__restrict__ acc,
-                                                          const VpKmState *__restrict__ state, uint4 *__restrict__ C)
+                                                          const VpKmState *__restrict__ state,
+                                                          const int32_t *__restrict__ was_split, uint4 *__restrict__ C)
 {
-    if (state->total_events == 0) return;
+    if (nothing_to_update(state, was_split)) return;
     const int j = blockIdx.x;
     const int m0 = start[j], m1 = start[j + 1];
     const bool anew = state->anew != 0;
     unsigned long long *const sum = acc + (size_t)j * pieces * 8;
-    if (m0 == m1) {                                            // nobody came or went: the centroid stays
+    if (m0 == m1 && !(was_split && state->split && was_split[j])) {         // nobody came or went: the centroid stays
         if (anew)
             for (int e = threadIdx.x; e < pieces * 8; e += MEAN_THREADS) sum[e] = 0ull;
         return;
@@ -923,26 +934,27 @@ __global__ __launch_bounds__(MEAN_THREADS) void kmeans_mean_kernel(const uint4 *
             sum[p * 8 + e] = v;
             h[e] = double_to_half_bits((double)(long long)v * 0x1p-24 / (double)c);
         }
-        // (a cluster that lost its last member keeps its centroid)
+        // (a cluster without members keeps its centroid)
         if (c > 0)
             C[(size_t)j * pieces + p] = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16),
                                                    h[6] | (h[7] << 16));
     }
 }
 
-// New centroids from the sums in memory, of the clusters with events.
+// New centroids from the sums in memory, of the clusters with events and of those that were split.
 __global__ __launch_bounds__(256) void kmeans_update_kernel(const unsigned long long *__restrict__ acc,
                                                             const int32_t *__restrict__ start,
                                                             const int32_t *__restrict__ counts,
-                                                            const VpKmState *__restrict__ state, int K, int d,
+                                                            const VpKmState *__restrict__ state,
+                                                            const int32_t *__restrict__ was_split, int K, int d,
                                                             uint16_t *__restrict__ C)
 {
-    if (state->total_events == 0) return;
+    if (nothing_to_update(state, was_split)) return;
     const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
     if (e >= (size_t)K * d) return;
     const int j = (int)(e / d);
     const int c = counts[j];
-    if (c > 0 && start[j] != start[j + 1]) {
+    if (c > 0 && (start[j] != start[j + 1] || (was_split && state->split && was_split[j]))) {
         const double sum = (double)(long long)acc[e];
         C[e] = double_to_half_bits(sum * 0x1p-24 / (double)c);
     }
@@ -959,7 +971,9 @@ __device__ inline double half_bits_to_double(uint32_t h)
 // has the most members at that moment (ties: lowest index; at least two members), whose centroid
 // c becomes c (1 - 2^-10) while c (1 + 2^-10) goes to the empty cluster; half of the members
 // (rounded down) are counted for the new cluster.  One workgroup; cnt lives in LDS.
+// A cluster whose members stay with it has their mean written again in the next iteration: was_split, for the kernels above.
 __global__ __launch_bounds__(1024) void kmeans_split_kernel(const int32_t *__restrict__ counts, int K, int d,
+                                                            VpKmState *__restrict__ state, int32_t *__restrict__ was_split,
                                                             uint16_t *__restrict__ C)
 {
     extern __shared__ int cnt[];   // [K]
@@ -970,9 +984,11 @@ __global__ __launch_bounds__(1024) void kmeans_split_kernel(const int32_t *__res
     __syncthreads();
     for (int j = tid; j < K; j += 1024) {
         cnt[j] = counts[j];
+        was_split[j] = 0;
         if (cnt[j] == 0) any_empty = 1;
     }
     __syncthreads();
+    if (tid == 0) state->split = any_empty;   // (cleared here after the iteration that wrote the means again)
     if (!any_empty) return;
     const double eps = 0x1p-10;
     for (int j = 0; j < K; ++j) {
@@ -1017,6 +1033,7 @@ __global__ __launch_bounds__(1024) void kmeans_split_kernel(const int32_t *__res
         __syncthreads();
         if (tid == 0) {
             const int c = cnt[big];
+            was_split[big] = 1;
             cnt[j] = c / 2;
             cnt[big] = c - c / 2;
         }
@@ -1208,24 +1225,24 @@ void vpk_kmeans_place(long n, int K, int d, const VpKmPass &pass, int32_t *start
 bool vpk_kmeans_mean_form(int K) { return K >= 256; }
 
 void vpk_kmeans_update(const void *X, int d, const int32_t *list, const int32_t *start, const int32_t *counts, int K,
-                       int splits, void *acc, const VpKmState *state, void *C, hipStream_t st)
+                       int splits, void *acc, const VpKmState *state, const int32_t *was_split, void *C, hipStream_t st)
 {
     if (vpk_kmeans_mean_form(K)) {
         // enough clusters to fill the chip with one workgroup each
         hipLaunchKernelGGL(kmeans_mean_kernel, dim3(K), dim3(MEAN_THREADS), 0, st, (const uint4 *)X, d / 8, list, start,
-                           counts, (unsigned long long *)acc, state, (uint4 *)C);
+                           counts, (unsigned long long *)acc, state, was_split, (uint4 *)C);
         return;
     }
     hipLaunchKernelGGL(kmeans_sum_kernel, dim3(K, splits), dim3(256), 0, st, (const uint4 *)X, d / 8, list, start,
                        splits, (unsigned long long *)acc, state);
     const size_t e = (size_t)K * d;
     hipLaunchKernelGGL(kmeans_update_kernel, dim3((unsigned)((e + 255) / 256)), dim3(256), 0, st,
-                       (const unsigned long long *)acc, start, counts, state, K, d, (uint16_t *)C);
+                       (const unsigned long long *)acc, start, counts, state, was_split, K, d, (uint16_t *)C);
 }
 
-void vpk_kmeans_split(const int32_t *counts, int K, int d, void *C, hipStream_t st)
+void vpk_kmeans_split(const int32_t *counts, int K, int d, VpKmState *state, int32_t *was_split, void *C, hipStream_t st)
 {
-    hipLaunchKernelGGL(kmeans_split_kernel, dim3(1), dim3(1024), (size_t)K * sizeof(int), st, counts, K, d,
+    hipLaunchKernelGGL(kmeans_split_kernel, dim3(1), dim3(1024), (size_t)K * sizeof(int), st, counts, K, d, state, was_split,
                        (uint16_t *)C);
 }
 

@@ -20,7 +20,7 @@ constexpr int CHUNK_ROWS = 65536;   // vectors per launch of the Eq. 2 kernel
 struct KmeansLayout {
     int d_pad, kt, ctiles, K_pad, parts, tpw;
     size_t cp, cnorm, cp_changed, cnorm_changed, which_changed, flag, cpart, start, cursor, events, order, list, prev, rank,
-        rank_old, parted, best, acc, state, total;
+        rank_old, parted, best, acc, was_split, state, total;
 };
 
 vp_status kmeans_layout(int64_t n, int d, int K, KmeansLayout *L)
@@ -57,6 +57,7 @@ vp_status kmeans_layout(int64_t n, int d, int K, KmeansLayout *L)
     L->parted = take((size_t)n * 4);
     L->best = take((size_t)n * 4);
     L->acc = take((size_t)K * d * 8);
+    L->was_split = take((size_t)K * 4);
     L->state = take(sizeof(VpKmState));
     L->total = o;
     return VP_OK;
@@ -121,6 +122,7 @@ vp_status vp_kmeans(const void *x, int64_t n, int32_t d, int32_t K, int32_t iter
     if (!mean_form) vpk_fill_u32(acc, (size_t)K * d * 2, 0u, st);
     const bool rows_in_lds = n >= 4096 && vpk_kmeans_rows_in_lds(L.kt, L.ctiles, (long)n);
     const bool split = (flags & VP_KMEANS_SPLIT_EMPTY) != 0;
+    pass.was_split = split ? ints(L.was_split) : nullptr;
     for (int it = 0; it <= iters; ++it) {
         pass.first = it == 0;
         pass.rank = it < iters && numbers ? ints(L.rank) : nullptr;   // (the last pass only assigns)
@@ -139,8 +141,8 @@ vp_status vp_kmeans(const void *x, int64_t n, int32_t d, int32_t K, int32_t iter
         if (it == iters) break;   // the last pass only assigns
         int32_t *const entries = pass.first ? order : list;
         vpk_kmeans_place((long)n, K, d, pass, start, entries, acc, st);
-        vpk_kmeans_update(x, d, entries, start, counts, K, splits, acc, state, centroids, st);
-        if (split) vpk_kmeans_split(counts, K, d, centroids, st);
+        vpk_kmeans_update(x, d, entries, start, counts, K, splits, acc, state, pass.was_split, centroids, st);
+        if (split) vpk_kmeans_split(counts, K, d, state, pass.was_split, centroids, st);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return (vp_status)vpi_fail(VP_ERR_HIP, "vp_kmeans: %s", hipGetErrorString(e));

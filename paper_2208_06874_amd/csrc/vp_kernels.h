@@ -99,8 +99,8 @@ bool vpk_kmeans_assign_gemm(const void *X, long n, int d, int K, int kt, int cti
 void vpk_kmeans_place(long n, int K, int d, const VpKmPass &pass, int32_t *start, int32_t *list, void *acc, hipStream_t st);
 bool vpk_kmeans_mean_form(int K);   // one workgroup per cluster
 void vpk_kmeans_update(const void *X, int d, const int32_t *list, const int32_t *start, const int32_t *counts, int K,
-                       int splits, void *acc, const VpKmState *state, void *C, hipStream_t st);
-void vpk_kmeans_split(const int32_t *counts, int K, int d, void *C, hipStream_t st);
+                       int splits, void *acc, const VpKmState *state, const int32_t *was_split, void *C, hipStream_t st);
+void vpk_kmeans_split(const int32_t *counts, int K, int d, VpKmState *state, int32_t *was_split, void *C, hipStream_t st);
 void vpk_aset_flags(const int32_t *top, const int32_t *assign, long n, int T, int K, int V, int words,
                     uint32_t *bitmaps, int32_t *sizes, int64_t *cand_off, hipStream_t st);
 void vpk_aset_emit(const uint32_t *bitmaps, int words, int K, const int64_t *cand_off, int32_t *cand_ids,

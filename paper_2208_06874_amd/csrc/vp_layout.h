@@ -299,7 +299,8 @@ struct VpKmState {
     int32_t total_events;   // members that came or went, both counted (first pass: all vectors)
     int32_t anew;           // the entries are all members, the sums begin at zero
     int32_t unsettled, settled;   // vectors in VpKmPass.parted from its front and from its end
-    int32_t pad[3];
+    int32_t split;          // the last split moved centroids of clusters with members
+    int32_t pad[2];
 };
 
 // The buffers of a membership pass.
@@ -320,6 +321,7 @@ struct VpKmPass {
     float *best;            // [n] score of the vector's cluster (rows-in-LDS kernel)
     const int32_t *order;   // [n] vectors in the order of their first clusters
     int32_t *parted;        // [n] those whose own centroids changed in front
+    int32_t *was_split;     // [K] the last split moved the centroid (null: empty clusters are left alone)
 };
 #define VP_KM_MAX_PIECES 512   // 16-byte pieces of the widest vector
 

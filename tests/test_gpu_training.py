@@ -131,6 +131,43 @@ def test_many_iterations_equal_single_ones(n, d, K, noise, split):
         assert np.array_equal(counts, np.bincount(assign, minlength=K))
 
 
+# A cluster that is split keeps members whose mean is not its centroid any more.  Where they are equal vectors none of them
+# may come or go, and the next iteration still has to give the cluster their mean.  All sums here are exact and the
+# two scores tie.
+@pytest.mark.parametrize("n,value", [(4, 1.25), (6, 1.0)])
+def test_a_split_cluster_gets_its_members_mean_again(oracle, n, value):
+    X = np.full((n, 8), value, np.float16)
+    C0 = np.stack([X[0], np.full(8, 200.0, np.float16)])
+    for iters in range(1, 5):
+        Cb, assign, counts = _gpu_kmeans(X, C0, iters, split_empty=True)
+        ref = oracle.kmeans(X, C0, iters, round_half=True, split_empty=True)
+        assert np.array_equal(Cb, ref["C_bits"]), (iters, Cb[:, 0], ref["C_bits"][:, 0])
+        assert np.array_equal(assign, ref["assign"]) and counts.tolist() == [n, 0]
+        assert np.array_equal(Cb[:, 0].view(np.float16), np.array([value * (1 - 2 ** -10), value * (1 + 2 ** -10)], np.float16))
+
+
+# The same in training of many clusters, against calls of one iteration: repeated vectors, the largest cluster of one vector
+# alone, centroids that nobody is near.  Fewer and more than 256 clusters (sums in memory, one workgroup per
+# cluster), fewer and more than 4,096 vectors (decode-time kernel, split-k and rows-in-LDS kernels).
+@pytest.mark.parametrize("n,d,K", [(900, 64, 40), (3000, 264, 300), (6000, 256, 60), (6000, 512, 300), (5000, 1536, 256),
+                                   (20000, 8, 300)])
+def test_splits_of_equal_vectors_in_many_iterations(n, d, K):
+    rs = np.random.default_rng(n + d + K)
+    distinct = rs.standard_normal((K // 2, d)).astype(np.float16)
+    X = distinct[rs.integers(0, K // 2, n)]
+    X[rs.random(n) < 0.3] = distinct[0]
+    C0 = np.full((K, d), 200.0, np.float16)
+    C0[: K // 2 - 3] = distinct[: K // 2 - 3]
+    C = C0.copy()
+    for it in range(7):
+        one, assign, counts = _gpu_kmeans(X, C, 1, split_empty=True)
+        C = one.view(np.float16)
+        many, assign_m, counts_m = _gpu_kmeans(X, C0, it + 1, split_empty=True)
+        assert np.array_equal(many, one), (it, int((many != one).sum()))
+        assert np.array_equal(assign_m, assign) and np.array_equal(counts_m, counts), it
+        assert np.array_equal(counts, np.bincount(assign, minlength=K))
+
+
 def test_twenty_iterations_and_determinism(oracle):
     cfg, X, q, C0 = _mixture("tiny", 8192)
     Cb, assign, counts = _gpu_kmeans(X, C0, 20)
