@@ -700,7 +700,7 @@ __global__ __launch_bounds__(PLACE_THREADS) void kmeans_place_kernel(long n, int
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bool first = pass.first != 0;
     auto scan = [&](const int32_t *v) {
-        int carry = 0;
+        uint32_t carry = 0;   // (events: up to 2 n)
         for (int j0 = 0; j0 < K; j0 += PLACE_THREADS) {
             const int j = j0 + tid;
             const int c = j < K ? v[j] : 0;
@@ -710,15 +710,15 @@ __global__ __launch_bounds__(PLACE_THREADS) void kmeans_place_kernel(long n, int
             __syncthreads();
             const int w = wave_inclusive_sum(lane < PLACE_THREADS / 64 ? wsum[lane] : 0);
             const int below = wave ? __builtin_amdgcn_readlane(w, wave - 1) : 0;
-            if (j < K) base[j] = carry + below + inc - c;
-            carry += __builtin_amdgcn_readlane(w, PLACE_THREADS / 64 - 1);
+            if (j < K) base[j] = (int)(carry + (uint32_t)below + (uint32_t)inc - (uint32_t)c);
+            carry += (uint32_t)__builtin_amdgcn_readlane(w, PLACE_THREADS / 64 - 1);
         }
-        if (tid == 0) base[K] = carry;
+        if (tid == 0) base[K] = (int)carry;
         __syncthreads();
         return carry;
     };
-    const int total = scan(first ? pass.counts : pass.events);
-    const bool anew = first || total > n;
+    const uint32_t total = scan(first ? pass.counts : pass.events);
+    const bool anew = first || vp_sums_begin_anew(total, n);
     if (blockIdx.x == 0 && tid == 0) {
         pass.state->total_events = total;
         pass.state->anew = anew;

@@ -293,10 +293,15 @@ struct VpSmallArgs {
     VpPlanHeader *hdr;          // (out)
 };
 
+// Whether an iteration adds up all members again in place of the `events` (members that came or went: two for every vector
+// that moved, so their number needs all 32 bits for the 2^31 - 1 vectors of the largest call).  They have to fit a
+// list of n entries, and more of them would read more vectors than there are.
+static inline __host__ __device__ bool vp_sums_begin_anew(uint32_t events, int64_t n) { return (int64_t)events > n; }
+
 // What one iteration of the training leaves for the next kernels.
 struct VpKmState {
     int32_t changed;        // centroids that are other ones than in the pass before (later passes)
-    int32_t total_events;   // members that came or went, both counted (first pass: all vectors)
+    uint32_t total_events;  // members that came or went, both counted (first pass: all vectors)
     int32_t anew;           // the entries are all members, the sums begin at zero
     int32_t unsettled, settled;   // vectors in VpKmPass.parted from its front and from its end
     int32_t split;          // the last split moved centroids of clusters with members

@@ -271,6 +271,19 @@ def test_item_count_of_many_row_groups(layout):
             assert items // rgs % 8 == 0, (rgs, vtiles, kt, items)
 
 
+def test_event_total_of_the_largest_training_call(layout):
+    """Every vector that moves is two events.  From 2^30 vectors that move on their total does not fit 31 bits; it must
+    still be seen to be more than the n entries of the event list."""
+    r = np.random.default_rng(4)
+    for n in (1, 1000, 2 ** 30 - 1, 2 ** 30, 2 ** 31 - 1):
+        for moved in {0, n // 2, n // 2 + 1, n, int(r.integers(0, n + 1))}:
+            total = np.uint32(0)
+            with np.errstate(over="ignore"):
+                for part in (moved // 3, moved - moved // 3, moved):      # (three clusters' counts)
+                    total += np.uint32(part)
+            assert layout.shim_sums_begin_anew(ctypes.c_uint32(int(total)), ctypes.c_int64(n)) == (2 * moved > n), (n, moved)
+
+
 def test_short_items_bound_of_the_raw_logit_form(layout):
     """The host considers raw logits only for calls of at most 8,192 candidate tiles.  With the default
     sizing (8,192 items asked for, 1,024 workgroup slots) such a plan has at most VP_RAW_TILES tiles per
