@@ -781,12 +781,15 @@ __device__ inline void add_units(double (&s)[8], const uint4 v, uint32_t entry)
 
 __device__ inline unsigned long long to_units(double sum) { return (unsigned long long)(long long)(sum * 0x1p24); }
 
-// Sum of the entries [first, last) taken every `step`-th, coordinates 8 * piece and following.
+// Sum of the entries [first, last) taken every `step`-th, coordinates 8 * piece and following; returns where it ended.
+// Members add up exactly by the bound on x.  EVENTS may be the members of two passes together: at most
+// VP_KM_EXACT_ENTRIES of them at a time.
 template <bool EVENTS>
-__device__ inline void sum_entries(double (&s)[8], const uint4 *__restrict__ X, int pieces, int piece,
-                                   const int32_t *__restrict__ list, int first, int last, int step)
+__device__ inline int sum_entries(double (&s)[8], const uint4 *__restrict__ X, int pieces, int piece,
+                                  const int32_t *__restrict__ list, int first, int last, int step)
 {
     int m = first;
+    if (EVENTS && last - first > VP_KM_EXACT_ENTRIES * step) last = first + VP_KM_EXACT_ENTRIES * step;
     for (; m + 7 * step < last; m += 8 * step) {
         // entries first, then all eight rows: written as one expression the loads of an entry and of its row
         // alternate and every one waits for the one before
@@ -803,6 +806,7 @@ __device__ inline void sum_entries(double (&s)[8], const uint4 *__restrict__ X, 
         const uint32_t r = (uint32_t)list[m];
         add_units<EVENTS>(s, X[(size_t)(r & 0x7fffffffu) * pieces + piece], r);
     }
+    return m;
 }
 
 // Sum of the entries of cluster blockIdx.x that fall to this workgroup (every `splits`-th one
@@ -828,18 +832,21 @@ __global__ __launch_bounds__(256) void kmeans_sum_kernel(const uint4 *__restrict
     const int step = splits * lanes;
     const int first = m0 + blockIdx.y * lanes + ml;
     for (int piece = lanes > 1 ? threadIdx.x - ml * pieces : threadIdx.x; piece < pieces && ml < lanes; piece += 256) {
-        double s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        if (state->anew) sum_entries<false>(s, X, pieces, piece, list, first, m1, step);
-        else sum_entries<true>(s, X, pieces, piece, list, first, m1, step);
-        if (lanes > 1) {
-            // the member lanes meet in LDS; one global addition per coordinate and workgroup
-            unsigned long long *slot = lsum + (size_t)piece * 8;
+        int m = first;
+        do {
+            double s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+            if (state->anew) m = sum_entries<false>(s, X, pieces, piece, list, m, m1, step);
+            else m = sum_entries<true>(s, X, pieces, piece, list, m, m1, step);
+            if (lanes > 1) {
+                // the member lanes meet in LDS; one global addition per coordinate and workgroup
+                unsigned long long *slot = lsum + (size_t)piece * 8;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) atomicAdd(slot + e, to_units(s[e]));
-        } else {
+                for (int e = 0; e < 8; ++e) atomicAdd(slot + e, to_units(s[e]));
+            } else {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) atomicAdd(&acc[((size_t)j * pieces + piece) * 8 + e], to_units(s[e]));
-        }
+                for (int e = 0; e < 8; ++e) atomicAdd(&acc[((size_t)j * pieces + piece) * 8 + e], to_units(s[e]));
+            }
+        } while (m < m1);
     }
     if (lanes > 1) {
         __syncthreads();
@@ -918,11 +925,14 @@ __global__ __launch_bounds__(MEAN_THREADS) void kmeans_mean_kernel(const uint4 *
     __syncthreads();
     const int piece = threadIdx.x - ml * pieces;
     if (ml < lanes && m0 + ml < m1) {
-        double s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        if (anew) sum_entries<false>(s, X, pieces, piece, list, m0 + ml, m1, lanes);
-        else sum_entries<true>(s, X, pieces, piece, list, m0 + ml, m1, lanes);
+        int m = m0 + ml;
+        do {
+            double s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+            if (anew) m = sum_entries<false>(s, X, pieces, piece, list, m, m1, lanes);
+            else m = sum_entries<true>(s, X, pieces, piece, list, m, m1, lanes);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) atomicAdd(lsum + (size_t)piece * 8 + e, to_units(s[e]));
+            for (int e = 0; e < 8; ++e) atomicAdd(lsum + (size_t)piece * 8 + e, to_units(s[e]));
+        } while (m < m1);
     }
     __syncthreads();
     const int c = counts[j];

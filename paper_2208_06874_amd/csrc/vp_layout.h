@@ -298,6 +298,9 @@ struct VpSmallArgs {
 // list of n entries, and more of them would read more vectors than there are.
 static inline __host__ __device__ bool vp_sums_begin_anew(uint32_t events, int64_t n) { return (int64_t)events > n; }
 
+// Entries that a double adds up exactly whatever their signs: binary16 values are multiples of 2^-24 below 2^16.
+#define VP_KM_EXACT_ENTRIES 8192
+
 // What one iteration of the training leaves for the next kernels.
 struct VpKmState {
     int32_t changed;        // centroids that are other ones than in the pass before (later passes)

@@ -29,3 +29,4 @@ extern "C" int shim_swept_item_count(int rgs, int slots, int vtiles, int kt, int
     return vp_swept_item_count(rgs, slots, vtiles, kt, max_items);
 }
 extern "C" int shim_sums_begin_anew(uint32_t events, int64_t n) { return vp_sums_begin_anew(events, n); }
+extern "C" int shim_km_exact_entries(void) { return VP_KM_EXACT_ENTRIES; }

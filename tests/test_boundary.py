@@ -284,6 +284,19 @@ def test_event_total_of_the_largest_training_call(layout):
             assert layout.shim_sums_begin_anew(ctypes.c_uint32(int(total)), ctypes.c_int64(n)) == (2 * moved > n), (n, moved)
 
 
+def test_a_double_adds_up_that_many_entries_exactly(layout):
+    """Members that came and members that left are bounded by 2^29 each, so together they may pass what a double holds
+    in units of 2^-24; the running sums of events are taken over in parts that cannot."""
+    n = layout.shim_km_exact_entries()
+    largest = int(float(np.finfo(np.float16).max) * 2 ** 24)
+    assert n * largest <= 2 ** 53 and 2 * 2 ** 29 * 2 ** 24 > 2 ** 53
+    s, units = 0.0, 0
+    for i in range(n):
+        v = float(np.finfo(np.float16).max) if i else 2.0 ** -24
+        s, units = s + v, units + int(v * 2 ** 24)
+    assert int(s * 2 ** 24) == units
+
+
 def test_short_items_bound_of_the_raw_logit_form(layout):
     """The host considers raw logits only for calls of at most 8,192 candidate tiles.  With the default
     sizing (8,192 items asked for, 1,024 workgroup slots) such a plan has at most VP_RAW_TILES tiles per
