@@ -147,6 +147,11 @@ __global__ __launch_bounds__(1024) void kmeans_prepare_kernel(const uint16_t *__
     for (int x = lane; x < X; x += 64) cc[place(slot, x)] = x < pieces ? row[x] : make_uint4(0, 0, 0, 0);
 }
 
+// rows-in-LDS membership kernel: wavefronts per workgroup, centroid groups per step, row tiles per item
+constexpr int KL_NW = 8;
+constexpr int KL_G = 2;
+constexpr int km_lds_row_tiles(int kt) { return kt > 32 ? 3 : 4; }
+
 // Whether a later pass is worth taking apart (below): with more centroids changed, nearly every vector meets
 // nearly all of them again.
 __device__ inline bool few_changed(int changed, int K) { return 5 * changed <= 2 * K; }
@@ -318,7 +323,15 @@ __global__ __launch_bounds__(256, (KW <= 8 ? 2 : 1)) void kmeans_assign_gemm_ker
     assign_split_k<KW, RANK, false>(X, n, d, K, ctiles, pass);
 }
 
-// The later passes of a call whose passes over everything run on the rows-in-LDS kernel: those in which few centroids changed.
+// The later passes of a call whose passes over everything run on the rows-in-LDS kernel: those in which few centroids changed,
+// with more vectors than that kernel takes in two rounds.  The vectors whose own centroids changed meet all centroids
+// here, one group behind the other, so the kernel takes about as long as a pass over everything takes it, however few they
+// are, and the rows-in-LDS kernel needs half of that for a round.  20 iterations in which five or so still change centroids, us, these
+// passes here / on the rows-in-LDS kernel: d = 1024, 2,000 clusters: 8,192 vectors 1,135 / 772, 16,384 1,620 / 1,146, 32,768
+// 1,366 / 1,377, 65,536 1,646 / 2,034; 260 clusters: 384 / 378 at 4,096, 517 / 531 at 32,768, 821 / 915 at 65,536; d = 1536, 1,000
+// clusters: 8,192 827 / 603, 24,576 780 / 786, 32,768 789 / 822; d = 512, 1,000 clusters: 16,384 492 / 402, 65,536 652 / 673.
+bool takes_passes_apart(int kt, long n) { return n > 2 * 256 * 16l * km_lds_row_tiles(kt); }
+
 template <int KW, bool RANK>
 __global__ __launch_bounds__(256, (KW <= 8 ? 2 : 1)) void kmeans_reassign_kernel(const uint4 *__restrict__ X, long n, int d,
                                                                                  int K, int ctiles, VpKmPass pass)
@@ -327,11 +340,6 @@ __global__ __launch_bounds__(256, (KW <= 8 ? 2 : 1)) void kmeans_reassign_kernel
     if (changed == 0 || !few_changed(changed, K)) return;
     assign_split_k<KW, RANK, true>(X, n, d, K, ctiles, pass);
 }
-
-// rows-in-LDS membership kernel: wavefronts per workgroup, centroid groups per step, row tiles per item
-constexpr int KL_NW = 8;
-constexpr int KL_G = 2;
-constexpr int km_lds_row_tiles(int kt) { return kt > 32 ? 3 : 4; }
 
 // Parts the vectors for the kernel above: those whose own centroids changed from the front of the list, the others from
 // its end (in no particular order).  Called by all workgroups of a grid of `threads` threads each; one pair of
@@ -385,10 +393,13 @@ __global__ __launch_bounds__(KL_NW * 64) void kmeans_assign_lds_kernel(const uin
 {
     const bool first = pass.first != 0;
     extern __shared__ uint4 lds[];        // [RT][KT][64]: the vectors in MFMA operand order
-    if (!first && few_changed(pass.state->changed, K)) {
-        // kmeans_reassign_kernel takes the pass
-        if (pass.state->changed > 0) part_vectors(n, pass, reinterpret_cast<int *>(lds), KL_NW * 64);
-        return;
+    if (!first) {
+        const int changed = pass.state->changed;
+        if (changed == 0) return;   // nobody moves
+        if (pass.apart && few_changed(changed, K)) {   // kmeans_reassign_kernel takes the pass
+            part_vectors(n, pass, reinterpret_cast<int *>(lds), KL_NW * 64);
+            return;
+        }
     }
     const uint4 *const cp = reinterpret_cast<const uint4 *>(pass.cp);
     const float *const cnorm = pass.cnorm;
@@ -664,6 +675,7 @@ void launch_assign_lds(const void *X, long n, int d, int K, int ctiles, const Vp
 //   d_pad 1536 (48 vectors an item here, 64 there), 288 clusters: 12,288 vectors 49 -> 42, 12,290 47 -> 55, 16,500 72 -> 57,
 //     25,000 80 -> 83, 131,072 293 -> 280; 480 clusters: 61 -> 47, 59 -> 63, 97 -> 64, 102 -> 90, 394 -> 315
 //   d_pad 512: faster everywhere (288 clusters: 16,400 36 -> 31, 131,072 140 -> 116)
+//   d_pad 768 and 1280 with the lines of 1024 and 1536: nowhere slower (0.56 to 0.99 and 0.55 to 0.95 of the time)
 bool rows_in_lds_faster(int kt, int ctiles, long n)
 {
     if (ctiles < KL_NW * KL_G || (kt != 16 && kt != 24 && kt != 32 && kt != 40 && kt != 48)) return false;
@@ -1185,6 +1197,8 @@ bool vpk_kmeans_rows_in_lds(int kt, int ctiles, long n)
     return false;
 }
 
+bool vpk_kmeans_takes_passes_apart(int kt, long n) { return takes_passes_apart(kt, n); }
+
 bool vpk_kmeans_assign_gemm(const void *X, long n, int d, int K, int kt, int ctiles, bool rows_in_lds, const VpKmPass &pass,
                             hipStream_t st)
 {
@@ -1196,7 +1210,7 @@ bool vpk_kmeans_assign_gemm(const void *X, long n, int d, int K, int kt, int cti
 #define VP_KM_CASE(KT)                                                            \
     case KT:                                                                      \
         launch_assign_lds<KT>(X, n, d, K, ctiles, pass, st);                      \
-        if (!pass.first) VP_KM_LAUNCH(kmeans_reassign_kernel, KT / 4);            \
+        if (!pass.first && pass.apart) VP_KM_LAUNCH(kmeans_reassign_kernel, KT / 4); \
         break;
         switch (kt) {
             VP_KM_CASE(16)

@@ -121,6 +121,7 @@ vp_status vp_kmeans(const void *x, int64_t n, int32_t d, int32_t K, int32_t iter
     const bool numbers = mean_form && (size_t)n * 4 <= (size_t)K * d * 8;
     if (!mean_form) vpk_fill_u32(acc, (size_t)K * d * 2, 0u, st);
     const bool rows_in_lds = n >= 4096 && vpk_kmeans_rows_in_lds(L.kt, L.ctiles, (long)n);
+    pass.apart = rows_in_lds && vpk_kmeans_takes_passes_apart(L.kt, (long)n);
     const bool split = (flags & VP_KMEANS_SPLIT_EMPTY) != 0;
     pass.was_split = split ? ints(L.was_split) : nullptr;
     for (int it = 0; it <= iters; ++it) {

@@ -94,6 +94,7 @@ void vpk_kmeans_prepare(const void *C, int K, int d, int kt, int K_pad, bool alw
 void vpk_kmeans_assign(const void *cpart, int parts, long row0, int rows, int K, const VpKmPass &pass, hipStream_t st);
 // (true: the rows-in-LDS kernel takes the passes of this call, and its LDS size is set)
 bool vpk_kmeans_rows_in_lds(int kt, int ctiles, long n);
+bool vpk_kmeans_takes_passes_apart(int kt, long n);   // (of such a call)
 bool vpk_kmeans_assign_gemm(const void *X, long n, int d, int K, int kt, int ctiles, bool rows_in_lds, const VpKmPass &pass,
                             hipStream_t st);
 void vpk_kmeans_place(long n, int K, int d, const VpKmPass &pass, int32_t *start, int32_t *list, void *acc, hipStream_t st);

@@ -314,7 +314,7 @@ struct VpKmState {
 // The buffers of a membership pass.
 struct VpKmPass {
     int32_t first;          // every vector against every centroid, nothing known before
-    int32_t pad;
+    int32_t apart;          // rows-in-LDS kernel: passes in which few centroids changed go to its companion
     VpKmState *state;
     void *cp;               // packed centroids, padded to whole groups
     float *cnorm;

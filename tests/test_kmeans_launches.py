@@ -24,17 +24,21 @@ def launches(tmp_path_factory):
                     os.path.join(ROOT, "tests", "kmeans_launch_main.cpp"), "-L", libdir, "-lvp", "-Wl,-rpath," + libdir,
                     "-Wl,--allow-shlib-undefined", "-o", str(exe)], check=True, capture_output=True)
 
-    def run(n, d, K, iters=0, fail_attribute=False):
-        """(status, attribute calls, error left behind, the membership kernel of every pass, which passes keep numbers)"""
+    def printed(n, d, K, iters=0, fail_attribute=False):
         r = subprocess.run([str(exe), str(int(fail_attribute)), str(n), str(d), str(K), str(iters)], capture_output=True,
                            text=True, timeout=60)
         assert r.returncode == 0, r.stdout + r.stderr
-        lines = r.stdout.split("\n")
+        return r.stdout.split("\n")
+
+    def run(n, d, K, iters=0, fail_attribute=False):
+        """(status, attribute calls, error left behind, the membership kernel of every pass, which passes keep numbers)"""
+        lines = printed(n, d, K, iters, fail_attribute)
         passes = [m for name in lines[3:] for m in MEMBERSHIP if m in name]
         # the counting kernels' RANK argument, as it stands in the mangled names
         kept = [bool(int(b)) for name in lines[3:] for b in re.findall(r"kmeans_assign\w*_kernelI(?:Li\d+E)?Lb([01])E", name)]
         return int(lines[0]), int(lines[1]), int(lines[2]), passes, kept
 
+    run.printed = printed
     return run
 
 
@@ -73,3 +77,13 @@ def test_membership_kernel_by_size(launches, d, n, K, lds):
     """Both sides of every line of the rule: where the rows-in-LDS kernel measured slower, the other one runs."""
     want = "kmeans_assign_lds_kernel" if lds else "kmeans_assign_gemm_kernel"
     assert launches(n, d, K)[:4] == (0, 2 * int(lds), 0, [want])
+
+
+@pytest.mark.parametrize("d,n,K,apart", [(1024, 32768, 1000, False), (1024, 32769, 1000, True), (512, 32769, 260, True),
+                                         (1536, 24576, 500, False), (1536, 24577, 500, True), (1288, 24577, 500, True),
+                                         (1024, 100000, 200, False), (2048, 100000, 500, False)])
+def test_passes_are_taken_apart_only_beyond_two_rounds(launches, d, n, K, apart):
+    """The companion of the rows-in-LDS kernel is launched in later passes only, and only where two rounds of that kernel
+    do not hold all vectors; the split-k kernel takes its passes apart by itself."""
+    names = launches.printed(n, d, K, iters=3)[3:]
+    assert sum("kmeans_reassign_kernel" in name for name in names) == 3 * int(apart)
