@@ -41,13 +41,24 @@ constexpr int L_NW = 8;        // wavefronts per workgroup
 // row tiles per item: four (64 rows), or three where four do not fit the LDS (48 rows: 120 KiB at d_pad = 1280,
 // 144 KiB at 1536)
 constexpr int lds_row_tiles(int kt) { return kt > 32 ? 3 : 4; }
-// Candidate groups per step: four (one 1 KiB read of the rows from LDS per four MFMAs), or one for items with less than
-// a step of four groups for every wavefront, which would leave wavefronts without work and the others
-// with a long chain of loads (full projection, V = 32,000, d = 1024, 64 rows, us: top-1 28.2 -> 26.4, top-4 37.1 -> 31.7,
-// top-8 47.8 -> 36.9; d = 1536, 48 rows, top-8: 45.3 -> 37.9, but 56.2 -> 57.2 with 16 groups an item, V = 60,000: the
-// line there).
+// Candidate groups per step: four (one 1 KiB read of the rows from LDS per four MFMAs), or one for short items (brief_to).
 // About 16 KiB per wavefront are kept in flight either way.
 constexpr int lds_k_tiles_in_flight(int kt, int g) { return g == 4 ? 4 : kt % 16 == 0 ? 16 : 8; }
+// The largest item that takes steps of one group.  In steps of four its wavefronts are partly without work, and the others have a
+// long chain of loads; in steps of one every group pays for a fold, and lists of more than one entry for their upkeep.
+// Full projection, time in steps of four / of one by groups per item: d = 1024, top-1, one row group: 4: 1.15, 8: 1.03, 15: 1.10, 20:
+// 1.04, 28: 1.04, and four row groups alike.  Lists of a few entries, several row groups (whose workgroups wait for the
+// same bytes): d = 1024, four of them, top-4: 4: 1.30, 8: 1.27, 12: 1.03, 20: 0.97, 28: 0.90; top-8: 1.46, 1.30, 1.05, 0.93, 0.83; two
+// of them, top-2: 1.22, 1.11, 0.94, 0.96, 0.92; d = 256 and 512 alike (at 28, top-8: 0.85, 0.80).  One row group, top-4, 24 rows: d =
+// 1024: 12: 1.03, 15: 1.04, 20: 1.05, 28: 1.05; d = 768: 1.00, 0.95, 1.03, 1.03; d = 512: 0.94, 1.01, 0.93, 0.97; d = 256: 0.94, 0.88, 0.91,
+// 0.88.  d = 1280 and 1536: 8: 1.11, 1.10, 12: 0.97, 0.99, beyond 16 0.98 at top-8.
+template <int KT, bool TOP1>
+__device__ constexpr int brief_to(bool shared, int k)
+{
+    if (TOP1) return (KT > 32 ? 2 : 4) * L_NW - 1;
+    if (shared) return k > 2 ? 12 : L_NW;
+    return KT > 32 ? 2 * L_NW - 1 : KT >= 24 ? 4 * L_NW - 1 : L_NW;
+}
 constexpr int VP_MAX_TOPK_LANES = 32;   // the epilogue writes a row's list with one lane per entry
 
 // (logit descending, position ascending), without branches
@@ -478,7 +489,7 @@ __global__ __launch_bounds__(L_NW * 64) void project_gemm_lds_kernel(
         if (hdr->mode == 1) perm = nullptr;   // the whole batch, in its own order
     }
     const int kk = TOP1 ? 1 : k;
-    const bool brief = item.ntiles < (KT > 32 ? 2 : 4) * L_NW;   // (see lds_k_tiles_in_flight)
+    const bool brief = item.ntiles <= brief_to<KT, TOP1>(item.shared, k);
     if (item.shared || GATHER) {
         if (brief) gemm_lds_item<KT, 1, MASKED, false, TOP1, GATHER>(set, hidden, d, item, it, kk, partials, floors, mask, perm);
         else gemm_lds_item<KT, 4, MASKED, false, TOP1, GATHER>(set, hidden, d, item, it, kk, partials, floors, mask, perm);

@@ -807,6 +807,27 @@ def test_crowded_clusters_on_the_many_row_kernel(oracle, d, k, N, K):
     pu.check_projection(oracle, W, b, C, off, ids, H, k, got[0], got[1], got[2])
 
 
+@pytest.mark.parametrize("d,N", [(256, 64), (512, 128), (768, 61), (1024, 64), (1024, 128), (1280, 48), (1536, 96)])
+def test_items_at_the_lines_between_the_step_widths(oracle, d, N):
+    """The rows-in-LDS kernel walks short items one candidate group a step, longer ones four: items of 8 to 32 groups on both
+    sides of every line (by k-extent, top-1 or lists, one row group or two), the last one short and ragged.  Eight items,
+    whole rounds of the option's count."""
+    per = 64 if d <= 1024 else 48
+    rgs = (N + per - 1) // per
+    for groups in (8, 12, 16, 28, 32):
+        V = 16 * groups * (8 // rgs) - 21
+        r, W, b, C = _small_model(40 + d + groups, d, V, 2)
+        off, ids = _random_lists(r, 2, V, 20, 60)
+        B = Built(W, b, C, off, ids, k_max=8)
+        B.index.set_option("gemm_lds_items", 8)
+        H = _rows(r, C, N)
+        for k in (1, 2, 3, 8):
+            f_ids, f_logp = B.project_full(H, k)
+            ws = B.index.workspace(N)
+            assert ws[:64].view(_torch().int32)[1].item() * 4 == groups, "the plan's items are of another size"
+            pu.check_full(oracle, W, b, H, k, f_ids, f_logp)
+
+
 def test_empty_active_sets(oracle):
     """A cluster whose active set is empty (a cluster that lost its members in training): rows that fall into
     it get ids -1 and log-probs -inf in every form of the projection; the other rows are untouched."""
