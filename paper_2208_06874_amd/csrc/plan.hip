@@ -14,6 +14,7 @@
 #include <hip/hip_runtime.h>
 #include "vp_kernels.h"
 #include "plan_common.h"
+#include "vp.h"
 #include "wave_ops.h"
 
 namespace {
@@ -97,34 +98,33 @@ __device__ inline void block_sum3(int a, int b, int c, int *ta, int *tb, int *tc
 // when its slab takes longer than that for its
 // rows (few rows, long list) and keeps its slab otherwise.  Which price per row is the best one depends on how much of
 // the pass over W the masked rows fill; the full one, its half and its quarter are tried, and masking nothing, and the cheapest
-// total wins if it is 5 % cheaper than either form for the whole batch (both projection kernels then have work, in one plan).
+// total wins if it is 8 % cheaper than either form for the whole batch (both projection kernels then have work, in one plan).
 // 4,096 Zipf(1.1) rows on 500 clusters of 2,000 to 40,000 tokens, d = 1536, top-8: slabs 2,830 us, masked 3,360, both
 // 2,100, crowded clusters grouped as well 1,500; 4,096 rows spread over 40 clusters of 8,000 to 16,000, d = 1024, top-6: 624
 // without groups, 322 with; 1,024 rows on lists of up to 30,000, d = 1024, top-4: 823, 521, 365;
 // 400 rows of that: 267 masked, 256.
 constexpr int MIX_CHOICES = 4;   // prices 1, 1/2, 1/4; nothing masked
 static_assert(MIX_CHOICES * PLAN_THREADS / 64 == 64, "one lane per choice and wavefront");
-// the matrix cores' rate over many row groups against the rate of the few that the choice between the two whole forms turns
-// on (N = 512 -> 4,096 masked rows: 14.1 -> 17.5 TB/s of W at d = 1024, 10 -> 15 at d = 512, 16.8 -> 18.9 at d = 1536)
-constexpr float MIX_GEMM = 1.3f;
-constexpr float MIX_TIME = VP_MIX_TIME;
+constexpr int SLAB_CLUSTER = 1 << 17;   // (counts clusters on the slab kernel above the masked rows)
+static_assert(VP_MAX_ROWS < SLAB_CLUSTER && (long long)VP_MAX_CLUSTERS * SLAB_CLUSTER < 0x7fffffff - VP_MAX_ROWS, "one word for both");
 constexpr int GROUP_TILES = 32;      // fewest candidate tiles of a grouped item
 
 enum { ON_SLAB = 0, GROUPED = 1, MASKED_OUT = 2 };   // a cluster's form
 
-// one cluster on its slab, with its share of the rows' time, and grouped
+// one cluster on its slab, in items of 1 / inv_tpi candidate groups, and grouped (in floats: integer divisions by what is not a
+// constant would take most of the time)
 struct ClusterTimes {
-    float t_row, pass_rate, k_factor;
-    int rpi;
+    float inv_pass_rate, inv_slab, inv_l2, k_factor, inv_rpi, inv_tpi;
     bool group;
     __device__ float slab(int rows, int tiles, const VpCostModel &cost) const
     {
-        return tiles / cost.bw_slab + (ceil_div(rows, VP_ROWS_PER_ITEM) - 1) * tiles / cost.bw_l2 + rows * t_row;
+        return tiles * (inv_slab + (ceil_div(rows, VP_ROWS_PER_ITEM) - 1) * inv_l2) +
+               rows * (ceilf(tiles * inv_tpi) * cost.t_list + cost.t_row_slab);
     }
-    __device__ float grouped(int rows, int tiles, const VpCostModel &cost) const
+    __device__ float grouped(int rows, int tiles) const
     {
         // (the many-row kernel streams a little slower than the slab kernel: 5.1 against 6.8 TB/s on W)
-        return group ? fmaxf(1.33f * tiles / cost.bw_slab, ceil_div(rows, rpi) * tiles / pass_rate) * k_factor : __builtin_inff();
+        return group ? tiles * fmaxf(1.33f * inv_slab, ceilf(rows * inv_rpi) * inv_pass_rate) * k_factor : __builtin_inff();
     }
 };
 
@@ -149,6 +149,7 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_kernel(
     __shared__ int wsum3[48];
     __shared__ float mix_t[MIX_CHOICES][PLAN_THREADS / 64];
     __shared__ int mix_n[MIX_CHOICES][PLAN_THREADS / 64];
+    __shared__ float wsum_f[PLAN_THREADS / 64];
     __shared__ int max_rgs;     // most row groups any bucket has
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -174,30 +175,39 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_kernel(
 
     // total candidate tiles of all row groups
     int my_tiles = 0, my_occ_tiles = 0, my_units = 0;
+    float my_row_tiles = 0.f;
     for (int j = tid; j < K; j += PLAN_THREADS) {
         const int c = cnt[j];
         my_tiles += ceil_div(c, VP_ROWS_PER_ITEM) * tl[j];
         my_units += ceil_div(c, VP_ROWS_PER_ITEM);
         if (c > 0) my_occ_tiles += tl[j];
+        my_row_tiles += (float)c * tl[j];
     }
+    my_row_tiles = wave_sum_float(my_row_tiles);
+    if (lane == 0) wsum_f[wave] = my_row_tiles;   // (read behind the barriers of block_sum3)
     int total_tiles, units, occ_tiles;
     block_sum3(my_tiles, my_units, my_occ_tiles, &total_tiles, &units, &occ_tiles, wsum3);
 
-    // all forms give the same results, so the cheapest one is taken (cost model in plan_common.h)
+    // all forms give the same results, so the cheapest one is taken (cost model in vp_layout.h)
     int masked_rows = 0, grouped_rows = 0;
     int m_rgs = 0, m_chunks = 0, m_tpi = 0;   // the masked projection's items, where some clusters are masked
     int g_tpi = 0;                            // candidate tiles of a grouped item
     if (dispatch) {
         const int rpi = dispatch;   // rows per item of the masked projection (16, 48 or 64)
-        const float t_slab = vp_time_slabs(occ_tiles, total_tiles, N, cost);
-        const float t_full = vp_time_masked(N, rpi, vtiles, k, cost);
-        const float pass = vtiles / (cost.bw_gemm * MIX_GEMM);   // of one row group
+        // candidate groups of a slab item, as vp_tiles_per_wave cuts them
+        const float tpi_slab = fmaxf(ceilf(total_tiles / (VP_WG_WAVES * fminf(fmaxf(total_tiles / (4.f * VP_WG_WAVES), (float)min_items), (float)target_items))), 1.f) * VP_WG_WAVES;
+        const float row_tiles = __int_as_float(__builtin_amdgcn_readlane(
+            __float_as_int(row_sum_float(lane < PLAN_THREADS / 64 ? wsum_f[lane] : 0.f)), PLAN_THREADS / 64 - 1));
+        const float t_slab = vp_time_slabs(occ_tiles, total_tiles, row_tiles / tpi_slab + 0.5f * N, N, cost);
+        const float t_full = vp_time_masked_rows(N, rpi, vtiles, k, cost.bw_gemm, cost) + cost.t_masked;
+        const float pass = vtiles / (cost.bw_gemm * VP_MIX_GEMM);   // of one row group
         const float one_pass = vtiles / cost.bw_full;
-        const float k_factor = 1.f + k * 0.0125f;
-        const float best = 0.95f * fminf(t_slab, ceil_div(N, rpi) * pass * k_factor);
+        const float k_factor = vp_lists_factor(k);
+        const float gemm = cost.bw_gemm * VP_MIX_GEMM;
+        const float best = 0.92f * fminf(t_slab, vp_time_masked_rows(N, rpi, vtiles, k, gemm, cost) + cost.t_masked);
         // (whatever is masked, W is streamed once)
-        if (mix.slots > 0 && (mix.group || best > MIX_TIME + one_pass * k_factor)) {
-            const ClusterTimes time = {vp_rows_time(N, cost.t_row_slab) / N, cost.bw_gemm * MIX_GEMM, k_factor, rpi, mix.group != 0};
+        if (mix.slots > 0 && (mix.group || best > cost.t_second + cost.t_mixed + one_pass * k_factor)) {
+            const ClusterTimes time = {1.f / gemm, 1.f / cost.bw_slab, 1.f / cost.bw_l2, k_factor, 1.f / rpi, 1.f / tpi_slab, mix.group != 0};
             const float price = pass / rpi * k_factor;
             float t[MIX_CHOICES];
             int n[MIX_CHOICES];
@@ -209,12 +219,13 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_kernel(
             for (int j = tid; j < K; j += PLAN_THREADS) {
                 const int c = cnt[j];
                 if (c == 0) continue;
-                const float tj = fminf(time.slab(c, tl[j], cost), time.grouped(c, tl[j], cost));
+                const float ta = time.slab(c, tl[j], cost);
+                const float tj = fminf(ta, time.grouped(c, tl[j]));
 #pragma unroll
                 for (int i = 0; i < MIX_CHOICES; ++i) {
                     const bool masked = i < MIX_CHOICES - 1 && mix.mask && tj > c * price * (1.f / (1 << i));
                     t[i] += masked ? 0.f : tj;
-                    n[i] += masked ? c : 0;
+                    n[i] += masked ? c : tj == ta ? SLAB_CLUSTER : 0;
                 }
             }
 #pragma unroll
@@ -230,8 +241,10 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_kernel(
             // lane l adds up wavefront l % 16's share under choice l / 16
             const float ts = row_sum_float(mix_t[lane >> 4][lane & 15]);
             const int ns = row_sum(mix_n[lane >> 4][lane & 15]);
-            float both = ts + MIX_TIME + (ns > 0 ? fmaxf(one_pass, ceil_div(ns, rpi) * pass) * k_factor : 0.f);
-            if (ns == N) both = __builtin_inff();
+            const int rows = ns & (SLAB_CLUSTER - 1);   // masked ones
+            float both = ts + cost.t_second + (ns >= SLAB_CLUSTER ? cost.t_slab : 0.f) +
+                         (rows > 0 ? vp_time_masked_rows(rows, rpi, vtiles, k, gemm, cost) + cost.t_mixed : 0.f);
+            if (rows == N) both = __builtin_inff();
             float chosen = -1.f, least = best;   // (the price above which a cluster is masked)
 #pragma unroll
             for (int i = 0; i < MIX_CHOICES; ++i) {
@@ -247,7 +260,7 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_kernel(
                 for (int j = tid; j < K; j += PLAN_THREADS) {
                     const int c = cnt[j];
                     if (c == 0) continue;
-                    const float ta = time.slab(c, tl[j], cost), tb = time.grouped(c, tl[j], cost);
+                    const float ta = time.slab(c, tl[j], cost), tb = time.grouped(c, tl[j]);
                     if (fminf(ta, tb) > c * chosen) {
                         form[j] = MASKED_OUT;
                         my_masked += c;

@@ -119,6 +119,7 @@ struct vp_index {
     // [n] = candidate groups of the n longest active sets together, n = 0 .. K: the most slab
     // bytes n rows can occupy (host-side bound of the planner's choice)
     std::vector<int64_t> longest_tiles;
+    float row_tiles_mean;   // candidate groups a row meets on average if clusters have rows in proportion to their lists
     VpProfile *prof;
 };
 
@@ -387,42 +388,54 @@ vp_status run_clustered(const char *fn, const vp_index *I, const void *hidden, i
     const int rt_masked = rt_single >= 3 ? rt_single : 1;
     int dispatch = (I->dispatch && !dbg_logits) ? VP_ROWS_PER_ITEM * rt_masked : 0;
     const int max_full = max_items_full(I, N);
-    // the tile counts of the cost model are in tiles of kt KiB: fold that into the constants
-    VpCostModel cost = I->cost;
-    const float tile_bytes = (float)I->L.kt * VP_TILE_BYTES;
-    cost.bw_slab /= tile_bytes;
-    cost.bw_full /= tile_bytes;
-    cost.bw_l2 /= tile_bytes;
+    // Few rows against short lists: at most 8,192 tiles in all, which the default item sizing cuts
+    // into items of one or two tiles per wavefront (unless the plan lands just past one round of
+    // workgroups and its items are lengthened; the kernel checks the plan's figure itself).
+    // For those, keeping raw logits beats building top-k lists from k = 4 on (measured: N = 1,
+    // top-8: 50 -> 40 us per call; top-1: no gain, so the lists stay).
+    const int raw_ok = I->raw_logits && !dbg_logits && k >= 4 && (long)N * I->L.max_tiles <= 8192;
+    VpCostModel cost = vp_cost_of_call(I->cost, k, I->L.kt, raw_ok);
     if (rt_masked >= 3 && !use_gemm_lds(I, rt_masked, k)) cost.bw_gemm = cost.bw_gemm_split;
-    cost.bw_gemm /= tile_bytes;
     const long row_groups = (long)row_tiles + std::min(N, I->K);
     const long by_tiles = row_groups * ceil_div(I->L.max_tiles, VP_WG_WAVES);
     // (+ one round of blocks: the XCD swizzle of plans with heavy buckets rounds the grid up)
     const int grid_items = (int)std::min<long>(max_items, by_tiles) + 8 * VP_XCD_BLOCK_ITEMS;
-    // If the slabs are the cheaper form even when every row sits in a cluster of its own and those
-    // are the clusters with the longest lists (the planner's cost model on that worst case), the planner has nothing to
-    // decide and the masked full projection is not launched at all (learned active sets of a
-    // fraction of a percent of V: the common case).
+    // If the slabs are the cheaper form even where they cost the most, the planner has nothing to decide and the masked full
+    // projection is not launched at all (learned active sets of a fraction of a percent of V: the common case).  They cost
+    // the most with the rows spread over the clusters with the longest lists, as many as are longer than what 16 rows more
+    // on the longest one cost, and the remaining rows on that one.
     VpMixLimits mix = {};
     if (dispatch) {
-        const int buckets = std::min(N, I->K);
+        int buckets = std::min(N, I->K);
+        const float one_row = (float)I->L.max_tiles / (VP_ROWS_PER_ITEM * cost.bw_l2) * cost.bw_slab;
+        for (int lo = 1; lo < buckets;) {   // (the lists in descending order: the last of them that is that long)
+            const int mid = (lo + buckets + 1) / 2;
+            if ((float)(I->longest_tiles[mid] - I->longest_tiles[mid - 1]) >= one_row) lo = mid;
+            else buckets = mid - 1;
+        }
         const float occ = (float)I->longest_tiles[buckets];
-        const float total = occ + (float)row_tiles * I->L.max_tiles;
-        const float t_slab = occ / cost.bw_slab + (total - occ) / cost.bw_l2 + vp_rows_time(N, cost.t_row_slab);
+        const int more_rgs = ceil_div(N - buckets, VP_ROWS_PER_ITEM);
+        const float total = occ + (float)more_rgs * I->L.max_tiles;
+        const int tpi = vp_tiles_per_wave_units((long long)total, buckets + more_rgs, I->target_items, I->min_items) * VP_WG_WAVES;
+        const float t_slab = vp_time_slabs(occ, total, (float)N * ceil_div(I->L.max_tiles, tpi), N, cost);
+        const float t_full = vp_time_masked_rows(N, dispatch, I->L.vtiles, k, cost.bw_gemm, cost) + cost.t_masked;
         const int rgs_full = ceil_div(N, dispatch);
-        const float t_full = dispatch >= 48
-            ? std::max(I->L.vtiles / cost.bw_full, rgs_full * (I->L.vtiles / cost.bw_gemm)) * (1.f + k * 0.0125f)
-            : std::max(I->L.vtiles / cost.bw_full, (float)rgs_full * I->L.vtiles / cost.bw_l2) * (1.f + k * 0.125f);
         // Where the matrix cores set the masked projection's time, twice what a pass over W takes at least, the
         // planner may also mask some clusters only (unless even the longest list is cheaper as a slab of one row).
         // Below that nothing is saved: 300 rows, d = 1024: 215 us masked, 254 us with the crowded clusters on slabs.
         const bool may_mix = dispatch >= 48 && use_gemm_lds(I, rt_masked, k) &&
                              rgs_full * (I->L.vtiles / cost.bw_gemm) > 2 * (I->L.vtiles / cost.bw_full) &&
                              I->L.max_tiles / cost.bw_slab > I->L.vtiles / cost.bw_gemm / dispatch &&
-                             occ / cost.bw_slab > I->L.vtiles / cost.bw_full + VP_MIX_TIME;   // (all that masking could save)
-        // Crowded clusters: a batch of a thousand rows may well have some, a smaller one if there are few clusters.
-        // (They gain where the many-row kernel outruns the slabs' stream.)
-        const bool may_group = dispatch >= 48 && use_gemm_lds(I, rt_masked, k) && cost.bw_gemm > cost.bw_slab && (N >= 1024 || (N >= 64 && N >= 32 * I->K));
+                             occ / cost.bw_slab > I->L.vtiles / cost.bw_full + cost.t_second + cost.t_mixed;   // (all that masking could save)
+        // Crowded clusters go to the many-row kernel where all rows in one cluster would save what a launch costs that leaves
+        // (4 us) beside that plan's own time (and the kernel outruns the slabs' stream), the cluster being the one that a
+        // row meets if clusters have rows in proportion to their lists.  Otherwise that launch is lost: 1,024 rows, lists of 40 to
+        // 80, d = 512: 29 us, 33 with it.  And from 1,024 rows on, or 32 a cluster: below, where few calls have such clusters, those
+        // that do not pay 2 to 4 us for the look and the launch (528 rows, 293 clusters, d = 512: 69 us, 72 with both; 3,151
+        // calls, more than 5 % behind what they took without such plans: 134 without that line, 123 with it).
+        const bool may_group = dispatch >= 48 && use_gemm_lds(I, rt_masked, k) && cost.bw_gemm > cost.bw_slab && N >= 64 &&
+                               (N >= 1024 || N >= 32 * I->K) &&
+                               vp_grouping_saves(N, dispatch, I->row_tiles_mean, tpi, k, cost) > cost.t_second - cost.t_slab + 4e-6f;
         if (t_slab <= t_full && !may_mix && !may_group) dispatch = 0;
         mix.mask = may_mix;
         mix.group = may_group;
@@ -431,7 +444,6 @@ vp_status run_clustered(const char *fn, const vp_index *I, const void *hidden, i
     // Batches of a few rows: no planning kernel; the projection workgroups find their own work
     // (project_small_kernel) - unless the planner has a choice to make.
     const bool small = I->small_path && N <= VP_SMALL_ROWS && !dbg_row_off && !dbg_logits && !dispatch;
-    const int raw_ok_all = I->raw_logits && !dbg_logits && k >= 4 && (long)N * I->L.max_tiles <= 8192;
     if (small) {
         VpSmallArgs a = {};
         a.cpart = reinterpret_cast<const int32_t *>(cpart);
@@ -461,7 +473,7 @@ vp_status run_clustered(const char *fn, const vp_index *I, const void *hidden, i
         a.min_items = I->cus * std::min(per_cu, pf == 32 ? 2 : pf == 16 ? 3 : 4);
         auto *ev = profile_slot(I);
         if (ev) (void)hipEventRecord(ev->first, st);
-        vpk_project_small(I->clusters, hidden, I->d, a, grid_small, k, I->rstar, partials, raw_ok_all, pf, st);
+        vpk_project_small(I->clusters, hidden, I->d, a, grid_small, k, I->rstar, partials, raw_ok, pf, st);
         if (ev) (void)hipEventRecord(ev->second, st);
         vpk_merge(I->clusters, rowplan, hdr, partials, k, N, out_ids, out_logp, st);
         return launch_status(fn);
@@ -492,12 +504,6 @@ vp_status run_clustered(const char *fn, const vp_index *I, const void *hidden, i
 
     auto *ev = profile_slot(I);
     if (ev) (void)hipEventRecord(ev->first, st);
-    // Few rows against short lists: at most 8,192 tiles in all, which the default item sizing cuts
-    // into items of one or two tiles per wavefront (unless the plan lands just past one round of
-    // workgroups and its items are lengthened; the kernel checks the plan's figure itself).
-    // For those, keeping raw logits beats building top-k lists from k = 4 on (measured: N = 1,
-    // top-8: 50 -> 40 us per call; top-1: no gain, so the lists stay).
-    const int raw_ok = raw_ok_all;
     vpk_project(I->clusters, hidden, I->d, perm, items, hdr, grid_items, 1, k, I->rstar, partials, floors, dbg_logits,
                 dbg_row_off, raw_ok, st);
     if (dispatch) {
@@ -679,7 +685,12 @@ vp_status vp_build(const vp_build_desc *D, void *hip_stream, vp_index **out)
         for (int j = 0; j < D->K; ++j)
             I->longest_tiles[j + 1] = ceil_div((long)(D->cand_offsets[j + 1] - D->cand_offsets[j]), VP_TILE_ITEMS);
         std::sort(I->longest_tiles.begin() + 1, I->longest_tiles.end(), [](int64_t a, int64_t b) { return a > b; });
-        for (int j = 0; j < D->K; ++j) I->longest_tiles[j + 1] += I->longest_tiles[j];
+        double squares = 0.0;
+        for (int j = 0; j < D->K; ++j) {
+            squares += (double)I->longest_tiles[j + 1] * (double)I->longest_tiles[j + 1];
+            I->longest_tiles[j + 1] += I->longest_tiles[j];
+        }
+        I->row_tiles_mean = (float)(squares / (double)std::max<int64_t>(I->longest_tiles[D->K], 1));
     } catch (...) {
         delete I;
         return fail(VP_ERR_INVALID_ARG, "vp_build: out of host memory");
@@ -697,8 +708,7 @@ vp_status vp_build(const vp_build_desc *D, void *hip_stream, vp_index **out)
     // active set.
     I->dispatch = 1;
     // measured on MI355X at d = 1024, V = 250,000: bytes per second of the regimes of the cost model.
-    // Slabs stream at 6.8 TB/s, and a row costs about 60 ns beyond its bytes (512 rows against 32
-    // short lists: 72 us for 10 us of bytes).  The masked full projection with 64-row items takes
+    // Slabs stream at 6.8 TB/s (what the forms cost beyond their bytes: vp_cost_of_call).  The masked full projection with 64-row items takes
     // about 100 us for one pass over W from HBM (5.1 TB/s) or, with more row groups, 35 us per row
     // group on the matrix cores (14 TB/s of W; the split-k kernel at d = 1536: 98 us per row group
     // over 0.77 GB, 8 TB/s); with 16-row items every row group re-reads W through the L2 at 17 TB/s.

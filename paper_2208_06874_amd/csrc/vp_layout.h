@@ -254,18 +254,73 @@ struct VpCostModel {
     float bw_gemm_split;   // the same for the split-k kernel (k-extents beyond d_pad = 1536, k > 32)
     float bw_gather; // batch-union form: columns of U gathered from the packed W into the union slab
     float t_gather;  // ... and the fixed time of the kernels only that gather needs (seconds)
-    float t_row_slab;  // per-cluster slabs: time per row beyond the bytes (staging, lists, partial results; seconds)
+    float t_row_slab;  // the option (seconds); in the model of a call the slabs' time per row beyond the bytes
+    // what else the forms of a call cost (vp_cost_of_call; seconds)
+    float t_list;      // slabs: per row and item that the row is in
+    float t_slab;      // slabs
+    float t_masked;    // masked full projection
+    float t_masked_row, t_masked_group;   // ... per row, and per row group
+    float t_second;    // a second form in one plan
+    float t_mixed;     // ... and if that masks some of the rows
 };
 
-// What N rows add to the time of the slabs beyond the bytes.  Up to 512 rows the workgroups wait for their rows and
-// lists (72 us for 10 us of bytes: 512 rows against 32 short lists); more rows mostly find others' bytes to wait for
-// (4,096 rows, 300 clusters of 1,000 to 12,000 tokens, d = 512: 265 us in the kernel for 242 us of bytes).
-static inline __host__ __device__ float vp_rows_time(int N, float t_row)
+// Cost model of the planner, the same on the host, which leaves out what cannot win, and in the planning kernel.  Slabs: the
+// occupied slabs are streamed once from HBM, further row groups of a bucket re-read them through the L2.  Masked full
+// projection with 48- or 64-row items: one pass over W from HBM, or the matrix cores' time for all row groups, whichever
+// is longer (W is then served by the L2; the rate of the matrix cores is expressed in bytes of W per second), and 1.25 %
+// for every entry of the lists.  With 16-row items every row group re-reads W through the L2, and the lists cost more (every
+// lane of every wavefront is busy there).  Tile counts are in candidate groups, the rates of a call in groups per second.
+// What the forms cost beyond that is fitted to 2,098 calls of 2 to 1,300 clusters, lists of 10 to 40,000 tokens, 17 to 8,192
+// rows, d = 256 to 1,536, top-1 to top-16, each timed on the slabs, masked and as planned.  Slabs: 0.25 ns per row and k-tile
+// (staging); every item a row is in builds a list, 0.4 ns per entry (512 rows, 32 lists of 2,000, d = 512, top-4: 1,484 items 58 us, cut
+// into 756 38 us), 1.2 us per entry for the chain of an item; no lists for top-1 or where raw logits are kept.  Masked: starts and
+// ends 6 us later, 0.25 us per row group, 1.6 ns per row and entry, 0.6 us per entry for the chain.  A second form in one plan: 12 us
+// and 1.1 us per entry, 28 us more where it masks.  With 60 ns for every row on the slabs (up to the 512th, an eighth of that beyond) and nothing else,
+// and 40 us for a second form, the planner's choice took 1.084 times the fastest form's time (geometric mean, up to top-8; 2 at
+// most: 817 rows, 12 short lists, d = 768: 68 us masked, 35 on the slabs), with these 1.018.
+static inline __host__ __device__ VpCostModel vp_cost_of_call(VpCostModel m, int k, int kt, bool raw)
 {
-    return N <= 512 ? N * t_row : (512 + (N - 512) / 8) * t_row;
+    const float tile_bytes = (float)kt * VP_TILE_BYTES, lists = k > 1 && !raw ? (float)k : 0.f;
+    m.bw_slab /= tile_bytes;
+    m.bw_full /= tile_bytes;
+    m.bw_l2 /= tile_bytes;
+    m.bw_gemm /= tile_bytes;
+    m.bw_gemm_split /= tile_bytes;
+    const float per_ns = m.t_row_slab * (1.f / 60.f);   // (the option's default is 60 ns: 1 ns)
+    m.t_row_slab = 0.25f * kt * per_ns;
+    m.t_list = 0.4f * lists * per_ns;
+    m.t_slab = 1.2e-6f * lists;
+    m.t_masked = 6e-6f + 0.6e-6f * (k > 1 ? k : 0);
+    m.t_masked_row = 1.6e-9f * k;
+    m.t_masked_group = 0.25e-6f;
+    m.t_second = 12e-6f + 1.1e-6f * (k > 1 ? k : 0);
+    m.t_mixed = 28e-6f;
+    return m;
+}
+// the matrix cores' rate over many row groups against the rate of the few that the choice between the two whole forms turns
+// on (N = 512 -> 4,096 masked rows: 14.1 -> 17.5 TB/s of W at d = 1024, 10 -> 15 at d = 512, 16.8 -> 18.9 at d = 1536)
+#define VP_MIX_GEMM 1.3f
+static inline __host__ __device__ float vp_lists_factor(int k) { return 1.f + k * 0.0125f; }
+// list_items: every row times the items its bucket is cut into
+static inline __host__ __device__ float vp_time_slabs(float occ_tiles, float total_tiles, float list_items, int N, const VpCostModel &cost)
+{
+    return occ_tiles / cost.bw_slab + (total_tiles - occ_tiles) / cost.bw_l2 + list_items * cost.t_list + N * cost.t_row_slab + cost.t_slab;
+}
+// gemm: the matrix cores' rate (48- and 64-row items); without t_masked
+static inline __host__ __device__ float vp_time_masked_rows(int N, int rpi, int vtiles, int k, float gemm, const VpCostModel &cost)
+{
+    const float rgs = (float)((N + rpi - 1) / rpi), one_pass = vtiles / cost.bw_full;
+    const float passes = rgs * (vtiles / (rpi >= 48 ? gemm : cost.bw_l2));
+    return (passes > one_pass ? passes : one_pass) * (rpi >= 48 ? vp_lists_factor(k) : 1.f + k * 0.125f) +
+           rgs * cost.t_masked_group + N * cost.t_masked_row;
+}
+// What the many-row kernel saves on crowded clusters if all rows are in one, of that many candidate groups in items of tpi.
+static inline __host__ __device__ float vp_grouping_saves(int N, int rpi, float tiles, int tpi, int k, const VpCostModel &cost)
+{
+    return (float)((N + VP_ROWS_PER_ITEM - 1) / VP_ROWS_PER_ITEM) * tiles / cost.bw_l2 + N * ((int)(tiles / tpi) + 1) * cost.t_list -
+           (float)((N + rpi - 1) / rpi) * tiles / (cost.bw_gemm * VP_MIX_GEMM) * vp_lists_factor(k);
 }
 
-#define VP_MIX_TIME 40e-6f   // a second kernel's start and end, and buckets of many rows in a slab kernel with little to do
 #define VP_GROUP_ITEMS 512   // grouped items of such a plan aimed at: two rounds of the compute units
 // What a plan that chooses the form per cluster may do and has to fit.
 struct VpMixLimits {

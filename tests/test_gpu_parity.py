@@ -828,6 +828,34 @@ def test_items_at_the_lines_between_the_step_widths(oracle, d, N):
             pu.check_full(oracle, W, b, H, k, f_ids, f_logp)
 
 
+def test_all_three_forms_in_one_plan_at_the_usual_rates(oracle):
+    """At the rates that users run the planner itself masks some clusters, sends crowded ones to the many-row kernel and keeps
+    the others on the slab kernel: same results as the slabs alone and as the oracle, twice to the bit."""
+    d, V, K, N, k = 512, 60000, 300, 1500, 4
+    r, W, b, C = _small_model(17, d, V, K)
+    sizes = np.exp(r.uniform(np.log(50), np.log(15000), K)).astype(np.int64)
+    off = np.zeros(K + 1, np.int64)
+    np.cumsum(sizes, out=off[1:])
+    ids = np.concatenate([np.sort(r.choice(V, size=n, replace=False)) for n in sizes]).astype(np.int32)
+    B = Built(W, b, C, off, ids)
+    p = np.arange(1, K + 1) ** -1.3
+    q = r.choice(r.permutation(K), size=N, p=p / p.sum())
+    q[:K] = np.arange(K)
+    H = _rows(r, C, N, clusters=q)
+    base = B.project(H, k)
+    B.index.set_option("dispatch", 1)
+    got = B.project(H, k)
+    assert _planner_mode(B.index, N) == 2 and _overflow(B.index, N) == 0
+    hdr = B.index.workspace(N)[:64].view(_torch().int32).tolist()
+    assert hdr[0] > 0 and hdr[8] > 0 and hdr[12] > 0, hdr      # (items of slabs, masked, of crowded clusters)
+    again = B.project(H, k)
+    for x, y in zip(got, again):
+        assert np.array_equal(x, y)
+    assert np.array_equal(got[0], base[0]) and np.array_equal(got[2], base[2])
+    assert np.allclose(got[1], base[1], rtol=0, atol=1e-4)
+    pu.check_projection(oracle, W, b, C, off, ids, H, k, got[0], got[1], got[2])
+
+
 def test_empty_active_sets(oracle):
     """A cluster whose active set is empty (a cluster that lost its members in training): rows that fall into
     it get ids -1 and log-probs -inf in every form of the projection; the other rows are untouched."""
