@@ -37,8 +37,17 @@ MEASURED_TRAFFIC_BYTES = {
 }
 
 
-# the planner's decision (mode word of the plan header)
-FORMS = {0: "per-cluster slabs", 1: "masked full projection", 2: "some clusters masked, the others on their slabs"}
+def planned_form(ws):
+    """The planner's decision, from the plan header at the start of the workspace: (mode word, whether a plan that chooses per
+    cluster masks any, what it is called)."""
+    import torch
+    hdr = ws[:64].view(torch.int32).tolist()
+    mode, masked, grouped = hdr[7], hdr[8] > 0, hdr[12] > 0
+    if mode < 2:
+        return mode, bool(mode), ("per-cluster slabs", "masked full projection")[mode]
+    parts = (["masked"] if masked else []) + (["crowded ones' slabs on the many-row kernel"] if grouped else []) + \
+        (["slabs"] if hdr[0] > 0 else [])
+    return mode, masked, "per cluster: " + ", ".join(parts)
 
 
 def cluster_sweep(args, dev):
@@ -243,7 +252,7 @@ def measure(wk, N, k, steps, warmup, nb=16, want_full=True, oracle_rows=4, singl
         before()
     ms_step, ms_kernel, launches = timed(index, step, warmup, steps, warm_ms=warm_ms if head_warm_ms is None else head_warm_ms)
     torch.cuda.synchronize()
-    mode = int(ws[:64].view(torch.int32)[7].item())
+    mode, masked, form = planned_form(ws)
     overflow = int(ws[:64].view(torch.int32)[2].item())
     ids0, logp0, g0 = out_ids[0].cpu().numpy(), out_logp[0].cpu().numpy(), out_g[0].cpu().numpy()
     g_all = {j: out_g[j].cpu().numpy() for j in sorted({i % nb for i in range(steps)})}
@@ -263,11 +272,11 @@ def measure(wk, N, k, steps, warmup, nb=16, want_full=True, oracle_rows=4, singl
         return max(nbytes / HBM_PEAK_BYTES, flops / MFMA_PEAK_FLOPS) * 1e3
 
     res = {"workload": cfg.name, "N": N, "k": k, "rows_per_s": N / (ms_step * 1e-3), "ms_per_step": ms_step,
-           "planner_chose": FORMS[mode],
+           "planner_chose": form,
            "plan_overflow": overflow, "occupied_clusters_per_step": occupied}
     if mode == 1:
         b_ms = bound_ms(alg_full + side, flops_full + 2.0 * N * cfg.K * d)
-        res["kernel"] = {"name": "project_gemm_lds_kernel (masked)" if cfg.d <= 1024 and k <= 32 else "project_gemm_kernel (masked)",
+        res["kernel"] = {"name": "project_gemm_lds_kernel (masked)" if cfg.d <= 1536 and k <= 32 else "project_gemm_kernel (masked)",
                          "kernel_ms": ms_kernel, "algorithmic_bytes": alg_full,
                          "hbm_gbs": alg_full / (ms_kernel * 1e-3) / 1e9,
                          "hbm_frac": alg_full / (ms_kernel * 1e-3) / HBM_PEAK_BYTES,
@@ -275,12 +284,14 @@ def measure(wk, N, k, steps, warmup, nb=16, want_full=True, oracle_rows=4, singl
                          "mfma_frac": flops_full / (ms_kernel * 1e-3) / MFMA_PEAK_FLOPS,
                          "bound": "hbm" if alg_full / HBM_PEAK_BYTES >= flops_full / MFMA_PEAK_FLOPS else "mfma"}
     elif mode == 2:
-        # both kernels, one after the other; what either form needs at least is the smaller of the two byte counts
-        least = min(alg_slab, alg_full)
+        # both kernels, one after the other.  Every occupied slab is read where no cluster is masked; else the plan reads W and some of
+        # the slabs, a byte count of neither form (at least the smaller of the two), and has no rate of its own
+        least = min(alg_slab, alg_full) if masked else alg_slab
         b_ms = bound_ms(least + side, flops_slab)
-        res["kernel"] = {"name": slab_kernel_name(wk.info, k, N, True) + " + project_gemm_lds_kernel (masked clusters)",
-                         "kernel_ms": ms_kernel, "algorithmic_bytes": least, "hbm_gbs": least / (ms_kernel * 1e-3) / 1e9,
-                         "hbm_frac": least / (ms_kernel * 1e-3) / HBM_PEAK_BYTES, "bound": "hbm"}
+        gbs = None if masked else least / (ms_kernel * 1e-3) / 1e9
+        res["kernel"] = {"name": slab_kernel_name(wk.info, k, N, True) + " + project_gemm_lds_kernel (%s)" % form,
+                         "kernel_ms": ms_kernel, "algorithmic_bytes": None if masked else least, "hbm_gbs": gbs,
+                         "hbm_frac": None if masked else gbs * 1e9 / HBM_PEAK_BYTES, "bound": "hbm" if not masked else "hbm and mfma"}
     else:
         b_ms = bound_ms(alg_slab + side, flops_slab)
         res["kernel"] = {"name": slab_kernel_name(wk.info, k, N, True), "kernel_ms": ms_kernel,
@@ -456,7 +467,7 @@ def main():
     rows_per_s = N / (ms_step * 1e-3)
 
     kern = head["kernel"]
-    form = {FORMS[0]: "slabs", FORMS[1]: "masked"}.get(head["planner_chose"], "mixed")
+    form = {"per-cluster slabs": "slabs", "masked full projection": "masked"}.get(head["planner_chose"], "mixed")
     traffic, traffic_source = MEASURED_TRAFFIC_BYTES.get((args.workload, N, form), (None, "none"))
     result = {
         "metric": "projected rows/sec fp16 at V=250K,d=1024; speedup vs full-vocab projection",
@@ -473,10 +484,10 @@ def main():
             "setup_seconds": wk.setup_seconds},
         # the kernel that dominates the call as shipped
         "roofline": {"bound": kern["bound"], "kernel": kern["name"],
-                     "achieved": kern["hbm_gbs"] if kern["bound"] == "hbm" else kern["mfma_tflops"],
-                     "peak": HBM_PEAK_GBS if kern["bound"] == "hbm" else 2500.0,
-                     "unit": "GB/s" if kern["bound"] == "hbm" else "TFLOP/s",
-                     "frac": kern["hbm_frac"] if kern["bound"] == "hbm" else kern["mfma_frac"],
+                     "achieved": kern["hbm_gbs"] if kern["bound"] != "mfma" else kern["mfma_tflops"],
+                     "peak": HBM_PEAK_GBS if kern["bound"] != "mfma" else 2500.0,
+                     "unit": "GB/s" if kern["bound"] != "mfma" else "TFLOP/s",
+                     "frac": kern["hbm_frac"] if kern["bound"] != "mfma" else kern["mfma_frac"],
                      "traffic": traffic, "traffic_source": traffic_source,
                      "algorithmic_bytes_per_launch": kern["algorithmic_bytes"], "kernel_ms": kern["kernel_ms"],
                      "mfma_tflops": kern.get("mfma_tflops"), "mfma_frac": kern.get("mfma_frac")},
@@ -748,7 +759,7 @@ def decode_loop(P, wl, index, cfg, C, dev):
         return (time.perf_counter() - t0) * 1e3 / T_d, final
 
     ms_dec, final = timed_decode()
-    mode = int(wsd[:64].view(torch.int32)[7].item())
+    form = planned_form(wsd)[2]
     # the same search confined to the per-cluster slabs (log-probs agree to 1e-4 between the two forms, so the
     # two searches may part ways at a near-tie; the timing is what is compared)
     index.set_option("dispatch", 0)
@@ -756,7 +767,7 @@ def decode_loop(P, wl, index, cfg, C, dev):
     index.set_option("dispatch", 1)
     return {"sentences": S_d, "beam": B_d, "topk": k_d, "steps": T_d, "ms_per_step": ms_dec,
             "rows_per_s": n_d / (ms_dec * 1e-3),
-            "planner_chose_last_step": FORMS[mode],
+            "planner_chose_last_step": form,
             "slabs_only_ms_per_step": ms_dec_s, "slabs_only_rows_per_s": n_d / (ms_dec_s * 1e-3),
             "finished_hypotheses": int(torch.isfinite(final).sum().item()),
             "note": "vp_project + vp_beam_step + a gather of the next rows per step"}

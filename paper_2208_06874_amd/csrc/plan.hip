@@ -289,7 +289,7 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_kernel(
                     m_chunks = ceil_div(vtiles, m_tpi);
                     m_items = m_rgs * m_chunks;
                 }
-                g_tpi = max(GROUP_TILES, (ceil_div(g_tiles, VP_GROUP_ITEMS) + 3) & ~3);
+                g_tpi = max(GROUP_TILES, (ceil_div(g_tiles, VP_GROUP_ROUNDS * mix.slots) + 3) & ~3);
                 const int g_items = grouped_rows > 0 ? ceil_div(g_tiles, g_tpi) + g_units : 0;   // (at most)
                 // all item lists and their partial results have to fit the workspace, which is laid out for one
                 // form at a time: the slabs get fewer, longer items if need be

@@ -293,7 +293,7 @@ std::pair<hipEvent_t, hipEvent_t> *profile_slot(const vp_index *I)
 int single_bucket_row_tiles(const vp_index *I, int N, int k)
 {
     if (I->gemm_min_rows > 0 && N >= I->gemm_min_rows) {
-        // (the kernel that keeps the rows in LDS has room for three row tiles at d_pad = 1536)
+        // (the kernel that keeps the rows in LDS has room for three row tiles at d_pad = 1280 and 1536)
         if (I->gemm_lds && vpk_project_rows_lds_supported(I->L.kt, k)) return vpk_project_rows_lds_row_tiles(I->L.kt);
         if (vpk_project_gemm_supported(I->L.kt)) return 4;
     }
@@ -490,7 +490,7 @@ vp_status run_clustered(const char *fn, const vp_index *I, const void *hidden, i
         if (mix.slots) {
             grid_full = ceil_div(std::max(grid_full, I->gemm_lds_items), 8) * 8;
             // (the grouped items aimed at, and a partly filled one per row group of a bucket of 33 rows and more)
-            if (mix.group) grid_full += VP_GROUP_ITEMS + ceil_div(ceil_div(N, 33) + ceil_div(N, dispatch), 8) * 8;
+            if (mix.group) grid_full += ceil_div(VP_GROUP_ROUNDS * I->gemm_lds_items, 8) * 8 + ceil_div(ceil_div(N, 33) + ceil_div(N, dispatch), 8) * 8;
             mix.kt = I->L.kt;
             mix.grid = grid_full;
             mix.list = W.max_items;

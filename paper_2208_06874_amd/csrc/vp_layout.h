@@ -25,12 +25,12 @@
 #define VP_RAW_TILES 2           // slab items of at most this many tiles per wavefront keep raw logits, no top-k lists
 #define VP_XCD_BLOCK_ITEMS 32    // clustered plans with heavy buckets: consecutive items one XCD takes at a time
 
-// One unit of projection work: up to 16 rows of one bucket against a range of
-// candidate tiles of that bucket's slab.
+// One unit of projection work: some rows of one bucket (up to 16, or 32, 48 or 64 on the kernels with that many row
+// slots) against a range of candidate tiles of that bucket's slab.
 struct VpItem {
     int32_t cluster;     // slab set entry (cluster id; 0 for the full-vocabulary set, -1 where it is masked)
     int32_t perm_start;  // first position in perm[] of this item's rows
-    int32_t nrows;       // 1..16
+    int32_t nrows;       // 1 .. row slots of the kernel that takes it
     int32_t tile0;       // first candidate tile, counted within the entry's slab
     int32_t ntiles;      // candidate tiles of this item (split among the 4 wavefronts)
     int32_t shared;      // 1 if other items (further row groups of the bucket) read the same tiles
@@ -150,7 +150,7 @@ static inline __host__ __device__ int vp_rounds_item_count(int rgs, int slots, i
 // 4,096: 1,220 -> 984.  Which multiple follows from how full it leaves an XCD's last round (N = 4,096, d = 1536, 86 row
 // groups: 8, 16 and 24 ranges fill 0.90 of their rounds, 3,400 to 3,547 us, 32 fill 0.98, 3,098 us) and from the 40
 // candidate groups or so that another round of shorter items costs (18 row groups, d = 1024: 14 ranges, one round, 535 us,
-// 56 ranges 571).  Ranges of up to 64 MB are short enough to be shared (8,192 rows, V = 60,000: two 882 us, eight 924).
+// 56 ranges 571).  Long shared ranges weigh 1.5, the geometric mean of the ratios above.  Ranges of up to 64 MB are short enough to be shared (8,192 rows, V = 60,000: two 882 us, eight 924).
 static inline __host__ __device__ int vp_swept_item_count(int rgs, int slots, int vtiles, int kt, int max_items)
 {
     const int whole = vp_rounds_item_count(rgs, slots, vtiles);
@@ -321,7 +321,7 @@ static inline __host__ __device__ float vp_grouping_saves(int N, int rpi, float 
            (float)((N + rpi - 1) / rpi) * tiles / (cost.bw_gemm * VP_MIX_GEMM) * vp_lists_factor(k);
 }
 
-#define VP_GROUP_ITEMS 512   // grouped items of such a plan aimed at: two rounds of the compute units
+#define VP_GROUP_ROUNDS 2   // grouped items of such a plan aimed at: rounds of the many-row kernel's workgroups
 // What a plan that chooses the form per cluster may do and has to fit.
 struct VpMixLimits {
     int32_t mask;         // some of the clusters may be masked
@@ -381,7 +381,8 @@ struct VpKmPass {
     int32_t *events, *cursor;   // [K]
     int32_t *prev;          // [n] the cluster in the pass before
     int32_t *rank, *rank_old;   // [n] numbers of the counting atomics (null: not kept)
-    float *best;            // [n] score of the vector's cluster (rows-in-LDS kernel)
+    float *best;            // [n] score of the vector's cluster: left by every pass of the GEMM-shaped kernels, read by passes over
+                            //     the changed centroids only
     const int32_t *order;   // [n] vectors in the order of their first clusters
     int32_t *parted;        // [n] those whose own centroids changed in front
     int32_t *was_split;     // [K] the last split moved the centroid (null: empty clusters are left alone)
