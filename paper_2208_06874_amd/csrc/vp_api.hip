@@ -719,8 +719,8 @@ vp_status vp_build(const vp_build_desc *D, void *hip_stream, vp_index **out)
     I->cost.bw_gemm_split = 8.0e12f;
     I->cost.t_row_slab = 60.0e-9f;
     // batch-union form: the gather of U's columns from the token-major copy into the union slab
-    // (fitted to the measured crossover at |U| = 28 % of V for 64 rows) and the kernels only the
-    // gathered form needs
+    // (fitted to the measured crossover at |U| = 28 % of V for 64 rows) and the kernels only that
+    // form needs; vp_project_union has other figures where the columns are read in place
     I->cost.bw_gather = 2.4e12f;
     I->cost.t_gather = 12.0e-6f;
     I->union_dispatch = 1;
@@ -1012,6 +1012,17 @@ vp_status vp_project_union(const vp_index *I, const void *hidden, int32_t N, int
     if (row_tiles_u >= 3 && !use_gemm_lds(I, row_tiles_u, k)) cost.bw_gemm = cost.bw_gemm_split;
     cost.bw_gemm /= tile_bytes;
     cost.bw_gather /= tile_bytes;
+    // (the many-row kernel reads the columns of U where they lie)
+    const bool fused_gather = use_gemm_lds(I, row_tiles_u, k) && (long)I->V * I->L.kt * 4 < (1L << 31);
+    if (fused_gather) {
+        // No kernels that only the gather needs, and columns at twice the rate of the gather kernel, which writes
+        // them as well.  800 calls at d = 512 to 1536, V = 10,000 to 250,000, |U| = 2 to 95 % of V, each timed either
+        // way: with the gather kernel's figures 1.048 times the faster form's time, 201 calls more than 10 % behind
+        // it (96 rows, 1,150 of 40,000 tokens, d = 768: 47 us over the whole vocabulary, 32 gathered), with these
+        // 1.009 and 23.
+        cost.t_gather = 0.f;
+        cost.bw_gather *= 2.1f;
+    }
     if (allow_full) {
         // the in-place form cannot win if the gathered form is cheaper even for the largest union this
         // batch can have (every row in a cluster of its own with the longest list): then it is not launched
@@ -1029,7 +1040,6 @@ vp_status vp_project_union(const vp_index *I, const void *hidden, int32_t N, int
     // the items of the rows-in-LDS kernel the columns of U are read where they lie, through U,
     // from the token-major copy of W (the bias of U's tokens was collected with U); otherwise they
     // are first gathered into a packed slab in the workspace.
-    const bool fused_gather = use_gemm_lds(I, row_tiles_u, k) && (long)I->V * I->L.kt * 4 < (1L << 31);
     VpSlabSet uset = I->full;
     uset.bias = ubias;
     uset.ids = uids;

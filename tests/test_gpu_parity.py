@@ -1085,6 +1085,23 @@ def test_union_form_either_way(oracle, tiny, mid):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("d, V", [(768, 20000), (1280, 12000)])
+def test_union_form_where_the_columns_are_read_in_place(oracle, d, V):
+    """The many-row kernel reads a small union's columns where they lie, in less time than one pass over a W of
+    20,000 tokens: such a union is gathered, and one of most of the vocabulary is not."""
+    r, W, b, C = _small_model(d, d, V, 8)
+    for lo, hi, mode in ((40, 120, 0), (V // 3, V // 2, 1)):
+        off, ids = _random_lists(r, 8, V, lo, hi)
+        B = Built(W, b, C, off, ids, k_max=4)
+        for N, k in ((17, 1), (65, 4)):
+            H = _rows(r, C, N)
+            print("union form: d", d, "V", V, "lists up to", hi, "N", N, "k", k, flush=True)
+            got = B.project_union(H, k)
+            assert _union_mode(B.index) == mode
+            pu.check_union(oracle, W, b, C, off, ids, H, k, got[0], got[1], got[2], got[3])
+
+
+@pytest.mark.gpu
 def test_union_form_over_a_long_boolean_list(oracle):
     """More than 262,144 tokens: the boolean list spans many blocks of the three-step scan.  Gathered and
     in-place forms against the oracle."""
