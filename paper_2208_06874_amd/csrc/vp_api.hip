@@ -1016,7 +1016,7 @@ vp_status vp_project_union(const vp_index *I, const void *hidden, int32_t N, int
     const bool fused_gather = use_gemm_lds(I, row_tiles_u, k) && (long)I->V * I->L.kt * 4 < (1L << 31);
     if (fused_gather) {
         // No kernels that only the gather needs, and columns at twice the rate of the gather kernel, which writes
-        // them as well.  800 calls at d = 512 to 1536, V = 10,000 to 250,000, |U| = 2 to 95 % of V, each timed either
+        // them as well.  800 calls at d = 512 to 1536, V = 10,000 to 250,000, |U| = 1 to 84 % of V, each timed either
         // way: with the gather kernel's figures 1.048 times the faster form's time, 201 calls more than 10 % behind
         // it (96 rows, 1,150 of 40,000 tokens, d = 768: 47 us over the whole vocabulary, 32 gathered), with these
         // 1.009 and 23.
