@@ -365,6 +365,8 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_kernel(
         const int p = off[j] + local;
         perm[p] = r;
         floors[r] = VP_FLOOR_NONE;   // no lower bound of the row's k-th best logit known yet
+        if (form[j] != ON_SLAB)
+            for (int s = 0; s < VP_BOUND_SETS; ++s) floors[N + r * VP_BOUND_SETS + s] = VP_FLOOR_NONE;
         VpRowPlan rp;
         rp.row = r;
         rp.cluster = j;

@@ -30,6 +30,16 @@
 // it (nor below the bound the workgroups that hold the same rows trade through global memory),
 // best first, re-reading the bound after every insertion - so even the first step, which finds
 // the list empty, costs a lane one or two insertions rather than sixteen.
+//
+// Where a row's candidates are spread over many items (and 3 <= k <= 8) the lists' upkeep is bound by how late the items learn of each
+// other: each starts with an empty list, and 64 of them insert 57 entries a row where one behind the other would need two.  So
+// behind the first step's MFMAs, before anything is inserted, the workgroups trade the best logits seen of eight sets that the row's
+// candidates fall into (by lane quarter and the wavefront's parity): the k-th largest of the eight cannot be above the row's k-th
+// best, and 64 items know it of 32,768 candidates at once.  It costs one wait for memory per item; after steps 1, 2 and 4 the
+// sets are traded again without waiting, later on the k-th bests as elsewhere.  Full projection, V = 250,000, d = 1024, top-8, us per
+// call before -> with it (256 to 32 items a row): 64 rows 112 -> 103, 128: 134 -> 122, 256: 182 -> 170, 333: 239 -> 224,
+// 512: 286 -> 274; top-3 within 2 %.  With fewer items a row (from 1,024 rows on) there is little to learn: top-3 1 % slower.
+// Keeping the candidates in an unsorted queue instead of the cascade: 5 to 20 % slower (registers, and the queue's overflow).
 #include <hip/hip_runtime.h>
 #include <type_traits>
 #include "vp_kernels.h"
@@ -60,7 +70,29 @@ __device__ constexpr int brief_to(bool shared, int k)
     if (shared) return k > 2 ? 12 : L_NW;
     return KT > 32 ? 2 * L_NW - 1 : KT >= 24 ? 4 * L_NW - 1 : L_NW;
 }
+constexpr int SET_ITEMS = 24;
+__host__ __device__ constexpr bool trades_sets(int k) { return k >= 3 && k <= VP_BOUND_SETS; }
 constexpr int VP_MAX_TOPK_LANES = 32;   // the epilogue writes a row's list with one lane per entry
+
+// The k-th largest of a row's eight keys (k = 1 .. 8; a sorting network of 19 compare-exchanges).
+__device__ inline unsigned int kth_of_sets(const unsigned int *set, int k)
+{
+    unsigned int v[VP_BOUND_SETS];
+#pragma unroll
+    for (int j = 0; j < VP_BOUND_SETS; ++j) v[j] = __hip_atomic_load(set + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    constexpr int pair[19][2] = {{0, 1}, {2, 3}, {4, 5}, {6, 7}, {0, 2}, {1, 3}, {4, 6}, {5, 7}, {1, 2}, {5, 6},
+                                 {0, 4}, {1, 5}, {2, 6}, {3, 7}, {2, 4}, {3, 5}, {1, 2}, {3, 4}, {5, 6}};
+#pragma unroll
+    for (int p = 0; p < 19; ++p) {
+        const unsigned int a = v[pair[p][0]], b = v[pair[p][1]];
+        v[pair[p][0]] = max(a, b);
+        v[pair[p][1]] = min(a, b);
+    }
+    unsigned int r = v[0];
+#pragma unroll
+    for (int j = 1; j < VP_BOUND_SETS; ++j) r = j < k ? v[j] : r;
+    return r;
+}
 
 // (logit descending, position ascending), without branches
 __device__ inline bool before_entry(float v, int i, float v2, int i2) { return (v > v2) | ((v == v2) & (i < i2)); }
@@ -69,7 +101,8 @@ template <int KT, int L_G, bool MASKED, bool NT, bool TOP1, bool GATHER>
 __device__ inline void gemm_lds_item(const VpSlabSet &set, const uint4 *__restrict__ hidden, int d,
                                      const VpItem &item, int it, int k,
                                      float *__restrict__ partials, unsigned int *__restrict__ floors,
-                                     const VpMaskInfo &mask, const int32_t *__restrict__ perm)
+                                     unsigned int *__restrict__ bounds, const VpMaskInfo &mask,
+                                     const int32_t *__restrict__ perm)
 {
     constexpr int L_RT = lds_row_tiles(KT);
     constexpr int L_ROWS = 16 * L_RT;
@@ -85,6 +118,7 @@ __device__ inline void gemm_lds_item(const VpSlabSet &set, const uint4 *__restri
     uint4 *ldsB = lds;                                                          // [L_RT][KT][64]: the rows
     unsigned long long *lkey = reinterpret_cast<unsigned long long *>(lds + L_RT * KT * 64);   // [k][64]: the rows' lists
     unsigned int *wg_floor = reinterpret_cast<unsigned int *>(lkey + k * L_ROWS);               // [64]
+    unsigned int *set_best = wg_floor + L_ROWS;                                                 // [64][VP_BOUND_SETS] (trades_sets)
     // after the loop, in place of the rows:
     float *hdr_m = reinterpret_cast<float *>(lds);                              // [L_NW][64]
     float *hdr_s = hdr_m + L_NW * L_ROWS;
@@ -181,6 +215,10 @@ __device__ inline void gemm_lds_item(const VpSlabSet &set, const uint4 *__restri
     if (tid < L_ROWS)
         wg_floor[tid] = !TOP1 && tid < item.nrows ? floors[MASKED && perm ? perm[item.perm_start + tid] : item.perm_start + tid]
                                                   : VP_FLOOR_NONE;
+    // the sets' bests are traded where the row has at least SET_ITEMS items (top of the file)
+    const bool sets = !TOP1 && L_G == 4 && trades_sets(k) && (long long)item.ntiles * (VP_TILE_ITEMS * SET_ITEMS) <= ncand;
+    if (sets)
+        for (int e = tid; e < L_ROWS * VP_BOUND_SETS; e += L_NW * 64) set_best[e] = VP_FLOOR_NONE;
     __syncthreads();
 
     // per row tile: running maximum, sum of exponentials, k-th best of this wavefront's list
@@ -197,9 +235,28 @@ __device__ inline void gemm_lds_item(const VpSlabSet &set, const uint4 *__restri
         moff[rt] = masked ? (unsigned int)(row_valid[rt] ? mask.g[myrow[rt]] : 0) * (unsigned int)mask.words : 0u;
     }
     constexpr bool top1 = TOP1;   // k == 1: the best entry stays in registers, no list traffic in the loop
-    unsigned int pending[L_RT];
+    unsigned int pending = 0;
     int pending_rt = -1;
     int done_steps = 0;
+    const int my_set = q + 4 * (wave & 1);   // (a candidate is one lane's: every candidate is in one set)
+    // this thread trades set tid % 8 of row slot tid / 8; its wavefront's eight rows then get their bounds anew
+    unsigned int pending_set = VP_FLOOR_NONE;
+    int slot_row = -1;
+    bool asked = false;
+    if (sets && tid / VP_BOUND_SETS < item.nrows)
+        slot_row = MASKED && perm ? perm[item.perm_start + tid / VP_BOUND_SETS] : item.perm_start + tid / VP_BOUND_SETS;
+    auto take_bests = [&]() {
+        if (slot_row >= 0) atomicMax(set_best + tid, pending_set);
+        wave_lds_fence();
+        if (lane < 8 && wave * 8 + lane < item.nrows) atomicMax(wg_floor + wave * 8 + lane, kth_of_sets(set_best + (wave * 8 + lane) * VP_BOUND_SETS, k));
+    };
+    // behind a wavefront's first step (those without one: at the end), once by each of the eight
+    auto trade_first_bests = [&]() {
+        __syncthreads();
+        if (slot_row >= 0) pending_set = atomicMax(bounds + (size_t)slot_row * VP_BOUND_SETS + (tid & (VP_BOUND_SETS - 1)), set_best[tid]);
+        take_bests();
+        __syncthreads();
+    };
 
     uint4 bnext[L_RT];   // the rows' operands of the k-tile to come
 #pragma unroll
@@ -275,18 +332,19 @@ __device__ inline void gemm_lds_item(const VpSlabSet &set, const uint4 *__restri
         // fold the 16 logits of each of this lane's four rows
         const int c_first = g0 * VP_TILE_ITEMS + q * 4;           // position of z[0] (j = 0, i = 0) in the slab
         const bool ragged = (g0 + L_G) * VP_TILE_ITEMS > ncand || g0 + L_G > ge;   // (wavefront-uniform)
+        if (asked) take_bests();   // (asked for a step ago)
+        asked = false;
         if (pending_rt >= 0) {
             // bounds read from the other workgroups a step ago
 #pragma unroll
             for (int rt = 0; rt < L_RT; ++rt)
-                if (rt == pending_rt && q == 0 && row_valid[rt]) atomicMax(wg_floor + rt * 16 + n, pending[rt]);
+                if (rt == pending_rt && q == 0 && row_valid[rt]) atomicMax(wg_floor + rt * 16 + n, pending);
             pending_rt = -1;
         }
         // (written per row tile with the tile's number a compile-time constant: the accumulators
         // and the per-tile state must stay in registers)
-        auto fold_row_tile = [&](auto rt_const) {
+        auto logits_of = [&](auto rt_const, float (&z)[L_G * 4]) {
             constexpr int rt = decltype(rt_const)::value;
-            float z[L_G * 4];
 #pragma unroll
             for (int j = 0; j < L_G; ++j) {
                 z[j * 4 + 0] = acc[rt][j][0] + bz[j].x;
@@ -314,6 +372,30 @@ __device__ inline void gemm_lds_item(const VpSlabSet &set, const uint4 *__restri
                     }
                 }
             }
+        };
+        if (sets && done_steps == 0) {   // (one row tile at a time: four at once spill)
+            auto best_of = [&](auto rt_const) {
+                constexpr int rt = decltype(rt_const)::value;
+                float z[L_G * 4];
+                logits_of(rt_const, z);
+                float tmax = z[0];
+#pragma unroll
+                for (int e = 1; e < L_G * 4; ++e) tmax = fmaxf(tmax, z[e]);
+                if (row_valid[rt] & (tmax > -__builtin_inff())) atomicMax(set_best + (rt * 16 + n) * VP_BOUND_SETS + my_set, float_key(tmax));
+            };
+            best_of(std::integral_constant<int, 0>{});
+            __builtin_amdgcn_sched_barrier(0);
+            best_of(std::integral_constant<int, 1>{});
+            __builtin_amdgcn_sched_barrier(0);
+            best_of(std::integral_constant<int, 2>{});
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (L_RT > 3) best_of(std::integral_constant<int, 3>{});
+            trade_first_bests();
+        }
+        auto fold_row_tile = [&](auto rt_const) {
+            constexpr int rt = decltype(rt_const)::value;
+            float z[L_G * 4];
+            logits_of(rt_const, z);
             float tmax = z[0];
 #pragma unroll
             for (int e = 1; e < L_G * 4; ++e) tmax = fmaxf(tmax, z[e]);
@@ -380,7 +462,14 @@ __device__ inline void gemm_lds_item(const VpSlabSet &set, const uint4 *__restri
         // workgroups that project the same rows onto other candidate ranges (one atomicMax
         // publishes ours and returns theirs, folded into the LDS copy a step later: no wait here)
         ++done_steps;
-        if (!top1 && (done_steps & 1) == 0) {
+        if (sets) asked = done_steps == 1 || done_steps == 2 || done_steps == 4;
+        if (asked) {
+#pragma unroll
+            for (int rt = 0; rt < L_RT; ++rt)
+                if (row_valid[rt] & (m_run[rt] > VP_NEG_BIG)) atomicMax(set_best + (rt * 16 + n) * VP_BOUND_SETS + my_set, float_key(m_run[rt]));
+            wave_lds_fence();
+            if (slot_row >= 0) pending_set = atomicMax(bounds + (size_t)slot_row * VP_BOUND_SETS + (tid & (VP_BOUND_SETS - 1)), set_best[tid]);
+        } else if (!top1 && (done_steps & 1) == 0) {
             const int rt_x = ((done_steps >> 1) + wave) % L_RT;
 #pragma unroll
             for (int rt = 0; rt < L_RT; ++rt)
@@ -390,7 +479,7 @@ __device__ inline void gemm_lds_item(const VpSlabSet &set, const uint4 *__restri
                     const unsigned int mine = max((unsigned int)(kth >> 32),
                                                   __hip_atomic_load(wg_floor + rt * 16 + n, __ATOMIC_RELAXED,
                                                                     __HIP_MEMORY_SCOPE_WORKGROUP));
-                    pending[rt] = atomicMax(floors + myrow[rt], max(mine, (unsigned int)VP_FLOOR_NONE));
+                    pending = atomicMax(floors + myrow[rt], max(mine, (unsigned int)VP_FLOOR_NONE));
                 }
             pending_rt = rt_x;
         }
@@ -398,6 +487,8 @@ __device__ inline void gemm_lds_item(const VpSlabSet &set, const uint4 *__restri
         for (int j = 0; j < L_G; ++j) cur[j] = nxt[j];
         step = next_step;
     }
+
+    if (sets && !active) trade_first_bests();   // (the others were there behind their first steps)
 
     // the row's four lanes (one per quarter of every group) -> one (m, s); top-1: one entry
 #pragma unroll
@@ -463,8 +554,8 @@ template <int KT, bool MASKED, bool TOP1, bool GATHER>
 __global__ __launch_bounds__(L_NW * 64) void project_gemm_lds_kernel(
     VpSlabSet set, const uint4 *__restrict__ hidden, int d,
     const VpItem *__restrict__ items, const VpPlanHeader *__restrict__ hdr, int k,
-    float *__restrict__ partials, unsigned int *__restrict__ floors, VpMaskInfo mask, const int32_t *__restrict__ perm,
-    VpSlabSet slabs)
+    float *__restrict__ partials, unsigned int *__restrict__ floors, unsigned int *__restrict__ bounds, VpMaskInfo mask,
+    const int32_t *__restrict__ perm, VpSlabSet slabs)
 {
     if (MASKED ? hdr->mode == 0 : hdr->mode != 0) return;   // the planner chose the other form
     const int total_items = MASKED ? hdr->masked_items : hdr->total_items;
@@ -492,27 +583,27 @@ __global__ __launch_bounds__(L_NW * 64) void project_gemm_lds_kernel(
     const int kk = TOP1 ? 1 : k;
     const bool brief = item.ntiles <= brief_to<KT, TOP1>(item.shared, k);
     if (item.shared || GATHER) {
-        if (brief) gemm_lds_item<KT, 1, MASKED, false, TOP1, GATHER>(set, hidden, d, item, it, kk, partials, floors, mask, perm);
-        else gemm_lds_item<KT, 4, MASKED, false, TOP1, GATHER>(set, hidden, d, item, it, kk, partials, floors, mask, perm);
+        if (brief) gemm_lds_item<KT, 1, MASKED, false, TOP1, GATHER>(set, hidden, d, item, it, kk, partials, floors, bounds, mask, perm);
+        else gemm_lds_item<KT, 4, MASKED, false, TOP1, GATHER>(set, hidden, d, item, it, kk, partials, floors, bounds, mask, perm);
     } else {
-        if (brief) gemm_lds_item<KT, 1, MASKED, true, TOP1, false>(set, hidden, d, item, it, kk, partials, floors, mask, perm);
-        else gemm_lds_item<KT, 4, MASKED, true, TOP1, false>(set, hidden, d, item, it, kk, partials, floors, mask, perm);
+        if (brief) gemm_lds_item<KT, 1, MASKED, true, TOP1, false>(set, hidden, d, item, it, kk, partials, floors, bounds, mask, perm);
+        else gemm_lds_item<KT, 4, MASKED, true, TOP1, false>(set, hidden, d, item, it, kk, partials, floors, bounds, mask, perm);
     }
 }
 
 template <int KT, bool MASKED, bool GATHER>
 void launch_lds(const VpSlabSet &set, const void *hidden, int d, const VpItem *items,
                 const VpPlanHeader *hdr, int grid_items, int k, float *partials, unsigned int *floors,
-                const VpMaskInfo &mask, const int32_t *perm, const VpSlabSet &slabs, hipStream_t st)
+                unsigned int *bounds, const VpMaskInfo &mask, const int32_t *perm, const VpSlabSet &slabs, hipStream_t st)
 {
     if (k == 1)
         hipLaunchKernelGGL((project_gemm_lds_kernel<KT, MASKED, true, GATHER>), dim3(grid_items), dim3(L_NW * 64),
                            vpk_project_rows_lds_bytes(k, KT), st, set, (const uint4 *)hidden, d, items, hdr, k,
-                           partials, floors, mask, perm, slabs);
+                           partials, floors, bounds, mask, perm, slabs);
     else
         hipLaunchKernelGGL((project_gemm_lds_kernel<KT, MASKED, false, GATHER>), dim3(grid_items), dim3(L_NW * 64),
                            vpk_project_rows_lds_bytes(k, KT), st, set, (const uint4 *)hidden, d, items, hdr, k,
-                           partials, floors, mask, perm, slabs);
+                           partials, floors, bounds, mask, perm, slabs);
 }
 
 template <int KT>
@@ -536,7 +627,8 @@ hipError_t allow_lds_bytes()
 size_t vpk_project_rows_lds_bytes(int k, int kt)
 {
     const int rows = 16 * lds_row_tiles(kt);
-    return (size_t)rows * kt * (VP_TILE_BYTES / 16) + (size_t)k * rows * 8 + rows * 4;
+    return (size_t)rows * kt * (VP_TILE_BYTES / 16) + (size_t)k * rows * 8 + rows * 4 +
+           (trades_sets(k) ? (size_t)rows * VP_BOUND_SETS * 4 : 0);
 }
 
 // Built for d_pad = 256 to 1536 (beyond, the rows of an item do not fit the LDS beside its lists).  The alternative at 768
@@ -567,14 +659,14 @@ hipError_t vpk_project_rows_lds_prepare()
 // chooses the form per cluster: a single-bucket plan keeps the rows in their own order.
 void vpk_project_rows_lds(const VpSlabSet &set, const void *hidden, int d, const int32_t *perm, const VpItem *items,
                           const VpPlanHeader *hdr, int grid_items, int k, float *partials, unsigned int *floors,
-                          const VpMaskInfo *mask, const VpSlabSet *slabs, bool gather, hipStream_t st)
+                          unsigned int *bounds, const VpMaskInfo *mask, const VpSlabSet *slabs, bool gather, hipStream_t st)
 {
     const VpMaskInfo none = {nullptr, nullptr, 0};
 #define VP_LDS_CASE(KT)                                                                                                   \
     case KT:                                                                                                              \
-        if (mask) launch_lds<KT, true, false>(set, hidden, d, items, hdr, grid_items, k, partials, floors, *mask, perm, slabs ? *slabs : set, st); \
-        else if (gather) launch_lds<KT, false, true>(set, hidden, d, items, hdr, grid_items, k, partials, floors, none, nullptr, set, st); \
-        else launch_lds<KT, false, false>(set, hidden, d, items, hdr, grid_items, k, partials, floors, none, nullptr, set, st); \
+        if (mask) launch_lds<KT, true, false>(set, hidden, d, items, hdr, grid_items, k, partials, floors, bounds, *mask, perm, slabs ? *slabs : set, st); \
+        else if (gather) launch_lds<KT, false, true>(set, hidden, d, items, hdr, grid_items, k, partials, floors, bounds, none, nullptr, set, st); \
+        else launch_lds<KT, false, false>(set, hidden, d, items, hdr, grid_items, k, partials, floors, bounds, none, nullptr, set, st); \
         break;
     switch (set.kt) {
         VP_LDS_CASE(8)

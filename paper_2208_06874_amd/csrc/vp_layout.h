@@ -19,7 +19,7 @@
 #define VP_WG_THREADS 256      // projection kernel: 4 wavefronts per workgroup
 #define VP_WG_WAVES 4
 #define VP_ROWS_PER_ITEM 16    // rows one work item projects (one MFMA row tile)
-#define VP_BOUND_SETS 8          // per row: candidate-range sets whose best logits bound the k-th best (GEMM kernel)
+#define VP_BOUND_SETS 8          // per row: sets of its candidates whose best logits bound the k-th best (GEMM-shaped kernels)
 #define VP_MAX_ROWS_PER_ITEM 64  // four row tiles: the GEMM-shaped kernel of single-bucket projections
 #define VP_GEMV_MAX_ROWS 4
 #define VP_RAW_TILES 2           // slab items of at most this many tiles per wavefront keep raw logits, no top-k lists

@@ -1350,3 +1350,38 @@ def test_index_without_the_token_major_copy(oracle):
     with pytest.raises(vp.VpError) as e:
         lean.project_union(Ht, 4)
     assert e.value.status == vp.VP_ERR_UNSUPPORTED and "NO_UNION" in str(e.value)
+
+
+@pytest.mark.parametrize("d,N", [(256, 64), (1024, 17), (1024, 65), (1536, 49)])
+def test_bests_of_sets_traded_between_many_items(oracle, d, N):
+    """Rows whose candidates are spread over many items (24 and more trade the bests of eight sets of candidates, fewer do not;
+    top-3 to top-8 only): equal logits in every set and item, a row with a few candidates only, a last item in which
+    wavefronts have no step, plain and masked, twice to the bit."""
+    V = 16 * 36 * 26 - 16 * 23 - 5          # items of 36 groups: 26 (the last: 12 groups and a piece) and, with 8 wanted, 8
+    r, W, b, C = _small_model(70 + d + N, d, V, 3)
+    W[:, ::3] = W[:, :1]                     # a third of the vocabulary ties, whatever the row
+    b[::3] = b[0]
+    off, ids = _random_lists(r, 3, V, 2, 9)
+    full = np.sort(r.choice(V, size=V // 2, replace=False)).astype(np.int32)
+    ids = np.concatenate([full, ids[off[1]:]]).astype(np.int32)
+    off = np.concatenate([[0], off[1:] - off[1] + len(full)]).astype(np.int64)
+    B = Built(W, b, C, off, ids, k_max=9)
+    rgs = (N + (64 if d <= 1024 else 48) - 1) // (64 if d <= 1024 else 48)
+    H = _rows(r, C, N)
+    for wanted in (26 * rgs, 8):
+        B.index.set_option("gemm_lds_items", wanted)
+        for k in (2, 3, 8, 9):
+            got = B.project_full(H, k)
+            again = B.project_full(H, k)
+            for x, y in zip(got, again):
+                assert np.array_equal(x, y)
+            pu.check_full(oracle, W, b, H, k, *got)
+            B.index.set_option("dispatch", 1)
+            B.index.set_option("cost_bw_slab_gbs", 1)      # force the masked projection
+            try:
+                got = B.project(H, k)
+                assert _planner_mode(B.index, N) == 1
+            finally:
+                B.index.set_option("cost_bw_slab_gbs", 6800)
+                B.index.set_option("dispatch", 0)
+            pu.check_projection(oracle, W, b, C, off, ids, H, k, *got)
