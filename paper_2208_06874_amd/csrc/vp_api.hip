@@ -347,8 +347,8 @@ void launch_single_bucket(const VpSlabSet &set, const vp_index *I, const void *h
 
 // Eq. 2 for a decode batch: up to VP_KSPLIT_ROWS rows with one workgroup per (centroid tile, row
 // tile) and the k-extent split over its wavefronts (every load in flight at once: 4.6 us instead
-// of 9.3 at 64 rows; at 256 rows its thousand small workgroups take 9.2 us against 7-8), beyond
-// that the kernel whose workgroups walk several centroid tiles.  Returns the number of per-row
+// of 9.3 at 64 rows; at 256 rows its thousand small workgroups take 9.2 us against 6.7), beyond
+// that the kernel whose wavefronts take several centroid tiles at a time (vp_centroid_tiles_per_wave).  Returns the number of per-row
 // minima left in cpart.
 constexpr int VP_KSPLIT_ROWS = 64;
 int launch_eq2(const vp_index *I, const void *hidden, int N, void *cpart, hipStream_t st)
@@ -357,10 +357,8 @@ int launch_eq2(const vp_index *I, const void *hidden, int N, void *cpart, hipStr
         vpk_centroid_small(hidden, N, I->d, I->cp, I->cnorm, I->K, I->L.kt, I->L.ctiles, cpart, st);
         return I->L.ctiles;
     }
-    const int row_tiles = ceil_div(N, 16);
-    int parts = std::min(ceil_div(I->L.ctiles, 4), std::max(1, 2048 / (4 * row_tiles)));
-    const int tpw_c = ceil_div(I->L.ctiles, parts * 4);
-    parts = ceil_div(I->L.ctiles, tpw_c * 4);
+    const int tpw_c = vp_centroid_tiles_per_wave(ceil_div(N, 16), I->L.ctiles);
+    const int parts = ceil_div(I->L.ctiles, 4 * tpw_c);
     vpk_centroid(hidden, N, I->d, I->cp, I->cnorm, I->K, I->L.kt, I->L.ctiles, tpw_c, parts, cpart, nullptr, st);
     return parts;
 }

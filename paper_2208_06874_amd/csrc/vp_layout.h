@@ -333,6 +333,34 @@ struct VpMixLimits {
     int64_t row_slots;    // row slots of the partial results
 };
 
+// Eq. 2 for many rows: how many centroid tiles a wavefront takes at a time (centroid_kernel), and whether it takes two row tiles.
+// A round of 256 workgroups of a form takes, d = 1024 (U = k-tiles fetched together): 1 row tile x 1 centroid tile 6.7 us, x 2 7.6,
+// x 4 9.7, x 8 14.4; 2 x 4 13.7, 2 x 8 18.5 (4 x 4 22.3, never the best); more workgroups take in proportion longer, fewer no
+// shorter.  So the form whose workgroups x time is least: 1,000 centroids, d = 1024, us before (1 x 1 throughout) -> with it:
+// 256 rows 6.9 -> 6.7, 512: 11.4 -> 7.7, 1,024: 20.3 -> 10.2, 2,048: 37.4 -> 14.2, 4,096: 71.0 -> 20.3; 500 centroids, d = 1536,
+// 4,096 rows: 54.2 -> 19.4; 1,300 centroids, d = 1000, 333 rows: 8.2 -> 6.4.
+static inline int vp_centroid_two_row_tiles(int row_tiles, int parts, int tiles_per_wave)
+{
+    return tiles_per_wave >= 4 && (long long)((row_tiles + 1) / 2) * parts >= (tiles_per_wave >= 8 ? 200 : 180);
+}
+static inline int vp_centroid_tiles_per_wave(int row_tiles, int ctiles)
+{
+    int best = 1;
+    float least = 0.f;
+    for (int ct = 1; ct <= 8; ct *= 2) {
+        const int parts = (ctiles + 4 * ct - 1) / (4 * ct);
+        const bool two = vp_centroid_two_row_tiles(row_tiles, parts, ct);
+        const float t = ct == 1 ? 6.7f : ct == 2 ? 7.6f : ct == 4 ? (two ? 13.7f : 9.7f) : two ? 18.5f : 14.4f;
+        const float wgs = (float)((row_tiles + two) / (1 + two)) * parts;
+        const float cost = t * (wgs > 256.f ? wgs * (1.f / 256.f) : 1.f);
+        if (ct == 1 || cost < least) {
+            least = cost;
+            best = ct;
+        }
+    }
+    return best;
+}
+
 #define VP_SMALL_ROWS 16   // batches up to this size are planned by the projection workgroups themselves
 
 // What a workgroup of the small-batch projection needs to find its own work (project.hip).

@@ -1385,3 +1385,19 @@ def test_bests_of_sets_traded_between_many_items(oracle, d, N):
                 B.index.set_option("cost_bw_slab_gbs", 6800)
                 B.index.set_option("dispatch", 0)
             pu.check_projection(oracle, W, b, C, off, ids, H, k, *got)
+
+
+@pytest.mark.parametrize("N,K", [(65, 40), (256, 1300), (333, 1990), (769, 1990), (2047, 2000)])
+def test_every_form_of_the_many_row_eq2_kernel(oracle, N, K):
+    """One or two row tiles x one to eight centroid tiles per wavefront, by how many workgroups each leaves: a last row tile
+    and a last centroid tile that are not full, duplicate centroids (ties to the lowest), a width that ends inside a
+    k-tile."""
+    d, V = 264, 300
+    r, W, b, C = _small_model(90 + N, d, V, K)
+    C[K // 2:K // 2 + 9] = C[3]
+    off, ids = _random_lists(r, K, V, 4, 12)
+    B = Built(W, b, C, off, ids)
+    H = _rows(r, C, N, clusters=np.concatenate([np.full(20, 3), r.integers(0, K, N - 20)]))
+    got = B.project(H, 2)
+    assert (got[2][:20] == 3).all()
+    pu.check_projection(oracle, W, b, C, off, ids, H, 2, *got)
