@@ -39,6 +39,7 @@
 // sets are traded again without waiting, later on the k-th bests as elsewhere.  Full projection, V = 250,000, d = 1024, top-8, us per
 // call before -> with it (256 to 32 items a row): 64 rows 112 -> 103, 128: 134 -> 122, 256: 182 -> 170, 333: 239 -> 224,
 // 512: 286 -> 274; top-3 within 2 %.  With fewer items a row (from 1,024 rows on) there is little to learn: top-3 1 % slower.
+// (Not where the columns are gathered: two rows of 20 sentences, short items, 1 % slower for the registers it takes.)
 // Keeping the candidates in an unsorted queue instead of the cascade: 5 to 20 % slower (registers, and the queue's overflow).
 #include <hip/hip_runtime.h>
 #include <type_traits>
@@ -216,7 +217,7 @@ __device__ inline void gemm_lds_item(const VpSlabSet &set, const uint4 *__restri
         wg_floor[tid] = !TOP1 && tid < item.nrows ? floors[MASKED && perm ? perm[item.perm_start + tid] : item.perm_start + tid]
                                                   : VP_FLOOR_NONE;
     // the sets' bests are traded where the row has at least SET_ITEMS items (top of the file)
-    const bool sets = !TOP1 && L_G == 4 && trades_sets(k) && (long long)item.ntiles * (VP_TILE_ITEMS * SET_ITEMS) <= ncand;
+    const bool sets = !TOP1 && !GATHER && L_G == 4 && trades_sets(k) && (long long)item.ntiles * (VP_TILE_ITEMS * SET_ITEMS) <= ncand;
     if (sets)
         for (int e = tid; e < L_ROWS * VP_BOUND_SETS; e += L_NW * 64) set_best[e] = VP_FLOOR_NONE;
     __syncthreads();

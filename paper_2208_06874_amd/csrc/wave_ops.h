@@ -89,6 +89,33 @@ __device__ inline float wave_sum_float(float v)
 }
 #undef VP_DPP_ADD
 
+// Largest float and smallest int over the wavefront, to every lane.
+#define VP_DPP_MAX(ctrl, rows) \
+    v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), ctrl, rows, 0xf, false)));
+__device__ inline float wave_max_float(float v)
+{
+    VP_DPP_MAX(0x111, 0xf)
+    VP_DPP_MAX(0x112, 0xf)
+    VP_DPP_MAX(0x114, 0xf)
+    VP_DPP_MAX(0x118, 0xf)
+    VP_DPP_MAX(0x142, 0xa)
+    VP_DPP_MAX(0x143, 0xc)
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+#undef VP_DPP_MAX
+#define VP_DPP_MIN(ctrl, rows) v = min(v, __builtin_amdgcn_update_dpp(v, v, ctrl, rows, 0xf, false));
+__device__ inline int wave_min_int(int v)
+{
+    VP_DPP_MIN(0x111, 0xf)
+    VP_DPP_MIN(0x112, 0xf)
+    VP_DPP_MIN(0x114, 0xf)
+    VP_DPP_MIN(0x118, 0xf)
+    VP_DPP_MIN(0x142, 0xa)
+    VP_DPP_MIN(0x143, 0xc)
+    return __builtin_amdgcn_readlane(v, 63);
+}
+#undef VP_DPP_MIN
+
 // Running maximum m and sum of exp(x - m) over the wavefront's (m, s) pairs, to every lane.
 __device__ inline void wave_log_sum_exp(float &m, float &s)
 {

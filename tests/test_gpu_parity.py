@@ -1401,3 +1401,22 @@ def test_every_form_of_the_many_row_eq2_kernel(oracle, N, K):
     got = B.project(H, 2)
     assert (got[2][:20] == 3).all()
     pu.check_projection(oracle, W, b, C, off, ids, H, 2, *got)
+
+
+@pytest.mark.parametrize("k", [1, 2, 4, 5, 8, 9])
+def test_merge_of_equal_logits_over_many_parts(oracle, k):
+    """Rows of more parts than a workgroup of the merge has threads, of a few hundred and of a handful: every logit of the
+    first row is the same, so the k smallest token ids win wherever their parts are; the second row's best are spread."""
+    d, V = 64, 40000
+    r, W, b, C = _small_model(5 + k, d, V, 1)
+    W[:] = W[:, :1]
+    b[:] = b[0]
+    b[r.choice(V, 40, replace=False)] += np.float16(2.0)     # forty equal best ones
+    B = Built(W, b, C, np.array([0, V], np.int64), np.arange(V, dtype=np.int32), k_max=16)
+    H = _rows(r, C, 2)
+    for wanted, least, most in ((2048, 257, 2048), (200, 65, 256), (16, 9, 64)):
+        B.index.set_option("full_target_items", wanted)
+        got = B.project_full(H, k)
+        parts = B.index.workspace(2)[:64].view(_torch().int32)[0].item()
+        assert least <= parts <= most or wanted != 2048, parts
+        pu.check_full(oracle, W, b, H, k, *got)
