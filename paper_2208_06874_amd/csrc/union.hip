@@ -68,7 +68,14 @@ __global__ __launch_bounds__(UNION_THREADS) void union_mark_kernel(
 #pragma unroll
             for (int u = 0; u < UNION_LISTS_IN_FLIGHT; ++u) acc |= b[u];
         }
-        for (; c < n_occ; ++c) acc |= bitmaps[(size_t)occ[c] * bm_words + w];
+        // (what is left by eight, the last list again where fewer are: one trip to memory for them, not one each)
+        for (; c < n_occ; c += 8) {
+            unsigned int b[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) b[u] = bitmaps[(size_t)occ[min(c + u, n_occ - 1)] * bm_words + w];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) acc |= b[u];
+        }
         mask[w] = acc;
     }
     const int cnt = wave_sum(__popc(acc));
