@@ -366,7 +366,7 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_kernel(
         perm[p] = r;
         floors[r] = VP_FLOOR_NONE;   // no lower bound of the row's k-th best logit known yet
         if (form[j] != ON_SLAB)
-            for (int s = 0; s < VP_BOUND_SETS; ++s) floors[N + r * VP_BOUND_SETS + s] = VP_FLOOR_NONE;
+            for (int s = 0; s < VP_BOUND_SETS; ++s) vp_set_bounds(floors, N)[(size_t)r * VP_BOUND_SETS + s] = VP_FLOOR_NONE;
         VpRowPlan rp;
         rp.row = r;
         rp.cluster = j;

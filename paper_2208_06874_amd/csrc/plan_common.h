@@ -68,7 +68,7 @@ __device__ inline void vp_plan_single_bucket(int N, int ncand, int vtiles, int r
     for (int p = gtid; p < N; p += gsize) {
         perm[p] = p;
         floors[p] = VP_FLOOR_NONE;
-        for (int j = 0; j < VP_BOUND_SETS; ++j) floors[N + p * VP_BOUND_SETS + j] = VP_FLOOR_NONE;
+        for (int j = 0; j < VP_BOUND_SETS; ++j) vp_set_bounds(floors, N)[(size_t)p * VP_BOUND_SETS + j] = VP_FLOOR_NONE;
         VpRowPlan rp;
         rp.row = p;
         rp.cluster = 0;

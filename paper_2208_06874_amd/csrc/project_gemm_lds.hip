@@ -6,8 +6,8 @@
 //
 // An item is 64 rows (48 at d_pad = 1280 and 1536, where 64 do not fit) x a range of candidate groups, one
 // workgroup of eight wavefronts.  The rows are staged once in LDS in MFMA operand order (4 or 3
-// row tiles x KT KiB) and never move again.  The range is cut into steps of four candidate groups (64 candidates; of one in short
-// items, brief_to); wavefront w takes steps w, w + 8, ...  A step streams its groups' tiles straight into registers
+// row tiles x KT KiB) and never move again.  The range is cut into steps of four candidate groups (64 candidates; of one or two in short
+// items); wavefront w takes steps w, w + 8, ...  A step streams its groups' tiles straight into registers
 // (a ring of a few k-tiles ahead, crossing step boundaries, so the loads never drain), and per
 // k-tile feeds each loaded 1 KiB slab tile to one v_mfma_f32_16x16x32_f16 per row tile,
 // whose row operands are read from LDS (one 1 KiB read per four MFMAs: four groups per step).  No wavefront waits
@@ -31,16 +31,23 @@
 // best first, re-reading the bound after every insertion - so even the first step, which finds
 // the list empty, costs a lane one or two insertions rather than sixteen.
 //
-// Where a row's candidates are spread over many items (and 3 <= k <= 8) the lists' upkeep is bound by how late the items learn of each
+// Where a row's candidates are spread over many items (and 4 <= k <= 8) the lists' upkeep is bound by how late the items learn of each
 // other: each starts with an empty list, and 64 of them insert 57 entries a row where one behind the other would need two.  So
 // behind the first step's MFMAs, before anything is inserted, the workgroups trade the best logits seen of eight sets that the row's
 // candidates fall into (by lane quarter and the wavefront's parity): the k-th largest of the eight cannot be above the row's k-th
 // best, and 64 items know it of 32,768 candidates at once.  It costs one wait for memory per item; after steps 1, 2 and 4 the
-// sets are traded again without waiting, later on the k-th bests as elsewhere.  Full projection, V = 250,000, d = 1024, top-8, us per
-// call before -> with it (256 to 32 items a row): 64 rows 112 -> 103, 128: 134 -> 122, 256: 182 -> 170, 333: 239 -> 224,
-// 512: 286 -> 274; top-3 within 2 %.  With fewer items a row (from 1,024 rows on) there is little to learn: top-3 1 % slower.
-// (Not where the columns are gathered: two rows of 20 sentences, short items, 1 % slower for the registers it takes.)
-// Keeping the candidates in an unsorted queue instead of the cascade: 5 to 20 % slower (registers, and the queue's overflow).
+// sets are traded again without waiting, later on the k-th bests as elsewhere.  Full projection, d = 1024, us per call without ->
+// with it: V = 250,000 (256 to 32 items a row), top-8: 128 rows 134 -> 122, 256: 182 -> 170, 333: 239 -> 224, 512: 286 -> 274;
+// V = 200,000, 64 rows, top-4 89 -> 84, top-8 97 -> 86.  Not used where it costs more than it saves:
+//   fewer than SET_ITEMS items a row: little to learn (from 1,024 rows on; top-3 1 % slower);
+//   top-2, top-3: few insertions either way (within 2 %);
+//   few rows of an item: every atomic still waits for 256 workgroups' (17 rows, V = 128,000, top-3: 60 -> 64);
+//   short items of several row groups, which all wait at once while the loads run dry: 256 rows, V = 128,000, 125 groups an item,
+//   top-4 87 -> 96, but 156 groups 108 -> 103; one row group: 32 groups 66 -> 63;
+//   gathered columns (the union): 40 rows 1 % slower for the registers it takes.
+// The sets of a row are in one line (vp_set_bounds): with N * 4 bytes of bounds in front of them 60 rows took 68 us, not 63.
+// Keeping the candidates in an unsorted queue instead of the cascade: 5 to 20 % slower (registers, and the queue's overflow);
+// fewer atomics and plain loads of the sets: 40 us slower (the loads wait behind every atomic on their line).
 #include <hip/hip_runtime.h>
 #include <type_traits>
 #include "vp_kernels.h"
@@ -53,9 +60,12 @@ constexpr int L_NW = 8;        // wavefronts per workgroup
 // row tiles per item: four (64 rows), or three where four do not fit the LDS (48 rows: 120 KiB at d_pad = 1280,
 // 144 KiB at 1536)
 constexpr int lds_row_tiles(int kt) { return kt > 32 ? 3 : 4; }
-// Candidate groups per step: four (one 1 KiB read of the rows from LDS per four MFMAs), or one for short items (brief_to).
+// Candidate groups per step: four (one 1 KiB read of the rows from LDS per four MFMAs), one for short items (brief_to), and two where
+// one row group alone reads the bytes and its items are at most 32 groups (64 at top-1): with four a wavefront has one step there, and
+// all of them fold at the end, behind the last load.  d = 1024, one row group, four -> two: V = 128,000 (32 groups), 64 rows, top-1
+// 60.6 -> 58.1, masked top-8 with its call 83.8 -> 79.9; V = 200,000 (49), top-1 82.5 -> 77.9; V = 180,000 (44), top-3 76 -> 79.
 // About 16 KiB per wavefront are kept in flight either way.
-constexpr int lds_k_tiles_in_flight(int kt, int g) { return g == 4 ? 4 : kt % 16 == 0 ? 16 : 8; }
+constexpr int lds_k_tiles_in_flight(int kt, int g) { return g == 4 ? 4 : g == 2 ? 8 : kt % 16 == 0 ? 16 : 8; }
 // The largest item that takes steps of one group.  In steps of four its wavefronts are partly without work, and the others have a
 // long chain of loads; in steps of one every group pays for a fold, and lists of more than one entry for their upkeep.
 // Full projection, time in steps of four / of one by groups per item: d = 1024, top-1, one row group: 4: 1.15, 8: 1.03, 15: 1.10, 20:
@@ -71,8 +81,8 @@ __device__ constexpr int brief_to(bool shared, int k)
     if (shared) return k > 2 ? 12 : L_NW;
     return KT > 32 ? 2 * L_NW - 1 : KT >= 24 ? 4 * L_NW - 1 : L_NW;
 }
-constexpr int SET_ITEMS = 24;
-__host__ __device__ constexpr bool trades_sets(int k) { return k >= 3 && k <= VP_BOUND_SETS; }
+constexpr int SET_ITEMS = 24, SET_GROUPS = 144;
+__host__ __device__ constexpr bool trades_sets(int k) { return k >= 4 && k <= VP_BOUND_SETS; }
 constexpr int VP_MAX_TOPK_LANES = 32;   // the epilogue writes a row's list with one lane per entry
 
 // The k-th largest of a row's eight keys (k = 1 .. 8; a sorting network of 19 compare-exchanges).
@@ -108,7 +118,7 @@ __device__ inline void gemm_lds_item(const VpSlabSet &set, const uint4 *__restri
     constexpr int L_RT = lds_row_tiles(KT);
     constexpr int L_ROWS = 16 * L_RT;
     constexpr int L_PF = lds_k_tiles_in_flight(KT, L_G);
-    static_assert(KT % L_PF == 0 && (L_G == 4 || L_G == 1), "whole passes; the mask's words");
+    static_assert(KT % L_PF == 0 && (L_G == 4 || L_G == 2 || L_G == 1), "whole passes; the mask's words");
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // (uniform: step numbers and tile offsets stay in scalar registers)
     const int lane = tid & 63;
@@ -216,8 +226,8 @@ __device__ inline void gemm_lds_item(const VpSlabSet &set, const uint4 *__restri
     if (tid < L_ROWS)
         wg_floor[tid] = !TOP1 && tid < item.nrows ? floors[MASKED && perm ? perm[item.perm_start + tid] : item.perm_start + tid]
                                                   : VP_FLOOR_NONE;
-    // the sets' bests are traded where the row has at least SET_ITEMS items (top of the file)
-    const bool sets = !TOP1 && !GATHER && L_G == 4 && trades_sets(k) && (long long)item.ntiles * (VP_TILE_ITEMS * SET_ITEMS) <= ncand;
+    // whether the sets' bests are traded: top of the file
+    const bool sets = !TOP1 && !GATHER && L_G != 1 && trades_sets(k) && 4 * item.nrows >= 3 * L_ROWS && (!item.shared || item.ntiles >= SET_GROUPS) && (long long)item.ntiles * (VP_TILE_ITEMS * SET_ITEMS) <= ncand;
     if (sets)
         for (int e = tid; e < L_ROWS * VP_BOUND_SETS; e += L_NW * 64) set_best[e] = VP_FLOOR_NONE;
     __syncthreads();
@@ -283,7 +293,7 @@ __device__ inline void gemm_lds_item(const VpSlabSet &set, const uint4 *__restri
             for (int rt = 0; rt < L_RT; ++rt) {
                 const uint32_t *words = mask.bitmaps + (moff[rt] + ((g0 * VP_TILE_ITEMS) >> 5));
                 if (L_G == 4) mw[rt] = *reinterpret_cast<const uint2 *>(words);
-                else mw[rt].x = words[0] >> ((g0 & 1) * VP_TILE_ITEMS);   // (one group: half a word)
+                else mw[rt].x = words[0] >> ((g0 & 1) * VP_TILE_ITEMS);   // (one group: half a word; two: a whole one, items start at even groups)
             }
         }
 
@@ -588,6 +598,7 @@ __global__ __launch_bounds__(L_NW * 64) void project_gemm_lds_kernel(
         else gemm_lds_item<KT, 4, MASKED, false, TOP1, GATHER>(set, hidden, d, item, it, kk, partials, floors, bounds, mask, perm);
     } else {
         if (brief) gemm_lds_item<KT, 1, MASKED, true, TOP1, false>(set, hidden, d, item, it, kk, partials, floors, bounds, mask, perm);
+        else if (item.ntiles <= (TOP1 ? 8 : 4) * L_NW) gemm_lds_item<KT, 2, MASKED, true, TOP1, false>(set, hidden, d, item, it, kk, partials, floors, bounds, mask, perm);
         else gemm_lds_item<KT, 4, MASKED, true, TOP1, false>(set, hidden, d, item, it, kk, partials, floors, bounds, mask, perm);
     }
 }

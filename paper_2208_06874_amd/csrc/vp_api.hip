@@ -230,7 +230,7 @@ WsLayout plan_workspace(const vp_index *I, int N)
     W.g = take(n * 4);
     W.perm = take(n * 4);
     W.rowplan = take(n * sizeof(VpRowPlan));
-    W.floors = take(n * 4 * (1 + VP_BOUND_SETS));   // [N] bounds, then [N][sets] of the GEMM-shaped kernels
+    W.floors = take(n * 4 * (1 + VP_BOUND_SETS));   // [N][sets] of the GEMM-shaped kernels, then [N] bounds
     // (workgroups read the record at their own index before they know the item count)
     W.items = take((size_t)(W.max_items + 8 * VP_XCD_BLOCK_ITEMS) * sizeof(VpItem));
     // one partial result per (item, row slot): 16 slots in the clustered plan, up to 64 in single-bucket plans
@@ -337,9 +337,9 @@ void launch_single_bucket(const VpSlabSet &set, const vp_index *I, const void *h
                           hipStream_t st)
 {
     if (use_gemm_lds(I, row_tiles, k))
-        vpk_project_rows_lds(set, hidden, I->d, perm, items, hdr, grid_items, k, partials, floors, floors + N, nullptr, nullptr, false, st);
+        vpk_project_rows_lds(set, hidden, I->d, perm, items, hdr, grid_items, k, partials, floors, vp_set_bounds(floors, N), nullptr, nullptr, false, st);
     else if (row_tiles == 4)
-        vpk_project_gemm(set, hidden, I->d, perm, items, hdr, grid_items, k, partials, floors + N, nullptr, st);
+        vpk_project_gemm(set, hidden, I->d, perm, items, hdr, grid_items, k, partials, vp_set_bounds(floors, N), nullptr, st);
     else
         vpk_project(set, hidden, I->d, perm, items, hdr, grid_items, row_tiles, k, rstar, partials, floors, dbg_logits,
                     dbg_row_off, 0, st);
@@ -374,7 +374,7 @@ vp_status run_clustered(const char *fn, const vp_index *I, const void *hidden, i
     int32_t *g = reinterpret_cast<int32_t *>(ws + W.g);
     int32_t *perm = reinterpret_cast<int32_t *>(ws + W.perm);
     VpRowPlan *rowplan = reinterpret_cast<VpRowPlan *>(ws + W.rowplan);
-    unsigned int *floors = reinterpret_cast<unsigned int *>(ws + W.floors);
+    unsigned int *floors = reinterpret_cast<unsigned int *>(ws + W.floors) + (size_t)N * VP_BOUND_SETS;
     VpItem *items = reinterpret_cast<VpItem *>(ws + W.items);
     float *partials = reinterpret_cast<float *>(ws + W.partials);
 
@@ -508,9 +508,9 @@ vp_status run_clustered(const char *fn, const vp_index *I, const void *hidden, i
         // launched as well; one of the two does the work, or each its clusters' share, as the planner decided
         const VpMaskInfo mask = {g, I->bitmaps, I->L.bm_words};
         if (use_gemm_lds(I, rt_masked, k))
-            vpk_project_rows_lds(I->full, hidden, I->d, perm, items, hdr, grid_full, k, partials, floors, floors + N, &mask, &I->clusters, false, st);
+            vpk_project_rows_lds(I->full, hidden, I->d, perm, items, hdr, grid_full, k, partials, floors, vp_set_bounds(floors, N), &mask, &I->clusters, false, st);
         else if (rt_masked == 4)
-            vpk_project_gemm(I->full, hidden, I->d, perm, items, hdr, grid_full, k, partials, floors + N, &mask, st);
+            vpk_project_gemm(I->full, hidden, I->d, perm, items, hdr, grid_full, k, partials, vp_set_bounds(floors, N), &mask, st);
         else
             vpk_project_masked(I->full, hidden, I->d, perm, items, hdr, grid_full, k, partials, floors, mask, st);
     }
@@ -527,7 +527,7 @@ vp_status run_full(const char *fn, const vp_index *I, const void *hidden, int N,
     VpPlanHeader *hdr = reinterpret_cast<VpPlanHeader *>(ws + W.hdr);
     int32_t *perm = reinterpret_cast<int32_t *>(ws + W.perm);
     VpRowPlan *rowplan = reinterpret_cast<VpRowPlan *>(ws + W.rowplan);
-    unsigned int *floors = reinterpret_cast<unsigned int *>(ws + W.floors);
+    unsigned int *floors = reinterpret_cast<unsigned int *>(ws + W.floors) + (size_t)N * VP_BOUND_SETS;
     VpItem *items = reinterpret_cast<VpItem *>(ws + W.items);
     float *partials = reinterpret_cast<float *>(ws + W.partials);
 
@@ -984,7 +984,7 @@ vp_status vp_project_union(const vp_index *I, const void *hidden, int32_t N, int
     int32_t *g = reinterpret_cast<int32_t *>(ws + W.g);
     int32_t *perm = reinterpret_cast<int32_t *>(ws + W.perm);
     VpRowPlan *rowplan = reinterpret_cast<VpRowPlan *>(ws + W.rowplan);
-    unsigned int *floors = reinterpret_cast<unsigned int *>(ws + W.floors);
+    unsigned int *floors = reinterpret_cast<unsigned int *>(ws + W.floors) + (size_t)N * VP_BOUND_SETS;
     VpItem *items = reinterpret_cast<VpItem *>(ws + W.items);
     float *partials = reinterpret_cast<float *>(ws + W.partials);
     VpUnionHeader *uh = reinterpret_cast<VpUnionHeader *>(ws + U.uh);
@@ -1046,7 +1046,7 @@ vp_status vp_project_union(const vp_index *I, const void *hidden, int32_t N, int
     const int grid_items = std::min(max_items, ceil_div(rgs * (long)ceil_div(I->L.vtiles, VP_WG_WAVES), 8) * 8 + 8 * rgs);
     if (fused_gather) {
         uset.tiles = I->arena + I->L.wt;
-        vpk_project_rows_lds(uset, hidden, I->d, perm, items, hdr, grid_items, k, partials, floors, floors + N, nullptr, nullptr, true, st);
+        vpk_project_rows_lds(uset, hidden, I->d, perm, items, hdr, grid_items, k, partials, floors, vp_set_bounds(floors, N), nullptr, nullptr, true, st);
     } else {
         vpk_union_gather(I->arena + I->L.wt, I->L.kt, uids, uh, I->L.vtiles, uslab, st);
         uset.tiles = uslab;
@@ -1060,9 +1060,9 @@ vp_status vp_project_union(const vp_index *I, const void *hidden, int32_t N, int
         const int grid_full = (rgs > 1 && chunks >= 8) ? ceil_div(chunks, 8) * 8 * rgs : chunks * rgs;
         const VpMaskInfo umask = {zero_g, mask, 0};   // every row reads list 0: the boolean list of the batch
         if (use_gemm_lds(I, row_tiles_u, k))
-            vpk_project_rows_lds(I->full, hidden, I->d, perm, items, hdr, grid_full, k, partials, floors, floors + N, &umask, nullptr, false, st);
+            vpk_project_rows_lds(I->full, hidden, I->d, perm, items, hdr, grid_full, k, partials, floors, vp_set_bounds(floors, N), &umask, nullptr, false, st);
         else if (row_tiles_u == 4)
-            vpk_project_gemm(I->full, hidden, I->d, perm, items, hdr, grid_full, k, partials, floors + N, &umask, st);
+            vpk_project_gemm(I->full, hidden, I->d, perm, items, hdr, grid_full, k, partials, vp_set_bounds(floors, N), &umask, st);
         else
             vpk_project_masked(I->full, hidden, I->d, perm, items, hdr, grid_full, k, partials, floors, umask, st);
     }

@@ -25,6 +25,10 @@
 #define VP_RAW_TILES 2           // slab items of at most this many tiles per wavefront keep raw logits, no top-k lists
 #define VP_XCD_BLOCK_ITEMS 32    // clustered plans with heavy buckets: consecutive items one XCD takes at a time
 
+// The sets of all rows lie in front of the rows' bounds `floors`, from a multiple of 256 bytes on: a row's sets are 32 bytes of one
+// line whatever N is, and what a wavefront trades (eight rows) is two lines.
+static inline __host__ __device__ unsigned int *vp_set_bounds(unsigned int *floors, int N) { return floors - (long long)N * VP_BOUND_SETS; }
+
 // One unit of projection work: some rows of one bucket (up to 16, or 32, 48 or 64 on the kernels with that many row
 // slots) against a range of candidate tiles of that bucket's slab.
 struct VpItem {

@@ -1352,12 +1352,14 @@ def test_index_without_the_token_major_copy(oracle):
     assert e.value.status == vp.VP_ERR_UNSUPPORTED and "NO_UNION" in str(e.value)
 
 
-@pytest.mark.parametrize("d,N", [(256, 64), (1024, 17), (1024, 65), (1536, 49)])
-def test_bests_of_sets_traded_between_many_items(oracle, d, N):
+@pytest.mark.parametrize("d,N,groups,items", [(256, 64, 36, 26), (1024, 47, 36, 26), (1024, 60, 28, 25), (1536, 37, 36, 24), (256, 127, 144, 24),
+                                              (256, 64, 64, 24)])
+def test_bests_of_sets_traded_between_many_items(oracle, d, N, groups, items):
     """Rows whose candidates are spread over many items (24 and more trade the bests of eight sets of candidates, fewer do not;
-    top-3 to top-8 only): equal logits in every set and item, a row with a few candidates only, a last item in which
-    wavefronts have no step, plain and masked, twice to the bit."""
-    V = 16 * 36 * 26 - 16 * 23 - 5          # items of 36 groups: 26 (the last: 12 groups and a piece) and, with 8 wanted, 8
+    top-4 to top-8 only, three quarters of the row slots in use): equal logits in every set and item, a row with a few
+    candidates only, a last item in which wavefronts have no step, steps of two groups and of four, plain and masked, twice
+    to the bit."""
+    V = 16 * groups * items - 16 * min(groups - 13, 60) - 5   # (the last item: 12 groups and a piece, or some more)
     r, W, b, C = _small_model(70 + d + N, d, V, 3)
     W[:, ::3] = W[:, :1]                     # a third of the vocabulary ties, whatever the row
     b[::3] = b[0]
@@ -1366,25 +1368,30 @@ def test_bests_of_sets_traded_between_many_items(oracle, d, N):
     ids = np.concatenate([full, ids[off[1]:]]).astype(np.int32)
     off = np.concatenate([[0], off[1:] - off[1] + len(full)]).astype(np.int64)
     B = Built(W, b, C, off, ids, k_max=9)
-    rgs = (N + (64 if d <= 1024 else 48) - 1) // (64 if d <= 1024 else 48)
+    per = 64 if d <= 1024 else 48
+    rgs = (N + per - 1) // per
     H = _rows(r, C, N)
-    for wanted in (26 * rgs, 8):
+    for wanted in (items * rgs, 8):
         B.index.set_option("gemm_lds_items", wanted)
-        for k in (2, 3, 8, 9):
+        for k in (1, 3, 4, 8, 9):
             got = B.project_full(H, k)
+            if wanted > 8:
+                ws = B.index.workspace(N)[:64].view(_torch().int32)
+                assert ws[0].item() == items * rgs and ws[1].item() * 4 == groups, (ws[0].item(), ws[1].item())
             again = B.project_full(H, k)
             for x, y in zip(got, again):
                 assert np.array_equal(x, y)
             pu.check_full(oracle, W, b, H, k, *got)
-            B.index.set_option("dispatch", 1)
-            B.index.set_option("cost_bw_slab_gbs", 1)      # force the masked projection
-            try:
+        B.index.set_option("dispatch", 1)
+        B.index.set_option("cost_bw_slab_gbs", 1)      # force the masked projection
+        try:
+            for k in (1, 4, 8):
                 got = B.project(H, k)
                 assert _planner_mode(B.index, N) == 1
-            finally:
-                B.index.set_option("cost_bw_slab_gbs", 6800)
-                B.index.set_option("dispatch", 0)
-            pu.check_projection(oracle, W, b, C, off, ids, H, k, *got)
+                pu.check_projection(oracle, W, b, C, off, ids, H, k, *got)
+        finally:
+            B.index.set_option("cost_bw_slab_gbs", 6800)
+            B.index.set_option("dispatch", 0)
 
 
 @pytest.mark.parametrize("N,K", [(65, 40), (256, 1300), (333, 1990), (769, 1990), (2047, 2000)])
