@@ -441,7 +441,7 @@ __device__ inline void gemm_lds_item(const VpSlabSet &set, const uint4 *__restri
                     // this lane's candidates, best first, until one is below the bound (the others,
                     // which are not better, then are too)
                     while (true) {
-                        float v = z[0];
+                        float v = fmaxf(z[0], -__builtin_inff());   // (NaN is no candidate, and none to measure the others by)
                         int e_best = 0;
 #pragma unroll
                         for (int e = 1; e < L_G * 4; ++e) {

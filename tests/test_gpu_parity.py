@@ -1427,3 +1427,33 @@ def test_merge_of_equal_logits_over_many_parts(oracle, k):
         parts = B.index.workspace(2)[:64].view(_torch().int32)[0].item()
         assert least <= parts <= most or wanted != 2048, parts
         pu.check_full(oracle, W, b, H, k, *got)
+
+
+@pytest.mark.parametrize("d,N,groups,items", [(256, 64, 36, 26), (1024, 64, 36, 25), (256, 128, 144, 24), (256, 20, 36, 10)])
+def test_nan_candidate_costs_no_other_candidate_its_place(oracle, d, N, groups, items):
+    """One token's bias is NaN (its logit is, and so is the row's log-sum-exp); eight others are far ahead of all the rest, one
+    of them among the sixteen candidates that the same lane of the many-row kernel folds.  The eight are the top-8 all the
+    same: NaN is never listed and costs no other candidate its place, whether or not items trade the bests of sets of candidates (which know the
+    eight from the first step on)."""
+    V = 16 * groups * items
+    r, W, b, C = _small_model(300 + d + N, d, V, 2)
+    nan_at = 16 * groups * 3                                 # the first candidate of the fourth item
+    # (one in each of the eight sets: lane quarter s % 4, of the first wavefront or the second)
+    top = np.array([nan_at + 1] + [16 * groups * ((s + 3) % items) + 4 * (s % 4) + 64 * (s // 4) + 2 for s in range(1, 8)])
+    b[top] = np.float16(60.0) + np.arange(8).astype(np.float16)
+    b[nan_at] = np.nan
+    B = Built(W, b, C, np.array([0, V, V + 9], np.int64), np.concatenate([np.arange(V), np.arange(9)]).astype(np.int32), k_max=9)
+    per = 64
+    B.index.set_option("gemm_lds_items", items * ((N + per - 1) // per))
+    H = _rows(r, C, N, clusters=np.zeros(N, int))
+    for form in ("full", "masked"):
+        for k in (8, 9, 4):
+            if form == "full":
+                ids, logp = B.project_full(H, k)
+            else:
+                (ids, logp, g), mode, ovf = _masked(B, H, k)
+                assert mode == 1 and ovf == 0 and (g == 0).all()
+            assert np.isnan(logp).all(), (form, k)
+            if k >= 8:
+                assert np.array_equal(np.sort(ids[:, :8], axis=1), np.tile(np.sort(top), (N, 1))), (form, k, ids[0], top)
+            assert (ids >= 0).all() and not (ids == nan_at).any() and (np.isin(ids[:, :4], top)).all()
