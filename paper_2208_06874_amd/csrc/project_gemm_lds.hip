@@ -74,15 +74,23 @@ constexpr int lds_k_tiles_in_flight(int kt, int g) { return g == 4 ? 4 : g == 2 
 // of them, top-2: 1.22, 1.11, 0.94, 0.96, 0.92; d = 256 and 512 alike (at 28, top-8: 0.85, 0.80).  One row group, top-4, 24 rows: d =
 // 1024: 12: 1.03, 15: 1.04, 20: 1.05, 28: 1.05; d = 768: 1.00, 0.95, 1.03, 1.03; d = 512: 0.94, 1.01, 0.93, 0.97; d = 256: 0.94, 0.88, 0.91,
 // 0.88.  d = 1280 and 1536: 8: 1.11, 1.10, 12: 0.97, 0.99, beyond 16 0.98 at top-8.
-template <int KT, bool TOP1>
-__device__ constexpr int brief_to(bool shared, int k)
+__host__ __device__ constexpr int brief_to(int kt, bool shared, int k)
 {
-    if (TOP1) return (KT > 32 ? 2 : 4) * L_NW - 1;
+    if (k == 1) return (kt > 32 ? 2 : 4) * L_NW - 1;
     if (shared) return k > 2 ? 12 : L_NW;
-    return KT > 32 ? 2 * L_NW - 1 : KT >= 24 ? 4 * L_NW - 1 : L_NW;
+    return kt > 32 ? 2 * L_NW - 1 : kt >= 24 ? 4 * L_NW - 1 : L_NW;
 }
+// Whether an item trades the bests of sets (top of the file).  The host asks the same of a plan's longest item: the code that
+// trades is compiled into kernels of its own (SETS), because where it stood in every list kernel the registers it takes were
+// lost to the calls that never trade (masked, d_pad = 1024: 20 vector registers spilled and
+// 72 scalar ones, without it none and 19; 64 rows, V = 200,000, d = 768, masked top-2: 90 us with it, 81
+// without).
 constexpr int SET_ITEMS = 24, SET_GROUPS = 144;
-__host__ __device__ constexpr bool trades_sets(int k) { return k >= 4 && k <= VP_BOUND_SETS; }
+__host__ __device__ constexpr bool trades_sets(int kt, int k, int nrows, bool shared, int ntiles, int ncand)
+{
+    return k >= 4 && k <= VP_BOUND_SETS && 4 * nrows >= 3 * 16 * lds_row_tiles(kt) && ntiles > brief_to(kt, shared, k) &&
+           (!shared || ntiles >= SET_GROUPS) && (long long)ntiles * (VP_TILE_ITEMS * SET_ITEMS) <= ncand;
+}
 constexpr int VP_MAX_TOPK_LANES = 32;   // the epilogue writes a row's list with one lane per entry
 
 // The k-th largest of a row's eight keys (k = 1 .. 8; a sorting network of 19 compare-exchanges).
@@ -108,7 +116,7 @@ __device__ inline unsigned int kth_of_sets(const unsigned int *set, int k)
 // (logit descending, position ascending), without branches
 __device__ inline bool before_entry(float v, int i, float v2, int i2) { return (v > v2) | ((v == v2) & (i < i2)); }
 
-template <int KT, int L_G, bool MASKED, bool NT, bool TOP1, bool GATHER>
+template <int KT, int L_G, bool MASKED, bool NT, bool TOP1, bool GATHER, bool SETS>
 __device__ inline void gemm_lds_item(const VpSlabSet &set, const uint4 *__restrict__ hidden, int d,
                                      const VpItem &item, int it, int k,
                                      float *__restrict__ partials, unsigned int *__restrict__ floors,
@@ -129,7 +137,7 @@ __device__ inline void gemm_lds_item(const VpSlabSet &set, const uint4 *__restri
     uint4 *ldsB = lds;                                                          // [L_RT][KT][64]: the rows
     unsigned long long *lkey = reinterpret_cast<unsigned long long *>(lds + L_RT * KT * 64);   // [k][64]: the rows' lists
     unsigned int *wg_floor = reinterpret_cast<unsigned int *>(lkey + k * L_ROWS);               // [64]
-    unsigned int *set_best = wg_floor + L_ROWS;                                                 // [64][VP_BOUND_SETS] (trades_sets)
+    unsigned int *set_best = wg_floor + L_ROWS;                                                 // [64][VP_BOUND_SETS] (SETS)
     // after the loop, in place of the rows:
     float *hdr_m = reinterpret_cast<float *>(lds);                              // [L_NW][64]
     float *hdr_s = hdr_m + L_NW * L_ROWS;
@@ -227,7 +235,7 @@ __device__ inline void gemm_lds_item(const VpSlabSet &set, const uint4 *__restri
         wg_floor[tid] = !TOP1 && tid < item.nrows ? floors[MASKED && perm ? perm[item.perm_start + tid] : item.perm_start + tid]
                                                   : VP_FLOOR_NONE;
     // whether the sets' bests are traded: top of the file
-    const bool sets = !TOP1 && !GATHER && L_G != 1 && trades_sets(k) && 4 * item.nrows >= 3 * L_ROWS && (!item.shared || item.ntiles >= SET_GROUPS) && (long long)item.ntiles * (VP_TILE_ITEMS * SET_ITEMS) <= ncand;
+    const bool sets = SETS && L_G != 1 && trades_sets(KT, k, item.nrows, item.shared, item.ntiles, ncand);
     if (sets)
         for (int e = tid; e < L_ROWS * VP_BOUND_SETS; e += L_NW * 64) set_best[e] = VP_FLOOR_NONE;
     __syncthreads();
@@ -561,7 +569,7 @@ __device__ inline void gemm_lds_item(const VpSlabSet &set, const uint4 *__restri
     }
 }
 
-template <int KT, bool MASKED, bool TOP1, bool GATHER>
+template <int KT, bool MASKED, bool TOP1, bool GATHER, bool SETS>
 __global__ __launch_bounds__(L_NW * 64) void project_gemm_lds_kernel(
     VpSlabSet set, const uint4 *__restrict__ hidden, int d,
     const VpItem *__restrict__ items, const VpPlanHeader *__restrict__ hdr, int k,
@@ -592,41 +600,42 @@ __global__ __launch_bounds__(L_NW * 64) void project_gemm_lds_kernel(
         if (hdr->mode == 1) perm = nullptr;   // the whole batch, in its own order
     }
     const int kk = TOP1 ? 1 : k;
-    const bool brief = item.ntiles <= brief_to<KT, TOP1>(item.shared, k);
+    const bool brief = item.ntiles <= brief_to(KT, item.shared, kk);
     if (item.shared || GATHER) {
-        if (brief) gemm_lds_item<KT, 1, MASKED, false, TOP1, GATHER>(set, hidden, d, item, it, kk, partials, floors, bounds, mask, perm);
-        else gemm_lds_item<KT, 4, MASKED, false, TOP1, GATHER>(set, hidden, d, item, it, kk, partials, floors, bounds, mask, perm);
+        if (brief) gemm_lds_item<KT, 1, MASKED, false, TOP1, GATHER, false>(set, hidden, d, item, it, kk, partials, floors, bounds, mask, perm);
+        else gemm_lds_item<KT, 4, MASKED, false, TOP1, GATHER, SETS>(set, hidden, d, item, it, kk, partials, floors, bounds, mask, perm);
     } else {
-        if (brief) gemm_lds_item<KT, 1, MASKED, true, TOP1, false>(set, hidden, d, item, it, kk, partials, floors, bounds, mask, perm);
-        else if (item.ntiles <= (TOP1 ? 8 : 4) * L_NW) gemm_lds_item<KT, 2, MASKED, true, TOP1, false>(set, hidden, d, item, it, kk, partials, floors, bounds, mask, perm);
-        else gemm_lds_item<KT, 4, MASKED, true, TOP1, false>(set, hidden, d, item, it, kk, partials, floors, bounds, mask, perm);
+        if (brief) gemm_lds_item<KT, 1, MASKED, true, TOP1, false, false>(set, hidden, d, item, it, kk, partials, floors, bounds, mask, perm);
+        else if (item.ntiles <= (TOP1 ? 8 : 4) * L_NW) gemm_lds_item<KT, 2, MASKED, true, TOP1, false, SETS>(set, hidden, d, item, it, kk, partials, floors, bounds, mask, perm);
+        else gemm_lds_item<KT, 4, MASKED, true, TOP1, false, SETS>(set, hidden, d, item, it, kk, partials, floors, bounds, mask, perm);
     }
 }
 
 template <int KT, bool MASKED, bool GATHER>
 void launch_lds(const VpSlabSet &set, const void *hidden, int d, const VpItem *items,
                 const VpPlanHeader *hdr, int grid_items, int k, float *partials, unsigned int *floors,
-                unsigned int *bounds, const VpMaskInfo &mask, const int32_t *perm, const VpSlabSet &slabs, hipStream_t st)
+                unsigned int *bounds, bool sets, const VpMaskInfo &mask, const int32_t *perm, const VpSlabSet &slabs, hipStream_t st)
 {
-    if (k == 1)
-        hipLaunchKernelGGL((project_gemm_lds_kernel<KT, MASKED, true, GATHER>), dim3(grid_items), dim3(L_NW * 64),
-                           vpk_project_rows_lds_bytes(k, KT), st, set, (const uint4 *)hidden, d, items, hdr, k,
-                           partials, floors, bounds, mask, perm, slabs);
-    else
-        hipLaunchKernelGGL((project_gemm_lds_kernel<KT, MASKED, false, GATHER>), dim3(grid_items), dim3(L_NW * 64),
-                           vpk_project_rows_lds_bytes(k, KT), st, set, (const uint4 *)hidden, d, items, hdr, k,
-                           partials, floors, bounds, mask, perm, slabs);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(grid_items), dim3(L_NW * 64), vpk_project_rows_lds_bytes(k, KT, sets), st, set,
+                           (const uint4 *)hidden, d, items, hdr, k, partials, floors, bounds, mask, perm, slabs);
+    };
+    if (k == 1) launch(project_gemm_lds_kernel<KT, MASKED, true, GATHER, false>);
+    else if (sets && !GATHER) launch(project_gemm_lds_kernel<KT, MASKED, false, GATHER, !GATHER>);
+    else launch(project_gemm_lds_kernel<KT, MASKED, false, GATHER, false>);
 }
 
 template <int KT>
 hipError_t allow_lds_bytes()
 {
-    const void *fns[] = {reinterpret_cast<const void *>(project_gemm_lds_kernel<KT, false, false, false>),
-                         reinterpret_cast<const void *>(project_gemm_lds_kernel<KT, false, true, false>),
-                         reinterpret_cast<const void *>(project_gemm_lds_kernel<KT, true, false, false>),
-                         reinterpret_cast<const void *>(project_gemm_lds_kernel<KT, true, true, false>),
-                         reinterpret_cast<const void *>(project_gemm_lds_kernel<KT, false, false, true>),
-                         reinterpret_cast<const void *>(project_gemm_lds_kernel<KT, false, true, true>)};
+    const void *fns[] = {reinterpret_cast<const void *>(project_gemm_lds_kernel<KT, false, false, false, false>),
+                         reinterpret_cast<const void *>(project_gemm_lds_kernel<KT, false, false, false, true>),
+                         reinterpret_cast<const void *>(project_gemm_lds_kernel<KT, false, true, false, false>),
+                         reinterpret_cast<const void *>(project_gemm_lds_kernel<KT, true, false, false, false>),
+                         reinterpret_cast<const void *>(project_gemm_lds_kernel<KT, true, false, false, true>),
+                         reinterpret_cast<const void *>(project_gemm_lds_kernel<KT, true, true, false, false>),
+                         reinterpret_cast<const void *>(project_gemm_lds_kernel<KT, false, false, true, false>),
+                         reinterpret_cast<const void *>(project_gemm_lds_kernel<KT, false, true, true, false>)};
     for (const void *f : fns) {
         const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (e != hipSuccess) return e;
@@ -636,11 +645,18 @@ hipError_t allow_lds_bytes()
 
 }  // namespace
 
-size_t vpk_project_rows_lds_bytes(int k, int kt)
+size_t vpk_project_rows_lds_bytes(int k, int kt, bool sets)
 {
     const int rows = 16 * lds_row_tiles(kt);
     return (size_t)rows * kt * (VP_TILE_BYTES / 16) + (size_t)k * rows * 8 + rows * 4 +
-           (trades_sets(k) ? (size_t)rows * VP_BOUND_SETS * 4 : 0);
+           (sets ? (size_t)rows * VP_BOUND_SETS * 4 : 0);
+}
+
+// Whether items trade the bests of sets in a plan of N rows in one bucket, cut into items of ntiles candidate groups each.
+bool vpk_project_rows_lds_trades_sets(int kt, int k, int N, int ntiles, int ncand)
+{
+    const int slots = 16 * lds_row_tiles(kt);
+    return trades_sets(kt, k, N < slots ? N : slots, N > slots, ntiles, ncand);
 }
 
 // Built for d_pad = 256 to 1536 (beyond, the rows of an item do not fit the LDS beside its lists).  The alternative at 768
@@ -668,17 +684,18 @@ hipError_t vpk_project_rows_lds_prepare()
 // mask: nullptr, or the membership lists of the masked full projection.  gather: the set's tiles
 // are the token-major copy of W and its ids the batch's union U (no mask then); the slab operands
 // are read through U instead of from a packed copy.  perm, and slabs, the clusters' own, are read only where the planner
-// chooses the form per cluster: a single-bucket plan keeps the rows in their own order.
+// chooses the form per cluster: a single-bucket plan keeps the rows in their own order.  sets: items may trade the bests of sets
+// (vpk_project_rows_lds_trades_sets).
 void vpk_project_rows_lds(const VpSlabSet &set, const void *hidden, int d, const int32_t *perm, const VpItem *items,
                           const VpPlanHeader *hdr, int grid_items, int k, float *partials, unsigned int *floors,
-                          unsigned int *bounds, const VpMaskInfo *mask, const VpSlabSet *slabs, bool gather, hipStream_t st)
+                          unsigned int *bounds, bool sets, const VpMaskInfo *mask, const VpSlabSet *slabs, bool gather, hipStream_t st)
 {
     const VpMaskInfo none = {nullptr, nullptr, 0};
 #define VP_LDS_CASE(KT)                                                                                                   \
     case KT:                                                                                                              \
-        if (mask) launch_lds<KT, true, false>(set, hidden, d, items, hdr, grid_items, k, partials, floors, bounds, *mask, perm, slabs ? *slabs : set, st); \
-        else if (gather) launch_lds<KT, false, true>(set, hidden, d, items, hdr, grid_items, k, partials, floors, bounds, none, nullptr, set, st); \
-        else launch_lds<KT, false, false>(set, hidden, d, items, hdr, grid_items, k, partials, floors, bounds, none, nullptr, set, st); \
+        if (mask) launch_lds<KT, true, false>(set, hidden, d, items, hdr, grid_items, k, partials, floors, bounds, sets, *mask, perm, slabs ? *slabs : set, st); \
+        else if (gather) launch_lds<KT, false, true>(set, hidden, d, items, hdr, grid_items, k, partials, floors, bounds, sets, none, nullptr, set, st); \
+        else launch_lds<KT, false, false>(set, hidden, d, items, hdr, grid_items, k, partials, floors, bounds, sets, none, nullptr, set, st); \
         break;
     switch (set.kt) {
         VP_LDS_CASE(8)

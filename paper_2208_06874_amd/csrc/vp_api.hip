@@ -330,14 +330,20 @@ inline int sb_tiles_per_wave(const vp_index *I, int N, int rgs, int row_tiles, i
     return vp_tiles_per_wave((long long)rgs * I->L.vtiles, sb_target(I, N, row_tiles, k), sb_min(I, N, row_tiles, k));
 }
 
+// whether the items of a plan that keeps all rows in one bucket, against the whole vocabulary, trade the bests of sets
+inline bool sb_trades_sets(const vp_index *I, int N, int k, int tpw)
+{
+    return vpk_project_rows_lds_trades_sets(I->L.kt, k, N, tpw * VP_WG_WAVES, I->V);
+}
+
 // Launches the projection kernel that goes with the plan's rows per item.
 void launch_single_bucket(const VpSlabSet &set, const vp_index *I, const void *hidden, const int32_t *perm,
-                          const VpItem *items, const VpPlanHeader *hdr, int N, int grid_items, int row_tiles, int k, int rstar,
+                          const VpItem *items, const VpPlanHeader *hdr, int N, int grid_items, int row_tiles, int k, bool sets, int rstar,
                           float *partials, unsigned int *floors, float *dbg_logits, const int64_t *dbg_row_off,
                           hipStream_t st)
 {
     if (use_gemm_lds(I, row_tiles, k))
-        vpk_project_rows_lds(set, hidden, I->d, perm, items, hdr, grid_items, k, partials, floors, vp_set_bounds(floors, N), nullptr, nullptr, false, st);
+        vpk_project_rows_lds(set, hidden, I->d, perm, items, hdr, grid_items, k, partials, floors, vp_set_bounds(floors, N), sets, nullptr, nullptr, false, st);
     else if (row_tiles == 4)
         vpk_project_gemm(set, hidden, I->d, perm, items, hdr, grid_items, k, partials, vp_set_bounds(floors, N), nullptr, st);
     else
@@ -480,11 +486,13 @@ vp_status run_clustered(const char *fn, const vp_index *I, const void *hidden, i
     // the planner may mask some clusters only (workgroups beyond that have to be handed out to leave at once:
     // 5 us for 2,048 of them)
     int grid_full = 0;
+    bool sets = false;   // (asked as if all rows were masked: what a plan of several forms holds only the device knows)
     if (dispatch) {
         const int rgs = ceil_div(N, dispatch);
         const int tpw = sb_tiles_per_wave(I, N, rgs, rt_masked, k);
         const int chunks = ceil_div(I->L.vtiles, (long)tpw * VP_WG_WAVES);
         grid_full = (rgs > 1 && chunks >= 8) ? ceil_div(chunks, 8) * 8 * rgs : chunks * rgs;
+        sets = sb_trades_sets(I, N, k, tpw);
         if (mix.slots) {
             grid_full = ceil_div(std::max(grid_full, I->gemm_lds_items), 8) * 8;
             // (the grouped items aimed at, and a partly filled one per row group of a bucket of 33 rows and more)
@@ -508,7 +516,7 @@ vp_status run_clustered(const char *fn, const vp_index *I, const void *hidden, i
         // launched as well; one of the two does the work, or each its clusters' share, as the planner decided
         const VpMaskInfo mask = {g, I->bitmaps, I->L.bm_words};
         if (use_gemm_lds(I, rt_masked, k))
-            vpk_project_rows_lds(I->full, hidden, I->d, perm, items, hdr, grid_full, k, partials, floors, vp_set_bounds(floors, N), &mask, &I->clusters, false, st);
+            vpk_project_rows_lds(I->full, hidden, I->d, perm, items, hdr, grid_full, k, partials, floors, vp_set_bounds(floors, N), sets, &mask, &I->clusters, false, st);
         else if (rt_masked == 4)
             vpk_project_gemm(I->full, hidden, I->d, perm, items, hdr, grid_full, k, partials, vp_set_bounds(floors, N), &mask, st);
         else
@@ -546,7 +554,7 @@ vp_status run_full(const char *fn, const vp_index *I, const void *hidden, int N,
     const int grid_items = (rgs > 1 && chunks >= 8) ? ceil_div(chunks, 8) * 8 * rgs : chunks * rgs;
     auto *ev = profile_slot(I);
     if (ev) (void)hipEventRecord(ev->first, st);
-    launch_single_bucket(I->full, I, hidden, perm, items, hdr, N, grid_items, row_tiles, k, N <= I->rstar ? I->rstar : 0,
+    launch_single_bucket(I->full, I, hidden, perm, items, hdr, N, grid_items, row_tiles, k, sb_trades_sets(I, N, k, tpw), N <= I->rstar ? I->rstar : 0,
                          partials, floors, dbg_logits, dbg_row_off, st);
     if (ev) (void)hipEventRecord(ev->second, st);
     if (out_ids)
@@ -1046,11 +1054,11 @@ vp_status vp_project_union(const vp_index *I, const void *hidden, int32_t N, int
     const int grid_items = std::min(max_items, ceil_div(rgs * (long)ceil_div(I->L.vtiles, VP_WG_WAVES), 8) * 8 + 8 * rgs);
     if (fused_gather) {
         uset.tiles = I->arena + I->L.wt;
-        vpk_project_rows_lds(uset, hidden, I->d, perm, items, hdr, grid_items, k, partials, floors, vp_set_bounds(floors, N), nullptr, nullptr, true, st);
+        vpk_project_rows_lds(uset, hidden, I->d, perm, items, hdr, grid_items, k, partials, floors, vp_set_bounds(floors, N), false, nullptr, nullptr, true, st);
     } else {
         vpk_union_gather(I->arena + I->L.wt, I->L.kt, uids, uh, I->L.vtiles, uslab, st);
         uset.tiles = uslab;
-        launch_single_bucket(uset, I, hidden, perm, items, hdr, N, grid_items, row_tiles_u, k, 0, partials, floors,
+        launch_single_bucket(uset, I, hidden, perm, items, hdr, N, grid_items, row_tiles_u, k, false, 0, partials, floors,
                              nullptr, nullptr, st);
     }
     if (allow_full) {
@@ -1060,7 +1068,7 @@ vp_status vp_project_union(const vp_index *I, const void *hidden, int32_t N, int
         const int grid_full = (rgs > 1 && chunks >= 8) ? ceil_div(chunks, 8) * 8 * rgs : chunks * rgs;
         const VpMaskInfo umask = {zero_g, mask, 0};   // every row reads list 0: the boolean list of the batch
         if (use_gemm_lds(I, row_tiles_u, k))
-            vpk_project_rows_lds(I->full, hidden, I->d, perm, items, hdr, grid_full, k, partials, floors, vp_set_bounds(floors, N), &umask, nullptr, false, st);
+            vpk_project_rows_lds(I->full, hidden, I->d, perm, items, hdr, grid_full, k, partials, floors, vp_set_bounds(floors, N), sb_trades_sets(I, N, k, tpw), &umask, nullptr, false, st);
         else if (row_tiles_u == 4)
             vpk_project_gemm(I->full, hidden, I->d, perm, items, hdr, grid_full, k, partials, vp_set_bounds(floors, N), &umask, st);
         else

@@ -60,13 +60,14 @@ void vpk_project_gemm(const VpSlabSet &set, const void *hidden, int d, const int
                       const VpMaskInfo *mask, hipStream_t st);
 
 // the same with the 64 rows of an item (48 at d_pad 1536) held in LDS; floors: [N] per-row bounds, bounds: [N][VP_BOUND_SETS]
-size_t vpk_project_rows_lds_bytes(int k, int kt);
+size_t vpk_project_rows_lds_bytes(int k, int kt, bool sets);
+bool vpk_project_rows_lds_trades_sets(int kt, int k, int N, int ntiles, int ncand);
 bool vpk_project_rows_lds_supported(int kt, int k);
 int vpk_project_rows_lds_row_tiles(int kt);
 hipError_t vpk_project_rows_lds_prepare();
 void vpk_project_rows_lds(const VpSlabSet &set, const void *hidden, int d, const int32_t *perm, const VpItem *items,
                           const VpPlanHeader *hdr, int grid_items, int k, float *partials, unsigned int *floors,
-                          unsigned int *bounds, const VpMaskInfo *mask, const VpSlabSet *slabs, bool gather, hipStream_t st);
+                          unsigned int *bounds, bool sets, const VpMaskInfo *mask, const VpSlabSet *slabs, bool gather, hipStream_t st);
 
 // per-row merge
 size_t vpk_merge_lds_bytes(int k);

@@ -56,3 +56,15 @@ def test_many_row_kernel_is_launched_where_it_may_win(launches, d, V, K, lo, hi,
     grid = [n for name, n in got.items() if "project_gemm_lds_kernel" in name]
     assert len(grid) == 1 and len(got) == 5, got
     assert (grid[0] >= 512 + 256) == grouped, grid
+
+
+# the many-row kernel that trades the bests of sets of candidates (project_gemm_lds_kernel's last template argument) only where items
+# of the call may trade: not for lists of another length, not with few rows of an item, nor in few ranges of candidates
+@pytest.mark.parametrize("d,V,K,lo,hi,k,N,trades", [
+    (1024, 128000, 200, 5000, 8000, 8, 64, True), (1024, 250000, 1000, 10000, 20000, 8, 256, True),
+    (1024, 250000, 1000, 10000, 20000, 8, 1024, False), (1024, 128000, 200, 5000, 8000, 8, 32, False),
+    (1024, 128000, 200, 5000, 8000, 3, 64, False), (1024, 128000, 200, 5000, 8000, 1, 64, False)])
+def test_kernel_that_trades_is_launched_only_where_items_trade(launches, d, V, K, lo, hi, k, N, trades):
+    got = [name for name in launches(d, V, K, lo, hi, k, N) if "project_gemm_lds_kernel" in name]
+    assert len(got) == 1
+    assert ("ELb%dEEEv" % trades) in got[0], got
