@@ -60,26 +60,9 @@ constexpr int L_NW = 8;        // wavefronts per workgroup
 // row tiles per item: four (64 rows), or three where four do not fit the LDS (48 rows: 120 KiB at d_pad = 1280,
 // 144 KiB at 1536)
 constexpr int lds_row_tiles(int kt) { return kt > 32 ? 3 : 4; }
-// Candidate groups per step: four (one 1 KiB read of the rows from LDS per four MFMAs), one for short items (brief_to), and two where
-// one row group alone reads the bytes and its items are at most 32 groups (64 at top-1): with four a wavefront has one step there, and
-// all of them fold at the end, behind the last load.  d = 1024, one row group, four -> two: V = 128,000 (32 groups), 64 rows, top-1
-// 60.6 -> 58.1, masked top-8 with its call 83.8 -> 79.9; V = 200,000 (49), top-1 82.5 -> 77.9; V = 180,000 (44), top-3 76 -> 79.
+// Candidate groups per step: four (one 1 KiB read of the rows from LDS per four MFMAs), one or two for short items (vp_step_groups).
 // About 16 KiB per wavefront are kept in flight either way.
 constexpr int lds_k_tiles_in_flight(int kt, int g) { return g == 4 ? 4 : g == 2 ? 8 : kt % 16 == 0 ? 16 : 8; }
-// The largest item that takes steps of one group.  In steps of four its wavefronts are partly without work, and the others have a
-// long chain of loads; in steps of one every group pays for a fold, and lists of more than one entry for their upkeep.
-// Full projection, time in steps of four / of one by groups per item: d = 1024, top-1, one row group: 4: 1.15, 8: 1.03, 15: 1.10, 20:
-// 1.04, 28: 1.04, and four row groups alike.  Lists of a few entries, several row groups (whose workgroups wait for the
-// same bytes): d = 1024, four of them, top-4: 4: 1.30, 8: 1.27, 12: 1.03, 20: 0.97, 28: 0.90; top-8: 1.46, 1.30, 1.05, 0.93, 0.83; two
-// of them, top-2: 1.22, 1.11, 0.94, 0.96, 0.92; d = 256 and 512 alike (at 28, top-8: 0.85, 0.80).  One row group, top-4, 24 rows: d =
-// 1024: 12: 1.03, 15: 1.04, 20: 1.05, 28: 1.05; d = 768: 1.00, 0.95, 1.03, 1.03; d = 512: 0.94, 1.01, 0.93, 0.97; d = 256: 0.94, 0.88, 0.91,
-// 0.88.  d = 1280 and 1536: 8: 1.11, 1.10, 12: 0.97, 0.99, beyond 16 0.98 at top-8.
-__host__ __device__ constexpr int brief_to(int kt, bool shared, int k)
-{
-    if (k == 1) return (kt > 32 ? 2 : 4) * L_NW - 1;
-    if (shared) return k > 2 ? 12 : L_NW;
-    return kt > 32 ? 2 * L_NW - 1 : kt >= 24 ? 4 * L_NW - 1 : L_NW;
-}
 // Whether an item trades the bests of sets (top of the file).  The host asks the same of a plan's longest item: the code that
 // trades is compiled into kernels of its own (SETS), because where it stood in every list kernel the registers it takes were
 // lost to the calls that never trade (masked, d_pad = 1024: 20 vector registers spilled and
@@ -88,7 +71,7 @@ __host__ __device__ constexpr int brief_to(int kt, bool shared, int k)
 constexpr int SET_ITEMS = 24, SET_GROUPS = 144;
 __host__ __device__ constexpr bool trades_sets(int kt, int k, int nrows, bool shared, int ntiles, int ncand)
 {
-    return k >= 4 && k <= VP_BOUND_SETS && 4 * nrows >= 3 * 16 * lds_row_tiles(kt) && ntiles > brief_to(kt, shared, k) &&
+    return k >= 4 && k <= VP_BOUND_SETS && 4 * nrows >= 3 * 16 * lds_row_tiles(kt) && vp_step_groups(kt, k, shared, ntiles) != 1 &&
            (!shared || ntiles >= SET_GROUPS) && (long long)ntiles * (VP_TILE_ITEMS * SET_ITEMS) <= ncand;
 }
 constexpr int VP_MAX_TOPK_LANES = 32;   // the epilogue writes a row's list with one lane per entry
@@ -600,13 +583,13 @@ __global__ __launch_bounds__(L_NW * 64) void project_gemm_lds_kernel(
         if (hdr->mode == 1) perm = nullptr;   // the whole batch, in its own order
     }
     const int kk = TOP1 ? 1 : k;
-    const bool brief = item.ntiles <= brief_to(KT, item.shared, kk);
+    const int groups = vp_step_groups(KT, kk, item.shared, item.ntiles);
     if (item.shared || GATHER) {
-        if (brief) gemm_lds_item<KT, 1, MASKED, false, TOP1, GATHER, false>(set, hidden, d, item, it, kk, partials, floors, bounds, mask, perm);
+        if (groups == 1) gemm_lds_item<KT, 1, MASKED, false, TOP1, GATHER, false>(set, hidden, d, item, it, kk, partials, floors, bounds, mask, perm);
         else gemm_lds_item<KT, 4, MASKED, false, TOP1, GATHER, SETS>(set, hidden, d, item, it, kk, partials, floors, bounds, mask, perm);
     } else {
-        if (brief) gemm_lds_item<KT, 1, MASKED, true, TOP1, false, false>(set, hidden, d, item, it, kk, partials, floors, bounds, mask, perm);
-        else if (item.ntiles <= (TOP1 ? 8 : 4) * L_NW) gemm_lds_item<KT, 2, MASKED, true, TOP1, false, SETS>(set, hidden, d, item, it, kk, partials, floors, bounds, mask, perm);
+        if (groups == 1) gemm_lds_item<KT, 1, MASKED, true, TOP1, false, false>(set, hidden, d, item, it, kk, partials, floors, bounds, mask, perm);
+        else if (groups == 2) gemm_lds_item<KT, 2, MASKED, true, TOP1, false, SETS>(set, hidden, d, item, it, kk, partials, floors, bounds, mask, perm);
         else gemm_lds_item<KT, 4, MASKED, true, TOP1, false, SETS>(set, hidden, d, item, it, kk, partials, floors, bounds, mask, perm);
     }
 }

@@ -194,6 +194,32 @@ static inline __host__ __device__ int vp_tiles_per_wave_units(long long total_ti
     return (int)(one_round > tpw ? one_round : tpw);
 }
 
+// Candidate groups per step of the many-row kernel (project_gemm_lds.hip; eight wavefronts) for an item of ntiles groups: four; one
+// or two in short items, where steps of four leave wavefronts without work, or all of them with one step, whose folds then run at
+// the same time behind the last load.  Every step pays for a fold, and lists of more than one entry for their upkeep.
+// One against four, time in steps of four / of one by groups per item, full projection: d = 1024, top-1, one row group: 4: 1.15, 8: 1.03,
+// 15: 1.10, 20: 1.04, 28: 1.04, and four row groups alike.  Lists of a few entries, several row groups (whose workgroups wait for the
+// same bytes): d = 1024, four of them, top-4: 4: 1.30, 8: 1.27, 12: 1.03, 20: 0.97, 28: 0.90; top-8: 1.46, 1.30, 1.05, 0.93, 0.83; two
+// of them, top-2: 1.22, 1.11, 0.94, 0.96, 0.92; d = 256 and 512 alike (at 28, top-8: 0.85, 0.80).  One row group, top-4, 24 rows: d =
+// 1024: 12: 1.03, 15: 1.04, 20: 1.05, 28: 1.05; d = 768: 1.00, 0.95, 1.03, 1.03; d = 512: 0.94, 1.01, 0.93, 0.97; d = 256: 0.94, 0.88, 0.91,
+// 0.88.  d = 1280 and 1536: 8: 1.11, 1.10, 12: 0.97, 0.99, beyond 16 0.98 at top-8.
+// Two, where one row group alone reads the bytes; the call, all row slots in use, us in steps of four -> two by groups per item.
+// Top-1: d = 256: 32: 31.6 -> 28.2, 64: 39.4 -> 36.9; 512: 48: 50.6 -> 47.8, 64: 62.3 -> 59.7; 768: 32: 49.2 -> 47.9; 1024: 32: 62.9 -> 60.6, 48: 85.4 ->
+// 81.1, 64: 102.3 -> 98.3; 1280: 16: 41.5 -> 41.6 (24 rows 5 % slower; of one 39.4), 20: 49.5 -> 48.2, 32: 67.5 -> 66.3; 1536: 16: 49.1 -> 47.5, 32: 83.9 -> 80.0.
+// Top-3: d = 256: 12: 26.2 -> 24.7, 16: 27.1 -> 26.4, 24: 30.0 -> 33.8, 28: 31.2 -> 36.4, 32: 37.2 -> 40.4; 512: 12: 29.5 -> 28.5, 16: 35.2 -> 32.6, 24:
+// 38.1 -> 39.4, 32: 48.7 -> 53.3; 768: 32: 53.4 -> 56.2; 1024: 32: 66.8 -> 66.7, 40: 76.0 -> 71.3, 48: 89.5 -> 83.7, 64: 106.6 -> 104.5; 1280: 16: 45.5 ->
+// 44.7, 20: 52.5 -> 51.8, 24: 58.2 -> 59.3, 32: 71.7 -> 72.4; 1536: 16: 52.4 -> 50.0, 24: 66.8 -> 66.4, 32: 86.9 -> 85.1, 36: 90.5 -> 91.4; longer lists alike.
+static inline __host__ __device__ constexpr int vp_step_groups(int kt, int k, bool shared, int ntiles)
+{
+    if (k == 1) {
+        if (ntiles < (kt <= 32 ? 32 : kt == 40 && !shared ? 20 : 16)) return 1;
+        return !shared && ntiles <= 64 ? 2 : 4;
+    }
+    if (shared) return ntiles <= (k > 2 ? 12 : 8) ? 1 : 4;
+    if (ntiles <= (kt > 32 ? 15 : kt >= 24 ? 31 : 8)) return 1;
+    return ntiles <= (kt <= 16 ? 16 : kt == 24 ? 0 : kt == 32 ? 64 : kt == 40 ? 20 : 32) ? 2 : 4;
+}
+
 // The workgroup -> item maps behind VpPlanHeader.swz_rgs (wg = the workgroup's index in the grid;
 // workgroups are handed to the 8 XCDs in turn).  Every item in [0, total_items) is taken by exactly
 // one workgroup of a grid that is large enough (total_items + 8 blocks for the first map, the chunk

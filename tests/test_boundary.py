@@ -271,6 +271,23 @@ def test_item_count_of_many_row_groups(layout):
             assert items // rgs % 8 == 0, (rgs, vtiles, kt, items)
 
 
+def test_candidate_groups_per_step_of_the_many_row_kernel(layout):
+    """Steps of one, two and four groups as items get longer, two where one row group alone reads the bytes only; each line of two
+    holds for a range of item lengths (plans cut items in multiples of four groups), not for a single one, and not where
+    steps of two leave wavefronts with one step more than others (20 to 28 groups of d_pad = 256 and 512)."""
+    for kt in (8, 16, 24, 32, 40, 48):
+        for k in (1, 2, 3, 4, 8, 9, 32):
+            for shared in (0, 1):
+                by_length = {n: layout.shim_step_groups(kt, k, shared, n) for n in range(1, 400)}
+                assert set(by_length.values()) <= {1, 2, 4} and by_length[1] == 1 and by_length[399] == 4
+                assert all(by_length[n] <= by_length[n + 1] for n in range(1, 399))
+                twos = [n for n in range(4, 400, 4) if by_length[n] == 2]
+                assert not (shared and twos) and len(twos) != 1, (kt, k, twos)
+                if k > 1 and not shared:
+                    edges = {8: (12, 16), 16: (12, 16), 24: None, 32: (32, 64), 40: (16, 20), 48: (16, 32)}[kt]
+                    assert (twos[0], twos[-1]) == edges if edges else not twos, (kt, k, twos)
+
+
 def test_event_total_of_the_largest_training_call(layout):
     """Every vector that moves is two events.  From 2^30 vectors that move on their total does not fit 31 bits; it must
     still be seen to be more than the n entries of the event list."""

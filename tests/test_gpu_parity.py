@@ -1429,6 +1429,28 @@ def test_merge_of_equal_logits_over_many_parts(oracle, k):
         pu.check_full(oracle, W, b, H, k, *got)
 
 
+@pytest.mark.parametrize("d,groups", [(256, 16), (256, 20), (512, 12), (768, 32), (1024, 64), (1024, 68), (1280, 20), (1280, 24),
+                                      (1536, 32), (1536, 36)])
+def test_steps_of_one_two_and_four_groups(oracle, d, groups):
+    """Single row groups at both sides of the lines between steps of one, two and four candidate groups, plain and masked: a last
+    item of another length, rows and candidates that fill no tile, d inside a k-tile."""
+    items, N = 5, 33
+    V = 16 * groups * items - 16 * 6 - 3
+    r, W, b, C = _small_model(500 + d + groups, d - 8, V, 3)
+    off, ids = _random_lists(r, 3, V, V // 3, V // 2)
+    B = Built(W, b, C, off, ids, k_max=9)
+    B.index.set_option("gemm_lds_items", items)
+    H = _rows(r, C, N)
+    for k in (1, 2, 9):
+        got = B.project_full(H, k)
+        ws = B.index.workspace(N)[:64].view(_torch().int32)
+        assert ws[0].item() == items and ws[1].item() * 4 == groups
+        pu.check_full(oracle, W, b, H, k, *got)
+        got, mode, ovf = _masked(B, H, k)
+        assert mode == 1 and ovf == 0
+        pu.check_projection(oracle, W, b, C, off, ids, H, k, *got)
+
+
 @pytest.mark.parametrize("d,N,groups,items", [(256, 64, 36, 26), (1024, 64, 36, 25), (256, 128, 144, 24), (256, 20, 36, 10)])
 def test_nan_candidate_costs_no_other_candidate_its_place(oracle, d, N, groups, items):
     """One token's bias is NaN (its logit is, and so is the row's log-sum-exp); eight others are far ahead of all the rest, one
