@@ -36,15 +36,10 @@
 // behind the first step's MFMAs, before anything is inserted, the workgroups trade the best logits seen of eight sets that the row's
 // candidates fall into (by lane quarter and the wavefront's parity): the k-th largest of the eight cannot be above the row's k-th
 // best, and 64 items know it of 32,768 candidates at once.  It costs one wait for memory per item; after steps 1, 2 and 4 the
-// sets are traded again without waiting, later on the k-th bests as elsewhere.  Full projection, d = 1024, us per call without ->
-// with it: V = 250,000 (256 to 32 items a row), top-8: 128 rows 134 -> 122, 256: 182 -> 170, 333: 239 -> 224, 512: 286 -> 274;
-// V = 200,000, 64 rows, top-4 89 -> 84, top-8 97 -> 86.  Not used where it costs more than it saves:
-//   fewer than SET_ITEMS items a row: little to learn (from 1,024 rows on; top-3 1 % slower);
-//   top-2, top-3: few insertions either way (within 2 %);
-//   few rows of an item: every atomic still waits for 256 workgroups' (17 rows, V = 128,000, top-3: 60 -> 64);
-//   short items of several row groups, which all wait at once while the loads run dry: 256 rows, V = 128,000, 125 groups an item,
-//   top-4 87 -> 96, but 156 groups 108 -> 103; one row group: 32 groups 66 -> 63;
-//   gathered columns (the union): 40 rows 1 % slower for the registers it takes.
+// sets are traded again without waiting, later on the k-th bests as elsewhere.  Which calls do, vp_trades_sets says; the code
+// is compiled into kernels of its own (SETS), because in every list kernel the registers it takes were lost to the calls that never trade
+// (masked, d_pad = 1024: 20 vector registers spilled and 72 scalar ones, without it none and 26; 64 rows, V = 200,000, d = 768, masked
+// top-2: 90 us with it, 81 without).  Not for gathered columns (the union): 40 rows 1 % slower for the registers.
 // The sets of a row are in one line (vp_set_bounds): with N * 4 bytes of bounds in front of them 60 rows took 68 us, not 63.
 // Keeping the candidates in an unsorted queue instead of the cascade: 5 to 20 % slower (registers, and the queue's overflow);
 // fewer atomics and plain loads of the sets: 40 us slower (the loads wait behind every atomic on their line).
@@ -63,17 +58,6 @@ constexpr int lds_row_tiles(int kt) { return kt > 32 ? 3 : 4; }
 // Candidate groups per step: four (one 1 KiB read of the rows from LDS per four MFMAs), one or two for short items (vp_step_groups).
 // About 16 KiB per wavefront are kept in flight either way.
 constexpr int lds_k_tiles_in_flight(int kt, int g) { return g == 4 ? 4 : g == 2 ? 8 : kt % 16 == 0 ? 16 : 8; }
-// Whether an item trades the bests of sets (top of the file).  The host asks the same of a plan's longest item: the code that
-// trades is compiled into kernels of its own (SETS), because where it stood in every list kernel the registers it takes were
-// lost to the calls that never trade (masked, d_pad = 1024: 20 vector registers spilled and
-// 72 scalar ones, without it none and 19; 64 rows, V = 200,000, d = 768, masked top-2: 90 us with it, 81
-// without).
-constexpr int SET_ITEMS = 24, SET_GROUPS = 144;
-__host__ __device__ constexpr bool trades_sets(int kt, int k, int nrows, bool shared, int ntiles, int ncand)
-{
-    return k >= 4 && k <= VP_BOUND_SETS && 4 * nrows >= 3 * 16 * lds_row_tiles(kt) && vp_step_groups(kt, k, shared, ntiles) != 1 &&
-           (!shared || ntiles >= SET_GROUPS) && (long long)ntiles * (VP_TILE_ITEMS * SET_ITEMS) <= ncand;
-}
 constexpr int VP_MAX_TOPK_LANES = 32;   // the epilogue writes a row's list with one lane per entry
 
 // The k-th largest of a row's eight keys (k = 1 .. 8; a sorting network of 19 compare-exchanges).
@@ -217,8 +201,7 @@ __device__ inline void gemm_lds_item(const VpSlabSet &set, const uint4 *__restri
     if (tid < L_ROWS)
         wg_floor[tid] = !TOP1 && tid < item.nrows ? floors[MASKED && perm ? perm[item.perm_start + tid] : item.perm_start + tid]
                                                   : VP_FLOOR_NONE;
-    // whether the sets' bests are traded: top of the file
-    const bool sets = SETS && L_G != 1 && trades_sets(KT, k, item.nrows, item.shared, item.ntiles, ncand);
+    const bool sets = SETS && L_G != 1 && vp_item_trades_sets(item.nrows, L_ROWS, item.ntiles, ncand);
     if (sets)
         for (int e = tid; e < L_ROWS * VP_BOUND_SETS; e += L_NW * 64) set_best[e] = VP_FLOOR_NONE;
     __syncthreads();
@@ -635,13 +618,6 @@ size_t vpk_project_rows_lds_bytes(int k, int kt, bool sets)
            (sets ? (size_t)rows * VP_BOUND_SETS * 4 : 0);
 }
 
-// Whether items trade the bests of sets in a plan of N rows in one bucket, cut into items of ntiles candidate groups each.
-bool vpk_project_rows_lds_trades_sets(int kt, int k, int N, int ntiles, int ncand)
-{
-    const int slots = 16 * lds_row_tiles(kt);
-    return trades_sets(kt, k, N < slots ? N : slots, N > slots, ntiles, ncand);
-}
-
 // Built for d_pad = 256 to 1536 (beyond, the rows of an item do not fit the LDS beside its lists).  The alternative at 768
 // and 1280, items of 16 rows, reads W once per 16 rows through the L2; full projection, V = 150,000, top-3, us per call,
 // those -> this kernel: d = 768, N = 17: 102 -> 50, 64: 119 -> 55, 256: 216 -> 82, 1,024: 660 -> 227, 8,192: 6,290 -> 1,667;
@@ -668,7 +644,7 @@ hipError_t vpk_project_rows_lds_prepare()
 // are the token-major copy of W and its ids the batch's union U (no mask then); the slab operands
 // are read through U instead of from a packed copy.  perm, and slabs, the clusters' own, are read only where the planner
 // chooses the form per cluster: a single-bucket plan keeps the rows in their own order.  sets: items may trade the bests of sets
-// (vpk_project_rows_lds_trades_sets).
+// (vp_trades_sets).
 void vpk_project_rows_lds(const VpSlabSet &set, const void *hidden, int d, const int32_t *perm, const VpItem *items,
                           const VpPlanHeader *hdr, int grid_items, int k, float *partials, unsigned int *floors,
                           unsigned int *bounds, bool sets, const VpMaskInfo *mask, const VpSlabSet *slabs, bool gather, hipStream_t st)

@@ -333,7 +333,7 @@ inline int sb_tiles_per_wave(const vp_index *I, int N, int rgs, int row_tiles, i
 // whether the items of a plan that keeps all rows in one bucket, against the whole vocabulary, trade the bests of sets
 inline bool sb_trades_sets(const vp_index *I, int N, int k, int tpw)
 {
-    return vpk_project_rows_lds_trades_sets(I->L.kt, k, N, tpw * VP_WG_WAVES, I->V);
+    return vp_trades_sets(I->L.kt, k, N, VP_ROWS_PER_ITEM * vpk_project_rows_lds_row_tiles(I->L.kt), tpw * VP_WG_WAVES, I->V);
 }
 
 // Launches the projection kernel that goes with the plan's rows per item.

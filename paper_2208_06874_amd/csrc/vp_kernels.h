@@ -61,7 +61,6 @@ void vpk_project_gemm(const VpSlabSet &set, const void *hidden, int d, const int
 
 // the same with the 64 rows of an item (48 at d_pad 1536) held in LDS; floors: [N] per-row bounds, bounds: [N][VP_BOUND_SETS]
 size_t vpk_project_rows_lds_bytes(int k, int kt, bool sets);
-bool vpk_project_rows_lds_trades_sets(int kt, int k, int N, int ntiles, int ncand);
 bool vpk_project_rows_lds_supported(int kt, int k);
 int vpk_project_rows_lds_row_tiles(int kt);
 hipError_t vpk_project_rows_lds_prepare();

@@ -220,6 +220,36 @@ static inline __host__ __device__ constexpr int vp_step_groups(int kt, int k, bo
     return ntiles <= (kt <= 16 ? 16 : kt == 24 ? 0 : kt == 32 ? 64 : kt == 40 ? 20 : 32) ? 2 : 4;
 }
 
+// Whether the items of the many-row kernel trade the bests of sets of candidates before the first list entry (project_gemm_lds.hip), for N
+// rows in one bucket, `slots` to an item, cut into items of ntiles candidate groups.  Of an item: most of its row slots in use (every
+// atomic waits for those of all items of the row: 17 rows, V = 128,000, top-3: 60 us, 64 with the trade) and 24 items or more
+// a row (below, from 1,024 rows on, there is little to learn).
+static inline __host__ __device__ constexpr bool vp_item_trades_sets(int nrows, int slots, int ntiles, int ncand)
+{
+    return 4 * nrows >= 3 * slots && (long long)ntiles * (VP_TILE_ITEMS * 24) <= ncand;
+}
+// Of a call: top-4 to top-8 (fewer entries cost few insertions, more than eight sets do not bound).  Full projection, us without -> with it:
+// Several row groups (their workgroups run side by side and the trade's wait is hidden): d = 256, V = 100,000, 256 rows: top-4 43.4 -> 37.5,
+// top-7 51.8 -> 43.3; V = 250,000, 384 rows: 85.4 -> 77.7, 104.3 -> 89.6; d = 512, V = 250,000, 192 rows: 80.1 -> 70.3, 93.0 -> 76.1; d = 1024, V =
+// 100,000, 256 rows (items of 100 groups): 76.5 -> 73.0, 84.8 -> 76.8, 192 rows: 71.2 -> 61.8, 78.6 -> 67.1.  Two row groups at top-4 and top-5: d =
+// 1024 0 to 5 % slower, masked 0 to 9 %.  d = 1280 and 1536: top-4 0 to 4 % slower, longer lists within 2 %.
+// One row group (HBM sets the pace, and the wait shows unless the bound is worth a step of every wavefront): top-7 and top-8 up to d_pad = 512
+// and at 1024 (d = 256, top-8, 48 groups an item: 51.8 -> 46.5; 512: 62.8 -> 59.8; 1024: 91.1 -> 87.1); shorter lists only where every
+// wavefront has two steps or nearly (d = 1024, 32 groups, top-4: 69.3 -> 65.0, 36: 68.6 -> 70.4; d = 512, 64 groups: 71.9 -> 67.9, 36: 50.0 ->
+// 52.1; d = 256, 36: 38.4 -> 40.6); d = 1536 from there on (48 groups, top-4 115.5 -> 113.7, top-8 119.4 -> 115.3; 16 groups, top-4 5 % slower); not
+// at d_pad = 768 (36 groups: top-4 58.0 -> 63.0, top-8 63.7 -> 67.1, masked 8 to 14 % slower), nor at 1280 (36 groups: 78.4 -> 82.6, 82.8 -> 85.4)
+// but for top-7 and top-8 in steps of two.
+static inline bool vp_trades_sets(int kt, int k, int N, int slots, int ntiles, int ncand)
+{
+    const int rgs = (N + slots - 1) / slots, groups = vp_step_groups(kt, k, rgs > 1, ntiles);
+    if (k < 4 || k > VP_BOUND_SETS || groups == 1 || !vp_item_trades_sets(rgs > 1 ? slots : N, slots, ntiles, ncand)) return false;
+    if (rgs > 1) return kt <= 32 && (rgs > 2 || k > 5);
+    const int steps = (ntiles + groups - 1) / groups;
+    if (kt == 48) return steps > 12;
+    if (kt == 40) return k > 6 && groups == 2;
+    return kt != 24 && (k > 6 || (kt >= 16 && steps > 12 && steps <= 16));
+}
+
 // The workgroup -> item maps behind VpPlanHeader.swz_rgs (wg = the workgroup's index in the grid;
 // workgroups are handed to the 8 XCDs in turn).  Every item in [0, total_items) is taken by exactly
 // one workgroup of a grid that is large enough (total_items + 8 blocks for the first map, the chunk

@@ -288,6 +288,29 @@ def test_candidate_groups_per_step_of_the_many_row_kernel(layout):
                     assert (twos[0], twos[-1]) == edges if edges else not twos, (kt, k, twos)
 
 
+def test_which_calls_trade_the_bests_of_sets(layout):
+    """Not outside top-4 to top-8, with few rows of an item, below 24 items a row, or in items in steps of one group; several row
+    groups up to d_pad = 1024, two from top-6 on; one row group of d_pad = 768 never (14 % slower there)."""
+    trades = layout.shim_trades_sets
+    V = 10 ** 6
+    for kt in (8, 16, 24, 32, 40, 48):
+        slots = 64 if kt <= 32 else 48
+        for ntiles in range(4, 1000, 4):
+            for N in (1, slots // 2, slots * 3 // 4, slots, slots + 1, 2 * slots, 3 * slots, 9 * slots):
+                by_k = [k for k in range(1, 33) if trades(kt, k, N, slots, ntiles, V)]
+                assert all(4 <= k <= 8 for k in by_k) and by_k == list(range(by_k[0], 9) if by_k else ())
+                if N < slots * 3 // 4 or ntiles * 16 * 24 > V or layout.shim_step_groups(kt, 4, N > slots, ntiles) == 1:
+                    assert not by_k
+                elif N > slots:
+                    assert by_k == ([] if kt > 32 else [6, 7, 8] if N <= 2 * slots else [4, 5, 6, 7, 8])
+                elif kt == 24:
+                    assert not by_k
+    for kt, ntiles, first in ((8, 64, 7), (16, 36, 7), (16, 56, 4), (32, 32, 4), (32, 36, 7), (40, 20, 7), (40, 24, None), (48, 24, None), (48, 28, 4),
+                              (48, 48, None), (48, 52, 4)):
+        by_k = [k for k in range(1, 33) if trades(kt, k, 48, 64 if kt <= 32 else 48, ntiles, V)]
+        assert by_k == ([] if first is None else list(range(first, 9))), (kt, ntiles, by_k)
+
+
 def test_event_total_of_the_largest_training_call(layout):
     """Every vector that moves is two events.  From 2^30 vectors that move on their total does not fit 31 bits; it must
     still be seen to be more than the n entries of the event list."""

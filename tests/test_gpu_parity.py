@@ -1352,17 +1352,46 @@ def test_index_without_the_token_major_copy(oracle):
     assert e.value.status == vp.VP_ERR_UNSUPPORTED and "NO_UNION" in str(e.value)
 
 
-@pytest.mark.parametrize("d,N,groups,items", [(256, 64, 36, 26), (1024, 47, 36, 26), (1024, 60, 28, 25), (1536, 37, 36, 24), (256, 127, 144, 24),
-                                              (256, 64, 64, 24)])
-def test_bests_of_sets_traded_between_many_items(oracle, d, N, groups, items):
-    """Rows whose candidates are spread over many items (24 and more trade the bests of eight sets of candidates, fewer do not;
-    top-4 to top-8 only, three quarters of the row slots in use): equal logits in every set and item, a row with a few
-    candidates only, a last item in which wavefronts have no step, steps of two groups and of four, plain and masked, twice
-    to the bit."""
+VP_FLOOR_NONE = 0x007fffff
+
+
+def _rows_that_traded(index, N, K):
+    """(rows whose items traded the bests of sets in the last many-row call, the plan's records by position) from the workspace: the
+    planner sets a row's eight bounds to the key of -infinity, a trade raises those of the sets that have a candidate."""
+    ws = index.workspace(N)
+    up = lambda x: (x + 255) // 256 * 256
+    at = 256 + up(N * ((K + 15) // 16) * 8) + 2 * up(4 * N)
+    plan = pu.to_np(ws[at:at + 32 * N]).view(np.int32).reshape(N, 8)
+    at += up(32 * N)
+    bounds = pu.to_np(ws[at:at + 32 * N]).view(np.uint32).reshape(N, 8)
+    return (bounds != VP_FLOOR_NONE).any(1), plan
+
+
+def _tied_ids_in_order(ids, tied):
+    """Of the tokens with one and the same logit a row lists the smallest ones, ascending."""
+    for row in ids:
+        mine = row[np.isin(row, tied)]
+        assert np.array_equal(mine, tied[:len(mine)]), (row, tied[:8])
+
+
+ALL = (4, 6, 8)
+
+
+@pytest.mark.parametrize("d,N,groups,items,trades", [
+    (256, 64, 36, 26, (8,)), (256, 64, 48, 24, ()), (256, 127, 144, 25, (6, 8)), (512, 64, 36, 25, (8,)), (512, 64, 56, 25, ALL), (512, 52, 56, 22, ()),
+    (768, 64, 36, 25, ()), (768, 192, 16, 25, ALL), (1024, 47, 36, 26, ()), (1024, 60, 28, 25, ()), (1024, 60, 32, 25, ALL),
+    (1024, 64, 68, 25, (8,)), (1024, 130, 36, 25, ALL), (1280, 48, 20, 25, (8,)), (1280, 100, 36, 25, ()), (1536, 36, 24, 25, ()),
+    (1536, 37, 28, 25, ALL), (1536, 48, 52, 25, ALL)])
+def test_bests_of_sets_traded_between_many_items(oracle, d, N, groups, items, trades):
+    """Rows whose candidates are spread over many items trade the bests of eight sets of candidates before the first list entry: by
+    width, list length, row groups and steps (vp_trades_sets), from 24 full items on, with three quarters of the row slots
+    in use, and in no item of a call that does not (trades: the list lengths among 4, 6 and 8 that do).  A third of the
+    vocabulary ties, in every set and item; a row with a few candidates only; a last item in which wavefronts have no step;
+    steps of two groups and of four, one row group and several; plain and masked, twice to the bit."""
     V = 16 * groups * items - 16 * min(groups - 13, 60) - 5   # (the last item: 12 groups and a piece, or some more)
     r, W, b, C = _small_model(70 + d + N, d, V, 3)
-    W[:, ::3] = W[:, :1]                     # a third of the vocabulary ties, whatever the row
-    b[::3] = b[0]
+    W[:, ::3] = W[:, :1]                     # the same logit, whatever the row, somewhere among or near the best ones
+    b[::3] = np.float16(3.5)
     off, ids = _random_lists(r, 3, V, 2, 9)
     full = np.sort(r.choice(V, size=V // 2, replace=False)).astype(np.int32)
     ids = np.concatenate([full, ids[off[1]:]]).astype(np.int32)
@@ -1371,27 +1400,61 @@ def test_bests_of_sets_traded_between_many_items(oracle, d, N, groups, items):
     per = 64 if d <= 1024 else 48
     rgs = (N + per - 1) // per
     H = _rows(r, C, N)
-    for wanted in (items * rgs, 8):
-        B.index.set_option("gemm_lds_items", wanted)
-        for k in (1, 3, 4, 8, 9):
-            got = B.project_full(H, k)
-            if wanted > 8:
-                ws = B.index.workspace(N)[:64].view(_torch().int32)
-                assert ws[0].item() == items * rgs and ws[1].item() * 4 == groups, (ws[0].item(), ws[1].item())
-            again = B.project_full(H, k)
-            for x, y in zip(got, again):
-                assert np.array_equal(x, y)
-            pu.check_full(oracle, W, b, H, k, *got)
-        B.index.set_option("dispatch", 1)
-        B.index.set_option("cost_bw_slab_gbs", 1)      # force the masked projection
-        try:
-            for k in (1, 4, 8):
-                got = B.project(H, k)
-                assert _planner_mode(B.index, N) == 1
-                pu.check_projection(oracle, W, b, C, off, ids, H, k, *got)
-        finally:
-            B.index.set_option("cost_bw_slab_gbs", 6800)
-            B.index.set_option("dispatch", 0)
+    # (a last row group of a few rows does not trade)
+    full_groups = np.arange(N) // per < rgs - (rgs > 1 and 0 < 4 * (N % per) < 3 * per)
+    B.index.set_option("gemm_lds_items", items * rgs)
+    for k in (3, 4, 6, 8, 9):
+        got = B.project_full(H, k)
+        ws = B.index.workspace(N)[:64].view(_torch().int32)
+        assert ws[0].item() == items * rgs and ws[1].item() * 4 == groups, (ws[0].item(), ws[1].item())
+        traded, _ = _rows_that_traded(B.index, N, 3)
+        assert np.array_equal(traded, full_groups if k in trades else np.full(N, False)), (k, traded)
+        again = B.project_full(H, k)
+        for x, y in zip(got, again):
+            assert np.array_equal(x, y)
+        pu.check_full(oracle, W, b, H, k, *got)
+        _tied_ids_in_order(got[0], np.arange(0, V, 3))
+        if k in (3, 9):
+            continue
+        got, mode, ovf = _masked(B, H, k)
+        assert mode == 1 and ovf == 0
+        traded, _ = _rows_that_traded(B.index, N, 3)
+        big = got[2] == 0                    # (rows of the long list: the others' few candidates may all be seen later than the first step)
+        assert np.array_equal(traded[big], full_groups[big] if k in trades else np.full(big.sum(), False)), (k, traded)
+        pu.check_projection(oracle, W, b, C, off, ids, H, k, *got)
+        _tied_ids_in_order(got[0][big], full[full % 3 == 0])
+
+
+def test_bests_of_sets_traded_in_a_plan_of_several_forms(oracle):
+    """Masked rows among rows on slabs: a masked row's sets are found by its number, not by its place in the plan, and begin anew
+    in every call (the call before it had larger logits in the same workspace)."""
+    d, V, K, N, k = 512, 40000, 40, 400, 8
+    r, W, b, C = _small_model(77, d, V, K)
+    off, ids = _random_lists(r, K, V, 200, 1500)
+    B = Built(W, b, C, off, ids)
+    p = np.arange(1, K + 1) ** -1.3
+    q = r.choice(r.permutation(K), size=N, p=p / p.sum())
+    q[:K] = np.arange(K)
+    H = _rows(r, C, N, clusters=q)
+    base = B.project(H, k)
+    B.index.set_option("dispatch", 1)
+    rates = {"cost_row_slab_ns": 0, "cost_bw_l2_gbs": 1000000, "cost_bw_full_gbs": 1000000, "cost_bw_slab_gbs": 2, "cost_bw_gemm_gbs": 14}
+    for name, v in rates.items():
+        B.index.set_option(name, v)
+    larger = B.project((H.astype(np.float32) * 4).astype(np.float16), k)
+    assert (larger[2] == base[2]).mean() > 0.9
+    got = B.project(H, k)
+    assert _planner_mode(B.index, N) == 2 and _overflow(B.index, N) == 0
+    traded, plan = _rows_that_traded(B.index, N, K)
+    masked = plan[plan[:, 5] == -1, 0]
+    assert len(masked) > 64 and len(masked) < N and traded[masked].sum() >= 64, (len(masked), traded[masked].sum())
+    assert not np.array_equal(masked, np.sort(masked))           # (the plan's order is not the rows')
+    again = B.project(H, k)
+    for x, y in zip(got, again):
+        assert np.array_equal(x, y)
+    assert np.array_equal(got[0], base[0]) and np.array_equal(got[2], base[2])
+    assert np.allclose(got[1], base[1], rtol=0, atol=1e-4)
+    pu.check_projection(oracle, W, b, C, off, ids, H, k, *got)
 
 
 @pytest.mark.parametrize("N,K", [(65, 40), (256, 1300), (333, 1990), (769, 1990), (2047, 2000)])
