@@ -40,7 +40,6 @@
 // is compiled into kernels of its own (SETS), because in every list kernel the registers it takes were lost to the calls that never trade
 // (masked, d_pad = 1024: 20 vector registers spilled and 72 scalar ones, without it none and 26; 64 rows, V = 200,000, d = 768, masked
 // top-2: 90 us with it, 81 without).  Not for gathered columns (the union): 40 rows 1 % slower for the registers.
-// The sets of a row are in one line (vp_set_bounds): with N * 4 bytes of bounds in front of them 60 rows took 68 us, not 63.
 // Keeping the candidates in an unsorted queue instead of the cascade: 5 to 20 % slower (registers, and the queue's overflow);
 // fewer atomics and plain loads of the sets: 40 us slower (the loads wait behind every atomic on their line).
 #include <hip/hip_runtime.h>

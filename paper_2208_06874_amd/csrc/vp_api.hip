@@ -230,7 +230,7 @@ WsLayout plan_workspace(const vp_index *I, int N)
     W.g = take(n * 4);
     W.perm = take(n * 4);
     W.rowplan = take(n * sizeof(VpRowPlan));
-    W.floors = take(n * 4 * (1 + VP_BOUND_SETS));   // [N][sets] of the GEMM-shaped kernels, then [N] bounds
+    W.floors = take(n * 4 * (1 + VP_BOUND_SETS));   // [N] bounds and [N][sets] of the GEMM-shaped kernels (vp_set_bounds)
     // (workgroups read the record at their own index before they know the item count)
     W.items = take((size_t)(W.max_items + 8 * VP_XCD_BLOCK_ITEMS) * sizeof(VpItem));
     // one partial result per (item, row slot): 16 slots in the clustered plan, up to 64 in single-bucket plans
@@ -380,7 +380,7 @@ vp_status run_clustered(const char *fn, const vp_index *I, const void *hidden, i
     int32_t *g = reinterpret_cast<int32_t *>(ws + W.g);
     int32_t *perm = reinterpret_cast<int32_t *>(ws + W.perm);
     VpRowPlan *rowplan = reinterpret_cast<VpRowPlan *>(ws + W.rowplan);
-    unsigned int *floors = reinterpret_cast<unsigned int *>(ws + W.floors) + (size_t)N * VP_BOUND_SETS;
+    unsigned int *floors = reinterpret_cast<unsigned int *>(ws + W.floors);
     VpItem *items = reinterpret_cast<VpItem *>(ws + W.items);
     float *partials = reinterpret_cast<float *>(ws + W.partials);
 
@@ -535,7 +535,7 @@ vp_status run_full(const char *fn, const vp_index *I, const void *hidden, int N,
     VpPlanHeader *hdr = reinterpret_cast<VpPlanHeader *>(ws + W.hdr);
     int32_t *perm = reinterpret_cast<int32_t *>(ws + W.perm);
     VpRowPlan *rowplan = reinterpret_cast<VpRowPlan *>(ws + W.rowplan);
-    unsigned int *floors = reinterpret_cast<unsigned int *>(ws + W.floors) + (size_t)N * VP_BOUND_SETS;
+    unsigned int *floors = reinterpret_cast<unsigned int *>(ws + W.floors);
     VpItem *items = reinterpret_cast<VpItem *>(ws + W.items);
     float *partials = reinterpret_cast<float *>(ws + W.partials);
 
@@ -992,7 +992,7 @@ vp_status vp_project_union(const vp_index *I, const void *hidden, int32_t N, int
     int32_t *g = reinterpret_cast<int32_t *>(ws + W.g);
     int32_t *perm = reinterpret_cast<int32_t *>(ws + W.perm);
     VpRowPlan *rowplan = reinterpret_cast<VpRowPlan *>(ws + W.rowplan);
-    unsigned int *floors = reinterpret_cast<unsigned int *>(ws + W.floors) + (size_t)N * VP_BOUND_SETS;
+    unsigned int *floors = reinterpret_cast<unsigned int *>(ws + W.floors);
     VpItem *items = reinterpret_cast<VpItem *>(ws + W.items);
     float *partials = reinterpret_cast<float *>(ws + W.partials);
     VpUnionHeader *uh = reinterpret_cast<VpUnionHeader *>(ws + U.uh);

@@ -25,9 +25,17 @@
 #define VP_RAW_TILES 2           // slab items of at most this many tiles per wavefront keep raw logits, no top-k lists
 #define VP_XCD_BLOCK_ITEMS 32    // clustered plans with heavy buckets: consecutive items one XCD takes at a time
 
-// The sets of all rows lie in front of the rows' bounds `floors`, from a multiple of 256 bytes on: a row's sets are 32 bytes of one
-// line whatever N is, and what a wavefront trades (eight rows) is two lines.
-static inline __host__ __device__ unsigned int *vp_set_bounds(unsigned int *floors, int N) { return floors - (long long)N * VP_BOUND_SETS; }
+// A section of N * (1 + VP_BOUND_SETS) words, rounded up to 256 bytes, holds the rows' bounds `floors`, from its start on, and the rows' sets,
+// at its end.  Both matter to the atomics that hundreds of workgroups send there at once: the bounds of sixteen rows are then 64
+// bytes of one line whatever N is (behind the sets of 33 rows, 32 bytes into a line, 33 rows took 45.9 us where they take 39.2: full
+// projection, V = 98,000, d = 768, top-2), a row's sets are 32 bytes of one line (N * 4 bytes behind the start 60 rows took 68 us, not 63),
+// and they begin with a line where there is room for it.
+static inline __host__ __device__ long long vp_set_bounds_at(int N)   // bytes
+{
+    const long long floors = 4ll * N, sets = floors * VP_BOUND_SETS, at = ((floors + sets + 255) & ~255ll) - sets;
+    return (at & ~127ll) >= floors ? at & ~127ll : at;
+}
+static inline __host__ __device__ unsigned int *vp_set_bounds(unsigned int *floors, int N) { return floors + vp_set_bounds_at(N) / 4; }
 
 // One unit of projection work: some rows of one bucket (up to 16, or 32, 48 or 64 on the kernels with that many row
 // slots) against a range of candidate tiles of that bucket's slab.

@@ -288,6 +288,18 @@ def test_candidate_groups_per_step_of_the_many_row_kernel(layout):
                     assert (twos[0], twos[-1]) == edges if edges else not twos, (kt, k, twos)
 
 
+def test_bounds_and_sets_of_rows_do_not_straddle_lines(layout):
+    """The rows' bounds are at the start of their section (256-byte aligned: sixteen rows in one line), their sets behind them,
+    32-byte aligned and inside the section, at the start of a line wherever the section has room."""
+    layout.shim_set_bounds_at.restype = ctypes.c_longlong
+    sets = 4 * layout.shim_bound_sets()
+    for N in list(range(1, 3000)) + [4096, 16384, 65535, 65536]:
+        at = layout.shim_set_bounds_at(N)
+        end = -(-N * (4 + sets) // 256) * 256
+        assert at >= 4 * N and at % sets == 0 and at + sets * N <= end, N
+        assert at % 128 == 0 or -(-4 * N // 128) * 128 + sets * N > end, N
+
+
 def test_which_calls_trade_the_bests_of_sets(layout):
     """Not outside top-4 to top-8, with few rows of an item, below 24 items a row, or in items in steps of one group; several row
     groups up to d_pad = 1024, two from top-6 on; one row group of d_pad = 768 never (14 % slower there)."""

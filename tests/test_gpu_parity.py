@@ -1362,7 +1362,7 @@ def _rows_that_traded(index, N, K):
     up = lambda x: (x + 255) // 256 * 256
     at = 256 + up(N * ((K + 15) // 16) * 8) + 2 * up(4 * N)
     plan = pu.to_np(ws[at:at + 32 * N]).view(np.int32).reshape(N, 8)
-    at += up(32 * N)
+    at += up(32 * N) + ((up(36 * N) - 32 * N) // 128 * 128 if (up(36 * N) - 32 * N) // 128 * 128 >= 4 * N else up(36 * N) - 32 * N)
     bounds = pu.to_np(ws[at:at + 32 * N]).view(np.uint32).reshape(N, 8)
     return (bounds != VP_FLOOR_NONE).any(1), plan
 
