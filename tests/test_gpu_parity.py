@@ -1458,10 +1458,10 @@ def test_bests_of_sets_traded_in_a_plan_of_several_forms(oracle):
 
 
 @pytest.mark.parametrize("N,K", [(65, 40), (256, 1300), (333, 1990), (769, 1990), (2047, 2000)])
-def test_every_form_of_the_many_row_eq2_kernel(oracle, N, K):
-    """One or two row tiles x one to eight centroid tiles per wavefront, by how many workgroups each leaves: a last row tile
-    and a last centroid tile that are not full, duplicate centroids (ties to the lowest), a width that ends inside a
-    k-tile."""
+def test_every_form_of_the_many_row_eq2_kernel_in_decoding(oracle, N, K):
+    """One or two row tiles x one to eight centroid tiles per wavefront, by how many workgroups each leaves (the sixth form, one
+    row tile x eight, serves the training alone): a last row tile and a last centroid tile that are not full, duplicate
+    centroids (ties to the lowest), a width that ends inside a k-tile."""
     d, V = 264, 300
     r, W, b, C = _small_model(90 + N, d, V, K)
     C[K // 2:K // 2 + 9] = C[3]
@@ -1475,20 +1475,23 @@ def test_every_form_of_the_many_row_eq2_kernel(oracle, N, K):
 
 @pytest.mark.parametrize("k", [1, 2, 4, 5, 8, 9])
 def test_merge_of_equal_logits_over_many_parts(oracle, k):
-    """Rows of more parts than a workgroup of the merge has threads, of a few hundred and of a handful: every logit of the
-    first row is the same, so the k smallest token ids win wherever their parts are; the second row's best are spread."""
+    """Rows of more parts than a workgroup of the merge has threads, of a few hundred and of at most a wavefront's lanes: forty
+    tokens, spread over the parts, share a row's largest logit, and the k smallest of them win, in order."""
     d, V = 64, 40000
     r, W, b, C = _small_model(5 + k, d, V, 1)
     W[:] = W[:, :1]
     b[:] = b[0]
-    b[r.choice(V, 40, replace=False)] += np.float16(2.0)     # forty equal best ones
+    best = np.sort(r.choice(V, 40, replace=False))
+    b[best] += np.float16(2.0)
     B = Built(W, b, C, np.array([0, V], np.int64), np.arange(V, dtype=np.int32), k_max=16)
     H = _rows(r, C, 2)
     for wanted, least, most in ((2048, 257, 2048), (200, 65, 256), (16, 9, 64)):
         B.index.set_option("full_target_items", wanted)
         got = B.project_full(H, k)
         parts = B.index.workspace(2)[:64].view(_torch().int32)[0].item()
-        assert least <= parts <= most or wanted != 2048, parts
+        assert least <= parts <= most, parts
+        assert np.array_equal(got[0], np.tile(best[:k], (2, 1))), (wanted, got[0], best[:k])
+        assert (got[1] == got[1][:, :1]).all()
         pu.check_full(oracle, W, b, H, k, *got)
 
 

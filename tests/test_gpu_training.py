@@ -90,6 +90,24 @@ def test_membership_with_the_vectors_in_lds(oracle, n, d, K):
 # Rows-in-LDS kernel with workgroups that carry the numbers from one item to the next (more than 256 items at d_pad 512, 1024
 # and 1536); the split-k kernel; two chunks of 65,536 vectors of the decode-time kernel (d_pad 768); and the scatter that
 # stays where the numbers have no room (256 clusters or more and n > 2 * K * d).
+@pytest.mark.parametrize("n,d,K", [(3000, 1024, 1000), (2000, 264, 1300), (700, 264, 1990), (3900, 264, 1990), (65536 + 264, 2056, 300)])
+def test_membership_by_the_decode_time_kernel(oracle, n, d, K):
+    """Few vectors, and any number of k-extents beyond the many-row kernels': one row tile x eight centroid tiles per wavefront, and
+    wavefronts with more centroid tiles than they take at a time (6 by 4, 3 by 2, 16 by 8), a short chunk behind 65,536
+    vectors in another form.  Duplicate centroids: ties to the lowest."""
+    r = np.random.default_rng(n + d + K)
+    C0 = r.standard_normal((K, d)).astype(np.float16)
+    C0[K // 2:K // 2 + 9] = C0[3]
+    q = r.integers(0, K, n)
+    q[-20:] = 3
+    X = (C0[q].astype(np.float32) + 0.3 * r.standard_normal((n, d), dtype=np.float32)).astype(np.float16)
+    bits, assign, counts = _gpu_kmeans(X, C0, 0)
+    assert np.array_equal(bits, C0.view(np.uint16)) and np.array_equal(counts, np.bincount(assign, minlength=K))
+    assert (assign[-20:] == 3).all()
+    some = np.unique(np.r_[np.arange(min(n, 700)), r.integers(0, n, 300), np.arange(n - 264, n)])
+    _check_membership(oracle, X[some], C0.view(np.uint16), assign[some])
+
+
 @pytest.mark.parametrize("n,d,K", [(16390, 504, 257), (16390, 1000, 256), (15400, 1288, 256), (16390, 1024, 257),
                                    (65800, 520, 256), (4200, 8, 256)])
 def test_members_are_placed_by_their_numbers(oracle, n, d, K):

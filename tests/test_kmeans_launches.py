@@ -87,3 +87,13 @@ def test_passes_are_taken_apart_only_beyond_two_rounds(launches, d, n, K, apart)
     do not hold all vectors; the split-k kernel takes its passes apart by itself."""
     names = launches.printed(n, d, K, iters=3)[3:]
     assert sum("kmeans_reassign_kernel" in name for name in names) == 3 * int(apart)
+
+
+@pytest.mark.parametrize("n,d,K,forms", [
+    (3000, 1024, 1000, [(1, 8)]), (2000, 264, 1300, [(2, 4)]), (700, 264, 1990, [(1, 2)]), (3900, 264, 1990, [(2, 8)]),
+    (66000, 2048, 40, [(1, 1)] * 2), (65536 + 264, 2056, 300, [(2, 4), (1, 4)])])
+def test_forms_of_the_decode_time_kernel_in_training(launches, n, d, K, forms):
+    """Row tiles x centroid tiles per wavefront, by chunk of 65,536 vectors."""
+    names = launches.printed(n, d, K)[3:]
+    got = [tuple(map(int, m.groups())) for m in (re.search(r"centroid_kernelILi(\d+)ELi(\d+)E", name) for name in names) if m]
+    assert got == forms

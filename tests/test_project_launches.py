@@ -1,6 +1,7 @@
 """Which kernels vp_project launches, read from the launches it makes (no GPU: the program of project_launch_main.cpp stands
 in front of the HIP runtime).  A launch that leaves at once costs 3 to 5 us, so the host leaves out what cannot win."""
 import os
+import re
 import shutil
 import subprocess
 
@@ -69,3 +70,13 @@ def test_kernel_that_trades_is_launched_only_where_items_trade(launches, d, V, K
     got = [name for name in launches(d, V, K, lo, hi, k, N) if "project_gemm_lds_kernel" in name]
     assert len(got) == 1
     assert ("ELb%dEEEv" % trades) in got[0], got
+
+
+@pytest.mark.parametrize("N,K,form", [(64, 1000, None), (65, 40, (1, 1)), (256, 1000, (1, 1)), (256, 1300, (1, 2)), (333, 1990, (1, 4)),
+                                      (769, 1990, (2, 4)), (2047, 2000, (2, 8))])
+def test_forms_of_the_many_row_eq2_kernel(launches, N, K, form):
+    """Row tiles x centroid tiles per wavefront; up to 64 rows the kernel that splits the k-extent."""
+    got = list(launches(264, 300, K, 4, 12, 2, N))
+    m = [re.search(r"centroid_kernelILi(\d+)ELi(\d+)E", name) for name in got]
+    assert [tuple(map(int, x.groups())) for x in m if x] == ([form] if form else [])
+    assert any("centroid_small_kernel" in name for name in got) == (form is None)
