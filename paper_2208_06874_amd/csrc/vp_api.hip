@@ -225,12 +225,12 @@ WsLayout plan_workspace(const vp_index *I, int N)
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes); return at; };
     const size_t n = (size_t)std::max(N, 1);
-    W.hdr = take(sizeof(VpPlanHeader));
+    W.hdr = take(vp_rows_head_bytes((int)n));   // and [N] bounds and [N][sets] of the GEMM-shaped kernels (vp_set_bounds)
+    W.floors = W.hdr + VP_FLOORS_AT;
     W.cpart = take(n * I->L.ctiles * 8);
     W.g = take(n * 4);
     W.perm = take(n * 4);
     W.rowplan = take(n * sizeof(VpRowPlan));
-    W.floors = take(n * 4 * (1 + VP_BOUND_SETS));   // [N] bounds and [N][sets] of the GEMM-shaped kernels (vp_set_bounds)
     // (workgroups read the record at their own index before they know the item count)
     W.items = take((size_t)(W.max_items + 8 * VP_XCD_BLOCK_ITEMS) * sizeof(VpItem));
     // one partial result per (item, row slot): 16 slots in the clustered plan, up to 64 in single-bucket plans

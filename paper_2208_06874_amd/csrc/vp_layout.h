@@ -25,15 +25,16 @@
 #define VP_RAW_TILES 2           // slab items of at most this many tiles per wavefront keep raw logits, no top-k lists
 #define VP_XCD_BLOCK_ITEMS 32    // clustered plans with heavy buckets: consecutive items one XCD takes at a time
 
-// A section of N * (1 + VP_BOUND_SETS) words, rounded up to 256 bytes, holds the rows' bounds `floors`, from its start on, and the rows' sets,
-// at its end.  Both matter to the atomics that hundreds of workgroups send there at once: the bounds of sixteen rows are then 64
-// bytes of one line whatever N is (behind the sets of 33 rows, 32 bytes into a line, 33 rows took 45.9 us where they take 39.2: full
-// projection, V = 98,000, d = 768, top-2), a row's sets are 32 bytes of one line (N * 4 bytes behind the start 60 rows took 68 us, not 63),
-// and they begin with a line where there is room for it.
-static inline __host__ __device__ long long vp_set_bounds_at(int N)   // bytes
+// A workspace begins with the header, the rows' bounds `floors` and the rows' sets.  Where they lie matters to the atomics that hundreds
+// of workgroups send there at once.  The bounds start 128 bytes behind a multiple of 256: sixteen rows are 64 bytes of one line (32 bytes
+// into a line 33 rows took 45.9 us where they take 39.2: full projection, V = 98,000, d = 768, top-2), and the 64 rows of an item are not
+// in one block of 256 bytes, which one L2 channel serves alone (64 rows, V = 65,000, d = 1024, top-3: 48.9 us in one, 43.5 in two).
+// A row's sets are 32 bytes of one line (N * 4 bytes behind a line's start 60 rows took 68 us, not 63), from a line's start on.
+#define VP_FLOORS_AT 128
+static inline __host__ __device__ long long vp_rows_head_bytes(int N) { return 256 + ((4ll * N * (1 + VP_BOUND_SETS) + 255) & ~255ll); }
+static inline __host__ __device__ long long vp_set_bounds_at(int N)   // bytes behind the floors
 {
-    const long long floors = 4ll * N, sets = floors * VP_BOUND_SETS, at = ((floors + sets + 255) & ~255ll) - sets;
-    return (at & ~127ll) >= floors ? at & ~127ll : at;
+    return (vp_rows_head_bytes(N) - VP_FLOORS_AT - 4ll * VP_BOUND_SETS * N) & ~127ll;
 }
 static inline __host__ __device__ unsigned int *vp_set_bounds(unsigned int *floors, int N) { return floors + vp_set_bounds_at(N) / 4; }
 
@@ -88,8 +89,9 @@ struct VpPlanHeader {
     int32_t masked_slot0;
     int32_t masked_swz;
     int32_t grouped_items;
-    int32_t pad[51];
+    int32_t pad[19];
 };
+static_assert(sizeof(VpPlanHeader) <= VP_FLOORS_AT, "the rows' bounds lie behind the header");
 
 // State of one batch-union projection (see union.hip).
 struct VpUnionHeader {

@@ -289,15 +289,16 @@ def test_candidate_groups_per_step_of_the_many_row_kernel(layout):
 
 
 def test_bounds_and_sets_of_rows_do_not_straddle_lines(layout):
-    """The rows' bounds are at the start of their section (256-byte aligned: sixteen rows in one line), their sets behind them,
-    32-byte aligned and inside the section, at the start of a line wherever the section has room."""
-    layout.shim_set_bounds_at.restype = ctypes.c_longlong
-    sets = 4 * layout.shim_bound_sets()
+    """The rows' bounds start half a block of 256 bytes behind the workspace's start (sixteen rows in one line, sixty-four in two
+    blocks), behind the header; their sets behind them, from a line's start on, inside the first sections' bytes, which are a
+    block and 36 bytes a row, rounded up."""
+    layout.shim_set_bounds_at.restype = layout.shim_rows_head_bytes.restype = ctypes.c_longlong
+    floors, sets = layout.shim_floors_at(), 4 * layout.shim_bound_sets()
+    assert floors % 256 == 128
     for N in list(range(1, 3000)) + [4096, 16384, 65535, 65536]:
-        at = layout.shim_set_bounds_at(N)
-        end = -(-N * (4 + sets) // 256) * 256
-        assert at >= 4 * N and at % sets == 0 and at + sets * N <= end, N
-        assert at % 128 == 0 or -(-4 * N // 128) * 128 + sets * N > end, N
+        at = floors + layout.shim_set_bounds_at(N)
+        assert layout.shim_rows_head_bytes(N) == 256 + -(-36 * N // 256) * 256
+        assert at % 128 == 0 and at >= floors + 4 * N and at + sets * N <= layout.shim_rows_head_bytes(N), N
 
 
 def test_which_calls_trade_the_bests_of_sets(layout):

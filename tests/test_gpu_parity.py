@@ -1360,10 +1360,10 @@ def _rows_that_traded(index, N, K):
     planner sets a row's eight bounds to the key of -infinity, a trade raises those of the sets that have a candidate."""
     ws = index.workspace(N)
     up = lambda x: (x + 255) // 256 * 256
-    at = 256 + up(N * ((K + 15) // 16) * 8) + 2 * up(4 * N)
-    plan = pu.to_np(ws[at:at + 32 * N]).view(np.int32).reshape(N, 8)
-    at += up(32 * N) + ((up(36 * N) - 32 * N) // 128 * 128 if (up(36 * N) - 32 * N) // 128 * 128 >= 4 * N else up(36 * N) - 32 * N)
+    at = 128 + (128 + up(36 * N) - 32 * N) // 128 * 128
     bounds = pu.to_np(ws[at:at + 32 * N]).view(np.uint32).reshape(N, 8)
+    at = 256 + up(36 * N) + up(N * ((K + 15) // 16) * 8) + 2 * up(4 * N)
+    plan = pu.to_np(ws[at:at + 32 * N]).view(np.int32).reshape(N, 8)
     return (bounds != VP_FLOOR_NONE).any(1), plan
 
 
@@ -1420,7 +1420,7 @@ def test_bests_of_sets_traded_between_many_items(oracle, d, N, groups, items, tr
         assert mode == 1 and ovf == 0
         traded, _ = _rows_that_traded(B.index, N, 3)
         big = got[2] == 0                    # (rows of the long list: the others' few candidates may all be seen later than the first step)
-        assert np.array_equal(traded[big], full_groups[big] if k in trades else np.full(big.sum(), False)), (k, traded)
+        assert np.array_equal(traded[big], full_groups[big] & (k in trades)), (k, traded)
         pu.check_projection(oracle, W, b, C, off, ids, H, k, *got)
         _tied_ids_in_order(got[0][big], full[full % 3 == 0])
 
