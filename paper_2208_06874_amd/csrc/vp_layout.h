@@ -242,7 +242,7 @@ static inline __host__ __device__ constexpr bool vp_item_trades_sets(int nrows, 
 // Several row groups (their workgroups run side by side and the trade's wait is hidden): d = 256, V = 100,000, 256 rows: top-4 43.4 -> 37.5,
 // top-7 51.8 -> 43.3; V = 250,000, 384 rows: 85.4 -> 77.7, 104.3 -> 89.6; d = 512, V = 250,000, 192 rows: 80.1 -> 70.3, 93.0 -> 76.1; d = 1024, V =
 // 100,000, 256 rows (items of 100 groups): 76.5 -> 73.0, 84.8 -> 76.8, 192 rows: 71.2 -> 61.8, 78.6 -> 67.1.  Two row groups at top-4 and top-5: d =
-// 1024 0 to 5 % slower, masked 0 to 9 %.  d = 1280 and 1536: top-4 0 to 4 % slower, longer lists within 2 %.
+// 1024 0 to 5 % slower, masked 0 to 9 %; with few rows in the second, d = 1024, V = 212,000, top-6: 65 rows 6 % slower, 96 4 %, 112 4 % faster.  d = 1280 and 1536: top-4 0 to 4 % slower, longer lists within 2 %.
 // One row group (HBM sets the pace, and the wait shows unless the bound is worth a step of every wavefront): top-7 and top-8 up to d_pad = 512
 // and at 1024 (d = 256, top-8, 48 groups an item: 51.8 -> 46.5; 512: 62.8 -> 59.8; 1024: 91.1 -> 87.1); shorter lists only where every
 // wavefront has two steps or nearly (d = 1024, 32 groups, top-4: 69.3 -> 65.0, 36: 68.6 -> 70.4; d = 512, 64 groups: 71.9 -> 67.9, 36: 50.0 ->
@@ -253,7 +253,7 @@ static inline bool vp_trades_sets(int kt, int k, int N, int slots, int ntiles, i
 {
     const int rgs = (N + slots - 1) / slots, groups = vp_step_groups(kt, k, rgs > 1, ntiles);
     if (k < 4 || k > VP_BOUND_SETS || groups == 1 || !vp_item_trades_sets(rgs > 1 ? slots : N, slots, ntiles, ncand)) return false;
-    if (rgs > 1) return kt <= 32 && (rgs > 2 || k > 5);
+    if (rgs > 1) return kt <= 32 && (rgs > 2 || (k > 5 && (kt < 32 || vp_item_trades_sets(N - slots, slots, ntiles, ncand))));
     const int steps = (ntiles + groups - 1) / groups;
     if (kt == 48) return steps > 12;
     if (kt == 40) return k > 6 && groups == 2;

@@ -309,13 +309,13 @@ def test_which_calls_trade_the_bests_of_sets(layout):
     for kt in (8, 16, 24, 32, 40, 48):
         slots = 64 if kt <= 32 else 48
         for ntiles in range(4, 1000, 4):
-            for N in (1, slots // 2, slots * 3 // 4, slots, slots + 1, 2 * slots, 3 * slots, 9 * slots):
+            for N in (1, slots // 2, slots * 3 // 4, slots, slots + 1, slots * 7 // 4 - 1, slots * 7 // 4, 2 * slots, 3 * slots, 9 * slots):
                 by_k = [k for k in range(1, 33) if trades(kt, k, N, slots, ntiles, V)]
                 assert all(4 <= k <= 8 for k in by_k) and by_k == list(range(by_k[0], 9) if by_k else ())
                 if N < slots * 3 // 4 or ntiles * 16 * 24 > V or layout.shim_step_groups(kt, 4, N > slots, ntiles) == 1:
                     assert not by_k
                 elif N > slots:
-                    assert by_k == ([] if kt > 32 else [6, 7, 8] if N <= 2 * slots else [4, 5, 6, 7, 8])
+                    assert by_k == ([] if kt > 32 or (kt == 32 and N < 112) else [6, 7, 8] if N <= 2 * slots else [4, 5, 6, 7, 8])
                 elif kt == 24:
                     assert not by_k
     for kt, ntiles, first in ((8, 64, 7), (16, 36, 7), (16, 56, 4), (32, 32, 4), (32, 36, 7), (40, 20, 7), (40, 24, None), (48, 24, None), (48, 28, 4),

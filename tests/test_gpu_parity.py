@@ -1457,6 +1457,33 @@ def test_bests_of_sets_traded_in_a_plan_of_several_forms(oracle):
     pu.check_projection(oracle, W, b, C, off, ids, H, k, *got)
 
 
+def test_crowded_clusters_do_not_trade(oracle):
+    """Crowded clusters' items run beside masked rows' in kernels that trade, without the code that does, however long their lists:
+    three clusters of 13,000 tokens with sixty rows each, a fourth of two rows."""
+    d, V, K, k = 512, 60000, 4, 8
+    r, W, b, C = _small_model(78, d, V, K)
+    lists = [np.sort(r.choice(V, size=n, replace=False)) for n in (13000, 13000, 13000, 400)]
+    off = np.cumsum([0] + [len(x) for x in lists]).astype(np.int64)
+    ids = np.concatenate(lists).astype(np.int32)
+    B = Built(W, b, C, off, ids)
+    q = r.permutation(np.r_[np.repeat([0, 1, 2], 60), 3, 3])
+    N = len(q)
+    H = _rows(r, C, N, clusters=q)
+    base = B.project(H, k)
+    B.index.set_option("dispatch", 1)
+    for name, v in {"cost_row_slab_ns": 0, "cost_bw_slab_gbs": 7, "cost_bw_l2_gbs": 17, "cost_bw_full_gbs": 5, "cost_bw_gemm_gbs": 14}.items():
+        B.index.set_option(name, v)
+    got = B.project(H, k)
+    assert _planner_mode(B.index, N) == 2 and _overflow(B.index, N) == 0
+    assert int(B.index.workspace(N)[:64].view(_torch().int32)[12].item()) >= 3 * 24     # (their items)
+    traded, plan = _rows_that_traded(B.index, N, K)
+    crowded = plan[np.isin(plan[:, 1], (0, 1, 2)), 0]
+    assert len(crowded) == 180 and not traded[crowded].any()
+    assert np.array_equal(got[0], base[0]) and np.array_equal(got[2], base[2])
+    assert np.allclose(got[1], base[1], rtol=0, atol=1e-4)
+    pu.check_projection(oracle, W, b, C, off, ids, H, k, *got)
+
+
 @pytest.mark.parametrize("N,K", [(65, 40), (256, 1300), (333, 1990), (769, 1990), (2047, 2000)])
 def test_every_form_of_the_many_row_eq2_kernel_in_decoding(oracle, N, K):
     """One or two row tiles x one to eight centroid tiles per wavefront, by how many workgroups each leaves (the sixth form, one
