@@ -10,9 +10,9 @@
 // items); wavefront w takes steps w, w + 8, ...  A step streams its groups' tiles straight into registers
 // (a ring of a few k-tiles ahead, crossing step boundaries, so the loads never drain), and per
 // k-tile feeds each loaded 1 KiB slab tile to one v_mfma_f32_16x16x32_f16 per row tile,
-// whose row operands are read from LDS (one 1 KiB read per four MFMAs: four groups per step).  No wavefront waits
-// for another inside the loop: there is no split of the k-extent, so nothing is exchanged and
-// there is no barrier between the staging of the rows and the end of the item.
+// whose row operands are read from LDS (one 1 KiB read per four MFMAs: four groups per step).  There is no split of the k-extent, so
+// no wavefront waits for another inside the loop and there is no barrier between the staging of the rows and the end of
+// the item - but for the two behind the first step of items that trade the bests of sets (below).
 //
 // After the 32 x 16 MFMAs of a step a lane holds, for each of the four row tiles, the 16 logits
 // of one row (its quarter of each of the four groups).  They are folded in one go: bias,
@@ -540,7 +540,7 @@ __device__ __forceinline__ void many_row_item(const VpSlabSet &set, const uint4 
                                               float *__restrict__ partials, unsigned int *__restrict__ floors,
                                               unsigned int *__restrict__ bounds, const VpMaskInfo &mask, const int32_t *__restrict__ perm)
 {
-    const int groups = vp_step_groups(KT, k, item.shared, item.ntiles);
+    const int groups = vp_step_groups(KT, k, item.shared, item.ntiles, SETS);
     if (item.shared || GATHER) {
         if (groups == 1) gemm_lds_item<KT, 1, MASKED, false, TOP1, GATHER, false>(set, hidden, d, item, it, k, partials, floors, bounds, mask, perm);
         else gemm_lds_item<KT, 4, MASKED, false, TOP1, GATHER, SETS>(set, hidden, d, item, it, k, partials, floors, bounds, mask, perm);

@@ -353,9 +353,11 @@ void launch_single_bucket(const VpSlabSet &set, const vp_index *I, const void *h
 
 // Eq. 2 for a decode batch: up to VP_KSPLIT_ROWS rows with one workgroup per (centroid tile, row
 // tile) and the k-extent split over its wavefronts (every load in flight at once: 4.6 us instead
-// of 9.3 at 64 rows; at 256 rows its thousand small workgroups take 9.2 us against 6.7), beyond
-// that the kernel whose wavefronts take several centroid tiles at a time (vp_centroid_tiles_per_wave).  Returns the number of per-row
-// minima left in cpart.
+// of 9.3 at 64 rows), beyond that the kernel whose wavefronts take several centroid tiles at a time (vp_centroid_tiles_per_wave).  At
+// 256 rows and 1,000 centroids, d = 1024, a thousand workgroups of either take as long (7.6 and 7.9 us in a trace), but the first
+// leaves 63 minima a row and the planner reads them all: a call on short lists takes 46.9 us with it, 44.2 without.  Up to about 512 workgroups
+// the first is ahead for more than 64 rows too (whole calls; 65 rows, 200 centroids 24.8 us against 28.1, 256 rows 30.6 against 33.8; its
+// scores add up in another order).  Returns the number of per-row minima left in cpart.
 constexpr int VP_KSPLIT_ROWS = 64;
 int launch_eq2(const vp_index *I, const void *hidden, int N, void *cpart, hipStream_t st)
 {

@@ -219,7 +219,9 @@ static inline __host__ __device__ int vp_tiles_per_wave_units(long long total_ti
 // Top-3: d = 256: 12: 26.2 -> 24.7, 16: 27.1 -> 26.4, 24: 30.0 -> 33.8, 28: 31.2 -> 36.4, 32: 37.2 -> 40.4; 512: 12: 29.5 -> 28.5, 16: 35.2 -> 32.6, 24:
 // 38.1 -> 39.4, 32: 48.7 -> 53.3; 768: 32: 53.4 -> 56.2; 1024: 32: 66.8 -> 66.7, 40: 76.0 -> 71.3, 48: 89.5 -> 83.7, 64: 106.6 -> 104.5; 1280: 16: 45.5 ->
 // 44.7, 20: 52.5 -> 51.8, 24: 58.2 -> 59.3, 32: 71.7 -> 72.4; 1536: 16: 52.4 -> 50.0, 24: 66.8 -> 66.4, 32: 86.9 -> 85.1, 36: 90.5 -> 91.4; longer lists alike.
-static inline __host__ __device__ constexpr int vp_step_groups(int kt, int k, bool shared, int ntiles)
+// trades: items of a kernel that trades the bests of sets (vp_trades_sets): at d = 256 and 512 two as well for 32 groups, two steps for
+// every wavefront with the trade between them (top-6 43.5 -> 40.3, 55.9 -> 50.6).
+static inline __host__ __device__ constexpr int vp_step_groups(int kt, int k, bool shared, int ntiles, bool trades)
 {
     if (k == 1) {
         if (ntiles < (kt <= 32 ? 32 : kt == 40 && !shared ? 20 : 16)) return 1;
@@ -227,6 +229,7 @@ static inline __host__ __device__ constexpr int vp_step_groups(int kt, int k, bo
     }
     if (shared) return ntiles <= (k > 2 ? 12 : 8) ? 1 : 4;
     if (ntiles <= (kt > 32 ? 15 : kt >= 24 ? 31 : 8)) return 1;
+    if (trades && kt <= 16 && ntiles > 28 && ntiles <= 32) return 2;
     return ntiles <= (kt <= 16 ? 16 : kt == 24 ? 0 : kt == 32 ? 64 : kt == 40 ? 20 : 32) ? 2 : 4;
 }
 
@@ -242,7 +245,8 @@ static inline __host__ __device__ constexpr bool vp_item_trades_sets(int nrows, 
 // Several row groups (their workgroups run side by side and the trade's wait is hidden): d = 256, V = 100,000, 256 rows: top-4 43.4 -> 37.5,
 // top-7 51.8 -> 43.3; V = 250,000, 384 rows: 85.4 -> 77.7, 104.3 -> 89.6; d = 512, V = 250,000, 192 rows: 80.1 -> 70.3, 93.0 -> 76.1; d = 1024, V =
 // 100,000, 256 rows (items of 100 groups): 76.5 -> 73.0, 84.8 -> 76.8, 192 rows: 71.2 -> 61.8, 78.6 -> 67.1.  Two row groups at top-4 and top-5: d =
-// 1024 0 to 5 % slower, masked 0 to 9 %; with few rows in the second, d = 1024, V = 212,000, top-6: 65 rows 6 % slower, 96 4 %, 112 4 % faster.  d = 1280 and 1536: top-4 0 to 4 % slower, longer lists within 2 %.
+// 1024 0 to 5 % slower, masked 0 to 9 %; with few rows in the second, d = 1024, V = 212,000, top-6: 65 rows 6 % slower, 96 4 %, 112 4 % faster.  d = 1280 and 1536: top-4 0 to 4 % slower, top-7 and top-8 1 to
+// 6 % faster (288 rows, V = 100,000, d = 1280, top-7: 105 -> 100) but for two row groups of 36 groups an item (4 % slower).
 // One row group (HBM sets the pace, and the wait shows unless the bound is worth a step of every wavefront): top-7 and top-8 up to d_pad = 512
 // and at 1024 (d = 256, top-8, 48 groups an item: 51.8 -> 46.5; 512: 62.8 -> 59.8; 1024: 91.1 -> 87.1); shorter lists only where every
 // wavefront has two steps or nearly (d = 1024, 32 groups, top-4: 69.3 -> 65.0, 36: 68.6 -> 70.4; d = 512, 64 groups: 71.9 -> 67.9, 36: 50.0 ->
@@ -251,13 +255,13 @@ static inline __host__ __device__ constexpr bool vp_item_trades_sets(int nrows, 
 // but for top-7 and top-8 in steps of two.
 static inline bool vp_trades_sets(int kt, int k, int N, int slots, int ntiles, int ncand)
 {
-    const int rgs = (N + slots - 1) / slots, groups = vp_step_groups(kt, k, rgs > 1, ntiles);
+    const int rgs = (N + slots - 1) / slots, groups = vp_step_groups(kt, k, rgs > 1, ntiles, true);
     if (k < 4 || k > VP_BOUND_SETS || groups == 1 || !vp_item_trades_sets(rgs > 1 ? slots : N, slots, ntiles, ncand)) return false;
-    if (rgs > 1) return kt <= 32 && (rgs > 2 || (k > 5 && (kt < 32 || vp_item_trades_sets(N - slots, slots, ntiles, ncand))));
+    if (rgs > 1) return kt > 32 ? rgs > 2 && k > 6 : rgs > 2 || (k > 5 && (kt < 32 || vp_item_trades_sets(N - slots, slots, ntiles, ncand)));
     const int steps = (ntiles + groups - 1) / groups;
     if (kt == 48) return steps > 12;
     if (kt == 40) return k > 6 && groups == 2;
-    return kt != 24 && (k > 6 || (kt >= 16 && steps > 12 && steps <= 16));
+    return kt != 24 && (k > 6 || (steps > 12 && steps <= 16 && (kt >= 16 || groups == 2)));
 }
 
 // The workgroup -> item maps behind VpPlanHeader.swz_rgs (wg = the workgroup's index in the grid;
@@ -406,9 +410,10 @@ struct VpMixLimits {
 // Eq. 2 for many rows: how many centroid tiles a wavefront takes at a time (centroid_kernel), and whether it takes two row tiles.
 // A round of 256 workgroups of a form takes, d = 1024 (U = k-tiles fetched together): 1 row tile x 1 centroid tile 6.7 us, x 2 7.6,
 // x 4 9.7, x 8 14.4; 2 x 4 13.7, 2 x 8 18.5 (4 x 4 22.3, never the best); more workgroups take in proportion longer, fewer no
-// shorter.  So the form whose workgroups x time is least: 1,000 centroids, d = 1024, us before (1 x 1 throughout) -> with it:
-// 256 rows 6.9 -> 6.7, 512: 11.4 -> 7.7, 1,024: 20.3 -> 10.2, 2,048: 37.4 -> 14.2, 4,096: 71.0 -> 20.3; 500 centroids, d = 1536,
-// 4,096 rows: 54.2 -> 19.4; 1,300 centroids, d = 1000, 333 rows: 8.2 -> 6.4.
+// shorter.  So the form whose workgroups x time is least.  The kernel in a trace of calls, us, 1 x 1 throughout -> with it, 1,000
+// centroids: d = 1024, 256 rows (1 x 1 either way) 7.8 -> 7.9, 512: 13.6 -> 9.4, 1,024: 21.6 -> 12.4, 2,048: 39.3 -> 17.1, 4,096: 73.9 -> 22.2;
+// d = 512: 512 rows 7.8 -> 6.3, 4,096: 39.1 -> 14.4; d = 1536: 512 rows 17.2 -> 12.8, 4,096: 107.5 -> 29.6; 500 centroids, d = 1536, 4,096 rows: 56.6
+// -> 21.5.  Of 220 sizes (d = 512 to 1536, 100 to 2,000 centroids, 65 to 4,096 rows) none is slower beyond what two traces of one side differ.
 static inline int vp_centroid_two_row_tiles(int row_tiles, int parts, int tiles_per_wave)
 {
     return tiles_per_wave >= 4 && (long long)((row_tiles + 1) / 2) * parts >= (tiles_per_wave >= 8 ? 200 : 180);

@@ -34,5 +34,5 @@ extern "C" long long shim_set_bounds_at(int N) { return vp_set_bounds_at(N); }
 extern "C" long long shim_rows_head_bytes(int N) { return vp_rows_head_bytes(N); }
 extern "C" int shim_floors_at(void) { return VP_FLOORS_AT; }
 extern "C" int shim_bound_sets(void) { return VP_BOUND_SETS; }
-extern "C" int shim_step_groups(int kt, int k, int shared, int ntiles) { return vp_step_groups(kt, k, shared != 0, ntiles); }
+extern "C" int shim_step_groups(int kt, int k, int shared, int ntiles, int trades) { return vp_step_groups(kt, k, shared != 0, ntiles, trades != 0); }
 extern "C" int shim_trades_sets(int kt, int k, int N, int slots, int ntiles, int ncand) { return vp_trades_sets(kt, k, N, slots, ntiles, ncand); }

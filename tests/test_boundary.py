@@ -278,7 +278,7 @@ def test_candidate_groups_per_step_of_the_many_row_kernel(layout):
     for kt in (8, 16, 24, 32, 40, 48):
         for k in (1, 2, 3, 4, 8, 9, 32):
             for shared in (0, 1):
-                by_length = {n: layout.shim_step_groups(kt, k, shared, n) for n in range(1, 400)}
+                by_length = {n: layout.shim_step_groups(kt, k, shared, n, 0) for n in range(1, 400)}
                 assert set(by_length.values()) <= {1, 2, 4} and by_length[1] == 1 and by_length[399] == 4
                 assert all(by_length[n] <= by_length[n + 1] for n in range(1, 399))
                 twos = [n for n in range(4, 400, 4) if by_length[n] == 2]
@@ -286,6 +286,9 @@ def test_candidate_groups_per_step_of_the_many_row_kernel(layout):
                 if k > 1 and not shared:
                     edges = {8: (12, 16), 16: (12, 16), 24: None, 32: (32, 64), 40: (16, 20), 48: (16, 32)}[kt]
                     assert (twos[0], twos[-1]) == edges if edges else not twos, (kt, k, twos)
+                # (items that trade: two steps for every wavefront and the trade between them, d_pad = 256 and 512)
+                apart = [n for n in range(1, 400) if layout.shim_step_groups(kt, k, shared, n, 1) != by_length[n]]
+                assert apart == ([29, 30, 31, 32] if kt <= 16 and k > 1 and not shared else [])
 
 
 def test_bounds_and_sets_of_rows_do_not_straddle_lines(layout):
@@ -312,13 +315,14 @@ def test_which_calls_trade_the_bests_of_sets(layout):
             for N in (1, slots // 2, slots * 3 // 4, slots, slots + 1, slots * 7 // 4 - 1, slots * 7 // 4, 2 * slots, 3 * slots, 9 * slots):
                 by_k = [k for k in range(1, 33) if trades(kt, k, N, slots, ntiles, V)]
                 assert all(4 <= k <= 8 for k in by_k) and by_k == list(range(by_k[0], 9) if by_k else ())
-                if N < slots * 3 // 4 or ntiles * 16 * 24 > V or layout.shim_step_groups(kt, 4, N > slots, ntiles) == 1:
+                if N < slots * 3 // 4 or ntiles * 16 * 24 > V or layout.shim_step_groups(kt, 4, N > slots, ntiles, 1) == 1:
                     assert not by_k
                 elif N > slots:
-                    assert by_k == ([] if kt > 32 or (kt == 32 and N < 112) else [6, 7, 8] if N <= 2 * slots else [4, 5, 6, 7, 8])
+                    two = N <= 2 * slots
+                    assert by_k == (([] if two else [7, 8]) if kt > 32 else ([] if kt == 32 and N < 112 else [6, 7, 8]) if two else [4, 5, 6, 7, 8])
                 elif kt == 24:
                     assert not by_k
-    for kt, ntiles, first in ((8, 64, 7), (16, 36, 7), (16, 56, 4), (32, 32, 4), (32, 36, 7), (40, 20, 7), (40, 24, None), (48, 24, None), (48, 28, 4),
+    for kt, ntiles, first in ((8, 64, 7), (8, 32, 4), (16, 32, 4), (16, 36, 7), (16, 56, 4), (32, 32, 4), (32, 36, 7), (40, 20, 7), (40, 24, None), (48, 24, None), (48, 28, 4),
                               (48, 48, None), (48, 52, 4)):
         by_k = [k for k in range(1, 33) if trades(kt, k, 48, 64 if kt <= 32 else 48, ntiles, V)]
         assert by_k == ([] if first is None else list(range(first, 9))), (kt, ntiles, by_k)

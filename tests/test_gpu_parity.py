@@ -1378,9 +1378,9 @@ ALL = (4, 6, 8)
 
 
 @pytest.mark.parametrize("d,N,groups,items,trades", [
-    (256, 64, 36, 26, (8,)), (256, 64, 48, 24, ()), (256, 127, 144, 25, (6, 8)), (512, 64, 36, 25, (8,)), (512, 64, 56, 25, ALL), (512, 52, 56, 22, ()),
+    (256, 64, 36, 26, (8,)), (256, 64, 32, 25, ALL), (256, 64, 48, 24, ()), (256, 127, 144, 25, (6, 8)), (512, 64, 36, 25, (8,)), (512, 64, 56, 25, ALL), (512, 52, 56, 22, ()),
     (768, 64, 36, 25, ()), (768, 192, 16, 25, ALL), (1024, 47, 36, 26, ()), (1024, 60, 28, 25, ()), (1024, 60, 32, 25, ALL),
-    (1024, 64, 68, 25, (8,)), (1024, 130, 36, 25, ALL), (1280, 48, 20, 25, (8,)), (1280, 100, 36, 25, ()), (1536, 36, 24, 25, ()),
+    (1024, 64, 68, 25, (8,)), (1024, 130, 36, 25, ALL), (1280, 48, 20, 25, (8,)), (1280, 96, 36, 25, ()), (1280, 100, 36, 25, (8,)), (1536, 36, 24, 25, ()),
     (1536, 37, 28, 25, ALL), (1536, 48, 52, 25, ALL)])
 def test_bests_of_sets_traded_between_many_items(oracle, d, N, groups, items, trades):
     """Rows whose candidates are spread over many items trade the bests of eight sets of candidates before the first list entry: by
@@ -1522,7 +1522,7 @@ def test_merge_of_equal_logits_over_many_parts(oracle, k):
         pu.check_full(oracle, W, b, H, k, *got)
 
 
-@pytest.mark.parametrize("d,groups", [(256, 16), (256, 20), (512, 12), (768, 32), (1024, 64), (1024, 68), (1280, 20), (1280, 24),
+@pytest.mark.parametrize("d,groups", [(256, 16), (256, 20), (512, 12), (512, 32), (768, 32), (1024, 64), (1024, 68), (1280, 20), (1280, 24),
                                       (1536, 32), (1536, 36)])
 def test_steps_of_one_two_and_four_groups(oracle, d, groups):
     """Single row groups at both sides of the lines between steps of one, two and four candidate groups, plain and masked: a last
@@ -1534,7 +1534,7 @@ def test_steps_of_one_two_and_four_groups(oracle, d, groups):
     B = Built(W, b, C, off, ids, k_max=9)
     B.index.set_option("gemm_lds_items", items)
     H = _rows(r, C, N)
-    for k in (1, 2, 9):
+    for k in (1, 2, 5, 9):
         got = B.project_full(H, k)
         ws = B.index.workspace(N)[:64].view(_torch().int32)
         assert ws[0].item() == items and ws[1].item() * 4 == groups

@@ -65,7 +65,7 @@ def test_many_row_kernel_is_launched_where_it_may_win(launches, d, V, K, lo, hi,
     (1024, 128000, 200, 5000, 8000, 8, 64, True), (1024, 250000, 1000, 10000, 20000, 8, 256, True),
     (1024, 250000, 1000, 10000, 20000, 8, 1024, False), (1024, 128000, 200, 5000, 8000, 8, 32, False),
     (1024, 128000, 200, 5000, 8000, 3, 64, False), (1024, 128000, 200, 5000, 8000, 1, 64, False),
-    (768, 200000, 100, 9000, 15000, 8, 64, False), (1536, 250000, 500, 2000, 40000, 8, 4096, False), (1024, 100000, 100, 5000, 8000, 4, 192, True)])
+    (768, 200000, 100, 9000, 15000, 8, 64, False), (1536, 250000, 500, 2000, 40000, 6, 4096, False), (1024, 100000, 100, 5000, 8000, 4, 192, True)])
 def test_kernel_that_trades_is_launched_only_where_items_trade(launches, d, V, K, lo, hi, k, N, trades):
     got = [name for name in launches(d, V, K, lo, hi, k, N) if "project_gemm_lds_kernel" in name]
     assert len(got) == 1
